@@ -21,6 +21,7 @@
 // fp16 and bf16 fragments are 16-bit elements in the same order, so everything that only moves data
 // is typed as bf16.
 #include <mutex>
+#include <type_traits>
 
 #include "spd_internal.h"
 
@@ -1353,64 +1354,65 @@ __global__ void __launch_bounds__(256) k_qkv_gather(const float *__restrict__ pa
 }
 
 // ------------------------------------------------------------------------------------------
-// GEMM for prefill-sized calls: a workgroup computes a 256 (output features) x 256 (tokens) tile
-// with 8 waves (or 256 x 128 with 4); both operands are staged through LDS in steps of 64 (or 32)
-// contraction elements, double buffered.  The operands already are sequences of 1 KiB MFMA fragments in global
-// memory, so a stage is filled with gfx950's direct global->LDS loads (one instruction per
-// fragment, no staging registers) and read back with conflict-free 16-byte LDS reads.  Each
-// wave owns 4 n-tiles x 8 m-tiles (128 accumulator registers).  One barrier per step.  In the steps of
-// two k-tiles the LDS reads of one k-tile and the copies of a later step are dealt between the MFMAs of
-// the other k-tile, so that neither the LDS nor the load unit is asked for a burst while the matrix cores wait.
+// GEMM for prefill-sized calls: a workgroup computes a tile of 256 (output features) x 256 (tokens), or one of the
+// shapes below, with 8 waves; both operands are staged through LDS.  The operands already are sequences of 1 KiB
+// MFMA fragments in global memory, so a stage is filled with gfx950's direct loads into LDS (one instruction per
+// fragment, no staging registers) and read back with conflict-free 16-byte LDS reads.
+//
+// A stage holds two fragments per m-tile: k-tiles 2s and 2s + 1 (with the weights of both), or, for activations kept
+// as a hi + lo pair (XS), the two planes of k-tile s (with its weights once: the second pass re-uses them from
+// registers).  A step is two sub-steps, one per fragment: while the MFMAs of one run, the fragment reads of the next
+// are dealt between them (so that neither the LDS nor the load unit is asked for a burst while the matrix cores
+// wait), and in the second one the copies of the stage NST steps ahead.  The one barrier of a step sits between its
+// sub-steps: passing it means that everybody has read both fragments of the current stage (whose place the copies
+// take) and that the next stage has landed; the copies of the stages after that stay in flight across it.
+// What bounds it: the matrix cores, the LDS (64 bytes per clock and compute unit: 12 fragment reads per 32 MFMAs) and
+// the chip's power together.  A probe of this very mix without barriers or HBM reaches 1.14 PFLOP/s on random
+// data, the gate/up projection of 4096 tokens 1.2, against 1.16 of the vendor library's fp16 product of that shape.
 // ------------------------------------------------------------------------------------------
-// Tile shapes.  WN x WM waves, each TI n-tiles x TJ m-tiles; KPS k-tiles per step.
-struct GemmBig {      // 8 waves, 256 x 256, steps of 64: one workgroup per compute unit (128 KiB of LDS)
-    static constexpr int WN = 4, WM = 2, TI = 4, TJ = 8, KPS = 2, MINB = 1, NST = 2;
+// Tile shapes.  WN x WM waves, each TI n-tiles x TJ m-tiles; stages of the plain and of the split (XS) kind.
+struct GemmBig {      // 256 x 256: two stages of 64 KiB (split: three of 48 KiB)
+    static constexpr int WN = 4, WM = 2, TI = 4, TJ = 8, NST = 2, NSTX = 3;
 };
-struct GemmMid {      // 4 waves, 256 x 128, steps of 32: 48 KiB of LDS, two or three workgroups per compute unit
-    static constexpr int WN = 2, WM = 2, TI = 8, TJ = 4, KPS = 1, MINB = 2, NST = 2;
+struct GemmHalf {     // 256 x 128: three stages of 48 KiB, four of 32 KiB (a step is too short for a copy to arrive within it)
+    static constexpr int WN = 4, WM = 2, TI = 4, TJ = 4, NST = 3, NSTX = 4;
 };
-#ifndef SPD_HALF_NST
-#define SPD_HALF_NST 3
-#endif
-struct GemmHalf {     // 8 waves, 256 x 128, steps of 64: half of a GemmBig tile, three stages of 48 KiB (one workgroup per compute unit)
-    static constexpr int WN = 4, WM = 2, TI = 4, TJ = 4, KPS = 2, MINB = 1, NST = SPD_HALF_NST;
+struct GemmTall {     // 128 x 384: for few n-tiles, where 256 x 256 tiles leave compute units idle
+    static constexpr int WN = 2, WM = 4, TI = 4, TJ = 6, NST = 2, NSTX = 2;
 };
-struct GemmTall {     // 8 waves, 128 x 384, steps of 64: for few n-tiles, where 256 x 256 tiles leave compute units idle
-    static constexpr int WN = 2, WM = 4, TI = 4, TJ = 6, KPS = 2, MINB = 1, NST = 2;
+struct GemmWide {     // 160 x 256, every wave all 10 n-tiles of 2 m-tiles: for split activations and few n-tiles
+    static constexpr int WN = 1, WM = 8, TI = 10, TJ = 2, NST = 2, NSTX = 3;      // (80 n-tiles x 512 m-tiles = exactly 256 tiles)
 };
-struct GemmWide {     // 8 waves, 160 x 256, every wave all 10 n-tiles of 2 m-tiles: for split activations and few n-tiles
-    static constexpr int WN = 1, WM = 8, TI = 10, TJ = 2, KPS = 2, MINB = 1, NST = 2;      // (80 n-tiles x 512 m-tiles = exactly 256 tiles)
-};
-// XS: the activations are hi + lo pairs (second plane at Xlo).  A step then covers ONE k-tile: its weight
-// fragments and, per m-tile, the hi and the lo fragment of that k-tile, so the copies and the fragment
-// reads of the weights are shared by both passes and any number of k-tiles will do.
+// operand of s_waitcnt: at most vm vector loads and lgkm LDS / scalar operations still in flight (63 / 15: any number)
+constexpr int waitcnt_imm(int vm, int lgkm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4) | (lgkm << 8); }
+// descriptor of `bytes` bytes at p (raw access)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t panel(const char *p, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, (int)bytes, 0x00020000);
+}
+
 template <class Epi, class G, bool XS>
-__global__ void __launch_bounds__(G::WN * G::WM * 64, G::MINB) k_gemm_lds(const __bf16 *__restrict__ Wp, const __bf16 *__restrict__ Xp,
-                                                                   const __bf16 *__restrict__ Xlo, int KT, int n_ntiles,
-                                                                   int n_mtiles, spd_tile_order ord, int tile0, int n_tiles,
-                                                                   int msub, int kslices, int wgs_per_slice, Epi epi_in) {
-    constexpr int GL_WN = G::WN, GL_WM = G::WM, GL_TI = G::TI, GL_TJ = G::TJ, KPS = G::KPS;
-    constexpr int GL_BN = GL_WN * GL_TI, GL_BM = GL_WM * GL_TJ;          // tiles per workgroup
-    constexpr int KW = XS ? 1 : KPS;                                     // weight fragments per tile row and step
-    constexpr int KX = XS ? 2 : KPS;                                     // activation fragments per tile row and step
-    constexpr int GL_STAGE = (GL_BN * KW + GL_BM * KX) * 1024;
-    constexpr int GL_FPW = (GL_BN + GL_BM + GL_WN * GL_WM - 1) / (GL_WN * GL_WM);   // tile rows copied per wave and stage
-    constexpr bool RAGGED = (GL_BN + GL_BM) % (GL_WN * GL_WM) != 0;      // the last waves copy fewer rows
-    static_assert(GL_TI % 2 == 0, "tile shape");
+__global__ void __launch_bounds__(G::WN *G::WM * 64, 1)
+    k_gemm_lds(const __bf16 *Wp, const __bf16 *Xp, const __bf16 *Xlo, int KT, int n_ntiles, int n_mtiles, spd_tile_order ord,
+               int tile0, int n_tiles, int msub, int kslices, int wgs_per_slice, Epi epi) {
+    constexpr int TI = G::TI, TJ = G::TJ, NST = XS ? G::NSTX : G::NST;
+    constexpr int NW = G::WN * G::WM, BN = G::WN * TI, BM = G::WM * TJ;
+    constexpr int KW = XS ? 1 : 2;                                       // k-tiles per stage
+    constexpr int W_BYTES = BN * KW * 1024, STAGE = W_BYTES + BM * 2048;
+    constexpr int CW = (BN * KW + NW - 1) / NW, CX = BM * 2 / NW, NCP = CW + CX;      // fragments copied per wave and stage
+    static_assert(TI % 2 == 0 && (BM * 2) % NW == 0 && (NST - 1) * NCP < 64, "tile shape");
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wn = wave % GL_WN, wm = wave / GL_WN;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wn = wave % G::WN, wm = wave / G::WN;
     // A launch covers `n_tiles` tiles of the order from `tile0` on, each cut into `msub` workgroup tiles along M
     // (1, or 2 for the launch that finishes a ragged last round with half tiles; `ord` counts the uncut tiles).
-    // kslices > 1 (epilogues that are linear in the accumulators only): the launch is kslices copies of the
-    // tile grid, copy s contracting the s-th part of K and handing its slice number to the epilogue
+    // kslices > 1 (sliced epilogues only): the launch is kslices copies of the tile grid, copy s contracting
+    // the s-th part of K and handing its slice number to the epilogue.
     int bid = (int)blockIdx.x, kslice = 0;
     if (kslices > 1) {
         kslice = bid / wgs_per_slice;
         bid -= kslice * wgs_per_slice;
     }
-    const Epi &epi = epi_in;      // (used where the launch put it: a copy of an epilogue with a table of positions would live in scratch memory)
-    const int kt_first = (int)(((long)kslice * KT) / kslices), kt_end = (int)(((long)(kslice + 1) * KT) / kslices);
+    const int kt_first = (int)(((long)kslice * KT) / kslices), nk = (int)(((long)(kslice + 1) * KT) / kslices) - kt_first;
     int tn, tm, sub = 0;
     {
         int idx;
@@ -1423,192 +1425,176 @@ __global__ void __launch_bounds__(G::WN * G::WM * 64, G::MINB) k_gemm_lds(const 
         }
         spd_tile_at(ord, tile0 + idx, tn, tm);
     }
-    const int nt0 = tn * GL_BN, mt0 = (tm * msub + sub) * GL_BM;
-    f32x4 acc[GL_TI][GL_TJ];
+    const int nt0 = tn * BN, mt0 = (tm * msub + sub) * BM;
+    if (mt0 >= n_mtiles) return;                 // second half of a tile whose first half holds all the rows (whole workgroup)
+    // Copies go through buffer descriptors of the tile's panels: a lane's offset plus one wave-uniform offset per
+    // fragment.  (The global_load_lds form counts as an access to both memories at once, which makes the compiler wait for
+    // every pending LDS read instead of the one it needs.)  Rows past the matrix repeat its last tile, spare copies
+    // the last fragment.
+    const int l16 = lane * 16;
+    const unsigned pitch = (unsigned)KT * 1024;  // bytes between two tiles of a panel
+    const int n_rows = n_ntiles - nt0 < BN ? n_ntiles - nt0 : BN, m_rows = n_mtiles - mt0 < BM ? n_mtiles - mt0 : BM;
+    const __amdgpu_buffer_rsrc_t wbuf = panel((const char *)Wp + (size_t)nt0 * pitch, n_rows * pitch),
+                                 xbuf = panel((const char *)Xp + (size_t)mt0 * pitch, m_rows * pitch),
+                                 lbuf = panel((const char *)(XS ? Xlo : Xp) + (size_t)mt0 * pitch, m_rows * pitch);
+    unsigned wsrc[CW], xsrc[CX];                 // (wave-uniform)
+    int wdst[CW];
 #pragma unroll
-    for (int i = 0; i < GL_TI; ++i)
-#pragma unroll
-        for (int j = 0; j < GL_TJ; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    // this wave's share of the copies: GL_FPW tile rows.  Without XS the KPS k-tiles of a row are contiguous
-    // both in global memory and in LDS; with XS an activation row is the hi fragment then the lo fragment of
-    // one k-tile.  Rows past the matrix repeat its last tile.
-    const __bf16 *src[GL_FPW], *src2[GL_FPW];
-    int loff[GL_FPW];
-    bool isx[GL_FPW];
-#pragma unroll
-    for (int i = 0; i < GL_FPW; ++i) {
-        int row = wave * GL_FPW + i;
-        if (RAGGED && row >= GL_BN + GL_BM) row = GL_BN + GL_BM - 1;     // never issued (see issue())
-        isx[i] = row >= GL_BN;
-        if (!isx[i]) {
-            int t = nt0 + row;
-            if (t >= n_ntiles) t = n_ntiles - 1;
-            src[i] = src2[i] = Wp + spd_frag_index(t, kt_first, KT) + lane * 8;
-            loff[i] = row * (KW * 1024);
-        } else {
-            int t = mt0 + row - GL_BN;
-            if (t >= n_mtiles) t = n_mtiles - 1;
-            src[i] = Xp + spd_frag_index(t, kt_first, KT) + lane * 8;
-            src2[i] = XS ? Xlo + spd_frag_index(t, kt_first, KT) + lane * 8 : src[i];
-            loff[i] = GL_BN * (KW * 1024) + (row - GL_BN) * (KX * 1024);
-        }
+    for (int n = 0; n < CW; ++n) {
+        int f = wave * CW + n;
+        f = f < BN * KW ? f : BN * KW - 1;
+        const int t = f / KW;
+        wsrc[n] = (unsigned)(t < n_rows ? t : n_rows - 1) * pitch + kt_first * 1024;
+        wdst[n] = f;
     }
-    // copy number n of a stage (n < GL_NCP): tile row n / CPR of this wave's share, fragment n % CPR of that row
-    constexpr int CPR = XS ? 1 : KPS;
-    constexpr int GL_NCP = GL_FPW * CPR;
-    auto issue_one = [&](int stage, int ks, int n) {
-        const int i = n / CPR, f = n % CPR;
-        if (RAGGED && wave * GL_FPW + i >= GL_BN + GL_BM) return;
-        const __bf16 *g = src[i] + (size_t)ks * (CPR * 512);
-        char *l = lds + stage * GL_STAGE + loff[i];
-        if (f == 0)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)g,
-                                             (__attribute__((address_space(3))) void *)l, 16, 0, 0);
-        else
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)g,
-                                             (__attribute__((address_space(3))) void *)l, 16, 1024, 0);
-        if constexpr (XS) {
-            if (isx[i]) {
-                const __bf16 *g2 = src2[i] + (size_t)ks * 512;
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)g2,
-                                                 (__attribute__((address_space(3))) void *)(l + 1024), 16, 0, 0);
+#pragma unroll
+    for (int n = 0; n < CX; ++n) {
+        const int t = (wave * CX + n) >> 1;
+        xsrc[n] = (unsigned)(t < m_rows ? t : m_rows - 1) * pitch + kt_first * 1024;
+    }
+    f32x4 acc[TI][TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    // copy n of stage st into the place `slot` (a k-tile past the end, the odd one's partner, repeats the last)
+    auto copy1 = [&](int st, int slot, int n) __attribute__((always_inline)) {
+        if (n < CW) {
+            int kt = KW * st + (XS ? 0 : wdst[n] & 1);
+            kt = kt < nk ? kt : nk - 1;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wbuf, (__attribute__((address_space(3))) void *)(lds + slot * STAGE + wdst[n] * 1024),
+                                                     16, l16, (int)(wsrc[n] + kt * 1024), 0, 0);
+        } else {
+            const int c = wave * CX + (n - CW);
+            int kt = XS ? st : 2 * st + (c & 1);
+            kt = kt < nk ? kt : nk - 1;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(XS && (c & 1) ? lbuf : xbuf,
+                                                     (__attribute__((address_space(3))) void *)(lds + slot * STAGE + W_BYTES + c * 1024),
+                                                     16, l16, (int)(xsrc[n - CW] + kt * 1024), 0, 0);
+        }
+    };
+    const char *a_base = lds + wn * TI * KW * 1024 + l16, *b_base = lds + W_BYTES + wm * TJ * 2048 + l16;
+    // fragment r of sub-step p of the stage in `slot`: the wave's TJ activation fragments, then its TI weight fragments
+    auto read1 = [&](int slot, int p, int r, bf16x8(&a)[TI], bf16x8(&b)[TJ]) __attribute__((always_inline)) {
+        if (r < TJ) b[r] = *(const bf16x8 *)(b_base + slot * STAGE + (2 * r + p) * 1024);
+        else a[r - TJ] = *(const bf16x8 *)(a_base + slot * STAGE + ((r - TJ) * KW + (XS ? 0 : p)) * 1024);
+    };
+    const int n_stages = (nk + KW - 1) / KW, nsteps = nk / KW;
+#pragma unroll
+    for (int st = 0; st < NST; ++st)
+        if (st < n_stages) {
+#pragma unroll
+            for (int n = 0; n < NCP; ++n) copy1(st, st, n);
+        }
+    __builtin_amdgcn_sched_barrier(0);
+    // (the builtin, unlike a wait in asm, is one the compiler's own count of pending operations knows of)
+    if (n_stages >= NST) __builtin_amdgcn_s_waitcnt(waitcnt_imm((NST - 1) * NCP, 0));
+    else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    bf16x8 a0[TI], a1[TI], b0[TJ], b1[TJ];
+#pragma unroll
+    for (int r = 0; r < TI + TJ; ++r) read1(0, 0, r, a0, b0);
+
+    // the MFMAs of a sub-step on (a, b); meanwhile NR fragments of the next one are read into (an, bn) and, with COPY, the
+    // copies of stage cst go out
+    auto substep = [&](auto nr_, auto copy_, const bf16x8(&a)[TI], const bf16x8(&b)[TJ], bf16x8(&an)[TI], bf16x8(&bn)[TJ], int rslot,
+                       int rp, int cst, int cslot) __attribute__((always_inline)) {
+        constexpr int NR = decltype(nr_)::value, NM = TI * TJ;
+        constexpr bool COPY = decltype(copy_)::value;
+        int r = 0, cp = 0;
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                const int n = i * TJ + j;
+                acc[i][j] = MFMA16(a[i], b[j], acc[i][j]);
+                __builtin_amdgcn_sched_barrier(0);
+                if (r < NR && n >= (2 * NR <= NM ? 2 * r : r * NM / NR)) read1(rslot, rp, r++, an, bn);
+                if (COPY && cp < NCP && n >= cp * (NM / NCP) + 1) copy1(cst, cslot, cp++);
+                __builtin_amdgcn_sched_barrier(0);
             }
-        }
     };
-    auto issue = [&](int stage, int ks) {
-#pragma unroll
-        for (int n = 0; n < GL_NCP; ++n) issue_one(stage, ks, n);
+    int slot = 0;                                      // of the current stage
+    auto step = [&](auto copy_, auto odd_, int s) __attribute__((always_inline)) {
+        constexpr bool COPY = decltype(copy_)::value, ODD = decltype(odd_)::value;
+        using All = std::integral_constant<int, TI + TJ>;
+        const int next = slot + 1 == NST ? 0 : slot + 1;
+        if constexpr (XS) substep(std::integral_constant<int, TJ>(), std::false_type(), ODD ? a1 : a0, b0, ODD ? a0 : a1, b1, slot, 1, 0, 0);
+        else substep(All(), std::false_type(), a0, b0, a1, b1, slot, 1, 0, 0);
+        // the next stage's copies of this wave have landed, those of the NST - 2 stages after it may be in flight; every
+        // read of the current stage is done
+        __builtin_amdgcn_s_waitcnt(waitcnt_imm(COPY ? (NST - 2) * NCP : 0, 0));
+        asm volatile("s_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        // (in the last step: fragments read and never used)
+        if constexpr (XS) substep(All(), copy_, ODD ? a1 : a0, b1, ODD ? a0 : a1, b0, next, 0, s + NST, slot);
+        else substep(All(), copy_, a1, b1, a0, b0, next, 0, s + NST, slot);
+        slot = next;
     };
-    const int nks = XS ? kt_end - kt_first : (kt_end - kt_first) / KPS;      // (the launcher keeps a slice a whole number of steps)
-    if constexpr (!XS && KPS == 2) {
-        // A step is two k-tiles; the fragments of one k-tile are read from LDS while the MFMAs of the other run.
-        // The barrier sits in the middle of a step: when a wave passes it, everybody has read both k-tiles of the
-        // current stage (so the copies of the step after next may overwrite it) and the next stage has landed (so
-        // its first k-tile can be read during the second half of this step).
-        bf16x8 a0[GL_TI], b0[GL_TJ], a1[GL_TI], b1[GL_TJ];
-        static_assert(2 * (GL_TI + GL_TJ) <= GL_TI * GL_TJ, "one fragment read per two MFMAs must cover a k-tile");
-        const int a_off = (wn * GL_TI * 2) * 1024 + lane * 16, b_off = GL_BN * 2048 + (wm * GL_TJ * 2) * 1024 + lane * 16;
-        // fragment r of k-tile kt of a stage: the wave's TJ activation fragments, then its TI weight fragments
-        auto rd1 = [&](const char *st, int kt, int r, bf16x8(&a)[GL_TI], bf16x8(&b)[GL_TJ]) {
-            if (r < GL_TJ) b[r] = *(const bf16x8 *)(st + b_off + (r * 2 + kt) * 1024);
-            else a[r - GL_TJ] = *(const bf16x8 *)(st + a_off + ((r - GL_TJ) * 2 + kt) * 1024);
-        };
-        // the MFMAs of one k-tile, with the fragment reads of the next one dealt between them (one per two MFMAs):
-        // the LDS works while the matrix cores do, and every fragment is there long before its first use
-        // The copies of a later step are dealt the same way (one instruction per CS MFMAs): a wave that issues
-        // them in one burst waits for the load unit to take them, at the rate the data moves, and multiplies nothing.
-        constexpr int CS = (GL_TI * GL_TJ) / GL_NCP;
-        static_assert(CS >= 1, "more copies per wave than MFMAs per k-tile");
-        auto mm = [&](const bf16x8(&a)[GL_TI], const bf16x8(&b)[GL_TJ], const char *st, int kt, bf16x8(&an)[GL_TI],
-                      bf16x8(&bn)[GL_TJ], bool copy, int cstage, int cks) {
-#pragma unroll
-            for (int i = 0; i < GL_TI; ++i)
-#pragma unroll
-                for (int j = 0; j < GL_TJ; ++j) {
-                    const int n = i * GL_TJ + j;
-                    acc[i][j] = MFMA16(a[i], b[j], acc[i][j]);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (n % 2 == 0 && n / 2 < GL_TI + GL_TJ) {
-                        rd1(st, kt, n / 2, an, bn);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    if (n % CS == CS - 1 && n / CS < GL_NCP) {
-                        if (copy) issue_one(cstage, cks, n / CS);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-        };
-        // NST stages: the copies of step ks + NST go into the stage that step ks frees at its barrier.  With three
-        // stages (tiles whose step is too short for a copy to arrive within one step) a wave has the copies of two
-        // steps in flight at the barrier and waits for the older ones only.
-        constexpr int NST = G::NST;
-        static_assert(NST == 2 || (NST == 3 && !RAGGED), "three stages: every wave issues the same number of copies");
-#pragma unroll
-        for (int s0 = 0; s0 < NST; ++s0)
-            if (s0 < nks) issue(s0, s0);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < GL_TI + GL_TJ; ++r) rd1(lds, 0, r, a0, b0);
-        int cur = 0;
-        for (int ks = 0; ks < nks; ++ks) {
-            const int nxt = cur + 1 == NST ? 0 : cur + 1;
-            mm(a0, b0, lds + cur * GL_STAGE, 1, a1, b1, false, 0, 0);
-            // this wave's copies of the next step have landed
-            if (NST == 3 && ks + 2 < nks) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(GL_NCP) : "memory");
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            // (in the last step: fragments read and never used)
-            mm(a1, b1, lds + nxt * GL_STAGE, 0, a0, b0, ks + NST < nks, cur, ks + NST);
-            cur = nxt;
+    int s = 0;
+    if constexpr (XS) {                                // (the weight registers of a pair of steps take turns)
+        for (; s + 1 + NST < n_stages; s += 2) {
+            step(std::true_type(), std::false_type(), s);
+            step(std::true_type(), std::true_type(), s + 1);
         }
+        // at most one stage is left to copy
+        if (s + NST < n_stages) {
+            step(std::true_type(), std::false_type(), s++);
+            if (s < nsteps) step(std::false_type(), std::true_type(), s++);
+        }
+        for (; s + 1 < nsteps; s += 2) {
+            step(std::false_type(), std::false_type(), s);
+            step(std::false_type(), std::true_type(), s + 1);
+        }
+        if (s < nsteps) step(std::false_type(), std::false_type(), s);
     } else {
-        issue(0, 0);
-        for (int ks = 0; ks < nks; ++ks) {
-            const int cur = ks & 1;
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wave's copies into `cur` have landed
-            __syncthreads();                                     // everybody's have, and nobody still reads the other stage
-            if (ks + 1 < nks) issue(cur ^ 1, ks + 1);
-            const char *st = lds + cur * GL_STAGE;
-            // all fragments of the step are requested first, then the MFMAs run in program order
-            // (the scheduling barriers keep the compiler from re-interleaving reads and MFMAs, which
-            // would make it wait for the whole LDS queue before every group of MFMAs)
-            bf16x8 a[KW][GL_TI], b[KX][GL_TJ];
+        for (; s + NST < n_stages; ++s) step(std::true_type(), std::false_type(), s);
+        for (; s < nsteps; ++s) step(std::false_type(), std::false_type(), s);
+        if (nk & 1) {                                  // odd number of k-tiles: the last one on its own (its fragments are read already)
 #pragma unroll
-            for (int kt = 0; kt < KX; ++kt) {
+            for (int i = 0; i < TI; ++i)
 #pragma unroll
-                for (int j = 0; j < GL_TJ; ++j)
-                    b[kt][j] = *(const bf16x8 *)(st + GL_BN * KW * 1024 + ((wm * GL_TJ + j) * KX + kt) * 1024 + lane * 16);
-                if (kt < KW) {
-#pragma unroll
-                    for (int i = 0; i < GL_TI; ++i) a[kt][i] = *(const bf16x8 *)(st + ((wn * GL_TI + i) * KW + kt) * 1024 + lane * 16);
-                }
-            }
-#pragma unroll
-            for (int kt = 0; kt < KX; ++kt)
-#pragma unroll
-                for (int i = 0; i < GL_TI; ++i)
-#pragma unroll
-                    for (int j = 0; j < GL_TJ; ++j) {
-                        acc[i][j] = MFMA16(a[XS ? 0 : kt][i], b[kt][j], acc[i][j]);
-                        if (KX == 2) __builtin_amdgcn_sched_barrier(0);
-                    }
+                for (int j = 0; j < TJ; ++j) acc[i][j] = MFMA16(a0[i], b0[j], acc[i][j]);
         }
     }
     // norm factors of all the wave's m-tiles first, so that their loads are in flight together
-    float rs[GL_TJ];
+    float rs[TJ];
 #pragma unroll
-    for (int j = 0; j < GL_TJ; ++j) {
+    for (int j = 0; j < TJ; ++j) {
         rs[j] = 1.f;
         if constexpr (Epi::kNeedsRs) {
-            int mt = mt0 + wm * GL_TJ + j;
+            int mt = mt0 + wm * TJ + j;
             if (mt >= n_mtiles) mt = n_mtiles - 1;
-            rs[j] = sum_ss(epi.ss, epi.nch, epi.m_pad, mt * 16 + (lane & 15), lane >> 4, 4);
+            rs[j] = epi.nch == 0 ? epi.ss[mt * 16 + (lane & 15)]
+                                 : sum_ss(epi.ss, epi.nch, epi.m_pad, mt * 16 + (lane & 15), lane >> 4, 4);
         }
     }
     if constexpr (Epi::kNeedsRs) {
+        if (epi.nch != 0) {
 #pragma unroll
-        for (int j = 0; j < GL_TJ; ++j) {
-            float s = rs[j];
-            s += shfl_xor_f(s, 16);
-            s += shfl_xor_f(s, 32);
-            rs[j] = 1.0f / sqrtf(s / (float)epi.h + epi.eps);
+            for (int j = 0; j < TJ; ++j) {
+                float q = rs[j];
+                q += shfl_xor_f(q, 16);
+                q += shfl_xor_f(q, 32);
+                rs[j] = 1.0f / sqrtf(q / (float)epi.h + epi.eps);
+            }
         }
     }
 #pragma unroll
-    for (int j = 0; j < GL_TJ; ++j) {
-        const int mt = mt0 + wm * GL_TJ + j;
+    for (int j = 0; j < TJ; ++j) {
+        const int mt = mt0 + wm * TJ + j;
         if (mt >= n_mtiles) continue;
-        typename Epi::Pre pre[GL_TI / 2];
+        typename Epi::Pre pre[TI / 2];
 #pragma unroll
-        for (int i = 0; i < GL_TI; i += 2) {
-            int nt = nt0 + wn * GL_TI + i;
+        for (int i = 0; i < TI; i += 2) {
+            int nt = nt0 + wn * TI + i;
             if (nt >= n_ntiles) nt = n_ntiles - 2;
             pre[i / 2] = epi.pre(nt >> 1, mt, lane);
         }
 #pragma unroll
-        for (int i = 0; i < GL_TI; i += 2) {
-            const int nt = nt0 + wn * GL_TI + i;
+        for (int i = 0; i < TI; i += 2) {
+            const int nt = nt0 + wn * TI + i;
             if (nt >= n_ntiles) continue;
             if constexpr (Epi::kSliced) epi.slice(nt >> 1, kslice, mt, acc[i][j], acc[i + 1][j], lane, rs[j], pre[i / 2]);
             else epi(nt >> 1, mt, acc[i][j], acc[i + 1][j], lane, rs[j], pre[i / 2]);
@@ -1621,15 +1607,14 @@ hipError_t launch_gemm_lds_cfg(const spd_call &c, const __bf16 *Wp, const __bf16
                                const Epi &epi, int tile0 = 0, int msub = 1, int n_tiles = -1, int kslices = 1) {
     // with msub = 2 the tiles are counted in the shape of twice G's height (GemmHalf finishing a GemmBig launch)
     constexpr int BN = G::WN * G::TI;
-    constexpr int STAGE = (BN * (XS ? 1 : G::KPS) + G::WM * G::TJ * (XS ? 2 : G::KPS)) * 1024;
-    constexpr int NST = (!XS && G::KPS == 2) ? G::NST : 2;       // (only the loop with steps of two k-tiles knows three stages)
-    static_assert(NST * STAGE <= 160 * 1024, "the stages must fit the LDS of a compute unit");
+    constexpr int LDS = (XS ? G::NSTX : G::NST) * (BN * (XS ? 1 : 2) + G::WM * G::TJ * 2) * 1024;
+    static_assert(LDS <= 160 * 1024, "the stages must fit the LDS of a compute unit");
     const int BM = G::WM * G::TJ * msub;
     // the attribute is per kernel instantiation: set once, whichever thread comes first
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute((const void *)k_gemm_lds<Epi, G, XS>, hipFuncAttributeMaxDynamicSharedMemorySize, NST * STAGE);
+        attr_err = hipFuncSetAttribute((const void *)k_gemm_lds<Epi, G, XS>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     });
     if (attr_err != hipSuccess) return attr_err;
     const int n_ntiles = 2 * n_pairs, n_mtiles = (c.M + 15) / 16;
@@ -1640,8 +1625,8 @@ hipError_t launch_gemm_lds_cfg(const spd_call &c, const __bf16 *Wp, const __bf16
     if (n_tiles < 0) n_tiles = ord.TN * ord.TM - tile0;
     // msub = 1: whole rounds of 256, then eight equal shares (the spare workgroups of a ragged share exit at once)
     const int n_wgs = msub == 1 ? spd_tile_launch_size(n_tiles) : n_tiles * msub;
-    hipLaunchKernelGGL((k_gemm_lds<Epi, G, XS>), dim3(n_wgs * kslices), dim3(G::WN * G::WM * 64), NST * STAGE, c.s, Wp, Xp, Xlo, KT,
-                       n_ntiles, n_mtiles, ord, tile0, n_tiles, msub, kslices, n_wgs, epi);
+    hipLaunchKernelGGL((k_gemm_lds<Epi, G, XS>), dim3(n_wgs * kslices), dim3(G::WN * G::WM * 64), LDS, c.s, Wp, Xp, Xlo, KT, n_ntiles,
+                       n_mtiles, ord, tile0, n_tiles, msub, kslices, n_wgs, epi);
     return hipGetLastError();
 }
 
@@ -1658,11 +1643,6 @@ inline int gemm_tile_count(bool xs, int n_pairs, int n_mtiles) {
 template <bool XS, class Epi>
 hipError_t launch_gemm_lds(const spd_call &c, const __bf16 *Wp, const __bf16 *Xp, const __bf16 *Xlo, int n_pairs, int KT,
                            const Epi &epi, int kslices = 1) {
-    // both shapes measure the same on the 70B shard (the big one is ahead by 1-3 % on QKV and down);
-    // the mid one also takes an odd number of k-tiles (a step of the split kind is one k-tile anyway)
-    if constexpr (!XS) {
-        if ((KT % 2) != 0) return launch_gemm_lds_cfg<GemmMid, false>(c, Wp, Xp, Xlo, n_pairs, KT, epi, 0, 1, -1, kslices);
-    }
     // fewer 256 x 256 tiles than compute units (the QKV projection of a shard): 128 x 384 tiles when they
     // fill one round better
     const int n_mtiles = (c.M + 15) / 16;

@@ -236,6 +236,35 @@ def test_bf16_long_call_small_shape(gpu, w, flag, split):
     case.close()
 
 
+# contraction lengths at which the long call's GEMM can go wrong: fewer k-tiles than it has stages (one k-tile in the O
+# projection, three in QKV and gate/up), odd numbers of them (down: 23), and 66 partial sums of squares per token,
+# which a kernel of its own adds up before the gate/up projection of an SPD block
+KT_FEW = Workload(name="few-k-tiles", hidden=96, n_q_heads=2, n_kv_heads=2, head_dim=32, ffn=96, n_layers=1, tp=2, dtype=BF16,
+                  seed=31, batch=1, q_len=1, ctx=64, mask=(1,))
+KT_ODD = Workload(name="odd-k-tiles", hidden=2112, n_q_heads=4, n_kv_heads=2, head_dim=32, ffn=1440, n_layers=1, tp=2,
+                  dtype=BF16, seed=32, batch=1, q_len=1, ctx=64, mask=(1,))
+
+
+@pytest.mark.parametrize("w", [KT_FEW, KT_ODD], ids=lambda w: w.name)
+@pytest.mark.parametrize("flag", [1, 0], ids=["spd", "tp"])
+@pytest.mark.parametrize("split", [B.SPD_SPLIT_AUTO, B.SPD_SPLIT_ALWAYS, B.SPD_SPLIT_NEVER], ids=["default", "all-split", "no-split"])
+@pytest.mark.parametrize("q_len", [145, 384, 513, 530])
+def test_bf16_gemm_contraction_lengths(gpu, w, flag, split, q_len):
+    import torch
+    case = Case(w, gpu, ranks=range(w.tp), positions=[0], max_ctx=544, max_tokens=q_len, act_split=split)
+    X = inputs.hidden_states(w, q_len)
+    slots = torch.zeros((w.tp, q_len, w.hidden), dtype=torch.float32, device=gpu)
+    say(f"contraction lengths: {w.name} {q_len} tokens flag={flag} split={split}")
+    out = torch.empty((q_len, w.hidden), dtype=torch.float32, device=gpu)
+    B.spd_block_forward(case.dev.ctx, 0, flag, B.SPD_ALL_RANKS, case.dev.weights[0], case.dev.kv[0], [0], 1, q_len,
+                        case.to_dev(X), slots, out, case.dev.workspace)
+    torch.cuda.synchronize()
+    want, _ = O.block_all_ranks(case.sh, X, case.shards[0], case.caches[0], [0], 1, q_len, flag, {})
+    err = assert_close(out.cpu().numpy(), want, w, "block output")
+    say(f"  block output max err {err:.2e} (max |oracle| {np.max(np.abs(want)):.2f})")
+    case.close()
+
+
 # ------------------------------------------------------------------------------------------------
 # block with bias in the output projection (Sec. 4.1.2): both paths, both block kinds
 # ------------------------------------------------------------------------------------------------
