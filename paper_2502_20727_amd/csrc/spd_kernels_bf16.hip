@@ -103,6 +103,25 @@ __device__ __forceinline__ float row_rsqrt(const float *__restrict__ ss, int nch
     return 1.0f / sqrtf(s / (float)h + eps);
 }
 
+// 1 / sqrt(mean(x^2) + eps) of every token from its `nch` partial sums of squares, written over the first of them
+// (ss[0][m]); a consumer told nch = 0 takes the factor as it is.  A projection's epilogue that adds 256 partials per
+// token by itself waits for eight dependent rounds of loads per m-tile: 28 of 150 us in the gate/up projection of 1000
+// tokens of the 70B shard, 42 of 440 at 4096 (with 8 partials: one round, the launch then costs more than it saves).
+// One workgroup per m-tile, the only one that touches its tokens' columns.
+constexpr int ROW_SCALE_MIN_NCH = 65;
+__global__ void __launch_bounds__(512) k_row_scale(float *ss, int nch, int m_pad, int h, float eps) {
+    __shared__ float red[32][16];
+    const int r = threadIdx.x & 15, part = threadIdx.x >> 4, m = blockIdx.x * 16 + r;
+    red[part][r] = sum_ss(ss, nch, m_pad, m, part, 32);
+    __syncthreads();
+    if (threadIdx.x < 16) {
+        float t = 0.f;
+#pragma unroll
+        for (int q = 0; q < 32; ++q) t += red[q][threadIdx.x];
+        ss[m] = 1.0f / sqrtf(t / (float)h + eps);
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // prep: out = base + (slot0 + slot1 + ...), xhat = fp16(out * gain) in packed layout (plus its
 // lo plane), and the partial sums of squares of `out` per (k-chunk, token).  One wave per
@@ -2641,6 +2660,11 @@ hipError_t mlp_half(const spd_call &c, const char *w, int spd, float *slot, cons
     e1.uhat = uhat; e1.ulo = ulo;
     if (c.on(SPD_STAGE_GATEUP)) {
         spd_stage_scope prof(c, SPD_STAGE_GATEUP);
+        if (M > 16 * SKINNY_MAX_MTILES && e1.nch >= ROW_SCALE_MIN_NCH) {
+            hipLaunchKernelGGL(k_row_scale, dim3(cdiv(M, 16)), dim3(512), 0, c.s, (float *)(c.ws + D.ws_ss2), e1.nch, D.m_pad, D.h, D.eps);
+            SPD_TRY(hipGetLastError());
+            e1.nch = 0;
+        }
         if (M <= 16) {
             if (D.gud_cols) {
                 // decode: the copy with narrow column groups, one workgroup per group
