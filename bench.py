@@ -104,10 +104,12 @@ def stage_kernel(w, stage: str) -> str:
                 if tiles > 256 and 0 < tiles % 256 <= 128:
                     one += "+k_gemm_lds<EpiGU,GemmHalf,false>"
             return one + ("x2" if two_chains else "")          # x2: one launch per chain of a two-chain prefill
-        if M > 16 and f_pairs >= 128:
-            return "k_mid<8>+k_mid_finish<EpiGU>"
         if M > 16:
-            return "k_skinny<8,MT,false,0,EpiGU>"
+            if M <= 128 and f_pairs * (w.hidden // 32) >= 48 * 1024:
+                return f"k_mid<{2 if M <= 32 else 4 if M <= 64 else 8}>+k_mid_finish<EpiGU>"
+            half = M > 128 and (f_pairs >= 64 or (2 * f_pairs + 15) // 16 * ((M + 127) // 128) >= 32)
+            shape = "GemmSmall" if M <= 64 else "GemmHalf" if half else "GemmSquare"
+            return f"k_gemm_lds<EpiPark,{shape},false>+k_mid_finish<EpiGU>"
         if f_pairs >= 192 or (f_pairs >= 64 and f_pairs % 256 != 0):
             return "k_gemv<16,2,false,0,EpiGU>"            # 16-column tiles, or the decode-only copy with narrow groups
         return "k_gemv<8,2,false,1,EpiGU>+k_gemv_finish<EpiGU>"

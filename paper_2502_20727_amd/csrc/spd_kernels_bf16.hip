@@ -27,6 +27,12 @@
 
 namespace {
 
+#define SPD_TRY(x)                       \
+    do {                                 \
+        hipError_t e_ = (x);             \
+        if (e_ != hipSuccess) return e_; \
+    } while (0)
+
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -479,6 +485,7 @@ const float4 tb##j = *(const float4 *)(slots + (size_t)min(s0 + j, last) * slot_
 // kNeedsRs: the tile must be scaled by 1/sqrt(mean(x^2)+eps) of the token, which the caller
 // computes from the partial sums of squares ss[nch][m_pad].
 struct EpiQKV {
+    static constexpr bool kLong = true;        // used by calls of any length
     static constexpr bool kNeedsRs = true;
     static constexpr bool kSliced = false;
     int M, q_len, q, kv, d, h, max_ctx, nch, m_pad;
@@ -553,7 +560,6 @@ struct EpiQKV {
 // the slices in ascending order, rounds, and appends the new key and value to the cache.
 struct EpiQKVPart {
     static constexpr bool kNeedsRs = true;
-    static constexpr bool kSliced = true;      // a kernel whose workgroups own one K slice each calls slice() with its slice number
     int M, q_len, q, kv, d, h, nqkv, nch, m_pad;
     int part_rows;             // token rows per slice of `part`
     float eps;
@@ -598,13 +604,11 @@ struct EpiQKVPart {
         *(float4 *)(dst + ca) = lo;
         *(float4 *)(dst + cb) = hi;
     }
-    __device__ __forceinline__ void operator()(int pair, int mt, f32x4 a, f32x4 b, int lane, float rs, const Pre &p) const {
-        slice(pair, 0, mt, a, b, lane, rs, p);
-    }
 };
 
 template <bool MID>      // MID: the epilogue can also perform the kept attention sync point (spd = 2)
 struct EpiOT {
+    static constexpr bool kLong = !MID;
     static constexpr bool kNeedsRs = false;
     static constexpr bool kSliced = false;
     int M, h, spd, m_pad;
@@ -706,6 +710,7 @@ struct EpiOT {
 };
 
 struct EpiGU {
+    static constexpr bool kLong = true;
     static constexpr bool kNeedsRs = true;
     static constexpr bool kSliced = false;
     int M, h, f_pad, nch, m_pad;
@@ -753,6 +758,7 @@ struct EpiGU {
 
 template <bool FUSED>
 struct EpiDownT {
+    static constexpr bool kLong = !FUSED;
     static constexpr bool kNeedsRs = false;
     static constexpr bool kSliced = false;
     int M, h, spd;
@@ -832,6 +838,25 @@ struct EpiDownT {
         sq += shfl_xor_f(sq, 16);
         sq += shfl_xor_f(sq, 32);
         if (g == 0) ss1[(size_t)pair * m_pad + m] = sq;
+    }
+};
+
+// Epilogue of a K-sliced launch whose real epilogue is not linear: parks the tile pair's partial sums in
+// kpart[pair][slice][m-tile] for k_mid_finish.
+struct EpiPark {
+    static constexpr bool kNeedsRs = false;
+    static constexpr bool kSliced = true;
+    int KS, n_mtiles;
+    f32x4 *kpart;
+    const float *ss = nullptr;
+    int nch = 0, m_pad = 0, h = 0;
+    float eps = 0.f;
+    struct Pre {};
+    __device__ __forceinline__ Pre pre(int, int, int) const { return Pre(); }
+    __device__ __forceinline__ void slice(int pair, int ks, int mt, f32x4 a, f32x4 b, int lane, float, const Pre &) const {
+        f32x4 *dst = kpart + ((((size_t)pair * KS + ks) * n_mtiles + mt) * 2) * 64 + lane;
+        dst[0] = a;
+        dst[64] = b;
     }
 };
 
@@ -1040,7 +1065,7 @@ __global__ void __launch_bounds__(256) k_gemv_finish(const float *__restrict__ k
 
 // ------------------------------------------------------------------------------------------
 // Projection for 17 .. 16*MT tokens per workgroup ("skinny": still bound by streaming the weights); fp16 operands.
-// Like k_gemv, one workgroup per pair of n-tiles (or narrow group) and slice of K, the W waves
+// Like k_gemv, one workgroup per pair of n-tiles and slice of K, the W waves
 // splitting K; every wave multiplies each weight fragment it streams with MT m-tiles of
 // activations (read through the L2, where they stay resident).  grid = (pairs, KS, groups of MT
 // m-tiles).  The W x MT partial tile pairs meet in LDS; wave w finishes m-tiles w, w + W, ...
@@ -1053,8 +1078,7 @@ struct SkinnyBatch {
 
 template <int W, int MT, bool SPLIT, int MODE, class Epi>
 __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp, const __bf16 *__restrict__ Xhi,
-                                                    const __bf16 *__restrict__ Xlo, int KT, int KS, int n_mtiles, int rows,
-                                                    Epi epi) {
+                                                    const __bf16 *__restrict__ Xlo, int KT, int KS, int n_mtiles, Epi epi) {
     extern __shared__ __attribute__((aligned(16))) char sk_lds[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int pair = blockIdx.x, ks = blockIdx.y, mt0 = blockIdx.z * MT;
@@ -1064,18 +1088,8 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
     f32x4 acc[MT][2];
 #pragma unroll
     for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const bf16x8 *wa, *wb;
-    size_t kstr;
-    if (rows == 16) {
-        wa = (const bf16x8 *)(Wp + spd_frag_index(2 * pair, 0, KT)) + lane;
-        wb = (const bf16x8 *)(Wp + spd_frag_index(2 * pair + 1, 0, KT)) + lane;
-        kstr = 64;
-    } else {
-        const int rr = (lane & 15) < rows ? (lane & 15) : rows - 1;
-        wa = (const bf16x8 *)Wp + (size_t)pair * KT * 8 * rows + (lane >> 4) * rows + rr;
-        wb = wa + 4 * rows;
-        kstr = 8 * rows;
-    }
+    const bf16x8 *wa = (const bf16x8 *)(Wp + spd_frag_index(2 * pair, 0, KT)) + lane;
+    const bf16x8 *wb = (const bf16x8 *)(Wp + spd_frag_index(2 * pair + 1, 0, KT)) + lane;
     // m-tiles past the call's last one repeat it (their results are dropped)
     const bf16x8 *xh[MT], *xl[MT];
 #pragma unroll
@@ -1085,8 +1099,8 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
         xl[i] = (const bf16x8 *)(Xlo + spd_frag_index(mt, 0, KT)) + lane;
     }
     auto load = [&](SkinnyBatch<MT, SPLIT> &B, int kt) {
-        B.fa = __builtin_nontemporal_load(wa + (size_t)kt * kstr);
-        B.fb = __builtin_nontemporal_load(wb + (size_t)kt * kstr);
+        B.fa = __builtin_nontemporal_load(wa + (size_t)kt * 64);
+        B.fb = __builtin_nontemporal_load(wb + (size_t)kt * 64);
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
             B.fh[i] = xh[i][(size_t)kt * 64];
@@ -1145,7 +1159,7 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
 }
 
 // ------------------------------------------------------------------------------------------
-// Projection with many n-tiles for 17 .. 512 tokens ("mid").  In k_skinny every workgroup pulls all
+// Projection with many n-tiles for 17 .. 128 tokens ("mid").  In k_skinny every workgroup pulls all
 // activations of its slice of K through the L2 for only two n-tiles, and from about 64 tokens on
 // that traffic (K x M x 2 B per workgroup), not the weight stream, sets the time.  Here a
 // workgroup owns 8 pairs of n-tiles (wave w: pair 8 * group + w) and one of KS slices of K; all
@@ -1160,30 +1174,27 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
 // ------------------------------------------------------------------------------------------
 constexpr int MID_KB = 2;        // k-tiles per stage
 constexpr int MID_PAIRS = 8;     // pairs of n-tiles per workgroup (one per wave)
-template <int MT, bool XS>
+template <int MT>
 struct MidSet {
-    bf16x8 wa[MID_KB], wb[MID_KB], x[MT >= 4 ? MT / 4 : 1], xl[XS ? (MT >= 4 ? MT / 4 : 1) : 1];
+    bf16x8 wa[MID_KB], wb[MID_KB], x[MT >= 4 ? MT / 4 : 1];
 };
 
-// XS: the activations are hi + lo pairs (second plane at Xlo); both planes go through LDS and every weight
-// fragment meets both.
-template <int MT, bool XS>
-__global__ void __launch_bounds__(MID_PAIRS * 64) k_mid(const __bf16 *__restrict__ Wp, const __bf16 *__restrict__ Xp,
-                                                        const __bf16 *__restrict__ Xlo, int KT, int KS, int n_pairs,
+template <int MT>
+__global__ void __launch_bounds__(MID_PAIRS * 64) k_mid(const __bf16 *__restrict__ Wp, const __bf16 *__restrict__ Xp, int KT, int KS, int n_pairs,
                                                         int n_mtiles, f32x4 *__restrict__ kpart) {
     // activation fragments of a stage fetched by one wave (with 2 m-tiles there are only 4 fragments: waves
     // 4 .. 7 fetch and store the same ones again, which keeps the loop free of branches)
-    constexpr int XPW = MT >= 4 ? MT / 4 : 1, NFRAG = MT * MID_KB, PLANES = XS ? 2 : 1;
-    __shared__ __attribute__((aligned(1024))) char lds[2 * PLANES * NFRAG * 1024];
+    constexpr int XPW = MT >= 4 ? MT / 4 : 1, NFRAG = MT * MID_KB;
+    __shared__ __attribute__((aligned(1024))) char lds[2 * NFRAG * 1024];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int pair = blockIdx.x * MID_PAIRS + wave;
     const bool live = pair < n_pairs;
     if (!live) pair = n_pairs - 1;        // a spare wave repeats the last pair and drops the result
-    const int ks = blockIdx.y, mt0 = blockIdx.z * MT;            // grid.z: groups of MT m-tiles (calls of more than 16 MT tokens)
+    const int ks = blockIdx.y;
     const int nst = (KT + MID_KB - 1) / MID_KB;                  // stages in all of K
     const int sb0 = (int)(((long)ks * nst) / KS), sb1 = (int)(((long)(ks + 1) * nst) / KS);
     const int ns = sb1 - sb0;                                    // >= 1: the launcher keeps KS <= nst
-    const int rot = (int)((blockIdx.x * 5u + blockIdx.y * 3u + blockIdx.z * 7u) % (unsigned)ns);
+    const int rot = (int)((blockIdx.x * 5u + blockIdx.y * 3u) % (unsigned)ns);
     auto stage_of = [&](int st) {
         st = st < ns ? st : ns - 1;
         st += rot;
@@ -1194,21 +1205,20 @@ __global__ void __launch_bounds__(MID_PAIRS * 64) k_mid(const __bf16 *__restrict
     size_t xoff[XPW];
 #pragma unroll
     for (int i = 0; i < XPW; ++i) {
-        const int mt = mt0 + ((wave * XPW + i) % NFRAG) / MID_KB;
+        const int mt = ((wave * XPW + i) % NFRAG) / MID_KB;
         xoff[i] = spd_frag_index(mt < n_mtiles ? mt : n_mtiles - 1, 0, KT) + (size_t)lane * 8;
     }
     f32x4 acc[MT][2];
 #pragma unroll
     for (int m = 0; m < MT; ++m) acc[m][0] = acc[m][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-    auto load = [&](MidSet<MT, XS> &S, int st) {
+    auto load = [&](MidSet<MT> &S, int st) {
         const int kt0 = stage_of(st) * MID_KB;
 #pragma unroll
         for (int i = 0; i < XPW; ++i) {
             const int kt = kt0 + ((wave * XPW + i) % NFRAG) % MID_KB;
             const size_t o = xoff[i] + (size_t)(kt < KT ? kt : KT - 1) * 512;
             S.x[i] = *(const bf16x8 *)(Xp + o);
-            if (XS) S.xl[i] = *(const bf16x8 *)(Xlo + o);
         }
 #pragma unroll
         for (int kb = 0; kb < MID_KB; ++kb) {
@@ -1217,35 +1227,29 @@ __global__ void __launch_bounds__(MID_PAIRS * 64) k_mid(const __bf16 *__restrict
             S.wb[kb] = __builtin_nontemporal_load(wb + (size_t)kt * 64);
         }
     };
-    auto put = [&](const MidSet<MT, XS> &S, int buf) {
+    auto put = [&](const MidSet<MT> &S, int buf) {
 #pragma unroll
         for (int i = 0; i < XPW; ++i) {
-            char *dst = lds + ((buf * PLANES) * NFRAG + (wave * XPW + i) % NFRAG) * 1024 + lane * 16;
+            char *dst = lds + (buf * NFRAG + (wave * XPW + i) % NFRAG) * 1024 + lane * 16;
             *(bf16x8 *)dst = S.x[i];
-            if (XS) *(bf16x8 *)(dst + NFRAG * 1024) = S.xl[i];
         }
     };
-    auto compute = [&](const MidSet<MT, XS> &S, int buf, int st) {
+    auto compute = [&](const MidSet<MT> &S, int buf, int st) {
         const int kt0 = stage_of(st) * MID_KB;
 #pragma unroll
         for (int kb = 0; kb < MID_KB; ++kb) {
             if (kb > 0 && kt0 + kb >= KT) break;                 // odd number of k-tiles: the last stage holds one
 #pragma unroll
             for (int m = 0; m < MT; ++m) {
-                const char *src = lds + ((buf * PLANES) * NFRAG + m * MID_KB + kb) * 1024 + lane * 16;
+                const char *src = lds + (buf * NFRAG + m * MID_KB + kb) * 1024 + lane * 16;
                 const bf16x8 x = *(const bf16x8 *)src;
                 acc[m][0] = MFMA16(S.wa[kb], x, acc[m][0]);
                 acc[m][1] = MFMA16(S.wb[kb], x, acc[m][1]);
-                if (XS) {
-                    const bf16x8 xl = *(const bf16x8 *)(src + NFRAG * 1024);
-                    acc[m][0] = MFMA16(S.wa[kb], xl, acc[m][0]);
-                    acc[m][1] = MFMA16(S.wb[kb], xl, acc[m][1]);
-                }
             }
         }
     };
     // stage t lives in set t % 4, its activations in LDS buffer t % 2
-    MidSet<MT, XS> st[4];
+    MidSet<MT> st[4];
     load(st[0], 0);
     load(st[1], 1);
     load(st[2], 2);
@@ -1272,8 +1276,8 @@ __global__ void __launch_bounds__(MID_PAIRS * 64) k_mid(const __bf16 *__restrict
     if (!live) return;
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
-        if (mt0 + m >= n_mtiles) break;
-        f32x4 *dst = kpart + ((((size_t)pair * KS + ks) * n_mtiles + mt0 + m) * 2) * 64 + lane;
+        if (m >= n_mtiles) break;
+        f32x4 *dst = kpart + ((((size_t)pair * KS + ks) * n_mtiles + m) * 2) * 64 + lane;
         dst[0] = acc[m][0];
         dst[64] = acc[m][1];
     }
@@ -1294,7 +1298,7 @@ __global__ void __launch_bounds__(MID_PAIRS * 64) k_mid_finish(const f32x4 *__re
     const bool live = pair < n_pairs;
     typename Epi::Pre pre;
     if (live) pre = epi.pre(pair, mt, lane);
-    // the first slices are requested before the norm statistics are dealt with
+    // the first eight slices are requested before the norm statistics are dealt with, the others eight at a time
     const f32x4 *src = kpart + (((size_t)(live ? pair : n_pairs - 1) * KS * n_mtiles + mt) * 2) * 64 + lane;
     const size_t sstr = (size_t)n_mtiles * 128;
     f32x4 ta[8], tb[8];
@@ -1306,19 +1310,21 @@ __global__ void __launch_bounds__(MID_PAIRS * 64) k_mid_finish(const f32x4 *__re
     }
     float rs = 1.f;
     if constexpr (Epi::kNeedsRs) {
-        const int r = threadIdx.x & 15, part = threadIdx.x >> 4;       // 32 parts
-        float sq = 0.f;
-        for (int c = part; c < epi.nch; c += 32) sq += epi.ss[(size_t)c * epi.m_pad + mt * 16 + r];
-        red[part][r] = sq;
-        __syncthreads();
-        if (threadIdx.x < 16) {
-            float t = 0.f;
+        if (epi.nch == 0) {                  // the factor itself (k_row_scale)
+            rs = epi.ss[mt * 16 + (lane & 15)];
+        } else {
+            const int r = threadIdx.x & 15, part = threadIdx.x >> 4;       // 32 parts
+            red[part][r] = sum_ss(epi.ss, epi.nch, epi.m_pad, mt * 16 + r, part, 32);
+            __syncthreads();
+            if (threadIdx.x < 16) {
+                float t = 0.f;
 #pragma unroll
-            for (int q = 0; q < 32; ++q) t += red[q][threadIdx.x];
-            rs_row[threadIdx.x] = 1.0f / sqrtf(t / (float)epi.h + epi.eps);
+                for (int q = 0; q < 32; ++q) t += red[q][threadIdx.x];
+                rs_row[threadIdx.x] = 1.0f / sqrtf(t / (float)epi.h + epi.eps);
+            }
+            __syncthreads();
+            rs = rs_row[lane & 15];
         }
-        __syncthreads();
-        rs = rs_row[lane & 15];
     }
     if (!live) return;
     f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
@@ -1328,48 +1334,21 @@ __global__ void __launch_bounds__(MID_PAIRS * 64) k_mid_finish(const f32x4 *__re
             a += ta[j];
             b += tb[j];
         }
-    for (int sl = 8; sl < KS; ++sl) {
-        a += src[(size_t)sl * sstr];
-        b += src[(size_t)sl * sstr + 64];
+    for (int s0 = 8; s0 < KS; s0 += 8) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int sl = s0 + j < KS ? s0 + j : KS - 1;
+            ta[j] = src[(size_t)sl * sstr];
+            tb[j] = src[(size_t)sl * sstr + 64];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (s0 + j < KS) {
+                a += ta[j];
+                b += tb[j];
+            }
     }
     epi(pair, mt, a, b, lane, rs, pre);
-}
-
-// Adds the K slices that EpiQKVPart left for a call of more than one token per sequence (the
-// decode kernel adds them itself): queries to hi + lo bf16 pairs, keys and values rounded into the
-// cache.  One thread per 4 consecutive columns of a token.
-__global__ void __launch_bounds__(256) k_qkv_gather(const float *__restrict__ part, int KS, int m_pad, int M, int q_len, int q,
-                                                    int kv, int d, int max_ctx, spd_positions P, __bf16 *__restrict__ qbuf,
-                                                    __bf16 *__restrict__ qlo, __bf16 *__restrict__ kc, __bf16 *__restrict__ vc) {
-    const int nqkv = (q + 2 * kv) * d, n4 = nqkv / 4;
-    const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (id >= (int64_t)M * n4) return;
-    const int m = (int)(id / n4), col = (int)(id % n4) * 4;
-    const float *src = part + (size_t)m * nqkv + col;
-    // all slices are requested before the first is added (KS <= SPD_MAX_QKV_SLICES)
-    float4 sl[SPD_MAX_QKV_SLICES];
-#pragma unroll
-    for (int s = 0; s < SPD_MAX_QKV_SLICES; ++s) sl[s] = *(const float4 *)(src + (size_t)(s < KS ? s : KS - 1) * m_pad * nqkv);
-    float4 acc = sl[0];
-#pragma unroll
-    for (int s = 1; s < SPD_MAX_QKV_SLICES; ++s)
-        if (s < KS) {
-            acc.x += sl[s].x; acc.y += sl[s].y; acc.z += sl[s].z; acc.w += sl[s].w;
-        }
-    const bf16x4 hi = cvt4(acc.x, acc.y, acc.z, acc.w);
-    const int qd = q * d, bseq = m / q_len, pos = P.pos[bseq] + (m % q_len);
-    if (col < qd) {
-        *(bf16x4 *)(qbuf + (size_t)m * qd + col) = hi;
-        *(bf16x4 *)(qlo + (size_t)m * qd + col) = cvt4_lo(acc.x, acc.y, acc.z, acc.w, hi);
-    } else if (col < qd + kv * d) {
-        const int c = col - qd, head = c / d, dc = c % d;
-        *(bf16x4 *)(kc + ((size_t)bseq * kv + head) * (size_t)max_ctx * d + spd_kcache_off(pos, dc, d)) = hi;
-    } else {
-        const int c = col - qd - kv * d, head = c / d, dc = c % d;
-        __bf16 *dst = vc + ((size_t)bseq * kv + head) * (size_t)max_ctx * d;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) dst[spd_vcache_off(pos, dc + i, d)] = hi[i];
-    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1402,6 +1381,12 @@ struct GemmTall {     // 128 x 384: for few n-tiles, where 256 x 256 tiles leave
 struct GemmWide {     // 160 x 256, every wave all 10 n-tiles of 2 m-tiles: for split activations and few n-tiles
     static constexpr int WN = 1, WM = 8, TI = 10, TJ = 2, NST = 2, NSTX = 3;      // (80 n-tiles x 512 m-tiles = exactly 256 tiles)
 };
+struct GemmSquare {   // 128 x 128, 64 KiB per k-tile pair and round of four stages: calls of 65 .. 256 tokens and few n-tiles, in K slices
+    static constexpr int WN = 4, WM = 2, TI = 2, TJ = 4, NST = 4, NSTX = 5;
+};
+struct GemmSmall {    // 128 x 64: calls of at most 64 tokens, in K slices
+    static constexpr int WN = 4, WM = 2, TI = 2, TJ = 2, NST = 6, NSTX = 6;
+};
 // operand of s_waitcnt: at most vm vector loads and lgkm LDS / scalar operations still in flight (63 / 15: any number)
 constexpr int waitcnt_imm(int vm, int lgkm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4) | (lgkm << 8); }
 // descriptor of `bytes` bytes at p (raw access)
@@ -1412,7 +1397,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t panel(const char *p, unsigned 
 template <class Epi, class G, bool XS>
 __global__ void __launch_bounds__(G::WN *G::WM * 64, 1)
     k_gemm_lds(const __bf16 *Wp, const __bf16 *Xp, const __bf16 *Xlo, int KT, int n_ntiles, int n_mtiles, spd_tile_order ord,
-               int tile0, int n_tiles, int msub, int kslices, int wgs_per_slice, Epi epi) {
+               int tile0, int n_tiles, int msub, int kslices, Epi epi) {
     constexpr int TI = G::TI, TJ = G::TJ, NST = XS ? G::NSTX : G::NST;
     constexpr int NW = G::WN * G::WM, BN = G::WN * TI, BM = G::WM * TJ;
     constexpr int KW = XS ? 1 : 2;                                       // k-tiles per stage
@@ -1424,26 +1409,25 @@ __global__ void __launch_bounds__(G::WN *G::WM * 64, 1)
     const int wn = wave % G::WN, wm = wave / G::WN;
     // A launch covers `n_tiles` tiles of the order from `tile0` on, each cut into `msub` workgroup tiles along M
     // (1, or 2 for the launch that finishes a ragged last round with half tiles; `ord` counts the uncut tiles).
-    // kslices > 1 (sliced epilogues only): the launch is kslices copies of the tile grid, copy s contracting
-    // the s-th part of K and handing its slice number to the epilogue.
-    int bid = (int)blockIdx.x, kslice = 0;
-    if (kslices > 1) {
-        kslice = bid / wgs_per_slice;
-        bid -= kslice * wgs_per_slice;
-    }
-    const int kt_first = (int)(((long)kslice * KT) / kslices), nk = (int)(((long)(kslice + 1) * KT) / kslices) - kt_first;
-    int tn, tm, sub = 0;
+    // kslices > 1 (sliced epilogues only): the launch covers the tiles once per slice of K, slice after slice, workgroups
+    // of slice s contracting the s-th part of K and handing s to the epilogue.  The XCDs take equal shares of all
+    // (slice, tile) items together: dealt slice by slice, 3 slices of 84 tiles gave most XCDs 33 workgroups for
+    // their 32 compute units, a second round for one of them.
+    int tn, tm, sub = 0, kslice = 0;
     {
         int idx;
         if (msub == 1) {
-            idx = spd_tile_deal(bid, n_tiles);
+            idx = spd_tile_deal((int)blockIdx.x, n_tiles * kslices);
             if (idx < 0) return;                 // spare workgroup of a ragged share (whole workgroup, before any barrier)
+            kslice = idx / n_tiles;
+            idx -= kslice * n_tiles;
         } else {
-            idx = bid / msub;
-            sub = bid % msub;
+            idx = (int)blockIdx.x / msub;
+            sub = (int)blockIdx.x % msub;
         }
         spd_tile_at(ord, tile0 + idx, tn, tm);
     }
+    const int kt_first = (int)(((long)kslice * KT) / kslices), nk = (int)(((long)(kslice + 1) * KT) / kslices) - kt_first;
     const int nt0 = tn * BN, mt0 = (tm * msub + sub) * BM;
     if (mt0 >= n_mtiles) return;                 // second half of a tile whose first half holds all the rows (whole workgroup)
     // Copies go through buffer descriptors of the tile's panels: a lane's offset plus one wave-uniform offset per
@@ -1471,11 +1455,16 @@ __global__ void __launch_bounds__(G::WN *G::WM * 64, 1)
         const int t = (wave * CX + n) >> 1;
         xsrc[n] = (unsigned)(t < m_rows ? t : m_rows - 1) * pitch + kt_first * 1024;
     }
-    f32x4 acc[TI][TJ];
+    // Where the registers allow, the lo plane's products are summed on their own: half as many roundings of the large sums.
+    constexpr bool LO_ACC = XS && TI * TJ <= 16;
+    f32x4 acc[TI][TJ], acc_lo[LO_ACC ? TI : 1][LO_ACC ? TJ : 1];
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < TJ; ++j) {
+            acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            if constexpr (LO_ACC) acc_lo[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
     // copy n of stage st into the place `slot` (a k-tile past the end, the odd one's partner, repeats the last)
     auto copy1 = [&](int st, int slot, int n) __attribute__((always_inline)) {
         if (n < CW) {
@@ -1517,7 +1506,7 @@ __global__ void __launch_bounds__(G::WN *G::WM * 64, 1)
 
     // the MFMAs of a sub-step on (a, b); meanwhile NR fragments of the next one are read into (an, bn) and, with COPY, the
     // copies of stage cst go out
-    auto substep = [&](auto nr_, auto copy_, const bf16x8(&a)[TI], const bf16x8(&b)[TJ], bf16x8(&an)[TI], bf16x8(&bn)[TJ], int rslot,
+    auto substep = [&](auto nr_, auto copy_, auto lo_, const bf16x8(&a)[TI], const bf16x8(&b)[TJ], bf16x8(&an)[TI], bf16x8(&bn)[TJ], int rslot,
                        int rp, int cst, int cslot) __attribute__((always_inline)) {
         constexpr int NR = decltype(nr_)::value, NM = TI * TJ;
         constexpr bool COPY = decltype(copy_)::value;
@@ -1527,7 +1516,8 @@ __global__ void __launch_bounds__(G::WN *G::WM * 64, 1)
 #pragma unroll
             for (int j = 0; j < TJ; ++j) {
                 const int n = i * TJ + j;
-                acc[i][j] = MFMA16(a[i], b[j], acc[i][j]);
+                if constexpr (LO_ACC && decltype(lo_)::value) acc_lo[i][j] = MFMA16(a[i], b[j], acc_lo[i][j]);
+                else acc[i][j] = MFMA16(a[i], b[j], acc[i][j]);
                 __builtin_amdgcn_sched_barrier(0);
                 if (r < NR && n >= (2 * NR <= NM ? 2 * r : r * NM / NR)) read1(rslot, rp, r++, an, bn);
                 if (COPY && cp < NCP && n >= cp * (NM / NCP) + 1) copy1(cst, cslot, cp++);
@@ -1539,16 +1529,16 @@ __global__ void __launch_bounds__(G::WN *G::WM * 64, 1)
         constexpr bool COPY = decltype(copy_)::value, ODD = decltype(odd_)::value;
         using All = std::integral_constant<int, TI + TJ>;
         const int next = slot + 1 == NST ? 0 : slot + 1;
-        if constexpr (XS) substep(std::integral_constant<int, TJ>(), std::false_type(), ODD ? a1 : a0, b0, ODD ? a0 : a1, b1, slot, 1, 0, 0);
-        else substep(All(), std::false_type(), a0, b0, a1, b1, slot, 1, 0, 0);
+        if constexpr (XS) substep(std::integral_constant<int, TJ>(), std::false_type(), std::false_type(), ODD ? a1 : a0, b0, ODD ? a0 : a1, b1, slot, 1, 0, 0);
+        else substep(All(), std::false_type(), std::false_type(), a0, b0, a1, b1, slot, 1, 0, 0);
         // the next stage's copies of this wave have landed, those of the NST - 2 stages after it may be in flight; every
         // read of the current stage is done
         __builtin_amdgcn_s_waitcnt(waitcnt_imm(COPY ? (NST - 2) * NCP : 0, 0));
         asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         // (in the last step: fragments read and never used)
-        if constexpr (XS) substep(All(), copy_, ODD ? a1 : a0, b1, ODD ? a0 : a1, b0, next, 0, s + NST, slot);
-        else substep(All(), copy_, a1, b1, a0, b0, next, 0, s + NST, slot);
+        if constexpr (XS) substep(All(), copy_, std::true_type(), ODD ? a1 : a0, b1, ODD ? a0 : a1, b0, next, 0, s + NST, slot);
+        else substep(All(), copy_, std::false_type(), a1, b1, a0, b0, next, 0, s + NST, slot);
         slot = next;
     };
     int s = 0;
@@ -1576,6 +1566,12 @@ __global__ void __launch_bounds__(G::WN *G::WM * 64, 1)
 #pragma unroll
                 for (int j = 0; j < TJ; ++j) acc[i][j] = MFMA16(a0[i], b0[j], acc[i][j]);
         }
+    }
+    if constexpr (LO_ACC) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) acc[i][j] += acc_lo[i][j];
     }
     // norm factors of all the wave's m-tiles first, so that their loads are in flight together
     float rs[TJ];
@@ -1643,25 +1639,16 @@ hipError_t launch_gemm_lds_cfg(const spd_call &c, const __bf16 *Wp, const __bf16
     spd_pick_block(ord.TN, ord.TM, BN * 16, BM * 16, ord.bn, ord.bm);
     if (n_tiles < 0) n_tiles = ord.TN * ord.TM - tile0;
     // msub = 1: whole rounds of 256, then eight equal shares (the spare workgroups of a ragged share exit at once)
-    const int n_wgs = msub == 1 ? spd_tile_launch_size(n_tiles) : n_tiles * msub;
-    hipLaunchKernelGGL((k_gemm_lds<Epi, G, XS>), dim3(n_wgs * kslices), dim3(G::WN * G::WM * 64), LDS, c.s, Wp, Xp, Xlo, KT, n_ntiles,
-                       n_mtiles, ord, tile0, n_tiles, msub, kslices, n_wgs, epi);
+    // (msub = 2 comes with one slice only)
+    const int n_wgs = msub == 1 ? spd_tile_launch_size(n_tiles * kslices) : n_tiles * msub;
+    hipLaunchKernelGGL((k_gemm_lds<Epi, G, XS>), dim3(n_wgs), dim3(G::WN * G::WM * 64), LDS, c.s, Wp, Xp, Xlo, KT, n_ntiles,
+                       n_mtiles, ord, tile0, n_tiles, msub, kslices, epi);
     return hipGetLastError();
 }
 
-// Number of workgroup tiles of the shape launch_gemm_lds() picks (below 256: one launch)
-inline int gemm_tile_count(bool xs, int n_pairs, int n_mtiles) {
-    const int big = ((2 * n_pairs + 15) / 16) * ((n_mtiles + 15) / 16), tall = ((2 * n_pairs + 7) / 8) * ((n_mtiles + 23) / 24);
-    const int wide = ((2 * n_pairs + 9) / 10) * ((n_mtiles + 15) / 16);
-    if (xs && big < 224 && wide <= 256 && wide > tall && 160 * ((wide + 255) / 256) < 192 * ((tall + 255) / 256)) return wide;
-    if (big < 224 && tall <= 256 && tall > big) return tall;
-    return big;
-}
-
-// kslices > 1: K is cut into that many parts, each part a copy of the tile grid in the same launch (sliced epilogues only)
 template <bool XS, class Epi>
 hipError_t launch_gemm_lds(const spd_call &c, const __bf16 *Wp, const __bf16 *Xp, const __bf16 *Xlo, int n_pairs, int KT,
-                           const Epi &epi, int kslices = 1) {
+                           const Epi &epi) {
     // fewer 256 x 256 tiles than compute units (the QKV projection of a shard): 128 x 384 tiles when they
     // fill one round better
     const int n_mtiles = (c.M + 15) / 16;
@@ -1669,28 +1656,30 @@ hipError_t launch_gemm_lds(const spd_call &c, const __bf16 *Wp, const __bf16 *Xp
     if constexpr (XS) {
         // split activations, few n-tiles: 160 x 256 tiles when they come to one full round of the chip with less work
         // per tile than the other shapes (the QKV projection of the 70B shard: 8 x 32 = 256 tiles)
-        const int wide = ((2 * n_pairs + 9) / 10) * ((n_mtiles + 15) / 16);
-        if (big < 224 && wide <= 256 && wide > tall && 160 * ((wide + 255) / 256) < 192 * ((tall + 255) / 256))
-            return launch_gemm_lds_cfg<GemmWide, XS>(c, Wp, Xp, Xlo, n_pairs, KT, epi, 0, 1, -1, kslices);
+        // (a call that is not one of two chains: only when the 256 x 128 tiles below would need a second round; 4096
+        // tokens: 128 wide tiles 176 us, 160 half tiles 155)
+        const int wide = ((2 * n_pairs + 9) / 10) * ((n_mtiles + 15) / 16), halves = ((2 * n_pairs + 15) / 16) * ((n_mtiles + 7) / 8);
+        if (big < 224 && wide <= 256 && wide > tall && (c.chained || halves > 256))
+            return launch_gemm_lds_cfg<GemmWide, XS>(c, Wp, Xp, Xlo, n_pairs, KT, epi);
     }
     {
         // at most half a round of 256 x 256 tiles: 256 x 128 half tiles when they occupy more compute units than
         // the other shapes
         const int halves = ((2 * n_pairs + 15) / 16) * ((n_mtiles + 7) / 8);
         const int other = (big < 224 && tall <= 256 && tall > big) ? tall : big;
-        if (kslices == 1 && big <= 128 && halves <= 256 && halves > other)
+        if (big <= 128 && halves <= 256 && halves > other)
             return launch_gemm_lds_cfg<GemmHalf, XS>(c, Wp, Xp, Xlo, n_pairs, KT, epi, 0, 2, big);
     }
-    if (big < 224 && tall <= 256 && tall > big) return launch_gemm_lds_cfg<GemmTall, XS>(c, Wp, Xp, Xlo, n_pairs, KT, epi, 0, 1, -1, kslices);
+    if (big < 224 && tall <= 256 && tall > big) return launch_gemm_lds_cfg<GemmTall, XS>(c, Wp, Xp, Xlo, n_pairs, KT, epi);
     // a last round that would occupy at most half of the compute units runs as twice as many half tiles
     // in a second launch (gate/up of the 70B shard: 896 tiles = 3.5 rounds of 256)
     const int rem = big % 256;
-    if (big > 256 && rem > 0 && rem <= 128 && kslices == 1) {
+    if (big > 256 && rem > 0 && rem <= 128) {
         const hipError_t e = launch_gemm_lds_cfg<GemmBig, XS>(c, Wp, Xp, Xlo, n_pairs, KT, epi, 0, 1, big - rem);
         if (e != hipSuccess) return e;
         return launch_gemm_lds_cfg<GemmHalf, XS>(c, Wp, Xp, Xlo, n_pairs, KT, epi, big - rem, 2, rem);
     }
-    return launch_gemm_lds_cfg<GemmBig, XS>(c, Wp, Xp, Xlo, n_pairs, KT, epi, 0, 1, -1, kslices);
+    return launch_gemm_lds_cfg<GemmBig, XS>(c, Wp, Xp, Xlo, n_pairs, KT, epi);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2157,11 +2146,6 @@ __global__ void k_bf16_to_f32(const __bf16 *__restrict__ src, const __bf16 *__re
 
 inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
 
-#define SPD_TRY(x)                       \
-    do {                                 \
-        hipError_t e_ = (x);             \
-        if (e_ != hipSuccess) return e_; \
-    } while (0)
 
 // Number of K slices of a weight-streaming launch: 1 when there are enough pairs of n-tiles to
 // occupy the chip, otherwise about two workgroups of 8 waves per compute unit.
@@ -2230,11 +2214,11 @@ hipError_t launch_gemv_sliced(const spd_call &c, bool split, const __bf16 *Wp, c
     return hipGetLastError();
 }
 
-// 17 .. 512 tokens: the skinny kernel, groups of MT m-tiles in grid.z.  KS > 1 only with MODE 2.
+// 17 .. 512 tokens, short contractions: the skinny kernel, groups of MT m-tiles in grid.z.  KS > 1 only with MODE 2.
 constexpr int SKINNY_W = 8;
 template <int MT, bool SPLIT, int MODE, class Epi>
-hipError_t launch_skinny_mt(const spd_call &c, const __bf16 *Wp, const __bf16 *Xhi, const __bf16 *Xlo, int n_groups, int KT,
-                            int KS, int n_mtiles, int rows, const Epi &epi) {
+hipError_t launch_skinny_mt(const spd_call &c, const __bf16 *Wp, const __bf16 *Xhi, const __bf16 *Xlo, int n_pairs, int KT,
+                            int KS, int n_mtiles, const Epi &epi) {
     constexpr int lds = SKINNY_W * MT * 2 * 1024;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
@@ -2243,96 +2227,147 @@ hipError_t launch_skinny_mt(const spd_call &c, const __bf16 *Wp, const __bf16 *X
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (attr_err != hipSuccess) return attr_err;
-    hipLaunchKernelGGL((k_skinny<SKINNY_W, MT, SPLIT, MODE, Epi>), dim3(n_groups, KS, (n_mtiles + MT - 1) / MT), dim3(SKINNY_W * 64),
-                       lds, c.s, Wp, Xhi, Xlo, KT, KS, n_mtiles, rows, epi);
+    hipLaunchKernelGGL((k_skinny<SKINNY_W, MT, SPLIT, MODE, Epi>), dim3(n_pairs, KS, (n_mtiles + MT - 1) / MT), dim3(SKINNY_W * 64),
+                       lds, c.s, Wp, Xhi, Xlo, KT, KS, n_mtiles, epi);
     return hipGetLastError();
 }
-template <int MODE, class Epi>
-hipError_t launch_skinny(const spd_call &c, bool split, const __bf16 *Wp, const __bf16 *Xhi, size_t plane, int n_groups, int KT,
-                         int KS, int rows, const Epi &epi) {
+template <int MODE = 0, class Epi>
+hipError_t launch_skinny(const spd_call &c, bool split, const __bf16 *Wp, const __bf16 *Xhi, size_t plane, int n_pairs, int KT,
+                         const Epi &epi, int KS = 1) {
     const int n_mtiles = (c.M + 15) / 16;
     const __bf16 *Xlo = Xhi + plane;
     if (n_mtiles <= 2)
-        return split ? launch_skinny_mt<2, true, MODE>(c, Wp, Xhi, Xlo, n_groups, KT, KS, n_mtiles, rows, epi)
-                     : launch_skinny_mt<2, false, MODE>(c, Wp, Xhi, Xlo, n_groups, KT, KS, n_mtiles, rows, epi);
+        return split ? launch_skinny_mt<2, true, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi)
+                     : launch_skinny_mt<2, false, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi);
     if (n_mtiles <= 4)
-        return split ? launch_skinny_mt<4, true, MODE>(c, Wp, Xhi, Xlo, n_groups, KT, KS, n_mtiles, rows, epi)
-                     : launch_skinny_mt<4, false, MODE>(c, Wp, Xhi, Xlo, n_groups, KT, KS, n_mtiles, rows, epi);
-    return split ? launch_skinny_mt<8, true, MODE>(c, Wp, Xhi, Xlo, n_groups, KT, KS, n_mtiles, rows, epi)
-                 : launch_skinny_mt<8, false, MODE>(c, Wp, Xhi, Xlo, n_groups, KT, KS, n_mtiles, rows, epi);
+        return split ? launch_skinny_mt<4, true, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi)
+                     : launch_skinny_mt<4, false, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi);
+    return split ? launch_skinny_mt<8, true, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi)
+                 : launch_skinny_mt<8, false, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi);
 }
-// 17 .. 512 tokens, activations not split, at least 128 pairs: the mid kernel and its finishing kernel
-// (beyond 128 tokens in groups of 8 m-tiles, every group streaming the weights again).
-// Used for the gate/up projection only: for the down projection the finishing kernel, which then
-// carries the closing sync point, costs more than the activation traffic it saves (measured).
-// Returns false in *done when the shape is not its kind (the caller then takes the skinny kernel).
-constexpr int SKINNY_MAX_MTILES = 32;      // beyond 512 tokens the LDS-tiled GEMM re-reads the weights less often
-constexpr int MID_MIN_PAIRS = 128;
-constexpr int MID_OTHERS_FROM = 10;    // m-tiles from which the QKV and down projections take the mid kernel too
+// 17 .. 128 tokens, activations not split, 96 MB of weights or more (the gate/up projection of the 70B shard): the mid
+// kernel and its finishing kernel.  It draws the HBM's rate better than the sliced GEMM, which is ahead on
+// everything smaller (main kernel, us at 32 / 64 / 128 tokens, mid against GEMM tiles: 117 MB 22 / 23.5 / 27 against
+// 25 / 26 / 31; 71 MB 15.4 / 17.2 / 20.9 against 14.3 / 15.4 / 18.3; 58 MB 12 / 14.1 / 19.8 against 12.3 / 12.9 / 14.9).
+// Returns false in *done when the shape is not its kind.
+constexpr int SKINNY_MAX_MTILES = 32;      // beyond 512 tokens one launch of the LDS-tiled GEMM does without K slices
+constexpr int MID_MAX_MTILES = 8;
+constexpr int MID_MIN_TILES = 48 * 1024;   // (pairs of n-tiles) x (k-tiles): 2 KiB each
 // K slices the mid kernel would use for this shape, 0 when the shape is not its kind
-inline int mid_slices(const spd_call &c, int n_pairs, int KT, int min_pairs = MID_MIN_PAIRS, int min_stages = 4) {
+inline int mid_slices(const spd_call &c, int n_pairs, int KT) {
     const spd_dims &D = *c.D;
     const int n_mtiles = (c.M + 15) / 16;
-    if (n_mtiles <= 1 || n_mtiles > SKINNY_MAX_MTILES || n_pairs < min_pairs) return 0;
+    if (n_mtiles <= 1 || n_mtiles > MID_MAX_MTILES || (long)n_pairs * KT < MID_MIN_TILES) return 0;
     const int groups = (n_pairs + MID_PAIRS - 1) / MID_PAIRS, nst = (KT + MID_KB - 1) / MID_KB;
-    const int MT = n_mtiles <= 2 ? 2 : (n_mtiles <= 4 ? 4 : 8), zg = (n_mtiles + MT - 1) / MT;
-    // one round of workgroups (one fits a compute unit), at least min_stages stages per slice
-    int KS = 256 / (groups * zg);
-    if (KS > nst / min_stages) KS = nst / min_stages;
+    // one round of workgroups (one fits a compute unit), at least four stages per slice
+    int KS = 256 / groups;
+    if (KS > nst / 4) KS = nst / 4;
     while (KS > 1 && (size_t)n_pairs * KS * n_mtiles > D.kpart_tiles) --KS;
     return KS < 2 ? 0 : KS;
 }
 template <class Epi>
-hipError_t launch_mid(const spd_call &c, const __bf16 *Wp, const __bf16 *Xhi, const __bf16 *Xlo, int n_pairs, int KT, const Epi &epi,
-                      bool *done, int min_pairs = MID_MIN_PAIRS, int min_stages = 4) {
+hipError_t launch_mid(const spd_call &c, const __bf16 *Wp, const __bf16 *X, int n_pairs, int KT, const Epi &epi, bool *done) {
     const spd_dims &D = *c.D;
     const int n_mtiles = (c.M + 15) / 16;
     *done = false;
-    const int KS = mid_slices(c, n_pairs, KT, min_pairs, min_stages);
+    const int KS = mid_slices(c, n_pairs, KT);
     if (KS == 0) return hipSuccess;
     const int groups = (n_pairs + MID_PAIRS - 1) / MID_PAIRS;
-    const int MT = n_mtiles <= 2 ? 2 : (n_mtiles <= 4 ? 4 : 8), zg = (n_mtiles + MT - 1) / MT;
     f32x4 *kpart = (f32x4 *)(c.ws + D.ws_kpart);
-    const dim3 grid(groups, KS, zg), wg(MID_PAIRS * 64);
-#define SPD_MID(MTV)                                                                                                          \
-    if (Xlo) hipLaunchKernelGGL((k_mid<MTV, true>), grid, wg, 0, c.s, Wp, Xhi, Xlo, KT, KS, n_pairs, n_mtiles, kpart);        \
-    else hipLaunchKernelGGL((k_mid<MTV, false>), grid, wg, 0, c.s, Wp, Xhi, Xlo, KT, KS, n_pairs, n_mtiles, kpart)
-    if (MT == 2) { SPD_MID(2); }
-    else if (MT == 4) { SPD_MID(4); }
-    else { SPD_MID(8); }
-#undef SPD_MID
+    const dim3 grid(groups, KS), wg(MID_PAIRS * 64);
+    if (n_mtiles <= 2) hipLaunchKernelGGL((k_mid<2>), grid, wg, 0, c.s, Wp, X, KT, KS, n_pairs, n_mtiles, kpart);
+    else if (n_mtiles <= 4) hipLaunchKernelGGL((k_mid<4>), grid, wg, 0, c.s, Wp, X, KT, KS, n_pairs, n_mtiles, kpart);
+    else hipLaunchKernelGGL((k_mid<8>), grid, wg, 0, c.s, Wp, X, KT, KS, n_pairs, n_mtiles, kpart);
     SPD_TRY(hipGetLastError());
     hipLaunchKernelGGL((k_mid_finish<Epi>), dim3(groups, n_mtiles), dim3(MID_PAIRS * 64), 0, c.s, kpart, KS, n_pairs, n_mtiles, epi);
     *done = true;
     return hipGetLastError();
 }
 
-
-// Number of m-tiles up to which a projection with few n-tiles stays in the skinny kernel beyond
-// SKINNY_MAX_MTILES: the LDS-tiled GEMM of such a projection has far fewer tiles than there are compute
-// units and takes the time of one full tile whatever the call size, the skinny kernel's time grows with
-// the call.  Both estimates are fits to measurements on the 70B shard (QKV: 180 us in the GEMM from 768
-// to 8192 tokens, 43 us in the skinny kernel at 512).
-inline int skinny_limit(int n_pairs, int KT, int n_mtiles) {
-    const int big = ((2 * n_pairs + 15) / 16) * ((n_mtiles + 15) / 16), tall = ((2 * n_pairs + 7) / 8) * ((n_mtiles + 23) / 24);
-    const int tiles = big < tall && tall <= 256 ? tall : big;
-    if (tiles >= 128) return SKINNY_MAX_MTILES;
-    const double t_gemm = (double)((tiles + 255) / 256) * (KT / 2) * 1.45 + 10.0;            // us
-    const double t_skinny = 7.7e-6 * n_pairs * KT * (16.0 * n_mtiles) + 5.0;
-    return t_skinny < t_gemm ? n_mtiles : SKINNY_MAX_MTILES;
+// Projection in K slices: the LDS-tiled GEMM in one launch of (tiles x slices) workgroups, at most one per compute unit,
+// that park their partial sums, and a finishing kernel that adds them in slice order and runs the epilogue.  For
+// calls whose tiles alone leave most compute units idle.  Tile shape: 128 x 64 up to 64 tokens, 256 x 128 beyond 128
+// tokens where there are 64 pairs of n-tiles or 32 such tiles, 128 x 128 otherwise (main kernel, us, 128 x 128 against 256 x 128: gate/up of
+// the 70B shard 256 tokens 48.7 / 44.5, 512: 84 / 72; its QKV projection on pairs 128 tokens 10.8 / 17, 256: 15 / 22.5,
+// 512: 23.3 / 24.6).  Slices: as many as fit the round of 256 with 8 k-tiles each (beyond 16 the partial sums cost more
+// than the idle compute units: gate/up of the 13B shard, 128 tokens, 18 / 13 slices: 13.8 + 9.3 / 12.6 + 5.1 us).
+// Returns false in *done when fewer than two slices come of it or they do not fit the workspace.
+template <class Epi>
+hipError_t launch_sliced(const spd_call &c, bool split, const __bf16 *Wp, const __bf16 *Xhi, size_t plane, int n_pairs, int KT,
+                         const Epi &epi, bool *done) {
+    const spd_dims &D = *c.D;
+    const int n_mtiles = (c.M + 15) / 16;
+    const int halves = ((2 * n_pairs + 15) / 16) * ((n_mtiles + 7) / 8);
+    const int kind = n_mtiles <= 4 ? 0 : (n_mtiles > 8 && (n_pairs >= 64 || halves >= 32) ? 2 : 1);      // 128 x 64, 128 x 128, 256 x 128
+    const int bn = kind == 2 ? 16 : 8, bm = kind == 0 ? 4 : 8;
+    const int tiles = ((2 * n_pairs + bn - 1) / bn) * ((n_mtiles + bm - 1) / bm);
+    int KS = 256 / tiles;
+    if (KS > 16) KS = 16;
+    if (KS > KT / 8) KS = KT / 8;
+    while (KS > 1 && (size_t)n_pairs * KS * n_mtiles > D.kpart_tiles) --KS;
+    *done = KS > 1;
+    if (!*done) return hipSuccess;
+    EpiPark park;
+    park.KS = KS; park.n_mtiles = n_mtiles; park.kpart = (f32x4 *)(c.ws + D.ws_kpart);
+    const __bf16 *Xlo = Xhi + plane;
+#define SPD_SLICED(G)                                                                                              \
+    SPD_TRY((split ? launch_gemm_lds_cfg<G, true>(c, Wp, Xhi, Xlo, n_pairs, KT, park, 0, 1, -1, KS)                \
+                   : launch_gemm_lds_cfg<G, false>(c, Wp, Xhi, Xlo, n_pairs, KT, park, 0, 1, -1, KS)))
+    if (kind == 0) SPD_SLICED(GemmSmall);
+    else if (kind == 1) SPD_SLICED(GemmSquare);
+    else SPD_SLICED(GemmHalf);
+#undef SPD_SLICED
+    hipLaunchKernelGGL((k_mid_finish<Epi>), dim3((n_pairs + MID_PAIRS - 1) / MID_PAIRS, n_mtiles), dim3(MID_PAIRS * 64), 0, c.s,
+                       (const f32x4 *)park.kpart, KS, n_pairs, n_mtiles, epi);
+    return hipGetLastError();
 }
 
-// Projection of a call of any size: the weight-streaming kernel up to 16 tokens, the skinny kernel up to
-// `skinny_max` m-tiles, the LDS-tiled GEMM beyond.
+// Projection of a call of any size: the weight-streaming kernel up to 16 tokens; K slices of the LDS-tiled GEMM up to 512
+// tokens, and beyond for a call of one chain whose tiles leave half of the compute units idle (the QKV projection of the
+// 70B shard, 1000 tokens: 6 slices 37 us, 160 x 256 tiles in 8 slices 58); one launch of the GEMM otherwise.  The skinny
+// kernel takes what is too short to slice.
 template <class Epi>
 hipError_t launch_proj(const spd_call &c, bool split, const __bf16 *Wp, const __bf16 *Xhi, size_t plane, int n_pairs, int KT,
-                       const Epi &epi, int skinny_max = SKINNY_MAX_MTILES) {
+                       const Epi &epi) {
     const int n_mtiles = (c.M + 15) / 16;
     const __bf16 *Xlo = Xhi + plane;
     if (n_mtiles == 1)
         return split ? launch_gemv<true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi) : launch_gemv<false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
-    if (n_mtiles <= skinny_max) return launch_skinny<0>(c, split, Wp, Xhi, plane, n_pairs, KT, 1, 16, epi);
-    return split ? launch_gemm_lds<true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi) : launch_gemm_lds<false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
+    if (!c.chained) {
+        bool done = false;
+        SPD_TRY(launch_sliced(c, split, Wp, Xhi, plane, n_pairs, KT, epi, &done));
+        if (done) return hipSuccess;
+    }
+    if (n_mtiles <= SKINNY_MAX_MTILES) {
+        // no slices: half a round of 256 x 128 tiles by themselves, the skinny kernel below that
+        const int halves = ((2 * n_pairs + 15) / 16) * ((n_mtiles + 7) / 8);
+        if (n_mtiles > 8 && halves >= 128)
+            return split ? launch_gemm_lds_cfg<GemmHalf, true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi)
+                         : launch_gemm_lds_cfg<GemmHalf, false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
+        return launch_skinny(c, split, Wp, Xhi, plane, n_pairs, KT, epi);
+    }
+    if constexpr (Epi::kLong) return split ? launch_gemm_lds<true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi) : launch_gemm_lds<false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
+    else return hipErrorInvalidValue;         // epilogues that carry a sync point: calls of up to 512 tokens
+}
+
+// The output projection's contraction is short (a rank's heads): up to 128 tokens the skinny kernel with the whole epilogue
+// beats slices and their finishing kernel; beyond, 256 x 128 tiles by themselves beat both once the skinny kernel would
+// take two rounds (70B shard, main kernel, us, skinny / tiles: 192 tokens 15.8 / 14.7, 512: 30.9 / 17.2; 13B 384: 10.8 / 11.4, 512:
+// 16.1 / 12.0), unless the epilogue carries a sync point, which wants the finishing kernel's many workgroups.
+template <bool MID>
+hipError_t launch_o(const spd_call &c, bool split, const __bf16 *Wp, const __bf16 *Xhi, size_t plane, int n_pairs, int KT,
+                    const EpiOT<MID> &epi) {
+    const int n_mtiles = (c.M + 15) / 16, zg = (n_mtiles + 7) / 8;
+    const __bf16 *Xlo = Xhi + plane;
+    if (n_mtiles > 1 && n_mtiles <= SKINNY_MAX_MTILES) {
+        if (n_mtiles <= 8 || n_pairs * zg < 512) return launch_skinny(c, split, Wp, Xhi, plane, n_pairs, KT, epi);
+        if (!MID)
+            return split ? launch_gemm_lds_cfg<GemmHalf, true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi)
+                         : launch_gemm_lds_cfg<GemmHalf, false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
+    } else if constexpr (!MID) {
+        if (n_mtiles > 1) return split ? launch_gemm_lds<true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi) : launch_gemm_lds<false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
+    }
+    return launch_proj(c, split, Wp, Xhi, plane, n_pairs, KT, epi);
 }
 
 // chunking of the sum-of-squares partials written by prep()
@@ -2397,24 +2432,6 @@ inline ProjW proj_weights(const spd_call &c, const char *w, int i) {
 }
 }  // namespace
 
-namespace {
-// K slices for the QKV GEMM of a long call (0 or 1: none): only where the GEMM would leave most compute
-// units idle, the call is not one of two chains (whose QKV GEMMs fill the chip together), every slice keeps
-// at least 16 k-tiles in whole steps, and the slices' partial rows fit the workspace
-inline int qkv_gemm_slices(const spd_call &c, int n_pairs, int KT, int n_mtiles) {
-    const spd_dims &D = *c.D;
-    if (n_mtiles <= SKINNY_MAX_MTILES || c.chained) return 0;
-    const int tiles = gemm_tile_count(c.sp_x, n_pairs, n_mtiles);
-    if (tiles > 128) return 0;
-    int s = 256 / tiles;
-    if (s > SPD_MAX_QKV_SLICES) s = SPD_MAX_QKV_SLICES;
-    while (s > 1 && (KT % (2 * s) != 0 || KT / s < 16 ||
-                     (size_t)s * 16 * n_mtiles * D.nqkv > D.kpart_tiles * 512))
-        --s;
-    return s;
-}
-}  // namespace
-
 hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const float *x, int spd, float *slot,
                           const spd_mid_sync *mid, bool *mid_done) {
     const spd_dims &D = *c.D;
@@ -2427,31 +2444,36 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
     float *ybuf = (float *)(c.ws + D.ws_y);
     const ProjW wqkv = proj_weights(c, w, 0), wo = proj_weights(c, w, 1);
 
-    // K-sliced QKV projections (too few column tiles to occupy the chip) with the linear epilogue:
-    //  - a decode step hands the slices to the attention kernel (no second kernel to add them up);
-    //  - a call of 17 .. 512 tokens adds them with a small gather kernel
+    // A decode step whose QKV projection has too few column tiles to occupy the chip: K slices with the linear epilogue (at
+    // most SPD_MAX_QKV_SLICES), whose partial rows the attention kernel adds itself.  Up to 16 sequences about 240
+    // workgroups of 16 waves, at least two k-tiles per wave; more of them, about 480 of the skinny kernel's 8 waves (two fit a compute unit).
     const int n_mtiles = (M + 15) / 16, qkv_pairs = D.nqkv / 32;
     int qkv_slices = 1;
-    bool fused_q = false, gather_q = false;
-    if (gemv_slices(qkv_pairs, D.h / 32) > 1) {
-        // decode: about 240 workgroups of 16 waves; 17 .. 512 tokens: one round of workgroups of 8 waves
-        // (two fit a compute unit with up to 4 m-tiles each, one beyond, because of the LDS they reduce
-        // through); at most SPD_MAX_QKV_SLICES slices and at least two k-tiles per wave
-        const bool dec = c.q_len == 1 && n_mtiles == 1;
-        const int zgroups = n_mtiles <= 4 ? 1 : (n_mtiles + 7) / 8;
-        const int room = dec ? 240 : (n_mtiles <= 4 ? 480 : 250);
-        const int want = dec ? (room + qkv_pairs - 1) / qkv_pairs : room / (qkv_pairs * zgroups);
-        const int wv = dec ? QKV_SLICE_W : SKINNY_W;
-        qkv_slices = want < 2 ? (dec ? 2 : 1) : (want > SPD_MAX_QKV_SLICES ? SPD_MAX_QKV_SLICES : want);
-        if (qkv_slices > D.h / 32 / (2 * wv)) qkv_slices = D.h / 32 / (2 * wv);
+    if (c.q_len == 1 && n_mtiles <= 4 && gemv_slices(qkv_pairs, D.h / 32) > 1) {
+        const int want = n_mtiles == 1 ? (240 + qkv_pairs - 1) / qkv_pairs : 480 / qkv_pairs;
+        qkv_slices = want < 2 ? 2 : (want > SPD_MAX_QKV_SLICES ? SPD_MAX_QKV_SLICES : want);
+        const int most = D.h / 32 / (2 * (n_mtiles == 1 ? QKV_SLICE_W : SKINNY_W));
+        if (qkv_slices > most) qkv_slices = most;
         while (qkv_slices > 1 && (size_t)qkv_slices * 16 * n_mtiles * D.nqkv > (size_t)SPD_MAX_KPART * 512) --qkv_slices;
-        // (a decode step of any batch size lets the attention kernel add the slices)
-        fused_q = qkv_slices > 1 && c.q_len == 1 && n_mtiles <= SKINNY_MAX_MTILES;
-        gather_q = qkv_slices > 1 && !fused_q && n_mtiles > 1 && n_mtiles <= SKINNY_MAX_MTILES;
-        if (!fused_q && !gather_q) qkv_slices = 1;
     }
+    const bool fused_q = qkv_slices > 1;
     float *qkvp = (float *)(c.ws + D.ws_kpart);
-    auto full_epilogue = [&]() {
+    if (fused_q) {
+        EpiQKVPart e1;
+        e1.M = M; e1.q_len = c.q_len; e1.q = D.q; e1.kv = D.kv; e1.d = D.d; e1.h = D.h; e1.nqkv = D.nqkv;
+        e1.nch = c.nch1; e1.m_pad = D.m_pad; e1.part_rows = 16 * n_mtiles; e1.eps = D.eps;
+        e1.ss = (const float *)(c.ws + D.ws_ss1);
+        e1.cosT = (const float *)(c.ws + D.ws_cos); e1.sinT = (const float *)(c.ws + D.ws_sin);
+        e1.wsc = wqkv.wsc;
+        e1.part = qkvp; e1.P = c.pos;
+        if (c.on(SPD_STAGE_QKV)) {
+            spd_stage_scope prof(c, SPD_STAGE_QKV);
+            if (n_mtiles == 1)
+                SPD_TRY(launch_gemv_sliced(c, c.sp_x, wqkv.w, xhat, D.pl_x, qkv_pairs, D.h / 32, qkv_slices, e1));
+            else
+                SPD_TRY(launch_skinny<2>(c, c.sp_x, wqkv.w, xhat, D.pl_x, qkv_pairs, D.h / 32, e1, qkv_slices));
+        }
+    } else {
         EpiQKV e1;
         e1.M = M; e1.q_len = c.q_len; e1.q = D.q; e1.kv = D.kv; e1.d = D.d; e1.h = D.h; e1.max_ctx = D.max_ctx;
         e1.nch = c.nch1; e1.m_pad = D.m_pad; e1.eps = D.eps;
@@ -2459,65 +2481,9 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
         e1.cosT = (const float *)(c.ws + D.ws_cos); e1.sinT = (const float *)(c.ws + D.ws_sin);
         e1.wsc = wqkv.wsc;
         e1.qbuf = qbuf; e1.qlo = qlo; e1.kc = kc; e1.vc = vc; e1.P = c.pos;
-        return e1;
-    };
-    // MID_OTHERS_FROM .. 32 m-tiles: the mid kernel (activation fragments shared by 8 pairs of n-tiles through LDS)
-    // where its slices fit; the skinny kernel pulls every activation through the L2 once per pair, which from about
-    // 200 tokens on costs more than the slice partials the mid kernel writes and reads back
-    if (!fused_q && n_mtiles >= MID_OTHERS_FROM && n_mtiles <= SKINNY_MAX_MTILES &&
-        mid_slices(c, qkv_pairs, D.h / 32, MID_PAIRS, 8) > 0) {
         if (c.on(SPD_STAGE_QKV)) {
             spd_stage_scope prof(c, SPD_STAGE_QKV);
-            bool done = false;
-            SPD_TRY(launch_mid(c, wqkv.w, xhat, c.sp_x ? xhat + D.pl_x : (const __bf16 *)nullptr, qkv_pairs, D.h / 32,
-                               full_epilogue(), &done, MID_PAIRS, 8));
-        }
-    } else if (fused_q || gather_q) {
-        EpiQKVPart e1;
-        e1.M = M; e1.q_len = c.q_len; e1.q = D.q; e1.kv = D.kv; e1.d = D.d; e1.h = D.h; e1.nqkv = D.nqkv;
-        e1.nch = c.nch1; e1.m_pad = D.m_pad; e1.part_rows = 16 * n_mtiles; e1.eps = D.eps;
-        e1.ss = (const float *)(c.ws + D.ws_ss1);
-        e1.cosT = (const float *)(c.ws + D.ws_cos); e1.sinT = (const float *)(c.ws + D.ws_sin);
-        e1.wsc = wqkv.wsc;
-        e1.part = qkvp; e1.P = c.pos;
-        if (c.on(SPD_STAGE_QKV)) {
-            spd_stage_scope prof(c, SPD_STAGE_QKV);
-            if (n_mtiles == 1) {
-                SPD_TRY(launch_gemv_sliced(c, c.sp_x, wqkv.w, xhat, D.pl_x, qkv_pairs, D.h / 32, qkv_slices, e1));
-            } else {
-                SPD_TRY(launch_skinny<2>(c, c.sp_x, wqkv.w, xhat, D.pl_x, qkv_pairs, D.h / 32, qkv_slices, 16, e1));
-            }
-            if (gather_q) {
-                hipLaunchKernelGGL(k_qkv_gather, dim3(cdiv((int64_t)M * (D.nqkv / 4), 256)), dim3(256), 0, c.s, qkvp, qkv_slices,
-                                   16 * n_mtiles, M, c.q_len, D.q, D.kv, D.d, D.max_ctx, c.pos, qbuf, qlo, kc, vc);
-                SPD_TRY(hipGetLastError());
-            }
-        }
-    } else if (const int gs = qkv_gemm_slices(c, qkv_pairs, D.h / 32, n_mtiles); gs > 1) {
-        // a long call of one chain whose QKV GEMM has far fewer tiles than there are compute units: K is cut
-        // into slices that run side by side, each applying the (linear) epilogue to its partial sums; the gather
-        // kernel adds the slices
-        EpiQKVPart e1;
-        e1.M = M; e1.q_len = c.q_len; e1.q = D.q; e1.kv = D.kv; e1.d = D.d; e1.h = D.h; e1.nqkv = D.nqkv;
-        e1.nch = c.nch1; e1.m_pad = D.m_pad; e1.part_rows = 16 * n_mtiles; e1.eps = D.eps;
-        e1.ss = (const float *)(c.ws + D.ws_ss1);
-        e1.cosT = (const float *)(c.ws + D.ws_cos); e1.sinT = (const float *)(c.ws + D.ws_sin);
-        e1.wsc = wqkv.wsc;
-        e1.part = qkvp; e1.P = c.pos;
-        if (c.on(SPD_STAGE_QKV)) {
-            spd_stage_scope prof(c, SPD_STAGE_QKV);
-            SPD_TRY(c.sp_x ? launch_gemm_lds<true>(c, wqkv.w, xhat, xhat + D.pl_x, qkv_pairs, D.h / 32, e1, gs)
-                           : launch_gemm_lds<false>(c, wqkv.w, xhat, xhat + D.pl_x, qkv_pairs, D.h / 32, e1, gs));
-            hipLaunchKernelGGL(k_qkv_gather, dim3(cdiv((int64_t)M * (D.nqkv / 4), 256)), dim3(256), 0, c.s, qkvp, gs,
-                               16 * n_mtiles, M, c.q_len, D.q, D.kv, D.d, D.max_ctx, c.pos, qbuf, qlo, kc, vc);
-            SPD_TRY(hipGetLastError());
-        }
-    } else {
-        const EpiQKV e1 = full_epilogue();
-        if (c.on(SPD_STAGE_QKV)) {
-            spd_stage_scope prof(c, SPD_STAGE_QKV);
-            SPD_TRY(launch_proj(c, c.sp_x, wqkv.w, xhat, D.pl_x, D.nqkv / 32, D.h / 32, e1,
-                                   skinny_limit(D.nqkv / 32, D.h / 32, n_mtiles)));
+            SPD_TRY(launch_proj(c, c.sp_x, wqkv.w, xhat, D.pl_x, qkv_pairs, D.h / 32, e1));
         }
     }
 
@@ -2613,15 +2579,11 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
             fill_o(e2);
             e2.spd = 2;
             e2.slots = mid->slots; e2.slot_stride = c.slot_stride; e2.tp = mid->tp; e2.rank = mid->rank; e2.rbuf = mid->rbuf;
-            if (M <= 16)
-                SPD_TRY(c.sp_a ? launch_gemv<true>(c, wo.w, ahat, ahat + D.pl_a, D.h / 32, qd / 32, e2)
-                               : launch_gemv<false>(c, wo.w, ahat, ahat + D.pl_a, D.h / 32, qd / 32, e2));
-            else
-                SPD_TRY(launch_skinny<0>(c, c.sp_a, wo.w, ahat, D.pl_a, D.h / 32, qd / 32, 1, 16, e2));
+            SPD_TRY(launch_o(c, c.sp_a, wo.w, ahat, D.pl_a, D.h / 32, qd / 32, e2));
         } else {
             EpiOT<false> e2;
             fill_o(e2);
-            SPD_TRY(launch_proj(c, c.sp_a, wo.w, ahat, D.pl_a, D.h / 32, qd / 32, e2));
+            SPD_TRY(launch_o(c, c.sp_a, wo.w, ahat, D.pl_a, D.h / 32, qd / 32, e2));
         }
     }
 
@@ -2677,7 +2639,7 @@ hipError_t mlp_half(const spd_call &c, const char *w, int spd, float *slot, cons
             }
         } else {
             bool mid = false;
-            if (!c.sp_m) SPD_TRY(launch_mid(c, wgu.w, xhat, (const __bf16 *)nullptr, D.f_pad / 16, D.h / 32, e1, &mid));
+            if (!c.sp_m) SPD_TRY(launch_mid(c, wgu.w, xhat, D.f_pad / 16, D.h / 32, e1, &mid));
             if (!mid) SPD_TRY(launch_proj(c, c.sp_m, wgu.w, xhat, D.pl_x, D.f_pad / 16, D.h / 32, e1));
         }
     }
@@ -2708,17 +2670,10 @@ hipError_t mlp_half(const spd_call &c, const char *w, int spd, float *slot, cons
         if (do_fuse) {
             EpiDownT<true> e2;
             fill(e2);
-            if (M <= 16)
-                SPD_TRY(c.sp_m ? launch_gemv<true>(c, wdn.w, uhat, uhat + D.pl_u, D.h / 32, D.f_pad / 32, e2)
-                               : launch_gemv<false>(c, wdn.w, uhat, uhat + D.pl_u, D.h / 32, D.f_pad / 32, e2));
-            else {
-                // (up to MID_OTHERS_FROM m-tiles the finishing kernel, which carries the closing sync point, costs more
-                // than the activation traffic the mid kernel saves)
-                bool mid = false;
-                if (!c.sp_m && (int)cdiv(M, 16) >= MID_OTHERS_FROM)
-                    SPD_TRY(launch_mid(c, wdn.w, uhat, (const __bf16 *)nullptr, D.h / 32, D.f_pad / 32, e2, &mid));
-                if (!mid) SPD_TRY(launch_skinny<0>(c, c.sp_m, wdn.w, uhat, D.pl_u, D.h / 32, D.f_pad / 32, 1, 16, e2));
-            }
+            // (up to 128 tokens the finishing kernel of the slices, which then carries the closing sync point, costs more than
+            // the better contraction saves: 70B shard, 48 tokens 15.7 + 8.3 us against 20.2, 128: 19.5 + 13.1 against 30)
+            if (M > 16 && M <= 128) SPD_TRY(launch_skinny(c, c.sp_m, wdn.w, uhat, D.pl_u, D.h / 32, D.f_pad / 32, e2));
+            else SPD_TRY(launch_proj(c, c.sp_m, wdn.w, uhat, D.pl_u, D.h / 32, D.f_pad / 32, e2));
         } else {
             EpiDownT<false> e2;
             fill(e2);

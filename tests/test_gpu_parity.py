@@ -236,9 +236,10 @@ def test_bf16_long_call_small_shape(gpu, w, flag, split):
     case.close()
 
 
-# contraction lengths at which the long call's GEMM can go wrong: fewer k-tiles than it has stages (one k-tile in the O
-# projection, three in QKV and gate/up), odd numbers of them (down: 23), and 66 partial sums of squares per token,
-# which a kernel of its own adds up before the gate/up projection of an SPD block
+# contraction lengths at which the LDS-tiled GEMM can go wrong: fewer k-tiles than it has stages (one k-tile in the O
+# projection, three in QKV and gate/up), odd numbers of them (down: 23), K slices of uneven lengths (66 k-tiles in 8
+# slices up to 512 tokens, all four tile shapes), and 66 partial sums of squares per token, which a kernel of its own
+# adds up before the gate/up projection of an SPD block of more than 512 tokens
 KT_FEW = Workload(name="few-k-tiles", hidden=96, n_q_heads=2, n_kv_heads=2, head_dim=32, ffn=96, n_layers=1, tp=2, dtype=BF16,
                   seed=31, batch=1, q_len=1, ctx=64, mask=(1,))
 KT_ODD = Workload(name="odd-k-tiles", hidden=2112, n_q_heads=4, n_kv_heads=2, head_dim=32, ffn=1440, n_layers=1, tp=2,
@@ -248,7 +249,7 @@ KT_ODD = Workload(name="odd-k-tiles", hidden=2112, n_q_heads=4, n_kv_heads=2, he
 @pytest.mark.parametrize("w", [KT_FEW, KT_ODD], ids=lambda w: w.name)
 @pytest.mark.parametrize("flag", [1, 0], ids=["spd", "tp"])
 @pytest.mark.parametrize("split", [B.SPD_SPLIT_AUTO, B.SPD_SPLIT_ALWAYS, B.SPD_SPLIT_NEVER], ids=["default", "all-split", "no-split"])
-@pytest.mark.parametrize("q_len", [145, 384, 513, 530])
+@pytest.mark.parametrize("q_len", [17, 64, 100, 145, 384, 513, 530])
 def test_bf16_gemm_contraction_lengths(gpu, w, flag, split, q_len):
     import torch
     case = Case(w, gpu, ranks=range(w.tp), positions=[0], max_ctx=544, max_tokens=q_len, act_split=split)
