@@ -123,13 +123,12 @@ int block_core(const spd_ctx *ctx, spd_call &c, int spd, int32_t rank, const cha
     }
     if (spd) {
         for (int r = r0; r < r1; ++r) {
-            SPD_HIP(spd_f32::attention_half(c, wr(r), kr(r), x, ybuf));
-            SPD_HIP(spd_common::rank_sum(x, ybuf, 1, (int64_t)c.M * D.h, rbuf, c.s, bo, D.h));   // local fold X + Y_r (+ b)
+            SPD_HIP(spd_f32::attention_half(c, wr(r), kr(r), x, ybuf, rbuf, bo));        // with the local fold X + Y_r (+ b)
             SPD_HIP(spd_f32::mlp_half(c, wr(r), rbuf, ybuf, slots + r * slot_n));        // slot = Y_r + Z_r
         }
         *base_out = x;
     } else {
-        for (int r = r0; r < r1; ++r) SPD_HIP(spd_f32::attention_half(c, wr(r), kr(r), x, slots + r * slot_n));
+        for (int r = r0; r < r1; ++r) SPD_HIP(spd_f32::attention_half(c, wr(r), kr(r), x, slots + r * slot_n, nullptr, nullptr));
         SPD_HIP(spd_common::rank_sum(x, slots, D.tp, (int64_t)slot_n, rbuf, c.s, bo, D.h));   // kept sync point
         *syncs += 1;
         for (int r = r0; r < r1; ++r) SPD_HIP(spd_f32::mlp_half(c, wr(r), rbuf, nullptr, slots + r * slot_n));

@@ -233,8 +233,8 @@ hipError_t copy2d(const float *src, int lds, float *dst, int ldd, int rows, int 
 }
 
 namespace spd_f32 {
-// attention half of a rank's share: X -> Y_r (into ybuf or the slot), fp32 path
-hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const float *x, float *y_out);
+// attention half of a rank's share: X -> Y_r (into ybuf or the slot), fp32 path; r_out (may be NULL) <- X + Y_r [+ bias]
+hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const float *x, float *y_out, float *r_out, const float *bias);
 // MLP half: r_in -> Z_r, out[m][n] = (add ? add[m][n] : 0) + Z_r
 hipError_t mlp_half(const spd_call &c, const char *w, const float *r_in, const float *add, float *out);
 }

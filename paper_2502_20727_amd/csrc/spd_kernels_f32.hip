@@ -1,5 +1,7 @@
 // fp32 path: small, plain kernels in natural layouts (used by the toy-sized configuration and
 // as the library's generic rank-sum), plus helpers shared by both paths.
+#include <mutex>
+
 #include "spd_internal.h"
 
 namespace {
@@ -131,53 +133,251 @@ __global__ void k_rope_append(float *__restrict__ qkv, float *__restrict__ kc, f
     }
 }
 
-// One workgroup per (token, query head): causal softmax attention over the cache.
-__global__ void k_attention(const float *__restrict__ qkv, const float *__restrict__ kc, const float *__restrict__ vc,
-                            float *__restrict__ out, spd_positions P, int q_len, int q, int kv, int d, int nqkv,
-                            int max_ctx) {
+// Small products (at most ROWS_MAX_M rows, ROWS_MAX_K contraction elements): bound by latency, not by work, so a kernel does
+// as much as it can between two launches.  A workgroup of 16 waves owns 8 rows of A and 64 columns of W: it loads
+// its rows once (optionally applying the RMS norm: the whole row is there), wave w contracts the w-th sixteenth of K
+// with lane = column, the waves' sums meet in LDS in wave order and an epilogue finishes the tile.  Toy model (hidden
+// 256), one rank and layer, us for 1 / 32 tokens: norm + QKV + rotation 27 / 35 -> 7 / 8 (three launches before), O + fold 21-27 / 38 -> 5,
+// norm + gate + up + SwiGLU 47 / 60 -> 9 / 11 (four launches before), down 23 / 33 -> 7 / 8.
+constexpr int RW = 16, RM = 8, RN = 64;
+constexpr int ROWS_MAX_M = 64, ROWS_MAX_K = 1024;
+
+struct RowsQKV {       // queries and keys rotated, keys and values appended to the cache; needs whole heads per tile (64 % d == 0)
+    static constexpr bool kDual = false;
+    float *qkv, *kc, *vc;
+    const float *cosT, *sinT;
+    int q_len, q, kv, d, nqkv, max_ctx;
+    spd_positions P;
+    __device__ __forceinline__ void operator()(const float *tile, const float *, int r, int cl, int m, int n) const {
+        const int half = d >> 1, head = n / d, j = n % d;
+        const int b = m / q_len, pos = P.pos[b] + (m % q_len);
+        float v = tile[r * RN + cl];
+        if (head < q + kv) {
+            const int jj = j < half ? j : j - half;
+            const float c = cosT[(size_t)pos * half + jj], sn = sinT[(size_t)pos * half + jj];
+            const float o = tile[r * RN + (j < half ? cl + half : cl - half)];
+            v = j < half ? v * c - o * sn : v * c + o * sn;
+        }
+        if (head < q) {
+            qkv[(size_t)m * nqkv + n] = v;
+        } else {
+            const int kh = head < q + kv ? head - q : head - q - kv;
+            (head < q + kv ? kc : vc)[(((size_t)b * kv + kh) * max_ctx + pos) * d + j] = v;
+        }
+    }
+};
+struct RowsO {         // y = the partial product; r_out (optional) = x + y [+ bias], the SPD block's local fold
+    static constexpr bool kDual = false;
+    float *y, *r_out;
+    const float *x, *bias;
+    int ld;
+    __device__ __forceinline__ void operator()(const float *tile, const float *, int r, int cl, int m, int n) const {
+        const size_t o = (size_t)m * ld + n;
+        const float v = tile[r * RN + cl];
+        y[o] = v;
+        if (r_out) r_out[o] = bias ? (x[o] + v) + bias[n] : x[o] + v;
+    }
+};
+struct RowsGU {        // silu(gate) * up
+    static constexpr bool kDual = true;
+    float *u;
+    int ld;
+    __device__ __forceinline__ void operator()(const float *tile, const float *tile2, int r, int cl, int m, int n) const {
+        const float x = tile[r * RN + cl];
+        u[(size_t)m * ld + n] = x / (1.0f + expf(-x)) * tile2[r * RN + cl];
+    }
+};
+struct RowsDown {      // out = [add +] z
+    static constexpr bool kDual = false;
+    float *out;
+    const float *add;
+    int ld;
+    __device__ __forceinline__ void operator()(const float *tile, const float *, int r, int cl, int m, int n) const {
+        const size_t o = (size_t)m * ld + n;
+        const float v = tile[r * RN + cl];
+        out[o] = add ? add[o] + v : v;
+    }
+};
+
+template <class Epi>
+__global__ void __launch_bounds__(RW * 64) k_rows(const float *__restrict__ A, int lda, const float *__restrict__ gain, float eps,
+                                                  const float *__restrict__ W, const float *__restrict__ W2, int ldw, int M, int N,
+                                                  int K, Epi epi) {
+    constexpr int NB = Epi::kDual ? 2 : 1;
+    extern __shared__ float rows_lds[];                 // rows [RM][K], then the waves' sums [NB][RW][RM][RN]
+    __shared__ float ssq[RM][2];
+    __shared__ float tile[NB][RM * RN];
+    float *xs = rows_lds, *red = rows_lds + RM * K;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n0 = blockIdx.x * RN, m0 = blockIdx.y * RM;
+    const int n = n0 + lane < N ? n0 + lane : N - 1;    // (columns past the matrix repeat its last one and are dropped)
+    // this wave's share of the weights does not depend on the rows: the first of them are requested ahead of everything
+    const int k0 = (wave * K) / RW, k1 = ((wave + 1) * K) / RW, klast = k1 > k0 ? k1 - 1 : k0;
+    constexpr int U = 16;
+    float w0[U], w1[NB == 2 ? U : 1];
+    auto load = [&](int kb) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = kb + u < klast ? kb + u : klast;
+            w0[u] = W[(size_t)k * ldw + n];
+            if constexpr (NB == 2) w1[u] = W2[(size_t)k * ldw + n];
+        }
+    };
+    load(k0);
+    {   // rows: wave w takes half w % 2 of row w / 2
+        const int r = wave >> 1, hk = (K + 1) / 2, kb = (wave & 1) * hk, ke = kb + hk < K ? kb + hk : K;
+        const bool valid = m0 + r < M;
+        const float *src = A + (size_t)(valid ? m0 + r : 0) * lda;
+        constexpr int V = (ROWS_MAX_K / 2 + 63) / 64;
+        float v[V], sq = 0.f;
+#pragma unroll
+        for (int t = 0; t < V; ++t) {
+            const int k = kb + t * 64 + lane;
+            v[t] = valid && k < ke ? src[k] : 0.f;
+        }
+        float rs = 1.f;
+        if (gain) {
+#pragma unroll
+            for (int t = 0; t < V; ++t) sq += v[t] * v[t];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
+            if (lane == 0) ssq[r][wave & 1] = sq;
+            __syncthreads();
+            rs = 1.0f / sqrtf((ssq[r][0] + ssq[r][1]) / (float)K + eps);
+        }
+#pragma unroll
+        for (int t = 0; t < V; ++t) {
+            const int k = kb + t * 64 + lane;
+            if (k < ke) xs[r * K + k] = gain ? v[t] * rs * gain[k] : v[t];
+        }
+    }
+    __syncthreads();
+    float acc[NB][RM];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int r = 0; r < RM; ++r) acc[b][r] = 0.f;
+    for (int kb = k0; kb < k1; kb += U) {
+        if (kb > k0) load(kb);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (kb + u < k1) {                          // (uniform)
+#pragma unroll
+                for (int r = 0; r < RM; ++r) {
+                    const float x = xs[r * K + kb + u];
+                    acc[0][r] += x * w0[u];
+                    if constexpr (NB == 2) acc[1][r] += x * w1[u];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int r = 0; r < RM; ++r) red[((b * RW + wave) * RM + r) * RN + lane] = acc[b][r];
+    __syncthreads();
+    if (threadIdx.x < NB * RM * RN) {
+        const int b = threadIdx.x / (RM * RN), e = threadIdx.x % (RM * RN);
+        float t = red[(b * RW) * RM * RN + e];
+#pragma unroll
+        for (int w = 1; w < RW; ++w) t += red[(b * RW + w) * RM * RN + e];
+        tile[b][e] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < RM * RN) {
+        const int r = threadIdx.x / RN, cl = threadIdx.x % RN;
+        if (m0 + r < M && n0 + cl < N) epi(tile[0], tile[NB - 1], r, cl, m0 + r, n0 + cl);
+    }
+}
+
+bool rows_fit(int M, int K) { return M <= ROWS_MAX_M && K <= ROWS_MAX_K && K >= 1; }
+
+template <class Epi>
+hipError_t launch_rows(hipStream_t s, const float *A, int lda, const float *gain, float eps, const float *W, const float *W2, int ldw,
+                       int M, int N, int K, const Epi &epi) {
+    constexpr int RED = (Epi::kDual ? 2 : 1) * RW * RM * RN * 4;
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [] {
+        attr_err = hipFuncSetAttribute((const void *)k_rows<Epi>, hipFuncAttributeMaxDynamicSharedMemorySize, RED + RM * ROWS_MAX_K * 4);
+    });
+    if (attr_err != hipSuccess) return attr_err;
+    hipLaunchKernelGGL((k_rows<Epi>), dim3((N + RN - 1) / RN, (M + RM - 1) / RM), dim3(RW * 64), RED + RM * K * 4, s, A, lda, gain, eps, W,
+                       W2, ldw, M, N, K, epi);
+    return hipGetLastError();
+}
+
+// One workgroup of 4 waves per (token, query head): causal softmax attention over the cache.  A thread takes a key at a time
+// for the scores; for the output wave w takes keys w, w + 4, ... with lane = feature, and the four sums meet in LDS.
+__global__ void __launch_bounds__(TB) k_attention(const float *__restrict__ qkv, const float *__restrict__ kc, const float *__restrict__ vc,
+                                                  float *__restrict__ out, spd_positions P, int q_len, int q, int kv, int d, int nqkv,
+                                                  int max_ctx) {
     extern __shared__ float sc[];          // [n_keys] scores, then probabilities
-    __shared__ float red[TB];
+    __shared__ float part[4][64];
+    __shared__ float qs[256];
+    __shared__ float red[2][4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = blockIdx.x / q, j = blockIdx.x % q;
     const int b = m / q_len, pos = P.pos[b] + (m % q_len);
     const int n_keys = pos + 1;            // causal: key position <= query position
     const int kh = j / (q / kv);
-    const float *qv = qkv + (size_t)m * nqkv + j * d;
+    for (int c = threadIdx.x; c < d; c += TB) qs[c] = qkv[(size_t)m * nqkv + j * d + c];
     const float *K = kc + ((size_t)b * kv + kh) * max_ctx * d;
     const float *V = vc + ((size_t)b * kv + kh) * max_ctx * d;
     const float scale = 1.0f / sqrtf((float)d);
+    __syncthreads();
     float mx = -INFINITY;
     for (int t = threadIdx.x; t < n_keys; t += TB) {
+        const float *kr = K + (size_t)t * d;
         float s = 0.f;
-        for (int c = 0; c < d; ++c) s += qv[c] * K[(size_t)t * d + c];
+        int c = 0;
+        for (; c + 32 <= d; c += 32) {     // 32 loads in flight
+            float kk[32];
+#pragma unroll
+            for (int u = 0; u < 32; ++u) kk[u] = kr[c + u];
+#pragma unroll
+            for (int u = 0; u < 32; ++u) s += qs[c + u] * kk[u];
+        }
+        for (; c < d; ++c) s += qs[c] * kr[c];
         s *= scale;
         sc[t] = s;
         mx = fmaxf(mx, s);
     }
-    red[threadIdx.x] = mx;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    if (lane == 0) red[0][wave] = mx;
     __syncthreads();
-    for (int o = TB / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + o]);
-        __syncthreads();
-    }
-    mx = red[0];
-    __syncthreads();
+    mx = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
     float sum = 0.f;
     for (int t = threadIdx.x; t < n_keys; t += TB) {
         const float e = expf(sc[t] - mx);
         sc[t] = e;
         sum += e;
     }
-    red[threadIdx.x] = sum;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if (lane == 0) red[1][wave] = sum;
     __syncthreads();
-    for (int o = TB / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    const float inv = 1.0f / red[0];
-    for (int c = threadIdx.x; c < d; c += TB) {
+    const float inv = 1.0f / (((red[1][0] + red[1][1]) + red[1][2]) + red[1][3]);
+    for (int c0 = 0; c0 < d; c0 += 64) {
+        const int c = c0 + lane < d ? c0 + lane : d - 1;
         float a = 0.f;
-        for (int t = 0; t < n_keys; ++t) a += sc[t] * V[(size_t)t * d + c];
-        out[(size_t)m * (q * d) + j * d + c] = a * inv;
+        for (int t0 = wave; t0 < n_keys; t0 += 32) {
+            float vv[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int t = t0 + 4 * u < n_keys ? t0 + 4 * u : n_keys - 1;
+                vv[u] = V[(size_t)t * d + c];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (t0 + 4 * u < n_keys) a += sc[t0 + 4 * u] * vv[u];
+        }
+        part[wave][lane] = a;
+        __syncthreads();
+        if (wave == 0 && c0 + lane < d)
+            out[(size_t)m * (q * d) + j * d + c0 + lane] = (((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane]) * inv;
+        __syncthreads();
     }
 }
 
@@ -243,23 +443,38 @@ namespace spd_f32 {
         if (e_ != hipSuccess) return e_;  \
     } while (0)
 
-hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const float *x, float *y_out) {
+// r_out (may be NULL) <- x + Y_r [+ bias], the local fold of an SPD block
+hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const float *x, float *y_out, float *r_out, const float *bias) {
     const spd_dims &D = *c.D;
     const int M = c.M, qd = D.q * D.d;
     float *xn = (float *)(c.ws + D.ws_xhat), *qkv = (float *)(c.ws + D.ws_qkv), *att = (float *)(c.ws + D.ws_ahat);
     const float *cosT = (const float *)(c.ws + D.ws_cos), *sinT = (const float *)(c.ws + D.ws_sin);
     float *kc = (float *)kvc, *vc = (float *)(kvc + D.kv_v);
-    hipLaunchKernelGGL(k_rmsnorm, dim3(M), dim3(TB), 0, c.s, x, (const float *)(w + D.w_g1), xn, D.h, D.eps);
-    SPD_TRY(hipGetLastError());
-    SPD_TRY(gemm(xn, D.h, (const float *)(w + D.w_qkv), D.nqkv, nullptr, qkv, D.nqkv, M, D.nqkv, D.h, c.s));
-    const int64_t nro = (int64_t)M * (D.q + D.kv) * (D.d / 2);
-    hipLaunchKernelGGL(k_rope_append, dim3(blocks_for(nro)), dim3(TB), 0, c.s, qkv, kc, vc, cosT, sinT, c.pos, M,
-                       c.q_len, D.q, D.kv, D.d, D.nqkv, D.max_ctx);
-    SPD_TRY(hipGetLastError());
+    if (rows_fit(M, D.h) && RN % D.d == 0) {
+        RowsQKV e;
+        e.qkv = qkv; e.kc = kc; e.vc = vc; e.cosT = cosT; e.sinT = sinT;
+        e.q_len = c.q_len; e.q = D.q; e.kv = D.kv; e.d = D.d; e.nqkv = D.nqkv; e.max_ctx = D.max_ctx; e.P = c.pos;
+        SPD_TRY(launch_rows(c.s, x, D.h, (const float *)(w + D.w_g1), D.eps, (const float *)(w + D.w_qkv), nullptr, D.nqkv, M, D.nqkv, D.h, e));
+    } else {
+        hipLaunchKernelGGL(k_rmsnorm, dim3(M), dim3(TB), 0, c.s, x, (const float *)(w + D.w_g1), xn, D.h, D.eps);
+        SPD_TRY(hipGetLastError());
+        SPD_TRY(gemm(xn, D.h, (const float *)(w + D.w_qkv), D.nqkv, nullptr, qkv, D.nqkv, M, D.nqkv, D.h, c.s));
+        const int64_t nro = (int64_t)M * (D.q + D.kv) * (D.d / 2);
+        hipLaunchKernelGGL(k_rope_append, dim3(blocks_for(nro)), dim3(TB), 0, c.s, qkv, kc, vc, cosT, sinT, c.pos, M,
+                           c.q_len, D.q, D.kv, D.d, D.nqkv, D.max_ctx);
+        SPD_TRY(hipGetLastError());
+    }
     hipLaunchKernelGGL(k_attention, dim3(M * D.q), dim3(TB), (size_t)c.max_pos_end * sizeof(float), c.s, qkv, kc, vc,
                        att, c.pos, c.q_len, D.q, D.kv, D.d, D.nqkv, D.max_ctx);
     SPD_TRY(hipGetLastError());
-    SPD_TRY(gemm(att, qd, (const float *)(w + D.w_o), D.h, nullptr, y_out, D.h, M, D.h, qd, c.s));
+    if (rows_fit(M, qd)) {
+        RowsO e;
+        e.y = y_out; e.r_out = r_out; e.x = x; e.bias = bias; e.ld = D.h;
+        SPD_TRY(launch_rows(c.s, att, qd, nullptr, 0.f, (const float *)(w + D.w_o), nullptr, D.h, M, D.h, qd, e));
+    } else {
+        SPD_TRY(gemm(att, qd, (const float *)(w + D.w_o), D.h, nullptr, y_out, D.h, M, D.h, qd, c.s));
+        if (r_out) SPD_TRY(spd_common::rank_sum(x, y_out, 1, (int64_t)M * D.h, r_out, c.s, bias, D.h));
+    }
     if (c.taps) {
         if (c.taps->q) SPD_TRY(spd_common::copy2d(qkv, D.nqkv, c.taps->q, qd, M, qd, c.s));
         if (c.taps->attn) SPD_TRY(spd_common::copy2d(att, qd, c.taps->attn, qd, M, qd, c.s));
@@ -272,14 +487,27 @@ hipError_t mlp_half(const spd_call &c, const char *w, const float *r_in, const f
     const spd_dims &D = *c.D;
     const int M = c.M, f = D.f;
     float *xn = (float *)(c.ws + D.ws_xhat), *gu = (float *)(c.ws + D.ws_gu), *u = (float *)(c.ws + D.ws_uhat);
-    hipLaunchKernelGGL(k_rmsnorm, dim3(M), dim3(TB), 0, c.s, r_in, (const float *)(w + D.w_g2), xn, D.h, D.eps);
-    SPD_TRY(hipGetLastError());
-    SPD_TRY(gemm(xn, D.h, (const float *)(w + D.w_g), f, nullptr, gu, f, M, f, D.h, c.s));
-    SPD_TRY(gemm(xn, D.h, (const float *)(w + D.w_u), f, nullptr, gu + (size_t)M * f, f, M, f, D.h, c.s));
-    hipLaunchKernelGGL(k_swiglu, dim3(blocks_for((int64_t)M * f)), dim3(TB), 0, c.s, gu, gu + (size_t)M * f, u,
-                       (int64_t)M * f);
-    SPD_TRY(hipGetLastError());
-    SPD_TRY(gemm(u, f, (const float *)(w + D.w_d), D.h, add, out, D.h, M, D.h, f, c.s));
+    if (rows_fit(M, D.h)) {
+        RowsGU e;
+        e.u = u; e.ld = f;
+        SPD_TRY(launch_rows(c.s, r_in, D.h, (const float *)(w + D.w_g2), D.eps, (const float *)(w + D.w_g), (const float *)(w + D.w_u), f, M, f,
+                            D.h, e));
+    } else {
+        hipLaunchKernelGGL(k_rmsnorm, dim3(M), dim3(TB), 0, c.s, r_in, (const float *)(w + D.w_g2), xn, D.h, D.eps);
+        SPD_TRY(hipGetLastError());
+        SPD_TRY(gemm(xn, D.h, (const float *)(w + D.w_g), f, nullptr, gu, f, M, f, D.h, c.s));
+        SPD_TRY(gemm(xn, D.h, (const float *)(w + D.w_u), f, nullptr, gu + (size_t)M * f, f, M, f, D.h, c.s));
+        hipLaunchKernelGGL(k_swiglu, dim3(blocks_for((int64_t)M * f)), dim3(TB), 0, c.s, gu, gu + (size_t)M * f, u,
+                           (int64_t)M * f);
+        SPD_TRY(hipGetLastError());
+    }
+    if (rows_fit(M, f)) {
+        RowsDown e;
+        e.out = out; e.add = add; e.ld = D.h;
+        SPD_TRY(launch_rows(c.s, u, f, nullptr, 0.f, (const float *)(w + D.w_d), nullptr, D.h, M, D.h, f, e));
+    } else {
+        SPD_TRY(gemm(u, f, (const float *)(w + D.w_d), D.h, add, out, D.h, M, D.h, f, c.s));
+    }
     if (c.taps && c.taps->u) SPD_TRY(spd_common::copy2d(u, f, c.taps->u, f, M, f, c.s));
     return hipSuccess;
 }

@@ -266,6 +266,38 @@ def test_bf16_gemm_contraction_lengths(gpu, w, flag, split, q_len):
     case.close()
 
 
+# fp32 path at the edges of its small-product kernel (at most 64 rows and 1024 contraction elements, rotation inside it when the
+# head size divides its 64 columns): odd widths, a head size that does not divide 64, one row, a full and a
+# started 8-row tile, the last size inside the range and the first beyond it in rows and in K
+F32_ODD = Workload(name="f32-odd", hidden=131, n_q_heads=6, n_kv_heads=2, head_dim=10, ffn=154, n_layers=1, tp=2, dtype=F32,
+                   seed=41, batch=1, q_len=1, ctx=96, mask=(1,))
+F32_HEADS = Workload(name="f32-d32", hidden=1024, n_q_heads=4, n_kv_heads=4, head_dim=32, ffn=2050, n_layers=1, tp=2, dtype=F32,
+                     seed=42, batch=1, q_len=1, ctx=96, mask=(1,))
+F32_WIDE = Workload(name="f32-k1025", hidden=1025, n_q_heads=2, n_kv_heads=2, head_dim=64, ffn=64, n_layers=1, tp=2, dtype=F32,
+                    seed=43, batch=1, q_len=1, ctx=96, mask=(1,))
+
+
+@pytest.mark.parametrize("w", [F32_ODD, F32_HEADS, F32_WIDE], ids=lambda w: w.name)
+@pytest.mark.parametrize("flag", [1, 0], ids=["spd", "tp"])
+@pytest.mark.parametrize("batch,q_len,positions", [(1, 1, [0]), (2, 4, [0, 13]), (3, 3, [5, 0, 30]), (1, 64, [7]), (1, 65, [0])],
+                         ids=["1", "8", "9", "64", "65"])
+def test_fp32_small_products(gpu, w, flag, batch, q_len, positions):
+    import torch
+    M = batch * q_len
+    case = Case(w, gpu, ranks=range(w.tp), positions=positions, max_ctx=96, max_tokens=M)
+    X = inputs.hidden_states(w, M)
+    slots = torch.zeros((w.tp, M, w.hidden), dtype=torch.float32, device=gpu)
+    say(f"fp32 small products: {w.name} {M} tokens flag={flag}")
+    out = torch.empty((M, w.hidden), dtype=torch.float32, device=gpu)
+    B.spd_block_forward(case.dev.ctx, 0, flag, B.SPD_ALL_RANKS, case.dev.weights[0], case.dev.kv[0], positions, batch, q_len,
+                        case.to_dev(X), slots, out, case.dev.workspace)
+    torch.cuda.synchronize()
+    want, _ = O.block_all_ranks(case.sh, X, case.shards[0], case.caches[0], positions, batch, q_len, flag, {})
+    err = assert_close(out.cpu().numpy(), want, w, "block output", scale=0.02)      # 2e-5: some 20 roundings of fp32 over K <= 2050
+    say(f"  block output max err {err:.2e}")
+    case.close()
+
+
 # ------------------------------------------------------------------------------------------------
 # block with bias in the output projection (Sec. 4.1.2): both paths, both block kinds
 # ------------------------------------------------------------------------------------------------
