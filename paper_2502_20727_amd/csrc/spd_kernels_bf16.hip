@@ -2148,10 +2148,13 @@ inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b);
 
 
 // Number of K slices of a weight-streaming launch: 1 when there are enough pairs of n-tiles to
-// occupy the chip, otherwise about two workgroups of 8 waves per compute unit.
+// occupy the chip, or half of it with at most four k-tiles for each of 16 waves (everything is requested at once
+// then, and the second kernel that adds slices takes 4 us: down projection of the 7B shard, 128 pairs x 43 k-tiles,
+// 5.0 + 3.4 -> 6.4 us, of the 13B shard, 160 x 54, 5.9 + 4.3 -> 8.6); otherwise about two workgroups of 8 waves per compute unit.
 constexpr int GEMV_SLICE_W = 8;
+inline bool gemv_whole(int n_pairs, int KT) { return n_pairs >= 192 || (n_pairs >= 96 && KT >= 32 && KT <= 64); }
 inline int gemv_slices(int n_pairs, int KT) {
-    if (n_pairs >= 192) return 1;
+    if (gemv_whole(n_pairs, KT)) return 1;
     int KS = (512 + n_pairs - 1) / n_pairs;
     const int ks_max = KT / (2 * GEMV_SLICE_W) > 0 ? KT / (2 * GEMV_SLICE_W) : 1;         // at least two k-tiles per wave
     if (KS > ks_max) KS = ks_max;
@@ -2167,8 +2170,8 @@ hipError_t launch_gemv(const spd_call &c, const __bf16 *Wp, const __bf16 *Xhi, c
                        const Epi &epi, int rows = 16) {
     const spd_dims &D = *c.D;
     float *kpart = (float *)(c.ws + D.ws_kpart);
-    if (n_pairs >= 192) {
-        // enough pairs to occupy the chip: one workgroup per pair, no slices
+    if (gemv_whole(n_pairs, KT)) {
+        // one workgroup per pair, no slices
         if (KT >= 32) {
             // 16 waves share 512 VGPRs per lane and SIMD: two batches of 2 k-tiles fit.  With as few as
             // 2 k-tiles per wave everything is requested at once, which is what a short kernel wants.
