@@ -2083,11 +2083,25 @@ __global__ void __launch_bounds__(256) k_attn_prefill(const __bf16 *__restrict__
     const __bf16 *vbase = vc + ((size_t)b * kv + kvh) * (size_t)max_ctx * d;
     const float scale = 1.0f / sqrtf((float)d);
     const int nblk = (last_key + 31) >> 5;
-    for (int vb = wave; vb < nblk; vb += 4) {
-        KVFrags<DT> f;
-        load_kv<DT>(f, kbase, vbase, vb, d, lane);
+    // The wave's blocks are wave + 4 j, j < nw.  Two register sets used alternately: the next block's keys and values are on
+    // their way while one is worked on (few waves share a SIMD here, so nobody else hides that latency); an index past
+    // the wave's last block repeats it and is not used.
+    const int nw = nblk > wave ? (nblk - wave + 3) >> 2 : 0;
+    auto blk = [&](int j) { return nw > 0 ? wave + 4 * (j < nw ? j : nw - 1) : 0; };
+    KVFrags<DT> f0, f1;
+    load_kv<DT>(f0, kbase, vbase, blk(0), d, lane);
+    for (int j = 0; j < nw; j += 2) {
+        load_kv<DT>(f1, kbase, vbase, blk(j + 1), d, lane);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int c = 0; c < CT; ++c) attn_block<DT, true>(st[c], qf[c], f, vb, nk[c], scale, lane);
+        for (int c = 0; c < CT; ++c) attn_block<DT, true>(st[c], qf[c], f0, blk(j), nk[c], scale, lane);
+        __builtin_amdgcn_sched_barrier(0);
+        load_kv<DT>(f0, kbase, vbase, blk(j + 2), d, lane);
+        __builtin_amdgcn_sched_barrier(0);
+        if (j + 1 < nw) {
+#pragma unroll
+            for (int c = 0; c < CT; ++c) attn_block<DT, true>(st[c], qf[c], f1, blk(j + 1), nk[c], scale, lane);
+        }
     }
     // partial states to LDS
 #pragma unroll
@@ -2536,11 +2550,14 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
                            D.d, splits);
         SPD_TRY(hipGetLastError());
     } else {
-        constexpr int CT = 2;
         const int n_ct = (c.q_len * D.group + 15) / 16;
-        const dim3 grid(cdiv(n_ct, CT), D.kv, c.batch);
-#define SPD_PREFILL(DTV)                                                                                                   \
+        // Two column tiles per workgroup read each key and value once for both; up to two rounds of such workgroups, one
+        // tile each gives twice the waves instead (70B shard, us: 128 tokens 6.4 -> 4.5, 512 behind 1536 positions 29 -> 26
+        // and 19 with the next block prefetched, 1000: 18 -> 16; 4 x 2048 tokens stay with two).
+        const bool one = (int64_t)cdiv(n_ct, 2) * D.kv * c.batch <= 512;
+#define SPD_PREFILL_CT(DTV, CT)                                                                                            \
     {                                                                                                                      \
+        const dim3 grid(cdiv(n_ct, CT), D.kv, c.batch);                                                                                                                      \
         constexpr int lds = 4 * CT * DTV * 64 * 16 + 4 * CT * 2 * 16 * 4;                                                  \
         static std::once_flag once;                                                                                        \
         static hipError_t attr_err = hipSuccess;                                                                           \
@@ -2551,6 +2568,9 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
         hipLaunchKernelGGL((k_attn_prefill<DTV, CT>), grid, dim3(256), lds, c.s, qbuf, qlo, kc, vc, ahat, alo, c.pos, c.q_len, \
                            D.q, D.kv, D.max_ctx);                                                                          \
     }
+#define SPD_PREFILL(DTV)           \
+    if (one) SPD_PREFILL_CT(DTV, 1) \
+    else SPD_PREFILL_CT(DTV, 2)
         switch (DT) {
             case 2: SPD_PREFILL(2); break;
             case 4: SPD_PREFILL(4); break;
@@ -2559,6 +2579,7 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
             default: return hipErrorInvalidValue;
         }
 #undef SPD_PREFILL
+#undef SPD_PREFILL_CT
         SPD_TRY(hipGetLastError());
     }
     spd_stage_end(c, SPD_STAGE_ATTN);
