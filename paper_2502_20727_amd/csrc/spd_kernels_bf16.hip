@@ -99,16 +99,6 @@ __device__ __forceinline__ float sum_ss(const float *__restrict__ ss, int nch, i
     return s;
 }
 
-// 1 / sqrt(mean(x^2) + eps) of row m from `nch` partial sums of squares ss[c][m]; the four
-// lanes that share a token each add a quarter of the partials (fixed order).
-__device__ __forceinline__ float row_rsqrt(const float *__restrict__ ss, int nch, int m_pad, int m, int g, int h,
-                                           float eps) {
-    float s = sum_ss(ss, nch, m_pad, m, g, 4);
-    s += shfl_xor_f(s, 16);
-    s += shfl_xor_f(s, 32);
-    return 1.0f / sqrtf(s / (float)h + eps);
-}
-
 // 1 / sqrt(mean(x^2) + eps) of every token from its `nch` partial sums of squares, written over the first of them
 // (ss[0][m]); a consumer told nch = 0 takes the factor as it is.  A projection's epilogue that adds 256 partials per
 // token by itself waits for eight dependent rounds of loads per m-tile: 28 of 150 us in the gate/up projection of 1000
@@ -231,7 +221,9 @@ __device__ __forceinline__ float4 ldnt4(const float *p) {
 }
 
 // The launch is a fixed number of workgroups (two per compute unit) that walk the (chunk, m-tile) items with a stride.
-template <int NP>     // NP pieces of 256 features per workgroup and token (1 or 2): NP KiB contiguous per token row
+// SLOTS = false (the first norm of a call: nothing to sum) needs few registers, so that four workgroups share a compute unit
+// and hide each other's latency: 1000 tokens of the 70B shard 22 -> 15 us.
+template <int NP, bool SLOTS>     // NP pieces of 256 features per workgroup and token (1 or 2): NP KiB contiguous per token row
 __global__ void __launch_bounds__(256) k_prep_rows(const float *__restrict__ base, const float *__restrict__ slots, int n_slots,
                                                    size_t slot_stride, float *__restrict__ out,
                                                    const float *__restrict__ gain, __bf16 *__restrict__ xhat,
@@ -254,7 +246,7 @@ __global__ void __launch_bounds__(256) k_prep_rows(const float *__restrict__ bas
     constexpr int TB = NP == 1 ? 4 : 1;      // tokens whose loads are in flight together
 #pragma unroll
     for (int it = 0; it < 4 / TB; ++it) {
-        float4 p[TB][NP][8], b[TB][NP], v[TB][NP];
+        float4 p[SLOTS ? TB : 1][NP][8], b[TB][NP], v[TB][NP];
         bool valid[TB];
         size_t off[TB];
 #pragma unroll
@@ -265,6 +257,7 @@ __global__ void __launch_bounds__(256) k_prep_rows(const float *__restrict__ bas
 #pragma unroll
             for (int q = 0; q < NP; ++q) v[t][q] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
+        if constexpr (SLOTS)
         for (int s0 = 0; s0 < n_slots; s0 += 8) {
 #pragma unroll
             for (int t = 0; t < TB; ++t)
@@ -1121,6 +1114,15 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
     const int n = k1 - k0;
     SkinnyBatch<MT, SPLIT> cur, oth;
     if (n > 0) load(cur, k0);
+    // the norm statistics by all threads while the first weights are on their way: at the end, a wave per m-tile, they were
+    // eight dependent rounds of loads for 256 partials per token
+    __shared__ float early_ss[Epi::kNeedsRs ? W * 64 : 1];
+    constexpr int RS_PARTS = W * 4 / MT;               // threads per token
+    if constexpr (Epi::kNeedsRs) {
+        int m = mt0 * 16 + (int)threadIdx.x % (MT * 16);
+        m = m < n_mtiles * 16 ? m : n_mtiles * 16 - 1;
+        early_ss[threadIdx.x] = sum_ss(epi.ss, epi.nch, epi.m_pad, m, (int)threadIdx.x / (MT * 16), RS_PARTS);
+    }
     int i = 0;
     for (; i + 2 < n; i += 2) {          // steady state: no branch between the loads and their use
         load(oth, k0 + i + 1);
@@ -1152,7 +1154,12 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
             b += red[((w * MT + t) * 2 + 1) * 64 + lane];
         }
         float rs = 1.f;
-        if constexpr (Epi::kNeedsRs) rs = row_rsqrt(epi.ss, epi.nch, epi.m_pad, mt * 16 + (lane & 15), lane >> 4, epi.h, epi.eps);
+        if constexpr (Epi::kNeedsRs) {
+            float q = 0.f;
+#pragma unroll
+            for (int part = 0; part < RS_PARTS; ++part) q += early_ss[part * MT * 16 + t * 16 + (lane & 15)];
+            rs = 1.0f / sqrtf(q / (float)epi.h + epi.eps);
+        }
         if constexpr (MODE == 2) epi.slice(pair, ks, mt, a, b, lane, rs, epi.pre(pair, mt, lane));
         else epi(pair, mt, a, b, lane, rs, epi.pre(pair, mt, lane));
     }
@@ -2422,8 +2429,12 @@ hipError_t prep(const spd_call &c, const float *base, const float *slots, int n_
     if (tpw == 8 && D.h % 256 == 0)
     {
         const int n_chunks = D.h / 256, n_items = n_chunks * (int)cdiv(c.M, 16);
-        hipLaunchKernelGGL(k_prep_rows<1>, dim3(n_items < PREP_ROWS_WGS ? n_items : PREP_ROWS_WGS), dim3(256), 0, c.s, base, slots,
-                           n_slots, c.slot_stride, out, gain, xhat, xlo, ss, c.M, D.h, D.m_pad, bias, n_chunks, n_items);
+        if (n_slots > 0)
+            hipLaunchKernelGGL((k_prep_rows<1, true>), dim3(n_items < PREP_ROWS_WGS ? n_items : PREP_ROWS_WGS), dim3(256), 0, c.s, base,
+                               slots, n_slots, c.slot_stride, out, gain, xhat, xlo, ss, c.M, D.h, D.m_pad, bias, n_chunks, n_items);
+        else
+            hipLaunchKernelGGL((k_prep_rows<1, false>), dim3(n_items < 4 * PREP_ROWS_WGS ? n_items : 4 * PREP_ROWS_WGS), dim3(256), 0, c.s,
+                               base, slots, 0, c.slot_stride, out, gain, xhat, xlo, ss, c.M, D.h, D.m_pad, bias, n_chunks, n_items);
     }
     else
         hipLaunchKernelGGL(k_prep, dim3(cdiv(nch, 4), cdiv(c.M, 16)), dim3(256), 0, c.s, base, slots, n_slots,
