@@ -479,6 +479,7 @@ const float4 tb##j = *(const float4 *)(slots + (size_t)min(s0 + j, last) * slot_
 // computes from the partial sums of squares ss[nch][m_pad].
 struct EpiQKV {
     static constexpr bool kLong = true;        // used by calls of any length
+    static constexpr bool kWideSum = true;     // K slices are added in 64 bits
     static constexpr bool kNeedsRs = true;
     static constexpr bool kSliced = false;
     int M, q_len, q, kv, d, h, max_ctx, nch, m_pad;
@@ -602,6 +603,7 @@ struct EpiQKVPart {
 template <bool MID>      // MID: the epilogue can also perform the kept attention sync point (spd = 2)
 struct EpiOT {
     static constexpr bool kLong = !MID;
+    static constexpr bool kWideSum = false;
     static constexpr bool kNeedsRs = false;
     static constexpr bool kSliced = false;
     int M, h, spd, m_pad;
@@ -704,6 +706,7 @@ struct EpiOT {
 
 struct EpiGU {
     static constexpr bool kLong = true;
+    static constexpr bool kWideSum = false;
     static constexpr bool kNeedsRs = true;
     static constexpr bool kSliced = false;
     int M, h, f_pad, nch, m_pad;
@@ -752,6 +755,7 @@ struct EpiGU {
 template <bool FUSED>
 struct EpiDownT {
     static constexpr bool kLong = !FUSED;
+    static constexpr bool kWideSum = false;
     static constexpr bool kNeedsRs = false;
     static constexpr bool kSliced = false;
     int M, h, spd;
@@ -1334,13 +1338,20 @@ __global__ void __launch_bounds__(MID_PAIRS * 64) k_mid_finish(const f32x4 *__re
         }
     }
     if (!live) return;
-    f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
+    // the QKV projection's slices are added in 64 bits: its keys and values are rounded to bf16 next, and the sums over up to
+    // 16 slices are the larger part of what decides the last place of a near tie
+    typedef typename std::conditional<Epi::kWideSum, double, float>::type Sum;
+    Sum sa[4] = {0, 0, 0, 0}, sb[4] = {0, 0, 0, 0};
+    auto add = [&](int j) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            sa[e] += (Sum)ta[j][e];
+            sb[e] += (Sum)tb[j][e];
+        }
+    };
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-        if (j < KS) {
-            a += ta[j];
-            b += tb[j];
-        }
+        if (j < KS) add(j);
     for (int s0 = 8; s0 < KS; s0 += 8) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -1350,11 +1361,9 @@ __global__ void __launch_bounds__(MID_PAIRS * 64) k_mid_finish(const f32x4 *__re
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            if (s0 + j < KS) {
-                a += ta[j];
-                b += tb[j];
-            }
+            if (s0 + j < KS) add(j);
     }
+    const f32x4 a = {(float)sa[0], (float)sa[1], (float)sa[2], (float)sa[3]}, b = {(float)sb[0], (float)sb[1], (float)sb[2], (float)sb[3]};
     epi(pair, mt, a, b, lane, rs, pre);
 }
 
