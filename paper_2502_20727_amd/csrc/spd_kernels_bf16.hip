@@ -437,12 +437,14 @@ __device__ __forceinline__ void rank_sum_pair(const float *__restrict__ slots, s
                                           const float *__restrict__ base, const float *__restrict__ bias, int h, size_t oa,
                                           size_t ob, float4 own_a, float4 own_b, float4 &ra, float4 &rb) {
     float4 acc_a = make_float4(0.f, 0.f, 0.f, 0.f), acc_b = acc_a;
-    const int last = tp - 1;
+    // (past the end: the last slot again; the own slot is in registers: a neighbour's line, which is on its way anyway)
+    const int last = tp - 1, other = rank > 0 ? rank - 1 : (tp > 1 ? 1 : 0);
+    auto at = [&](int s) { return s == rank ? other : min(s, last); };
     const float4 bs_a = *(const float4 *)(base + oa), bs_b = *(const float4 *)(base + ob);
     for (int s0 = 0; s0 < tp; s0 += 8) {
 #define SPD_LD(j)                                                                                         \
-const float4 ta##j = *(const float4 *)(slots + (size_t)min(s0 + j, last) * slot_stride + oa);         \
-const float4 tb##j = *(const float4 *)(slots + (size_t)min(s0 + j, last) * slot_stride + ob);
+const float4 ta##j = *(const float4 *)(slots + (size_t)at(s0 + j) * slot_stride + oa);                \
+const float4 tb##j = *(const float4 *)(slots + (size_t)at(s0 + j) * slot_stride + ob);
         SPD_LD(0) SPD_LD(1) SPD_LD(2) SPD_LD(3) SPD_LD(4) SPD_LD(5) SPD_LD(6) SPD_LD(7)
 #undef SPD_LD
         auto add = [&](int s, const float4 &ta, const float4 &tb) {
@@ -1116,8 +1118,13 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
         }
     };
     const int n = k1 - k0;
+    const int rot = n > 0 ? (int)((unsigned)pair * 5u % (unsigned)n) : 0;
+    auto at = [&](int q) {
+        q += rot;
+        return k0 + (q >= n ? q - n : q);
+    };
     SkinnyBatch<MT, SPLIT> cur, oth;
-    if (n > 0) load(cur, k0);
+    if (n > 0) load(cur, at(0));
     // the norm statistics by all threads while the first weights are on their way: at the end, a wave per m-tile, they were
     // eight dependent rounds of loads for 256 partials per token
     __shared__ float early_ss[Epi::kNeedsRs ? W * 64 : 1];
@@ -1129,13 +1136,13 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
     }
     int i = 0;
     for (; i + 2 < n; i += 2) {          // steady state: no branch between the loads and their use
-        load(oth, k0 + i + 1);
+        load(oth, at(i + 1));
         consume(cur);
-        load(cur, k0 + i + 2);
+        load(cur, at(i + 2));
         consume(oth);
     }
     if (i + 1 < n) {
-        load(oth, k0 + i + 1);
+        load(oth, at(i + 1));
         consume(cur);
         consume(oth);
     } else if (i < n) {
