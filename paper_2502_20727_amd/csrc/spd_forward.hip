@@ -73,7 +73,7 @@ int check_call(const spd_ctx *ctx, int32_t rank, const int32_t *positions, int32
 // slots hold the partial sums of the final sync point and *base_out is what they are added
 // to: X for an SPD block (Sec. 4.1.1: the block input joins after the remaining sync point), R = X + sum Y for a TP
 // block.  *syncs is incremented by the number of kept attention sync points (0 or 1).
-// With end_sync_out (one rank, bf16 path, at most 16 tokens) the last kernel of the block also
+// With end_sync_out (one rank, bf16 path, at most 512 tokens) the last kernel of the block also
 // performs that final rank-sum into x_out (and the next block's first-norm preparation when
 // next_g1 is given); *end_done tells the caller whether it did.
 int block_core(const spd_ctx *ctx, spd_call &c, int spd, int32_t rank, const char *weights, char *kv,
@@ -106,7 +106,7 @@ int block_core(const spd_ctx *ctx, spd_call &c, int spd, int32_t rank, const cha
             *base_out = x;
         } else {
             // kept sync point: R = X + sum_r Y_r (+ bias), with the second norm's elementwise part; for one
-            // rank and a call of at most 512 tokens the O projection's epilogue does it, otherwise prep()
+            // rank and a call of at most 128 tokens the O projection's epilogue does it, otherwise prep()
             spd_bf16::spd_mid_sync ms;
             ms.slots = slots; ms.tp = D.tp; ms.rank = r0; ms.rbuf = rbuf;
             bool mid_done = false;

@@ -155,7 +155,7 @@ void compute_dims(const spd_config &c, spd_dims &D) {
         D.ws_ss1 = o; o = spd_align256(o + (h / 32) * M * 4);
         D.ws_ss2 = o; o = spd_align256(o + (h / 32) * M * 4);
         D.ws_uhat = o; o = spd_align256(o + 2 * M * f * 2);
-        // partial tiles of the K-sliced launches: the decode sizes always, the 17 .. 128 token kind when calls can be that long
+        // partial tiles of the K-sliced launches: the decode sizes always, the kind of longer calls when they can be longer
         D.kpart_tiles = D.max_tokens > 16 ? (size_t)SPD_MID_KPART : (size_t)SPD_MAX_KPART;
         // ... and, when calls can be longer than 512 tokens, the slice partials of a K-sliced QKV GEMM: up to
         // 8192 (slice, token) rows of fp32

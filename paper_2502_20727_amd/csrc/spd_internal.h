@@ -35,7 +35,7 @@ constexpr int SPD_AUTO_SPLIT_TOKENS = 16;    // SPD_SPLIT_AUTO: calls of more th
 constexpr int SPD_MAX_QKV_SLICES = 8;  // K slices of a decode QKV projection that the attention kernel adds up itself
 constexpr int SPD_DUAL_MIN_TOKENS = 1024;   // a prefill runs as two chains when each half has at least this many tokens
 constexpr int SPD_MAX_KPART = 4096;   // split-K partial tiles (pairs x splits) a GEMV may park in the workspace
-constexpr int SPD_MID_KPART = 2304 * 8;   // ... and a call of 17 .. 128 tokens (pairs x splits x m-tiles)
+constexpr int SPD_MID_KPART = 2304 * 8;   // ... and a call of more than 16 tokens (pairs x splits x m-tiles)
 
 SPD_HD size_t spd_frag_index(int tile, int ktile, int n_ktiles) {
     return ((size_t)tile * (size_t)n_ktiles + (size_t)ktile) * SPD_FRAG_ELEMS;
@@ -252,7 +252,7 @@ hipError_t prep(const spd_call &c, const float *base, const float *slots, int n_
 // QKV + rotary + cache append + attention + O projection.
 //   spd = 1: ybuf <- Y_r, xhat2 <- fp16((X + Y_r) g2) and its partial sums of squares
 //   spd = 0: slot <- Y_r
-// With `mid` (TP block, one rank, calls of at most 512 tokens) the O projection's epilogue also performs
+// With `mid` (TP block, one rank, calls of at most 128 tokens) the O projection's epilogue also performs
 // the kept attention sync point: R = X + sum of the slots (+ bias) -> mid->rbuf, second norm prepared;
 // *mid_done tells whether it did (otherwise the caller runs prep()).
 struct spd_mid_sync {
@@ -274,7 +274,7 @@ struct spd_end_sync {
     const float *bias;        // [h] added once after the sum (SPD block with bias), or NULL
 };
 // gate/up + SwiGLU + down.  spd = 1: slot <- ybuf + Z_r; spd = 0: slot <- Z_r.  With `fuse`
-// (calls of at most 16 tokens) the down projection's epilogue also performs the end-of-block
+// (calls of at most 512 tokens) the down projection's epilogue also performs the end-of-block
 // sync point; returns through *fused whether it did.
 // ss_per_pair: the sums of squares of the MLP input were left per pair of n-tiles (by the O projection's
 // epilogue) rather than per prep() chunk

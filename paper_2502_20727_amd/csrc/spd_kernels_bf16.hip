@@ -604,7 +604,6 @@ struct EpiQKVPart {
 
 template <bool MID>      // MID: the epilogue can also perform the kept attention sync point (spd = 2)
 struct EpiOT {
-    static constexpr bool kLong = !MID;
     static constexpr bool kWideSum = false;
     static constexpr bool kNeedsRs = false;
     static constexpr bool kSliced = false;
@@ -2290,6 +2289,7 @@ hipError_t launch_skinny(const spd_call &c, bool split, const __bf16 *Wp, const 
 // everything smaller (main kernel, us at 32 / 64 / 128 tokens, mid against GEMM tiles: 117 MB 22 / 23.5 / 27 against
 // 25 / 26 / 31; 71 MB 15.4 / 17.2 / 20.9 against 14.3 / 15.4 / 18.3; 58 MB 12 / 14.1 / 19.8 against 12.3 / 12.9 / 14.9).
 // Returns false in *done when the shape is not its kind.
+constexpr int MID_SYNC_TOKENS = 128;       // calls whose O projection's epilogue performs a kept attention sync point
 constexpr int SKINNY_MAX_MTILES = 32;      // beyond 512 tokens one launch of the LDS-tiled GEMM does without K slices
 constexpr int MID_MAX_MTILES = 8;
 constexpr int MID_MIN_TILES = 48 * 1024;   // (pairs of n-tiles) x (k-tiles): 2 KiB each
@@ -2393,21 +2393,23 @@ hipError_t launch_proj(const spd_call &c, bool split, const __bf16 *Wp, const __
 // The output projection's contraction is short (a rank's heads): up to 128 tokens the skinny kernel with the whole epilogue
 // beats slices and their finishing kernel; beyond, 256 x 128 tiles by themselves beat both once the skinny kernel would
 // take two rounds (70B shard, main kernel, us, skinny / tiles: 192 tokens 15.8 / 14.7, 512: 30.9 / 17.2; 13B 384: 10.8 / 11.4, 512:
-// 16.1 / 12.0), unless the epilogue carries a sync point, which wants the finishing kernel's many workgroups.
+// 16.1 / 12.0).
 template <bool MID>
 hipError_t launch_o(const spd_call &c, bool split, const __bf16 *Wp, const __bf16 *Xhi, size_t plane, int n_pairs, int KT,
                     const EpiOT<MID> &epi) {
     const int n_mtiles = (c.M + 15) / 16, zg = (n_mtiles + 7) / 8;
     const __bf16 *Xlo = Xhi + plane;
-    if (n_mtiles > 1 && n_mtiles <= SKINNY_MAX_MTILES) {
-        if (n_mtiles <= 8 || n_pairs * zg < 512) return launch_skinny(c, split, Wp, Xhi, plane, n_pairs, KT, epi);
-        if (!MID)
+    if (n_mtiles == 1)
+        return split ? launch_gemv<true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi) : launch_gemv<false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
+    if (n_mtiles <= 8 || (n_mtiles <= SKINNY_MAX_MTILES && n_pairs * zg < 512)) return launch_skinny(c, split, Wp, Xhi, plane, n_pairs, KT, epi);
+    if constexpr (MID) {
+        return hipErrorInvalidValue;         // the epilogue that carries a sync point serves calls of up to 128 tokens
+    } else {
+        if (n_mtiles <= SKINNY_MAX_MTILES)
             return split ? launch_gemm_lds_cfg<GemmHalf, true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi)
                          : launch_gemm_lds_cfg<GemmHalf, false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
-    } else if constexpr (!MID) {
-        if (n_mtiles > 1) return split ? launch_gemm_lds<true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi) : launch_gemm_lds<false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
+        return split ? launch_gemm_lds<true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi) : launch_gemm_lds<false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
     }
-    return launch_proj(c, split, Wp, Xhi, plane, n_pairs, KT, epi);
 }
 
 // chunking of the sum-of-squares partials written by prep()
@@ -2611,7 +2613,8 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
     }
     spd_stage_end(c, SPD_STAGE_ATTN);
 
-    const bool fuse_mid = mid && !spd && M <= 16 * SKINNY_MAX_MTILES;
+    // (beyond 128 tokens the rank-sum as a kernel of its own: 13B shard, 333 tokens, O + sync point 31.4 -> 12.6 + 17.2 us)
+    const bool fuse_mid = mid && !spd && M <= MID_SYNC_TOKENS;
     if (mid_done) *mid_done = fuse_mid;
     auto fill_o = [&](auto &e2) {
         e2.M = M; e2.h = D.h; e2.spd = spd; e2.m_pad = D.m_pad;
