@@ -1403,7 +1403,7 @@ struct GemmTall {     // 128 x 384: for few n-tiles, where 256 x 256 tiles leave
 struct GemmWide {     // 160 x 256, every wave all 10 n-tiles of 2 m-tiles: for split activations and few n-tiles
     static constexpr int WN = 1, WM = 8, TI = 10, TJ = 2, NST = 2, NSTX = 3;      // (80 n-tiles x 512 m-tiles = exactly 256 tiles)
 };
-struct GemmSquare {   // 128 x 128, 64 KiB per k-tile pair and round of four stages: calls of 65 .. 256 tokens and few n-tiles, in K slices
+struct GemmSquare {   // 128 x 128, four stages of 32 KiB (split: five of 24 KiB): calls of 65 .. 256 tokens and few n-tiles, in K slices
     static constexpr int WN = 4, WM = 2, TI = 2, TJ = 4, NST = 4, NSTX = 5;
 };
 struct GemmSmall {    // 128 x 64: calls of at most 64 tokens, in K slices

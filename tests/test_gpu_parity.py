@@ -141,9 +141,8 @@ NARROW_GU = Workload(name="narrow-gate-up", hidden=256, n_q_heads=4, n_kv_heads=
                      tp=2, dtype=BF16, seed=14, batch=3, q_len=1, ctx=64, mask=(1,))
 
 
-# 2080 FFN columns per rank (130 pairs of gate/up tiles: 17 groups of 8, the last with 2) and 37 k-tiles
-# (19 stages of two, the last with one, in 4 slices of 4 or 5): a call of 17 .. 128 tokens takes the
-# gate/up kernel that shares the activations through LDS and cuts K into slices
+# 2080 FFN columns per rank (130 pairs of gate/up tiles, no whole number of GEMM tiles) and 37 k-tiles (the last step
+# of two holds one): a call of 17 .. 512 tokens takes K slices of the LDS-tiled GEMM
 WIDE_MID = Workload(name="wide-ffn-mid", hidden=1184, n_q_heads=4, n_kv_heads=2, head_dim=64, ffn=4160, n_layers=1,
                     tp=2, dtype=BF16, seed=17, batch=2, q_len=1, ctx=64, mask=(1,))
 
