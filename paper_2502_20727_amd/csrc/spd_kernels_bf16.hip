@@ -99,13 +99,14 @@ __device__ __forceinline__ float sum_ss(const float *__restrict__ ss, int nch, i
     return s;
 }
 
-// 1 / sqrt(mean(x^2) + eps) of every token from its `nch` partial sums of squares, written over the first of them
-// (ss[0][m]); a consumer told nch = 0 takes the factor as it is.  A projection's epilogue that adds 256 partials per
+// 1 / sqrt(mean(x^2) + eps) of every token from its `nch` partial sums of squares, written to `rs`: the partials stay as they
+// are (one preparation serves every emulated rank's MLP).  A consumer told nch = 0 takes the factor as it is.  A projection's epilogue that adds 256 partials per
 // token by itself waits for eight dependent rounds of loads per m-tile: 28 of 150 us in the gate/up projection of 1000
 // tokens of the 70B shard, 42 of 440 at 4096 (with 8 partials: one round, the launch then costs more than it saves).
-// One workgroup per m-tile, the only one that touches its tokens' columns.
+// One workgroup per m-tile.
 constexpr int ROW_SCALE_MIN_NCH = 65;
-__global__ void __launch_bounds__(512) k_row_scale(float *ss, int nch, int m_pad, int h, float eps) {
+__global__ void __launch_bounds__(512) k_row_scale(const float *__restrict__ ss, int nch, int m_pad, int h, float eps,
+                                                   float *__restrict__ rs) {
     __shared__ float red[32][16];
     const int r = threadIdx.x & 15, part = threadIdx.x >> 4, m = blockIdx.x * 16 + r;
     red[part][r] = sum_ss(ss, nch, m_pad, m, part, 32);
@@ -114,7 +115,7 @@ __global__ void __launch_bounds__(512) k_row_scale(float *ss, int nch, int m_pad
         float t = 0.f;
 #pragma unroll
         for (int q = 0; q < 32; ++q) t += red[q][threadIdx.x];
-        ss[m] = 1.0f / sqrtf(t / (float)h + eps);
+        rs[m] = 1.0f / sqrtf(t / (float)h + eps);
     }
 }
 
@@ -2677,8 +2678,11 @@ hipError_t mlp_half(const spd_call &c, const char *w, int spd, float *slot, cons
     if (c.on(SPD_STAGE_GATEUP)) {
         spd_stage_scope prof(c, SPD_STAGE_GATEUP);
         if (M > 16 * SKINNY_MAX_MTILES && e1.nch >= ROW_SCALE_MIN_NCH) {
-            hipLaunchKernelGGL(k_row_scale, dim3(cdiv(M, 16)), dim3(512), 0, c.s, (float *)(c.ws + D.ws_ss2), e1.nch, D.m_pad, D.h, D.eps);
+            // the factors (4 bytes per token) go where this rank's queries were (64 bytes per token and more): attention is done with them
+            float *rs = (float *)(c.ws + D.ws_q);
+            hipLaunchKernelGGL(k_row_scale, dim3(cdiv(M, 16)), dim3(512), 0, c.s, e1.ss, e1.nch, D.m_pad, D.h, D.eps, rs);
             SPD_TRY(hipGetLastError());
+            e1.ss = rs;
             e1.nch = 0;
         }
         if (M <= 16) {

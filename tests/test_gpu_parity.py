@@ -265,6 +265,39 @@ def test_bf16_gemm_contraction_lengths(gpu, w, flag, split, q_len):
     case.close()
 
 
+# 65 partial sums of squares per token after a kept attention sync point of more than 512 tokens (hidden sizes that the row-wise
+# and the tile-wise preparation kernel serve): one preparation for all emulated ranks, whose partial sums every rank's
+# gate/up projection needs whole
+ROWS_65 = Workload(name="65-partials-rows", hidden=16640, n_q_heads=2, n_kv_heads=2, head_dim=32, ffn=2048, n_layers=1, tp=2, dtype=BF16,
+                   seed=33, batch=1, q_len=1, ctx=64, mask=(0,))
+TILES_65 = Workload(name="65-partials-tiles", hidden=16416, n_q_heads=2, n_kv_heads=2, head_dim=32, ffn=2048, n_layers=1, tp=2, dtype=BF16,
+                    seed=34, batch=1, q_len=1, ctx=64, mask=(0,))
+
+
+@pytest.mark.parametrize("w", [ROWS_65, TILES_65], ids=lambda w: w.name)
+@pytest.mark.parametrize("flag", [1, 0], ids=["spd", "tp"])
+def test_bf16_norm_partials_serve_every_rank(gpu, w, flag):
+    import torch
+    q_len = 513
+    case = Case(w, gpu, ranks=range(w.tp), positions=[0], max_ctx=544, max_tokens=q_len)
+    X = inputs.hidden_states(w, q_len)
+    slots = torch.zeros((w.tp, q_len, w.hidden), dtype=torch.float32, device=gpu)
+    say(f"norm partials: {w.name} flag={flag}")
+    out = torch.empty((q_len, w.hidden), dtype=torch.float32, device=gpu)
+    B.spd_block_forward(case.dev.ctx, 0, flag, B.SPD_ALL_RANKS, case.dev.weights[0], case.dev.kv[0], [0], 1, q_len,
+                        case.to_dev(X), slots, out, case.dev.workspace)
+    torch.cuda.synchronize()
+    det = {}
+    want, _ = O.block_all_ranks(case.sh, X, case.shards[0], case.caches[0], [0], 1, q_len, flag, det)
+    got = slots.cpu().numpy().astype(np.float64)
+    # a partial lost moves the factor by 1/130 and Z by twice that; fp16 operands leave 2^-11 each: 4 operands, 4 x 2^-11 at most
+    for r in range(w.tp):
+        err = float(np.linalg.norm(got[r] - det["P"][r]) / np.linalg.norm(det["P"][r]))
+        say(f"  slot {r}: relative error {err:.2e}")
+        assert err <= 4 * 2.0 ** -11, (r, err)
+    case.close()
+
+
 # fp32 path at the edges of its small-product kernel (at most 64 rows and 1024 contraction elements, rotation inside it when the
 # head size divides its 64 columns): odd widths, a head size that does not divide 64, one row, a full and a
 # started 8-row tile, the last size inside the range and the first beyond it in rows and in K
