@@ -298,6 +298,44 @@ def test_bf16_norm_partials_serve_every_rank(gpu, w, flag):
     case.close()
 
 
+def _one_rank_block(gpu, w, batch, q_len, positions, flag, split=B.SPD_SPLIT_AUTO, max_ctx=None, bias_std=0.0, bound_scale=1.0):
+    """One rank's block call with peer slots as inputs against the oracle: the output, the slot the rank wrote, and the
+    peers' slots unchanged."""
+    import torch
+    rank, M = 1, batch * q_len
+    case = Case(w, gpu, ranks=[rank], positions=positions, max_ctx=max_ctx or (max(positions) + q_len + 31) // 32 * 32, max_tokens=M,
+                act_split=split, bias_std=bias_std)
+    X = inputs.hidden_states(w, M)
+    peers = inputs.peer_slots(w, M)
+    slots = case.to_dev(peers).reshape(w.tp, M, w.hidden)
+    say(f"one rank: {w.name} {batch} x {q_len} tokens flag={flag} split={split}")
+    out = torch.empty((M, w.hidden), dtype=torch.float32, device=gpu)
+    B.spd_block_forward(case.dev.ctx, 0, flag, rank, case.dev.weights[0], case.dev.kv[0], positions, batch, q_len, case.to_dev(X),
+                        slots, out, case.dev.workspace)
+    torch.cuda.synchronize()
+    o_slots = peers.astype(np.float64).reshape(w.tp, M, w.hidden)
+    want = O.block_single_rank(case.sh, X, case.shards[0][0], case.caches[0][0], positions, batch, q_len, flag, rank, o_slots)
+    err = assert_close(out.cpu().numpy(), want, w, "block output", scale=bound_scale)
+    got = slots.cpu().numpy()
+    assert_close(got[rank], o_slots[rank], w, "own slot", scale=bound_scale)
+    for r in range(w.tp):
+        if r != rank:
+            assert np.array_equal(got[r], peers.reshape(w.tp, M, w.hidden)[r])
+    say(f"  block output max err {err:.2e} (max |oracle| {np.max(np.abs(want)):.2f})")
+    case.close()
+
+
+# the kernel that streams a large gate/up matrix for up to 128 tokens, at its edges: 194 pairs of n-tiles (24 groups of
+# eight and one with six spare waves) x 255 k-tiles (the last stage of two holds one)
+MID_EDGE = Workload(name="mid-edges", hidden=8160, n_q_heads=2, n_kv_heads=2, head_dim=32, ffn=6208, n_layers=1, tp=2, dtype=BF16,
+                    seed=35, batch=1, q_len=1, ctx=64, mask=(1,))
+
+
+@pytest.mark.parametrize("q_len,flag", [(17, 1), (64, 0), (100, 1), (128, 0)])
+def test_bf16_large_gate_up_short_call(gpu, q_len, flag):
+    _one_rank_block(gpu, MID_EDGE, 1, q_len, [0], flag)
+
+
 # fp32 path at the edges of its small-product kernel (at most 64 rows and 1024 contraction elements, rotation inside it when the
 # head size divides its 64 columns): odd widths, a head size that does not divide 64, one row, a full and a
 # started 8-row tile, the last size inside the range and the first beyond it in rows and in K
