@@ -2189,7 +2189,8 @@ inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b);
 // then, and the second kernel that adds slices takes 4 us: down projection of the 7B shard, 128 pairs x 43 k-tiles,
 // 5.0 + 3.4 -> 6.4 us, of the 13B shard, 160 x 54, 5.9 + 4.3 -> 8.6); otherwise about two workgroups of 8 waves per compute unit.
 constexpr int GEMV_SLICE_W = 8;
-inline bool gemv_whole(int n_pairs, int KT) { return n_pairs >= 192 || (n_pairs >= 96 && KT >= 32 && KT <= 64); }
+constexpr int GEMV_MANY_PAIRS = 192;
+inline bool gemv_whole(int n_pairs, int KT) { return n_pairs >= GEMV_MANY_PAIRS || (n_pairs >= 96 && KT >= 32 && KT <= 64); }
 inline int gemv_slices(int n_pairs, int KT) {
     if (gemv_whole(n_pairs, KT)) return 1;
     int KS = (512 + n_pairs - 1) / n_pairs;
@@ -2494,9 +2495,11 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
     // A decode step whose QKV projection has too few column tiles to occupy the chip: K slices with the linear epilogue (at
     // most SPD_MAX_QKV_SLICES), whose partial rows the attention kernel adds itself.  Up to 16 sequences about 240
     // workgroups of 16 waves, at least two k-tiles per wave; more of them, about 480 of the skinny kernel's 8 waves (two fit a compute unit).
+    // (Also where gemv_whole() would contract K in one launch: the slices cost no second kernel here.  hidden 2048, 96 pairs,
+    // slices / whole, us per layer: 4 sequences of 4000 positions 52 / 53.6, 8: 67.5 / 70, 16: 102 / 104.5.)
     const int n_mtiles = (M + 15) / 16, qkv_pairs = D.nqkv / 32;
     int qkv_slices = 1;
-    if (c.q_len == 1 && n_mtiles <= 4 && gemv_slices(qkv_pairs, D.h / 32) > 1) {
+    if (c.q_len == 1 && n_mtiles <= 4 && qkv_pairs < GEMV_MANY_PAIRS) {
         const int want = n_mtiles == 1 ? (240 + qkv_pairs - 1) / qkv_pairs : 480 / qkv_pairs;
         qkv_slices = want < 2 ? 2 : (want > SPD_MAX_QKV_SLICES ? SPD_MAX_QKV_SLICES : want);
         const int most = D.h / 32 / (2 * (n_mtiles == 1 ? QKV_SLICE_W : SKINNY_W));

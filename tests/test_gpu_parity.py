@@ -336,6 +336,22 @@ def test_bf16_large_gate_up_short_call(gpu, q_len, flag):
     _one_rank_block(gpu, MID_EDGE, 1, q_len, [0], flag)
 
 
+# decode QKV projections that K slices or one whole contraction could serve: 96 pairs of n-tiles (from which a
+# contraction of 32 .. 64 k-tiles is done whole in the other projections), 64 and 32 k-tiles, up to four m-tiles
+QKV_96 = Workload(name="qkv-96-pairs", hidden=2048, n_q_heads=16, n_kv_heads=16, head_dim=128, ffn=256, n_layers=1, tp=2, dtype=BF16,
+                  seed=36, batch=1, q_len=1, ctx=64, mask=(1,))
+QKV_96_SHORT = Workload(name="qkv-96-pairs-short", hidden=1024, n_q_heads=32, n_kv_heads=32, head_dim=64, ffn=256, n_layers=1, tp=2,
+                        dtype=BF16, seed=37, batch=1, q_len=1, ctx=64, mask=(1,))
+
+
+@pytest.mark.parametrize("w", [QKV_96, QKV_96_SHORT], ids=lambda w: w.name)
+@pytest.mark.parametrize("split", [B.SPD_SPLIT_AUTO, B.SPD_SPLIT_ALWAYS], ids=["default", "all-split"])
+@pytest.mark.parametrize("batch", [1, 3, 16, 17, 40, 64])
+def test_bf16_decode_qkv_of_medium_width(gpu, w, split, batch):
+    positions = [(7 * i) % 61 for i in range(batch)]
+    _one_rank_block(gpu, w, batch, 1, positions, batch % 2, split, max_ctx=64)
+
+
 # fp32 path at the edges of its small-product kernel (at most 64 rows and 1024 contraction elements, rotation inside it when the
 # head size divides its 64 columns): odd widths, a head size that does not divide 64, one row, a full and a
 # started 8-row tile, the last size inside the range and the first beyond it in rows and in K
