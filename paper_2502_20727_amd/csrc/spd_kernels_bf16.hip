@@ -2364,10 +2364,27 @@ hipError_t launch_sliced(const spd_call &c, bool split, const __bf16 *Wp, const 
     return hipGetLastError();
 }
 
-// Projection of a call of any size: the weight-streaming kernel up to 16 tokens; K slices of the LDS-tiled GEMM up to 512
-// tokens, and beyond for a call of one chain whose tiles leave half of the compute units idle (the QKV projection of the
+// 17 .. 512 tokens, short contractions: the skinny kernel with the whole epilogue is done before K slices and the launch that
+// adds them are.  Beyond 128 tokens (one workgroup per compute unit: 128 KiB of LDS each) its workgroups should fill half a
+// round of the chip and not begin a second one, unless the contraction is very short.  Skinny against slices, weights
+// from HBM, us per layer:
+//   gate/up, 24 tokens: 44 x 32 (pairs x k-tiles) 33 / 37, 86 x 64 38 / 40, 128 x 96 48.5 / 50, 216 x 160 62 / 66; but 108 x 160 53.5 / 52.4;
+//     64 tokens: 88 x 32 41 / 43, 172 x 64 52 / 56; but 44 x 64 and 64 x 96 equal / + 1 %; 128 tokens: 44 .. 176 x 32 - 4 .. - 6 %, x 64 + 1 .. + 4 %
+//   QKV on pairs of planes (twice the k-tiles): 24 tokens x 32 - 10 %, x 64 - 3 .. - 9 %, x 128 + 3 %
+//   decode QKV of 17 .. 32 sequences that fill the chip: 192 x 64 - 10 %, 240 x 160 - 6 %; 320 x 256 + 1 %
+//   down, 200 tokens: 128 x 43 - 8 %, 96 x 64 - 11 %, 128 x 86 - 5 %, 96 x 128 equal, 160 x 108 + 12 %; 384: 128 x 43 - 3 %, 128 x 86 + 6 %
+inline bool skinny_first(int n_pairs, int KT, bool split, int n_mtiles) {
+    const int kp = split ? 2 * KT : KT, wgs = n_pairs * ((n_mtiles + 7) / 8);
+    if (n_mtiles <= 2) return kp <= 128 || (!split && KT <= 160 && n_pairs >= 128);
+    if (n_mtiles <= 4) return kp <= 32 || (kp <= 64 && n_pairs >= 48);
+    if (n_mtiles <= 8) return kp <= 32;
+    return (kp <= 48 && wgs <= 512) || (kp <= 96 && wgs >= 128 && wgs <= 256);
+}
+
+// Projection of a call of any size: the weight-streaming kernel up to 16 tokens; up to 512 tokens the skinny kernel for short
+// contractions and K slices of the LDS-tiled GEMM for the others; slices beyond for a call of one chain whose tiles leave half of the compute units idle (the QKV projection of the
 // 70B shard, 1000 tokens: 6 slices 37 us, 160 x 256 tiles in 8 slices 58); one launch of the GEMM otherwise.  The skinny
-// kernel takes what is too short to slice.
+// kernel also takes what is left with a single slice.
 template <class Epi>
 hipError_t launch_proj(const spd_call &c, bool split, const __bf16 *Wp, const __bf16 *Xhi, size_t plane, int n_pairs, int KT,
                        const Epi &epi) {
@@ -2375,6 +2392,8 @@ hipError_t launch_proj(const spd_call &c, bool split, const __bf16 *Wp, const __
     const __bf16 *Xlo = Xhi + plane;
     if (n_mtiles == 1)
         return split ? launch_gemv<true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi) : launch_gemv<false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
+    if (n_mtiles <= SKINNY_MAX_MTILES && skinny_first(n_pairs, KT, split, n_mtiles))
+        return launch_skinny(c, split, Wp, Xhi, plane, n_pairs, KT, epi);
     if (!c.chained) {
         bool done = false;
         SPD_TRY(launch_sliced(c, split, Wp, Xhi, plane, n_pairs, KT, epi, &done));

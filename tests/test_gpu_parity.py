@@ -352,6 +352,21 @@ def test_bf16_decode_qkv_of_medium_width(gpu, w, split, batch):
     _one_rank_block(gpu, w, batch, 1, positions, batch % 2, split, max_ctx=64)
 
 
+# projections on either side of the lines between the skinny kernel and K slices: 101 k-tiles (slices of all tile shapes in
+# QKV and gate/up; odd), 65 in down (skinny beyond 128 tokens, slices beyond 256), and 63 .. 65 of them at 33 .. 128 tokens
+KT_101 = Workload(name="101-k-tiles", hidden=3232, n_q_heads=8, n_kv_heads=4, head_dim=32, ffn=4160, n_layers=1, tp=2, dtype=BF16,
+                  seed=38, batch=1, q_len=1, ctx=64, mask=(1,))
+KT_64 = Workload(name="64-k-tiles", hidden=2048, n_q_heads=20, n_kv_heads=4, head_dim=64, ffn=1600, n_layers=1, tp=2, dtype=BF16,
+                 seed=39, batch=1, q_len=1, ctx=64, mask=(1,))
+
+
+@pytest.mark.parametrize("w", [KT_101, KT_64], ids=lambda w: w.name)
+@pytest.mark.parametrize("split", [B.SPD_SPLIT_AUTO, B.SPD_SPLIT_ALWAYS, B.SPD_SPLIT_NEVER], ids=["default", "all-split", "no-split"])
+@pytest.mark.parametrize("q_len", [17, 32, 33, 64, 65, 128, 129, 256, 257, 512])
+def test_bf16_short_and_sliced_contractions(gpu, w, split, q_len):
+    _one_rank_block(gpu, w, 1, q_len, [0], q_len % 2, split)
+
+
 # fp32 path at the edges of its small-product kernel (at most 64 rows and 1024 contraction elements, rotation inside it when the
 # head size divides its 64 columns): odd widths, a head size that does not divide 64, one row, a full and a
 # started 8-row tile, the last size inside the range and the first beyond it in rows and in K
