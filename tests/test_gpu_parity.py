@@ -367,6 +367,12 @@ def test_bf16_short_and_sliced_contractions(gpu, w, split, q_len):
     _one_rank_block(gpu, w, 1, q_len, [0], q_len % 2, split)
 
 
+@pytest.mark.parametrize("q_len,flag", [(17, 1), (40, 0), (100, 1)])
+def test_bf16_short_call_of_a_wide_model(gpu, q_len, flag):
+    """More pairs of n-tiles (520 in the O and down projections) than compute units, and two sync-point epilogues on them."""
+    _one_rank_block(gpu, ROWS_65, 1, q_len, [0], flag)
+
+
 # fp32 path at the edges of its small-product kernel (at most 64 rows and 1024 contraction elements, rotation inside it when the
 # head size divides its 64 columns): odd widths, a head size that does not divide 64, one row, a full and a
 # started 8-row tile, the last size inside the range and the first beyond it in rows and in K
