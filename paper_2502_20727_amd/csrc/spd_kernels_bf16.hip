@@ -2555,7 +2555,14 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
         e1.qbuf = qbuf; e1.qlo = qlo; e1.kc = kc; e1.vc = vc; e1.P = c.pos;
         if (c.on(SPD_STAGE_QKV)) {
             spd_stage_scope prof(c, SPD_STAGE_QKV);
-            SPD_TRY(launch_proj(c, c.sp_x, wqkv.w, xhat, D.pl_x, qkv_pairs, D.h / 32, e1));
+            // decode of 17 .. 64 sequences that fills the chip: one launch of the skinny kernel. After slices and their finishing
+            // kernel the attention kernel waits longer for the appended keys too (192 pairs x 128 k-tiles, 64 sequences:
+            // 13.4 + 15.0 and attention 21.4 us; skinny 26.0 and 16.7; 240 x 160, us per layer, 33 sequences 131 / 125.5, 64: 159 / 150; 320 x
+            // 256 the other way, 393 / 404)
+            if (c.q_len == 1 && n_mtiles > 1 && n_mtiles <= 4 && !c.sp_x && D.h / 32 <= 160)
+                SPD_TRY(launch_skinny(c, false, wqkv.w, xhat, D.pl_x, qkv_pairs, D.h / 32, e1));
+            else
+                SPD_TRY(launch_proj(c, c.sp_x, wqkv.w, xhat, D.pl_x, qkv_pairs, D.h / 32, e1));
         }
     }
 

@@ -373,6 +373,19 @@ def test_bf16_short_call_of_a_wide_model(gpu, q_len, flag):
     _one_rank_block(gpu, ROWS_65, 1, q_len, [0], flag)
 
 
+# decode QKV projections of 192 pairs and more, which the attention kernel does not add up: one launch up to 160 k-tiles
+QKV_192 = Workload(name="qkv-192-pairs", hidden=5120, n_q_heads=32, n_kv_heads=32, head_dim=128, ffn=256, n_layers=1, tp=2, dtype=BF16,
+                   seed=40, batch=1, q_len=1, ctx=64, mask=(1,))
+QKV_192_LONG = Workload(name="qkv-192-pairs-long", hidden=5152, n_q_heads=32, n_kv_heads=32, head_dim=128, ffn=256, n_layers=1, tp=2,
+                        dtype=BF16, seed=41, batch=1, q_len=1, ctx=64, mask=(1,))
+
+
+@pytest.mark.parametrize("w", [QKV_192, QKV_192_LONG], ids=lambda w: w.name)
+@pytest.mark.parametrize("batch", [16, 17, 33, 64])
+def test_bf16_decode_qkv_of_a_wide_shard(gpu, w, batch):
+    _one_rank_block(gpu, w, batch, 1, [(7 * i) % 61 for i in range(batch)], batch % 2, max_ctx=64)
+
+
 # fp32 path at the edges of its small-product kernel (at most 64 rows and 1024 contraction elements, rotation inside it when the
 # head size divides its 64 columns): odd widths, a head size that does not divide 64, one row, a full and a
 # started 8-row tile, the last size inside the range and the first beyond it in rows and in K
