@@ -105,8 +105,13 @@ def stage_kernel(w, stage: str) -> str:
                     one += "+k_gemm_lds<EpiGU,GemmHalf,false>"
             return one + ("x2" if two_chains else "")          # x2: one launch per chain of a two-chain prefill
         if M > 16:
-            if M <= 128 and f_pairs * (w.hidden // 32) >= 48 * 1024:
+            kt, mt = w.hidden // 32, (M + 15) // 16
+            tiles, wgs = f_pairs * kt, f_pairs * ((mt + 7) // 8)
+            if M <= 128 and (tiles >= 40 * 1024 or (M > 64 and f_pairs >= 128 and tiles >= 20 * 1024)):
                 return f"k_mid<{2 if M <= 32 else 4 if M <= 64 else 8}>+k_mid_finish<EpiGU>"
+            if (kt <= 128 or (kt <= 160 and f_pairs >= 128) if mt <= 2 else kt <= 32 or (kt <= 64 and f_pairs >= 48) if mt <= 4 else
+                    kt <= 32 if mt <= 8 else (kt <= 48 and wgs <= 512) or (kt <= 96 and 128 <= wgs <= 256)):
+                return f"k_skinny<8,{2 if M <= 32 else 4 if M <= 64 else 8},false,0,EpiGU>"
             half = M > 128 and (f_pairs >= 64 or (2 * f_pairs + 15) // 16 * ((M + 127) // 128) >= 32)
             shape = "GemmSmall" if M <= 64 else "GemmHalf" if half else "GemmSquare"
             return f"k_gemm_lds<EpiPark,{shape},false>+k_mid_finish<EpiGU>"

@@ -2289,20 +2289,24 @@ hipError_t launch_skinny(const spd_call &c, bool split, const __bf16 *Wp, const 
     return split ? launch_skinny_mt<8, true, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi)
                  : launch_skinny_mt<8, false, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi);
 }
-// 17 .. 128 tokens, activations not split, 96 MB of weights or more (the gate/up projection of the 70B shard): the mid
-// kernel and its finishing kernel.  It draws the HBM's rate better than the sliced GEMM, which is ahead on
-// everything smaller (main kernel, us at 32 / 64 / 128 tokens, mid against GEMM tiles: 117 MB 22 / 23.5 / 27 against
-// 25 / 26 / 31; 71 MB 15.4 / 17.2 / 20.9 against 14.3 / 15.4 / 18.3; 58 MB 12 / 14.1 / 19.8 against 12.3 / 12.9 / 14.9).
+// 17 .. 128 tokens, activations not split, large gate/up projections: the mid kernel and its finishing kernel.  It draws
+// the HBM's rate better than the sliced GEMM; on what is small enough to stay in a cache the two are level or the GEMM is
+// ahead.  Weights from HBM, us per layer, mid against slices: 88 MB (344 pairs x 128 k-tiles) 17 tokens 73.6 / 80.6,
+// 64: 87.7 / 93.2, 128: 120 / 124; beyond 64 tokens also 71 MB (216 x 160) 86.5 / 88.3 at 65, 99.6 / 101.8 at 128, 45 MB
+// (172 x 128) 74.9 / 75.8, 84.8 / 85.0; but 35 MB (108 x 160) 69.3 / 65.5, and 45 MB at 33 sequences 73.5 / 72.0.
 // Returns false in *done when the shape is not its kind.
 constexpr int MID_SYNC_TOKENS = 128;       // calls whose O projection's epilogue performs a kept attention sync point
 constexpr int SKINNY_MAX_MTILES = 32;      // beyond 512 tokens one launch of the LDS-tiled GEMM does without K slices
 constexpr int MID_MAX_MTILES = 8;
-constexpr int MID_MIN_TILES = 48 * 1024;   // (pairs of n-tiles) x (k-tiles): 2 KiB each
+constexpr int MID_MIN_TILES = 40 * 1024;         // (pairs of n-tiles) x (k-tiles): 2 KiB each
+constexpr int MID_LONG_MIN_TILES = 20 * 1024;    // ... of calls of more than 64 tokens, with at least 128 pairs
 // K slices the mid kernel would use for this shape, 0 when the shape is not its kind
 inline int mid_slices(const spd_call &c, int n_pairs, int KT) {
     const spd_dims &D = *c.D;
     const int n_mtiles = (c.M + 15) / 16;
-    if (n_mtiles <= 1 || n_mtiles > MID_MAX_MTILES || (long)n_pairs * KT < MID_MIN_TILES) return 0;
+    const long tiles = (long)n_pairs * KT;
+    if (n_mtiles <= 1 || n_mtiles > MID_MAX_MTILES) return 0;
+    if (tiles < MID_MIN_TILES && !(n_mtiles > 4 && n_pairs >= 128 && tiles >= MID_LONG_MIN_TILES)) return 0;
     const int groups = (n_pairs + MID_PAIRS - 1) / MID_PAIRS, nst = (KT + MID_KB - 1) / MID_KB;
     // one round of workgroups (one fits a compute unit), at least four stages per slice
     int KS = 256 / groups;

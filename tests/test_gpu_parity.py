@@ -331,9 +331,15 @@ MID_EDGE = Workload(name="mid-edges", hidden=8160, n_q_heads=2, n_kv_heads=2, he
                     seed=35, batch=1, q_len=1, ctx=64, mask=(1,))
 
 
-@pytest.mark.parametrize("q_len,flag", [(17, 1), (64, 0), (100, 1), (128, 0)])
-def test_bf16_large_gate_up_short_call(gpu, q_len, flag):
-    _one_rank_block(gpu, MID_EDGE, 1, q_len, [0], flag)
+# ... and the medium one that it serves beyond 64 tokens: 130 pairs x 159 k-tiles
+MID_LONG_EDGE = Workload(name="mid-long-edges", hidden=5088, n_q_heads=2, n_kv_heads=2, head_dim=32, ffn=4160, n_layers=1, tp=2, dtype=BF16,
+                         seed=42, batch=1, q_len=1, ctx=64, mask=(1,))
+
+
+@pytest.mark.parametrize("w", [MID_EDGE, MID_LONG_EDGE], ids=lambda w: w.name)
+@pytest.mark.parametrize("q_len,flag", [(17, 1), (64, 0), (65, 0), (100, 1), (128, 0)])
+def test_bf16_large_gate_up_short_call(gpu, w, q_len, flag):
+    _one_rank_block(gpu, w, 1, q_len, [0], flag)
 
 
 # decode QKV projections that K slices or one whole contraction could serve: 96 pairs of n-tiles (from which a
