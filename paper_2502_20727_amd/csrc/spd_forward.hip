@@ -106,7 +106,7 @@ int block_core(const spd_ctx *ctx, spd_call &c, int spd, int32_t rank, const cha
             *base_out = x;
         } else {
             // kept sync point: R = X + sum_r Y_r (+ bias), with the second norm's elementwise part; for one
-            // rank and a call of at most 128 tokens the O projection's epilogue does it, otherwise prep()
+            // rank and a call of at most 512 tokens the O projection's epilogue may do it, otherwise prep()
             spd_bf16::spd_mid_sync ms;
             ms.slots = slots; ms.tp = D.tp; ms.rank = r0; ms.rbuf = rbuf;
             bool mid_done = false;

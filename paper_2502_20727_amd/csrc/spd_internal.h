@@ -252,7 +252,7 @@ hipError_t prep(const spd_call &c, const float *base, const float *slots, int n_
 // QKV + rotary + cache append + attention + O projection.
 //   spd = 1: ybuf <- Y_r, xhat2 <- fp16((X + Y_r) g2) and its partial sums of squares
 //   spd = 0: slot <- Y_r
-// With `mid` (TP block, one rank, calls of at most 128 tokens) the O projection's epilogue also performs
+// With `mid` (TP block, one rank, calls of at most 512 tokens) the O projection's epilogue may also perform
 // the kept attention sync point: R = X + sum of the slots (+ bias) -> mid->rbuf, second norm prepared;
 // *mid_done tells whether it did (otherwise the caller runs prep()).
 struct spd_mid_sync {

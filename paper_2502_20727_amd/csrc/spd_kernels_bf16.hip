@@ -2295,7 +2295,6 @@ hipError_t launch_skinny(const spd_call &c, bool split, const __bf16 *Wp, const 
 // 64: 87.7 / 93.2, 128: 120 / 124; beyond 64 tokens also 71 MB (216 x 160) 86.5 / 88.3 at 65, 99.6 / 101.8 at 128, 45 MB
 // (172 x 128) 74.9 / 75.8, 84.8 / 85.0; but 35 MB (108 x 160) 69.3 / 65.5, and 45 MB at 33 sequences 73.5 / 72.0.
 // Returns false in *done when the shape is not its kind.
-constexpr int MID_SYNC_TOKENS = 128;       // calls whose O projection's epilogue performs a kept attention sync point
 constexpr int SKINNY_MAX_MTILES = 32;      // beyond 512 tokens one launch of the LDS-tiled GEMM does without K slices
 constexpr int MID_MAX_MTILES = 8;
 constexpr int MID_MIN_TILES = 40 * 1024;         // (pairs of n-tiles) x (k-tiles): 2 KiB each
@@ -2418,10 +2417,19 @@ hipError_t launch_proj(const spd_call &c, bool split, const __bf16 *Wp, const __
     else return hipErrorInvalidValue;         // epilogues that carry a sync point: calls of up to 512 tokens
 }
 
+// Does the O projection's epilogue perform a kept attention sync point (one rank, TP block)?  In the skinny kernel, as long
+// as its workgroups (128 KiB of LDS each, one per compute unit) come to two rounds of the chip at most; a rank-sum of its
+// own beyond.  Whole layer, weights from HBM, us, in the epilogue / kernel of its own: 70B 129 tokens 135.6 / 143.1, 256 (512
+// workgroups) 165.4 / 172.3, 384 (768) 211.8 / 210.0, 512 263.2 / 252.7; 13B 129 tokens 88.0 / 93.5, 384 (480) 129.7 / 132.2, 512
+// (640) 157.4 / 157.4; 7B 129 tokens 76.5 / 80.2, 512 (512) 126.4 / 132.8; up to 128 tokens 2 .. 4 us less on every shard.
+inline bool sync_in_o(int n_pairs, int n_mtiles) {
+    return n_mtiles <= SKINNY_MAX_MTILES && (n_mtiles <= 8 || n_pairs * ((n_mtiles + 7) / 8) <= 512);
+}
+
 // The output projection's contraction is short (a rank's heads): up to 128 tokens the skinny kernel with the whole epilogue
 // beats slices and their finishing kernel; beyond, 256 x 128 tiles by themselves beat both once the skinny kernel would
 // take two rounds (70B shard, main kernel, us, skinny / tiles: 192 tokens 15.8 / 14.7, 512: 30.9 / 17.2; 13B 384: 10.8 / 11.4, 512:
-// 16.1 / 12.0).
+// 16.1 / 12.0).  With a kept sync point in its epilogue (MID) always the skinny kernel.
 template <bool MID>
 hipError_t launch_o(const spd_call &c, bool split, const __bf16 *Wp, const __bf16 *Xhi, size_t plane, int n_pairs, int KT,
                     const EpiOT<MID> &epi) {
@@ -2429,9 +2437,10 @@ hipError_t launch_o(const spd_call &c, bool split, const __bf16 *Wp, const __bf1
     const __bf16 *Xlo = Xhi + plane;
     if (n_mtiles == 1)
         return split ? launch_gemv<true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi) : launch_gemv<false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
-    if (n_mtiles <= 8 || (n_mtiles <= SKINNY_MAX_MTILES && n_pairs * zg < 512)) return launch_skinny(c, split, Wp, Xhi, plane, n_pairs, KT, epi);
+    if (n_mtiles <= 8 || (n_mtiles <= SKINNY_MAX_MTILES && (MID || n_pairs * zg < 512)))
+        return launch_skinny(c, split, Wp, Xhi, plane, n_pairs, KT, epi);
     if constexpr (MID) {
-        return hipErrorInvalidValue;         // the epilogue that carries a sync point serves calls of up to 128 tokens
+        return hipErrorInvalidValue;         // (see sync_in_o())
     } else {
         if (n_mtiles <= SKINNY_MAX_MTILES)
             return split ? launch_gemm_lds_cfg<GemmHalf, true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi)
@@ -2650,8 +2659,7 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
     }
     spd_stage_end(c, SPD_STAGE_ATTN);
 
-    // (beyond 128 tokens the rank-sum as a kernel of its own: 13B shard, 333 tokens, O + sync point 31.4 -> 12.6 + 17.2 us)
-    const bool fuse_mid = mid && !spd && M <= MID_SYNC_TOKENS;
+    const bool fuse_mid = mid && !spd && sync_in_o(D.h / 32, n_mtiles);
     if (mid_done) *mid_done = fuse_mid;
     auto fill_o = [&](auto &e2) {
         e2.M = M; e2.h = D.h; e2.spd = spd; e2.m_pad = D.m_pad;

@@ -392,6 +392,19 @@ def test_bf16_decode_qkv_of_a_wide_shard(gpu, w, batch):
     _one_rank_block(gpu, w, batch, 1, [(7 * i) % 61 for i in range(batch)], batch % 2, max_ctx=64)
 
 
+# a kept attention sync point of 129 .. 512 tokens: in the O projection's epilogue up to 512 workgroups (130 pairs x groups of 128
+# tokens: 390 up to 384 tokens, 520 beyond), a kernel of its own from there; with bias and with paired activations
+SYNC_130 = Workload(name="sync-130-pairs", hidden=4160, n_q_heads=8, n_kv_heads=8, head_dim=64, ffn=256, n_layers=1, tp=8, dtype=BF16,
+                    seed=43, batch=1, q_len=1, ctx=64, mask=(0,))
+
+
+@pytest.mark.parametrize("bias_std,split", [(0.0, B.SPD_SPLIT_AUTO), (1.0, B.SPD_SPLIT_AUTO), (0.0, B.SPD_SPLIT_ALWAYS)],
+                         ids=["plain", "bias", "all-split"])
+@pytest.mark.parametrize("q_len", [128, 129, 300, 384, 385, 512])
+def test_bf16_kept_sync_point_of_a_medium_call(gpu, q_len, bias_std, split):
+    _one_rank_block(gpu, SYNC_130, 1, q_len, [0], 0, split, bias_std=bias_std)
+
+
 # fp32 path at the edges of its small-product kernel (at most 64 rows and 1024 contraction elements, rotation inside it when the
 # head size divides its 64 columns): odd widths, a head size that does not divide 64, one row, a full and a
 # started 8-row tile, the last size inside the range and the first beyond it in rows and in K
