@@ -141,6 +141,10 @@ __global__ void k_rope_append(float *__restrict__ qkv, float *__restrict__ kc, f
 // norm + gate + up + SwiGLU 47 / 60 -> 9 / 11 (four launches before), down 23 / 33 -> 7 / 8.
 constexpr int RW = 16, RM = 8, RN = 64;
 constexpr int ROWS_MAX_M = 64, ROWS_MAX_K = 1024;
+// Every group of 8 rows reads the weights again, so a very wide product is left to the 32 x 32 tiles.  hidden 1024, two layers,
+// us, tiles / rows by workgroups of the gate/up launch: 64 rows 1024 2119 / 1752, 2048 3605 / 3323, 4096 8422 / 8457, 8192 16821 / 17845;
+// 32 rows 2048 8537 / 8280, 3072 12412 / 12626; hidden 256: 64 rows 2048 3157 / 3108, 4096 6358 / 6394
+constexpr int ROWS_MAX_WGS = 2048;
 
 struct RowsQKV {       // queries and keys rotated, keys and values appended to the cache; needs whole heads per tile (64 % d == 0)
     static constexpr bool kDual = false;
@@ -290,7 +294,9 @@ __global__ void __launch_bounds__(RW * 64) k_rows(const float *__restrict__ A, i
     }
 }
 
-bool rows_fit(int M, int K) { return M <= ROWS_MAX_M && K <= ROWS_MAX_K && K >= 1; }
+bool rows_fit(int M, int N, int K) {
+    return M <= ROWS_MAX_M && K <= ROWS_MAX_K && K >= 1 && (int64_t)((N + RN - 1) / RN) * ((M + RM - 1) / RM) <= ROWS_MAX_WGS;
+}
 
 template <class Epi>
 hipError_t launch_rows(hipStream_t s, const float *A, int lda, const float *gain, float eps, const float *W, const float *W2, int ldw,
@@ -450,7 +456,7 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
     float *xn = (float *)(c.ws + D.ws_xhat), *qkv = (float *)(c.ws + D.ws_qkv), *att = (float *)(c.ws + D.ws_ahat);
     const float *cosT = (const float *)(c.ws + D.ws_cos), *sinT = (const float *)(c.ws + D.ws_sin);
     float *kc = (float *)kvc, *vc = (float *)(kvc + D.kv_v);
-    if (rows_fit(M, D.h) && RN % D.d == 0) {
+    if (rows_fit(M, D.nqkv, D.h) && RN % D.d == 0) {
         RowsQKV e;
         e.qkv = qkv; e.kc = kc; e.vc = vc; e.cosT = cosT; e.sinT = sinT;
         e.q_len = c.q_len; e.q = D.q; e.kv = D.kv; e.d = D.d; e.nqkv = D.nqkv; e.max_ctx = D.max_ctx; e.P = c.pos;
@@ -467,7 +473,7 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
     hipLaunchKernelGGL(k_attention, dim3(M * D.q), dim3(TB), (size_t)c.max_pos_end * sizeof(float), c.s, qkv, kc, vc,
                        att, c.pos, c.q_len, D.q, D.kv, D.d, D.nqkv, D.max_ctx);
     SPD_TRY(hipGetLastError());
-    if (rows_fit(M, qd)) {
+    if (rows_fit(M, D.h, qd)) {
         RowsO e;
         e.y = y_out; e.r_out = r_out; e.x = x; e.bias = bias; e.ld = D.h;
         SPD_TRY(launch_rows(c.s, att, qd, nullptr, 0.f, (const float *)(w + D.w_o), nullptr, D.h, M, D.h, qd, e));
@@ -487,7 +493,7 @@ hipError_t mlp_half(const spd_call &c, const char *w, const float *r_in, const f
     const spd_dims &D = *c.D;
     const int M = c.M, f = D.f;
     float *xn = (float *)(c.ws + D.ws_xhat), *gu = (float *)(c.ws + D.ws_gu), *u = (float *)(c.ws + D.ws_uhat);
-    if (rows_fit(M, D.h)) {
+    if (rows_fit(M, f, D.h)) {
         RowsGU e;
         e.u = u; e.ld = f;
         SPD_TRY(launch_rows(c.s, r_in, D.h, (const float *)(w + D.w_g2), D.eps, (const float *)(w + D.w_g), (const float *)(w + D.w_u), f, M, f,
@@ -501,7 +507,7 @@ hipError_t mlp_half(const spd_call &c, const char *w, const float *r_in, const f
                            (int64_t)M * f);
         SPD_TRY(hipGetLastError());
     }
-    if (rows_fit(M, f)) {
+    if (rows_fit(M, D.h, f)) {
         RowsDown e;
         e.out = out; e.add = add; e.ld = D.h;
         SPD_TRY(launch_rows(c.s, u, f, nullptr, 0.f, (const float *)(w + D.w_d), nullptr, D.h, M, D.h, f, e));

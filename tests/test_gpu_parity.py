@@ -437,6 +437,16 @@ def test_fp32_small_products(gpu, w, flag, batch, q_len, positions):
     case.close()
 
 
+# ... and at its widest product: 2048 workgroups of 64 columns x 8 rows, and one column more
+@pytest.mark.parametrize("ffn", [16384, 16385])
+@pytest.mark.parametrize("q_len", [57, 64])
+def test_fp32_small_products_width(gpu, ffn, q_len):
+    w = Workload(name=f"f32-wide-{ffn}", hidden=64, n_q_heads=4, n_kv_heads=4, head_dim=32, ffn=2 * ffn, n_layers=1, tp=2, dtype=F32, seed=44,
+                 batch=1, q_len=1, ctx=64, mask=(1,))
+    # (the bound of the fp32 path with 0.1: 1e-4, the down projection sums 16384 products in fp32 one after the other)
+    _one_rank_block(gpu, w, 1, q_len, [0], 1, bound_scale=0.1)
+
+
 # ------------------------------------------------------------------------------------------------
 # block with bias in the output projection (Sec. 4.1.2): both paths, both block kinds
 # ------------------------------------------------------------------------------------------------
