@@ -437,6 +437,17 @@ def test_fp32_small_products(gpu, w, flag, batch, q_len, positions):
     case.close()
 
 
+# fp32 attention where a thread takes a second key (256 keys and more), the waves' shares end unevenly and the output needs a
+# second and a fourth pass of 64 features
+@pytest.mark.parametrize("head_dim", [2, 64, 66, 128, 256])
+@pytest.mark.parametrize("batch,q_len,positions", [(3, 1, [254, 255, 256]), (2, 1, [257, 1000]), (1, 40, [230])], ids=["256", "1001", "chunk"])
+def test_fp32_attention_edges(gpu, head_dim, batch, q_len, positions):
+    w = Workload(name=f"f32-attn-d{head_dim}", hidden=64, n_q_heads=4, n_kv_heads=2, head_dim=head_dim, ffn=64, n_layers=1, tp=2, dtype=F32,
+                 seed=45, batch=1, q_len=1, ctx=64, mask=(1,))
+    # 2e-5 of the largest output: some 20 roundings of fp32 over at most 1001 keys
+    _one_rank_block(gpu, w, batch, q_len, positions, 1, bound_scale=0.02)
+
+
 # ... and at its widest product: 2048 workgroups of 64 columns x 8 rows, and one column more
 @pytest.mark.parametrize("ffn", [16384, 16385])
 @pytest.mark.parametrize("q_len", [57, 64])
