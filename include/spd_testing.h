@@ -93,6 +93,10 @@ int spd_gemm_launch_size(int32_t n_tiles);
 int spd_gemm_tile_of(int32_t TN, int32_t TM, int32_t rn, int32_t rm, int32_t tile0, int32_t n_tiles, int32_t b,
                      int32_t *tn, int32_t *tm);
 
+/* Whether the LDS-tiled GEMM can take a contraction of k_tiles (32 elements each): 1, or 0 when a panel of its
+ * largest tile does not fit 32-bit byte offsets and other kernels serve the call; SPD_EINVAL: negative.  Host only. */
+int spd_gemm_panels_fit(int32_t k_tiles);
+
 #ifdef __cplusplus
 }
 #endif

@@ -113,6 +113,10 @@ SPD_HD int spd_tile_deal(int b, int n_tiles) {
     return (q >= share || idx >= n_tiles) ? -1 : idx;
 }
 SPD_HD int spd_tile_launch_size(int n_tiles) { return (n_tiles & ~255) + (((n_tiles & 255) + 7) / 8) * 8; }
+// The LDS-tiled GEMM copies its operands through one buffer descriptor per panel (the at most 24 rows of 1 KiB fragments that a
+// workgroup's tile spans), with 32-bit offsets.  Longer contractions take the kernels with 64-bit addresses.
+constexpr int SPD_GEMM_MAX_ROWS = 24;
+SPD_HD bool spd_gemm_fits(int k_tiles) { return (uint64_t)k_tiles * 1024 * SPD_GEMM_MAX_ROWS <= 0xffffffffull; }
 // block shape for tiles of rn x rm rows: at most 32 tiles, the fewest panel rows per tile in flight
 inline void spd_pick_block(int TN, int TM, int rn, int rm, int &bn, int &bm) {
     static const int cand[][2] = {{4, 8}, {8, 4}, {5, 6}, {6, 5}, {3, 10}, {10, 3}, {2, 16}, {16, 2}, {1, 32}, {32, 1}};

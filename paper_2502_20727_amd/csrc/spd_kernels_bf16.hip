@@ -1650,6 +1650,8 @@ hipError_t launch_gemm_lds_cfg(const spd_call &c, const __bf16 *Wp, const __bf16
     constexpr int BN = G::WN * G::TI;
     constexpr int LDS = (XS ? G::NSTX : G::NST) * (BN * (XS ? 1 : 2) + G::WM * G::TJ * 2) * 1024;
     static_assert(LDS <= 160 * 1024, "the stages must fit the LDS of a compute unit");
+    static_assert(BN <= SPD_GEMM_MAX_ROWS && G::WM * G::TJ <= SPD_GEMM_MAX_ROWS, "panel rows, see spd_gemm_fits()");
+    if (!spd_gemm_fits(KT)) return hipErrorInvalidValue;         // (the callers take another kernel)
     const int BM = G::WM * G::TJ * msub;
     // the attribute is per kernel instantiation: set once, whichever thread comes first
     static std::once_flag once;
@@ -2398,7 +2400,7 @@ hipError_t launch_proj(const spd_call &c, bool split, const __bf16 *Wp, const __
     const __bf16 *Xlo = Xhi + plane;
     if (n_mtiles == 1)
         return split ? launch_gemv<true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi) : launch_gemv<false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
-    if (n_mtiles <= SKINNY_MAX_MTILES && skinny_first(n_pairs, KT, split, n_mtiles))
+    if ((n_mtiles <= SKINNY_MAX_MTILES && skinny_first(n_pairs, KT, split, n_mtiles)) || !spd_gemm_fits(KT))
         return launch_skinny(c, split, Wp, Xhi, plane, n_pairs, KT, epi);
     if (!c.chained) {
         bool done = false;
@@ -2437,7 +2439,7 @@ hipError_t launch_o(const spd_call &c, bool split, const __bf16 *Wp, const __bf1
     const __bf16 *Xlo = Xhi + plane;
     if (n_mtiles == 1)
         return split ? launch_gemv<true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi) : launch_gemv<false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
-    if (n_mtiles <= 8 || (n_mtiles <= SKINNY_MAX_MTILES && (MID || n_pairs * zg < 512)))
+    if (n_mtiles <= 8 || (n_mtiles <= SKINNY_MAX_MTILES && (MID || n_pairs * zg < 512)) || !spd_gemm_fits(KT))
         return launch_skinny(c, split, Wp, Xhi, plane, n_pairs, KT, epi);
     if constexpr (MID) {
         return hipErrorInvalidValue;         // (see sync_in_o())
@@ -2721,7 +2723,8 @@ hipError_t mlp_half(const spd_call &c, const char *w, int spd, float *slot, cons
     e1.uhat = uhat; e1.ulo = ulo;
     if (c.on(SPD_STAGE_GATEUP)) {
         spd_stage_scope prof(c, SPD_STAGE_GATEUP);
-        if (M > 16 * SKINNY_MAX_MTILES && e1.nch >= ROW_SCALE_MIN_NCH) {
+        // (the skinny kernel, which takes what the GEMM cannot, adds the partials itself)
+        if (M > 16 * SKINNY_MAX_MTILES && e1.nch >= ROW_SCALE_MIN_NCH && spd_gemm_fits(D.h / 32)) {
             // the factors (4 bytes per token) go where this rank's queries were (64 bytes per token and more): attention is done with them
             float *rs = (float *)(c.ws + D.ws_q);
             hipLaunchKernelGGL(k_row_scale, dim3(cdiv(M, 16)), dim3(512), 0, c.s, e1.ss, e1.nch, D.m_pad, D.h, D.eps, rs);

@@ -524,3 +524,14 @@ def test_gemm_tile_order_rejects():
     assert f(4, 4, 256, 256, 8, 16, 0, C.byref(tn), C.byref(tm)) == B.SPD_EINVAL       # more tiles than the matrix has
     assert f(0, 4, 256, 256, 0, 0, 0, C.byref(tn), C.byref(tm)) == B.SPD_EINVAL
     assert f(4, 4, 256, 256, 0, 16, 0, None, C.byref(tm)) == B.SPD_EINVAL
+
+
+def test_gemm_panels_stay_within_32_bit_offsets():
+    """The largest panel the LDS-tiled GEMM addresses through one buffer descriptor: 24 rows of k_tiles fragments of 1 KiB."""
+    fits = lambda k: B.lib().spd_gemm_panels_fit(k)
+    for k in (1, 256, 896, 131072, 174762, 174763, 174764, 262143, 262144, 262145, 524288, 2 ** 26):
+        bytes_ = 24 * k * 1024
+        assert fits(k) == (1 if bytes_ < 2 ** 32 else 0), k
+        if fits(k):      # the last byte of the last row's last fragment, as lane offset + row offset + k-tile offset
+            assert 63 * 16 + 15 + 23 * k * 1024 + (k - 1) * 1024 < 2 ** 32
+    assert fits(-1) == B.SPD_EINVAL
