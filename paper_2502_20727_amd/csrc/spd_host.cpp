@@ -155,10 +155,11 @@ void compute_dims(const spd_config &c, spd_dims &D) {
         D.ws_ss1 = o; o = spd_align256(o + (h / 32) * M * 4);
         D.ws_ss2 = o; o = spd_align256(o + (h / 32) * M * 4);
         D.ws_uhat = o; o = spd_align256(o + 2 * M * f * 2);
-        // partial tiles of the K-sliced launches: the decode sizes always, the kind of longer calls when they can be longer
+        // partial sums of the K-sliced launches, in tile pairs of 2 KiB (pairs of n-tiles x slices x m-tiles) of whichever
+        // projection is sliced: the decode sizes always, the kind of longer calls when they can be longer
         D.kpart_tiles = D.max_tokens > 16 ? (size_t)SPD_MID_KPART : (size_t)SPD_MAX_KPART;
-        // ... and, when calls can be longer than 512 tokens, the slice partials of a K-sliced QKV GEMM: up to
-        // 8192 (slice, token) rows of fp32
+        // ... and, when calls can be longer than 512 tokens, room for a QKV projection in slices: 8192 (slice, token) rows. The
+        // sliced launches lower their number of slices until the partial sums fit
         if (D.max_tokens > 512) D.kpart_tiles = std::max(D.kpart_tiles, (size_t)8192 * D.nqkv / 512 + 1);
         D.ws_kpart = o; o = spd_align256(o + D.kpart_tiles * 512 * 4);
         D.ws_apart = o;

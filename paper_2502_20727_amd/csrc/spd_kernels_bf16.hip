@@ -1390,9 +1390,9 @@ __global__ void __launch_bounds__(MID_PAIRS * 64) k_mid_finish(const f32x4 *__re
 // wait), and in the second one the copies of the stage NST steps ahead.  The one barrier of a step sits between its
 // sub-steps: passing it means that everybody has read both fragments of the current stage (whose place the copies
 // take) and that the next stage has landed; the copies of the stages after that stay in flight across it.
-// What bounds it: the matrix cores, the LDS (64 bytes per clock and compute unit: 12 fragment reads per 32 MFMAs) and
-// the chip's power together.  A probe of this very mix without barriers or HBM reaches 1.14 PFLOP/s on random
-// data, the gate/up projection of 4096 tokens 1.2, against 1.16 of the vendor library's fp16 product of that shape.
+// What bounds it: the matrix cores at the clock they hold under load, and beside them the LDS (64 bytes per clock and
+// compute unit: 12 fragment reads per 32 MFMAs).  gate/up of 4096 tokens of the 70B shard runs at 1.3 PFLOP/s, spd_mfma_probe() (the
+// same MFMAs on register-resident random data, nothing else) at 1.63 .. 1.76; matrix cores busy 70 % of the cycles.
 // ------------------------------------------------------------------------------------------
 // Tile shapes.  WN x WM waves, each TI n-tiles x TJ m-tiles; stages of the plain and of the split (XS) kind.
 struct GemmBig {      // 256 x 256: two stages of 64 KiB (split: three of 48 KiB)
@@ -2451,13 +2451,13 @@ hipError_t launch_o(const spd_call &c, bool split, const __bf16 *Wp, const __bf1
     }
 }
 
-// chunking of the sum-of-squares partials written by prep()
-// k-tiles per wave of k_prep: enough waves to occupy the chip at every call size
 constexpr int PREP_ROWS_WGS = 512;       // workgroups of the row-wise preparation kernel (two per compute unit)
 // workgroups (one compute unit each) of a chain's rank-sum in a two-chain prefill.  70B shard, 4 x 2048 tokens, us per
 // layer with all sync points dropped / all kept: 64: 2459 / 2790, 96: 2408 / 2702, 112: 2374 / 2699, 128: 2367 / 2552,
 // 144: 2442 / 2712, 192: 2426 / 2718; k_prep_rows: 2454 / 2690
-constexpr int PREP_CU_WGS = 128;       // workgroups of the row-wise preparation kernel (two per compute unit)
+constexpr int PREP_CU_WGS = 128;
+// chunking of the sum-of-squares partials written by prep(): k-tiles per wave of k_prep, enough waves to occupy the chip
+// at every call size
 inline int prep_tpw(int M) { return M <= 64 ? 1 : (M <= 512 ? 2 : 8); }
 inline int prep_nch(int h, int M) { return (int)cdiv(h / 32, prep_tpw(M)); }
 
@@ -2675,7 +2675,7 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
     if (c.on(SPD_STAGE_O)) {
         spd_stage_scope prof(c, SPD_STAGE_O);
         if (fuse_mid) {
-            // the weight-streaming kernels only
+            // k_gemv and k_skinny only
             EpiOT<true> e2;
             fill_o(e2);
             e2.spd = 2;
@@ -2749,8 +2749,8 @@ hipError_t mlp_half(const spd_call &c, const char *w, int spd, float *slot, cons
         }
     }
 
-    // the closing sync point rides in the down projection's epilogue in the weight-streaming kernels (up
-    // to 512 tokens).  In the LDS-tiled GEMM it gains nothing: measured on the 70B prefill shape, the
+    // the closing sync point rides in the down projection's epilogue up to 512 tokens: that of the weight-streaming kernels, of the
+    // kernel that adds K slices, or of one launch of 256 x 128 tiles.  In a long call's GEMM it gains nothing: measured on the 70B prefill shape, the
     // workgroups of a compute unit reach their epilogues together, so the slot reads do not overlap with
     // anybody's contraction and the fused kernel takes exactly as long as GEMM + rank-sum kernel.
     const bool do_fuse = fuse && M <= 16 * SKINNY_MAX_MTILES;

@@ -142,7 +142,7 @@ NARROW_GU = Workload(name="narrow-gate-up", hidden=256, n_q_heads=4, n_kv_heads=
 
 
 # 2080 FFN columns per rank (130 pairs of gate/up tiles, no whole number of GEMM tiles) and 37 k-tiles (the last step
-# of two holds one): a call of 17 .. 512 tokens takes K slices of the LDS-tiled GEMM
+# of two holds one): gate/up takes K slices of the LDS-tiled GEMM at 65 .. 128 tokens, the skinny kernel at 17 .. 64 and beyond
 WIDE_MID = Workload(name="wide-ffn-mid", hidden=1184, n_q_heads=4, n_kv_heads=2, head_dim=64, ffn=4160, n_layers=1,
                     tp=2, dtype=BF16, seed=17, batch=2, q_len=1, ctx=64, mask=(1,))
 
@@ -237,7 +237,7 @@ def test_bf16_long_call_small_shape(gpu, w, flag, split):
 
 # contraction lengths at which the LDS-tiled GEMM can go wrong: fewer k-tiles than it has stages (one k-tile in the O
 # projection, three in QKV and gate/up), odd numbers of them (down: 23), K slices of uneven lengths (66 k-tiles in 8
-# slices up to 512 tokens, all four tile shapes), and 66 partial sums of squares per token, which a kernel of its own
+# slices), and 66 partial sums of squares per token, which a kernel of its own
 # adds up before the gate/up projection of an SPD block of more than 512 tokens
 KT_FEW = Workload(name="few-k-tiles", hidden=96, n_q_heads=2, n_kv_heads=2, head_dim=32, ffn=96, n_layers=1, tp=2, dtype=BF16,
                   seed=31, batch=1, q_len=1, ctx=64, mask=(1,))
@@ -797,8 +797,8 @@ def test_full_size_short_prefill(gpu, q_len):
 
 @pytest.mark.parametrize("q_len", [700, 1100, 2048])
 def test_full_size_single_sequence_prefill(gpu, q_len):
-    """LLaMA2-70B shard, one sequence of 700 / 1100 / 2048 tokens: a single chain, whose QKV GEMM (24, 40 or 64 tiles
-    for 256 compute units) runs in 8 or 4 K slices side by side, the slices' partial rows added by the gather kernel;
+    """LLaMA2-70B shard, one sequence of 700 / 1100 / 2048 tokens: a single chain, whose QKV GEMM has too few tiles
+    for 256 compute units and runs in K slices side by side, whose partial rows a finishing kernel adds;
     at 700 tokens the other projections run as 256 x 128 half tiles throughout (a ragged last one).  An SPD
     block and a TP block, sampled output rows against the oracle at 2e-2."""
     import torch
