@@ -1077,7 +1077,7 @@ struct SkinnyBatch {
 
 template <int W, int MT, bool SPLIT, int MODE, class Epi>
 __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp, const __bf16 *__restrict__ Xhi,
-                                                    const __bf16 *__restrict__ Xlo, int KT, int KS, int n_mtiles, Epi epi) {
+                                                    const __bf16 *__restrict__ Xlo, int KT, int KS, int n_mtiles, unsigned rot_step, Epi epi) {
     extern __shared__ __attribute__((aligned(16))) char sk_lds[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int pair = blockIdx.x, ks = blockIdx.y, mt0 = blockIdx.z * MT;
@@ -1118,10 +1118,9 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
         }
     };
     const int n = k1 - k0;
-    // Each workgroup starts at its own k-tile, so that an XCD's compute units don't all ask one L2 channel for the same
-    // activations; front to back when there are more pairs than compute units (from HBM, 32 sequences: down of
-    // 7B, 128 pairs x 344 k-tiles, 34.6 us front to back / 31.0 rotated, 160 x 216 24.4 / 22.2; but QKV, 384 x 128, 31.4 / 39.6).
-    const int rot = n > 0 && gridDim.x <= 256 ? (int)((unsigned)pair * 5u % (unsigned)n) : 0;
+    // Each workgroup starts at its own k-tile (rot_step, see launch_skinny_mt()), so that an XCD's compute units don't all ask
+    // one L2 channel for the same activations.
+    const int rot = n > 0 ? (int)((unsigned)pair * rot_step % (unsigned)n) : 0;
     auto at = [&](int q) {
         q += rot;
         return k0 + (q >= n ? q - n : q);
@@ -2273,8 +2272,11 @@ hipError_t launch_skinny_mt(const spd_call &c, const __bf16 *Wp, const __bf16 *X
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (attr_err != hipSuccess) return attr_err;
+    // k-tiles in a rotated order, but front to back when there are more pairs than compute units (from HBM, 32 sequences: down
+    // of 7B, 128 pairs x 344 k-tiles, 34.6 us front to back / 31.0 rotated, 160 x 216 24.4 / 22.2; but QKV, 384 x 128, 31.4 / 39.6)
+    const unsigned rot_step = n_pairs <= 256 ? 5 : 0;
     hipLaunchKernelGGL((k_skinny<SKINNY_W, MT, SPLIT, MODE, Epi>), dim3(n_pairs, KS, (n_mtiles + MT - 1) / MT), dim3(SKINNY_W * 64),
-                       lds, c.s, Wp, Xhi, Xlo, KT, KS, n_mtiles, epi);
+                       lds, c.s, Wp, Xhi, Xlo, KT, KS, n_mtiles, rot_step, epi);
     return hipGetLastError();
 }
 template <int MODE = 0, class Epi>
