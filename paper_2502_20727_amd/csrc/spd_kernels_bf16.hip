@@ -2425,9 +2425,11 @@ hipError_t launch_proj(const spd_call &c, bool split, const __bf16 *Wp, const __
 // as its workgroups (128 KiB of LDS each, one per compute unit) come to two rounds of the chip at most; a rank-sum of its
 // own beyond.  Whole layer, weights from HBM, us, in the epilogue / kernel of its own: 70B 129 tokens 135.6 / 143.1, 256 (512
 // workgroups) 165.4 / 172.3, 384 (768) 211.8 / 210.0, 512 263.2 / 252.7; 13B 129 tokens 88.0 / 93.5, 384 (480) 129.7 / 132.2, 512
-// (640) 157.4 / 157.4; 7B 129 tokens 76.5 / 80.2, 512 (512) 126.4 / 132.8; up to 128 tokens 2 .. 4 us less on every shard.
-inline bool sync_in_o(int n_pairs, int n_mtiles) {
-    return n_mtiles <= SKINNY_MAX_MTILES && (n_mtiles <= 8 || n_pairs * ((n_mtiles + 7) / 8) <= 512);
+// (640) 157.4 / 157.4; 7B 129 tokens 76.5 / 80.2, 512 (512) 126.4 / 132.8; up to 128 tokens 2 .. 4 us less on every shard.  With fewer slots the
+// kernel of its own has less to read: 7B 4-way (32 k-tiles) 256 tokens 104.0 / 111.4, 384 139.7 / 139.1, 512 156.6 / 162.3, but 13B
+// 4-way (40) 256 142.5 / 141.6, 333 155.8 / 155.3.
+inline bool sync_in_o(int n_pairs, int KT, int tp, int n_mtiles) {
+    return n_mtiles <= 8 || (n_mtiles <= SKINNY_MAX_MTILES && n_pairs * ((n_mtiles + 7) / 8) <= 512 && KT <= 8 * tp);
 }
 
 // The output projection's contraction is short (a rank's heads): up to 128 tokens the skinny kernel with the whole epilogue
@@ -2663,7 +2665,7 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
     }
     spd_stage_end(c, SPD_STAGE_ATTN);
 
-    const bool fuse_mid = mid && !spd && sync_in_o(D.h / 32, n_mtiles);
+    const bool fuse_mid = mid && !spd && sync_in_o(D.h / 32, qd / 32, D.tp, n_mtiles);
     if (mid_done) *mid_done = fuse_mid;
     auto fill_o = [&](auto &e2) {
         e2.M = M; e2.h = D.h; e2.spd = spd; e2.m_pad = D.m_pad;

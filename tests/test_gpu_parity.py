@@ -393,9 +393,22 @@ def test_bf16_decode_qkv_of_a_wide_shard(gpu, w, batch):
 
 
 # a kept attention sync point of 129 .. 512 tokens: in the O projection's epilogue up to 512 workgroups (130 pairs x groups of 128
-# tokens: 390 up to 384 tokens, 520 beyond), a kernel of its own from there; with bias and with paired activations
+# tokens: 390 up to 384 tokens, 520 beyond) and eight k-tiles per slot, a kernel of its own from there; with bias and with paired
+# activations
 SYNC_130 = Workload(name="sync-130-pairs", hidden=4160, n_q_heads=8, n_kv_heads=8, head_dim=64, ffn=256, n_layers=1, tp=8, dtype=BF16,
                     seed=43, batch=1, q_len=1, ctx=64, mask=(0,))
+
+
+SYNC_16_KT = Workload(name="sync-16-k-tiles", hidden=512, n_q_heads=16, n_kv_heads=16, head_dim=64, ffn=256, n_layers=1, tp=2, dtype=BF16,
+                      seed=46, batch=1, q_len=1, ctx=64, mask=(0,))
+SYNC_18_KT = Workload(name="sync-18-k-tiles", hidden=512, n_q_heads=18, n_kv_heads=18, head_dim=64, ffn=256, n_layers=1, tp=2, dtype=BF16,
+                      seed=47, batch=1, q_len=1, ctx=64, mask=(0,))
+
+
+@pytest.mark.parametrize("w", [SYNC_16_KT, SYNC_18_KT], ids=lambda w: w.name)
+@pytest.mark.parametrize("q_len", [128, 300])
+def test_bf16_kept_sync_point_of_two_ranks(gpu, w, q_len):
+    _one_rank_block(gpu, w, 1, q_len, [0], 0)
 
 
 @pytest.mark.parametrize("bias_std,split", [(0.0, B.SPD_SPLIT_AUTO), (1.0, B.SPD_SPLIT_AUTO), (0.0, B.SPD_SPLIT_ALWAYS)],
