@@ -99,6 +99,22 @@ __device__ __forceinline__ float sum_ss(const float *__restrict__ ss, int nch, i
     return s;
 }
 
+// the same sum in two parts: the first eight loads now, the rest and the additions when they are needed
+struct SsLoads {
+    float t[8];
+    __device__ __forceinline__ void load(const float *__restrict__ ss, int nch, int m_pad, int m, int start, int stride) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) t[j] = (start + j * stride < nch) ? ss[(size_t)(start + j * stride) * m_pad + m] : 0.f;
+    }
+    __device__ __forceinline__ float sum(const float *__restrict__ ss, int nch, int m_pad, int m, int start, int stride) const {
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s += t[j];
+        for (int c = start + 8 * stride; c < nch; c += stride) s += ss[(size_t)c * m_pad + m];
+        return s;
+    }
+};
+
 // 1 / sqrt(mean(x^2) + eps) of every token from its `nch` partial sums of squares, written to `rs`: the partials stay as they
 // are (one preparation serves every emulated rank's MLP).  A consumer told nch = 0 takes the factor as it is.  A projection's epilogue that adds 256 partials per
 // token by itself waits for eight dependent rounds of loads per m-tile: 28 of 150 us in the gate/up projection of 1000
@@ -435,8 +451,8 @@ hipError_t launch_prep_cu(hipStream_t s, int n_wgs, const float *base, const flo
 // loads) are issued together (indices clamped, named registers: nothing here may end up in
 // scratch memory); additions in ascending slot order, the base last, then the bias
 __device__ __forceinline__ void rank_sum_pair(const float *__restrict__ slots, size_t slot_stride, int tp, int rank,
-                                          const float *__restrict__ base, const float *__restrict__ bias, int h, size_t oa,
-                                          size_t ob, float4 own_a, float4 own_b, float4 &ra, float4 &rb) {
+                                          const float *__restrict__ base, size_t oa, float4 own_a, float4 own_b, float4 &ra, float4 &rb) {
+    const size_t ob = oa + 16;
     float4 acc_a = make_float4(0.f, 0.f, 0.f, 0.f), acc_b = acc_a;
     // (past the end: the last slot again; the own slot is in registers: a neighbour's line, which is on its way anyway)
     const int last = tp - 1, other = rank > 0 ? rank - 1 : (tp > 1 ? 1 : 0);
@@ -464,13 +480,79 @@ const float4 tb##j = *(const float4 *)(slots + (size_t)at(s0 + j) * slot_stride 
     }
     ra = make_float4(bs_a.x + acc_a.x, bs_a.y + acc_a.y, bs_a.z + acc_a.z, bs_a.w + acc_a.w);
     rb = make_float4(bs_b.x + acc_b.x, bs_b.y + acc_b.y, bs_b.z + acc_b.z, bs_b.w + acc_b.w);
-    if (bias) {
-        const float4 ba = *(const float4 *)(bias + (oa % (size_t)h)), bb = *(const float4 *)(bias + (ob % (size_t)h));
+}
+
+// What such a sum reads, requested ahead of the contraction: the first slots and the base of one (pair of n-tiles, m-tile).  Asked
+// for in the epilogue, which all workgroups of a launch reach together, it was a trip to the memory of its own after the weights.
+constexpr int SYNC_EARLY = 8;
+struct SyncRegs {          // ... in registers
+    float4 s[SYNC_EARLY][2], base[2];      // (the own slot's place is not used)
+    __device__ __forceinline__ float4 slot(int i, int half) const { return s[i][half]; }
+    __device__ __forceinline__ float4 at_base(int half) const { return base[half]; }
+};
+struct SyncLds {           // ... in LDS, [slot][half][lane]; the base in the own slot's place or, with a rank beyond them, behind the slots
+    const f32x4 *p;
+    int rank;
+    __device__ __forceinline__ float4 slot(int i, int half) const { return __builtin_bit_cast(float4, p[(i * 2 + half) * 64]); }
+    __device__ __forceinline__ float4 at_base(int half) const { return slot(rank < SYNC_EARLY ? rank : SYNC_EARLY, half); }
+};
+struct SyncNone {};        // nothing requested yet
+struct SyncSum {           // the sync point an epilogue performs
+    const float *slots, *base, *bias;
+    size_t slot_stride;
+    int tp, rank, M, h;
+    // offset of a lane's first feature (rows past the call: its last one)
+    __device__ __forceinline__ size_t at(int pair, int mt, int lane) const {
+        const int m = mt * 16 + (lane & 15);
+        return (size_t)(m < M ? m : M - 1) * h + pair * 32 + 4 * (lane >> 4);
+    }
+    __device__ __forceinline__ void load(SyncRegs &t, size_t o) const {
+        t.base[0] = *(const float4 *)(base + o);
+        t.base[1] = *(const float4 *)(base + o + 16);
+#pragma unroll
+        for (int s = 0; s < SYNC_EARLY; ++s) {
+            const float *p = (s == rank ? base : slots + (size_t)(s < tp ? s : tp - 1) * slot_stride) + o;
+            t.s[s][0] = *(const float4 *)p;
+            t.s[s][1] = *(const float4 *)(p + 16);
+        }
+    }
+    // the sum of rank_sum_pair(), in the same order; o: offset of the first half's features, na: its column
+    template <class T>
+    __device__ __forceinline__ void sum(const T &t, size_t o, int na, float4 own_a, float4 own_b, float4 &ra, float4 &rb) const {
+        float4 acc_a = own_a, acc_b = own_b;
+        auto add = [&](int s, float4 va, float4 vb) {
+            if (s == rank) { va = own_a; vb = own_b; }
+            if (s == 0) {
+                acc_a = va;
+                acc_b = vb;
+            } else {
+                acc_a.x += va.x; acc_a.y += va.y; acc_a.z += va.z; acc_a.w += va.w;
+                acc_b.x += vb.x; acc_b.y += vb.y; acc_b.z += vb.z; acc_b.w += vb.w;
+            }
+        };
+#pragma unroll
+        for (int s = 0; s < SYNC_EARLY; ++s)
+            if (s < tp) add(s, t.slot(s, 0), t.slot(s, 1));
+        for (int s = SYNC_EARLY; s < tp; ++s) {
+            const float *p = (s == rank ? base : slots + (size_t)s * slot_stride) + o;
+            add(s, *(const float4 *)p, *(const float4 *)(p + 16));
+        }
+        const float4 ba = t.at_base(0), bb = t.at_base(1);
+        ra = make_float4(ba.x + acc_a.x, ba.y + acc_a.y, ba.z + acc_a.z, ba.w + acc_a.w);
+        rb = make_float4(bb.x + acc_b.x, bb.y + acc_b.y, bb.z + acc_b.z, bb.w + acc_b.w);
+        add_bias(na, ra, rb);
+    }
+    __device__ __forceinline__ void sum(const SyncNone &, size_t o, int na, float4 own_a, float4 own_b, float4 &ra, float4 &rb) const {
+        rank_sum_pair(slots, slot_stride, tp, rank, base, o, own_a, own_b, ra, rb);
+        add_bias(na, ra, rb);
+    }
+    __device__ __forceinline__ void add_bias(int na, float4 &ra, float4 &rb) const {
+        if (!bias) return;
+        const float4 ba = *(const float4 *)(bias + na), bb = *(const float4 *)(bias + na + 16);
         ra.x += ba.x; ra.y += ba.y; ra.z += ba.z; ra.w += ba.w;
         rb.x += bb.x; rb.y += bb.y; rb.z += bb.z; rb.w += bb.w;
     }
-}
-
+};
 
 // ------------------------------------------------------------------------------------------
 // Epilogues.  Each receives the accumulators of one (pair of n-tiles, m-tile): a = tile
@@ -481,6 +563,7 @@ const float4 tb##j = *(const float4 *)(slots + (size_t)at(s0 + j) * slot_stride 
 // kNeedsRs: the tile must be scaled by 1/sqrt(mean(x^2)+eps) of the token, which the caller
 // computes from the partial sums of squares ss[nch][m_pad].
 struct EpiQKV {
+    static constexpr bool kSync = false;
     static constexpr bool kLong = true;        // used by calls of any length
     static constexpr bool kWideSum = true;     // K slices are added in 64 bits
     static constexpr bool kNeedsRs = true;
@@ -556,6 +639,7 @@ struct EpiQKV {
 // part[slice][token][column] (columns in natural order: head * d + j).  The attention kernel adds
 // the slices in ascending order, rounds, and appends the new key and value to the cache.
 struct EpiQKVPart {
+    static constexpr bool kSync = false;
     static constexpr bool kNeedsRs = true;
     int M, q_len, q, kv, d, h, nqkv, nch, m_pad;
     int part_rows;             // token rows per slice of `part`
@@ -605,6 +689,7 @@ struct EpiQKVPart {
 
 template <bool MID>      // MID: the epilogue can also perform the kept attention sync point (spd = 2)
 struct EpiOT {
+    static constexpr bool kSync = MID;         // can perform a sync point (one rank, the peers' partial sums are inputs)
     static constexpr bool kWideSum = false;
     static constexpr bool kNeedsRs = false;
     static constexpr bool kSliced = false;
@@ -620,6 +705,7 @@ struct EpiOT {
     size_t slot_stride = 0;
     int tp = 0, rank = 0;
     float *rbuf = nullptr;
+    __device__ __forceinline__ SyncSum sync() const { return SyncSum{slots, x, bo, slot_stride, tp, rank, M, h}; }
     struct Pre {
         float4 x0, x1, ga, gb;
     };
@@ -647,7 +733,9 @@ struct EpiOT {
         return p;
     }
 
-    __device__ __forceinline__ void operator()(int pair, int mt, f32x4 a, f32x4 b, int lane, float, const Pre &p) const {
+    template <class Peers = SyncNone>
+    __device__ __forceinline__ void operator()(int pair, int mt, f32x4 a, f32x4 b, int lane, float, const Pre &p,
+                                               const Peers &peers = Peers()) const {
         const int r = lane & 15, m = mt * 16 + r, g = lane >> 4;
         const int na = pair * 32 + 4 * g, nb = na + 16;
         const bool valid = m < M;
@@ -671,7 +759,7 @@ struct EpiOT {
             *(float4 *)(slot + o + na) = own_a;
             *(float4 *)(slot + o + nb) = own_b;
             float4 qa, qb;
-            rank_sum_pair(slots, slot_stride, tp, rank, x, bo, h, o + na, o + nb, own_a, own_b, qa, qb);
+            sync().sum(peers, o + na, na, own_a, own_b, qa, qb);
             *(float4 *)(rbuf + o + na) = qa;
             *(float4 *)(rbuf + o + nb) = qb;
             ra[0] = qa.x; ra[1] = qa.y; ra[2] = qa.z; ra[3] = qa.w;
@@ -707,6 +795,7 @@ struct EpiOT {
 };
 
 struct EpiGU {
+    static constexpr bool kSync = false;
     static constexpr bool kLong = true;
     static constexpr bool kWideSum = false;
     static constexpr bool kNeedsRs = true;
@@ -756,6 +845,7 @@ struct EpiGU {
 
 template <bool FUSED>
 struct EpiDownT {
+    static constexpr bool kSync = FUSED;
     static constexpr bool kLong = !FUSED;
     static constexpr bool kWideSum = false;
     static constexpr bool kNeedsRs = false;
@@ -772,14 +862,19 @@ struct EpiDownT {
     int tp, rank, m_pad;
     float *x_out, *ss1;
     __bf16 *xhat, *xlo;        // next block's first-norm activations (xhat NULL: last block)
+    __device__ __forceinline__ SyncSum sync() const { return SyncSum{slots, base, bias, slot_stride, tp, rank, M, h}; }
     struct Pre {
-        float4 ya, yb;
+        float4 ya, yb, ga, gb;
     };
 
     __device__ __forceinline__ Pre pre(int pair, int mt, int lane) const {
         Pre p;
-        p.ya = p.yb = make_float4(0.f, 0.f, 0.f, 0.f);
+        p.ya = p.yb = p.ga = p.gb = make_float4(0.f, 0.f, 0.f, 0.f);
         const int m = mt * 16 + (lane & 15), g = lane >> 4;
+        if (FUSED && xhat) {
+            p.ga = *(const float4 *)(g1 + pair * 32 + 4 * g);
+            p.gb = *(const float4 *)(g1 + pair * 32 + 16 + 4 * g);
+        }
         if (spd && m < M) {
             const size_t oa = (size_t)m * h + pair * 32 + 4 * g;
             p.ya = *(const float4 *)(ybuf + oa);
@@ -788,13 +883,9 @@ struct EpiDownT {
         return p;
     }
 
-    // out = base + (slot_0 + slot_1 + ...), own partial standing in for slot `rank`: the same
-    // order of additions as the stand-alone rank-sum
-    __device__ __forceinline__ void sync_sum2(size_t oa, size_t ob, float4 own_a, float4 own_b, float4 &ra, float4 &rb) const {
-        rank_sum_pair(slots, slot_stride, tp, rank, base, bias, h, oa, ob, own_a, own_b, ra, rb);
-    }
-
-    __device__ __forceinline__ void operator()(int pair, int mt, f32x4 a, f32x4 b, int lane, float, const Pre &p) const {
+    template <class Peers = SyncNone>
+    __device__ __forceinline__ void operator()(int pair, int mt, f32x4 a, f32x4 b, int lane, float, const Pre &p,
+                                               const Peers &peers = Peers()) const {
         const int r = lane & 15, m = mt * 16 + r, g = lane >> 4;
         const bool valid = m < M;
         const size_t oa = (size_t)m * h + pair * 32 + 4 * g, ob = oa + 16;
@@ -813,16 +904,17 @@ struct EpiDownT {
         if (!FUSED) return;
         float4 xa = make_float4(0.f, 0.f, 0.f, 0.f), xb = xa;
         if (valid) {
-            sync_sum2(oa, ob, pa, pb, xa, xb);
+            // out = base + (slot_0 + slot_1 + ...), own partial standing in for slot `rank`: the same
+            // order of additions as the stand-alone rank-sum
+            sync().sum(peers, oa, pair * 32 + 4 * g, pa, pb, xa, xb);
             *(float4 *)(x_out + oa) = xa;
             *(float4 *)(x_out + ob) = xb;
         }
         if (!xhat) return;
         float qa[4] = {0.f, 0.f, 0.f, 0.f}, qb[4] = {0.f, 0.f, 0.f, 0.f};
         if (valid) {
-            const float4 ga = *(const float4 *)(g1 + pair * 32 + 4 * g), gb = *(const float4 *)(g1 + pair * 32 + 16 + 4 * g);
-            qa[0] = xa.x * ga.x; qa[1] = xa.y * ga.y; qa[2] = xa.z * ga.z; qa[3] = xa.w * ga.w;
-            qb[0] = xb.x * gb.x; qb[1] = xb.y * gb.y; qb[2] = xb.z * gb.z; qb[3] = xb.w * gb.w;
+            qa[0] = xa.x * p.ga.x; qa[1] = xa.y * p.ga.y; qa[2] = xa.z * p.ga.z; qa[3] = xa.w * p.ga.w;
+            qb[0] = xb.x * p.gb.x; qb[1] = xb.y * p.gb.y; qb[2] = xb.z * p.gb.z; qb[3] = xb.w * p.gb.w;
         }
         const bf16x4 ha = cvt4h(qa[0], qa[1], qa[2], qa[3]), hb = cvt4h(qb[0], qb[1], qb[2], qb[3]);
         const size_t fo = spd_frag_index(mt, pair, h >> 5);
@@ -864,23 +956,83 @@ struct EpiPark {
 //   out^T[n][m] = sum_k W[k][n] x[m][k]
 // grid = (pairs of n-tiles, KS).  A workgroup owns one pair and one of KS slices of K; its W
 // waves split that slice, each wave streaming its weight fragments straight from HBM into
-// registers in batches of U k-tiles, the next batch in flight while the current one feeds the
-// MFMAs.  The waves' partial tiles are added through LDS in wave order.  With KS = 1 the first
+// registers, four k-tiles in flight while a fifth feeds the MFMAs (70B shard, 16 tokens, us, the ring against two sets of two k-tiles
+// that the compiler had put back into one: gate/up 22.4 / 21.3, down 13.7 / 13.0, QKV 7.6 / 7.2; 3, 4, 6 and 8 sets: gate/up 22.0,
+// 21.9, 21.6, 21.7; four more with no memory access past the end instead of a branch: 23.0, every load of zeros
+// takes its turn).  What the epilogue reads besides, the peers' partial sums above all, is requested in the same breath
+// (down 13.0 -> 12.5).  The rest of a small launch is latency: 2 us to start, one trip to the memory, the
+// sum over the waves.  The waves' partial tiles are added through LDS in wave order.  With KS = 1 the first
 // wave then runs the epilogue; with KS > 1 and MODE 1 the workgroup parks its tile in `kpart`
 // and k_gemv_finish adds the KS tiles in slice order: sums never depend on timing.  MODE 2 is
 // for epilogues that are linear in the accumulators: every slice runs Epi::slice() on its own
 // partial sums and the consumer of the result adds the slices.
 // ------------------------------------------------------------------------------------------
-template <int U, bool SPLIT>
-struct GemvBatch {
-    bf16x8 fa[U], fb[U], fh[U], fl[SPLIT ? U : 1];
+// A wave's walk over its n k-tiles with a ring of NB register sets: the loads of NB - 1 k-tiles are in flight while one is
+// multiplied.  The scheduling barriers are what makes it so: without them the compiler puts a set's loads after the
+// MFMAs of the one before and directly in front of their own.  The steady state has no branch between the loads and their use,
+// otherwise the compiler's counts of what is in flight assume the worst (it may, for the last few).  `between` runs once, after the first loads.
+#define SPD_SCHED_BARRIER() __builtin_amdgcn_sched_barrier(0)
+template <int NB, class Set, class Load, class Use, class Between>
+__device__ __forceinline__ void stream_tiles(int n, const Load &load, const Use &use, const Between &between) {
+    Set R[NB];
+    if (n < NB) {                            // everything is requested at once
+#pragma unroll
+        for (int j = 0; j < NB - 1; ++j)
+            if (j < n) load(R[j], j);
+        SPD_SCHED_BARRIER();
+        between();
+        SPD_SCHED_BARRIER();
+#pragma unroll
+        for (int j = 0; j < NB - 1; ++j)
+            if (j < n) use(R[j]);
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < NB - 1; ++j) load(R[j], j);
+    SPD_SCHED_BARRIER();
+    between();
+    SPD_SCHED_BARRIER();
+    int i = 0;
+    for (; i + 2 * NB - 1 <= n; i += NB) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            load(R[(j + NB - 1) % NB], i + j + NB - 1);
+            SPD_SCHED_BARRIER();
+            use(R[j]);
+            SPD_SCHED_BARRIER();
+        }
+    }
+    const int left = n - i;                  // NB - 1 of them are on their way: NB - 1 <= left < 2 NB - 1
+#pragma unroll
+    for (int j = 0; j < NB - 1; ++j) {
+        if (j + NB - 1 < left) load(R[(j + NB - 1) % NB], i + j + NB - 1);
+        SPD_SCHED_BARRIER();
+        use(R[j]);
+        SPD_SCHED_BARRIER();
+    }
+#pragma unroll
+    for (int j = NB - 1; j < 2 * NB - 2; ++j)
+        if (j < left) use(R[j % NB]);
+}
+// 16 bytes per lane at p + off of the `bytes` bytes from the wave-uniform address p on (zeros past them).  A buffer load: the
+// address stays in scalar registers.  STREAM: data that is read once.
+template <bool STREAM>
+__device__ __forceinline__ bf16x8 frag(const char *p, unsigned bytes, unsigned off) {
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, (int)bytes, 0x00020000);
+    return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, STREAM ? 2 : 0));
+}
+
+template <bool SPLIT>
+struct GemvSet {
+    bf16x8 fa, fb, fh, fl;      // fl: SPLIT only
+    static constexpr int kRing = SPLIT ? 3 : 5;      // (16 waves: 128 registers each)
 };
 
-template <int W, int U, bool SPLIT, int MODE, class Epi>     // MODE 0: whole K, 1: slices -> kpart, 2: slices -> Epi::slice
+template <int W, bool SPLIT, int MODE, class Epi>     // MODE 0: whole K, 1: slices -> kpart, 2: slices -> Epi::slice
 __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, const __bf16 *__restrict__ Xhi,
                                                   const __bf16 *__restrict__ Xlo, int KT, int KS,
                                                   float *__restrict__ kpart, int rows, Epi epi) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int pair = blockIdx.x, ks = blockIdx.y;
     const int kb0 = (int)(((long)ks * KT) / KS), kb1 = (int)(((long)(ks + 1) * KT) / KS);
     const int nk = kb1 - kb0;
@@ -890,95 +1042,88 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
     // gate/up copy): per k-tile `rows` rows of the first tile then `rows` rows of the second, 16
     // bytes per row and quarter of the k-tile; the lanes of the missing rows repeat the last row
     // (same cache lines; the epilogue does not store them).
-    const bf16x8 *wa, *wb;
-    size_t kstr;        // distance between k-tiles, in 16-byte units
+    // (wave-uniform addresses plus a lane's offset: the loads need no vector registers for addresses)
+    const char *wa, *wb;
+    unsigned wlane, kstr;        // a lane's offset, distance between k-tiles, in bytes
     if (rows == 16) {
-        wa = (const bf16x8 *)(Wp + spd_frag_index(2 * pair, 0, KT)) + lane;
-        wb = (const bf16x8 *)(Wp + spd_frag_index(2 * pair + 1, 0, KT)) + lane;
-        kstr = 64;
+        wa = (const char *)(Wp + spd_frag_index(2 * pair, 0, KT));
+        wb = (const char *)(Wp + spd_frag_index(2 * pair + 1, 0, KT));
+        wlane = lane * 16;
+        kstr = 1024;
     } else {
         const int rr = (lane & 15) < rows ? (lane & 15) : rows - 1;
-        wa = (const bf16x8 *)Wp + (size_t)pair * KT * 8 * rows + (lane >> 4) * rows + rr;
-        wb = wa + 4 * rows;
-        kstr = 8 * rows;
+        wa = (const char *)Wp + (size_t)pair * KT * 128 * rows;
+        wb = wa + 64 * rows;
+        wlane = ((lane >> 4) * rows + rr) * 16;
+        kstr = 128 * rows;
     }
-    const bf16x8 *xh = (const bf16x8 *)Xhi + lane;
-    const bf16x8 *xl = (const bf16x8 *)Xlo + lane;
+    const char *xh = (const char *)Xhi, *xl = (const char *)Xlo;
+    const unsigned xlane = lane * 16;
 
-    auto load = [&](GemvBatch<U, SPLIT> &B, int kt) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            B.fa[u] = __builtin_nontemporal_load(wa + (size_t)(kt + u) * kstr);
-            B.fb[u] = __builtin_nontemporal_load(wb + (size_t)(kt + u) * kstr);
-            B.fh[u] = xh[(size_t)(kt + u) * 64];
-            if (SPLIT) B.fl[u] = xl[(size_t)(kt + u) * 64];
-        }
+    auto load = [&](GemvSet<SPLIT> &B, int i) {
+        const size_t kt = k0 + i;
+        const unsigned wn = 64 * rows, xn = 1024;
+        B.fa = frag<true>(wa + kt * kstr, wn, wlane);
+        B.fb = frag<true>(wb + kt * kstr, wn, wlane);
+        B.fh = frag<false>(xh + kt * 1024, xn, xlane);
+        if (SPLIT) B.fl = frag<false>(xl + kt * 1024, xn, xlane);
     };
-    auto consume = [&](const GemvBatch<U, SPLIT> &B) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            a = MFMA16(B.fa[u], B.fh[u], a);
-            b = MFMA16(B.fb[u], B.fh[u], b);
-            if (SPLIT) {
-                a = MFMA16(B.fa[u], B.fl[u], a);
-                b = MFMA16(B.fb[u], B.fl[u], b);
-            }
+    auto consume = [&](const GemvSet<SPLIT> &B) {
+        a = MFMA16(B.fa, B.fh, a);
+        b = MFMA16(B.fb, B.fh, b);
+        if (SPLIT) {
+            a = MFMA16(B.fa, B.fl, a);
+            b = MFMA16(B.fb, B.fl, b);
         }
     };
 
     // every wave walks its share of K front to back (measured: any other order, e.g. one rotated
     // per workgroup to spread the activation reads, costs a fifth of the streaming rate)
-    const int nfull = (k1 - k0) / U;
-    GemvBatch<U, SPLIT> cur;
-    if (nfull > 0) load(cur, k0);
-
-    // loads that do not depend on the stream: the epilogue's inputs (first wave) and this wave's
-    // share of the sum-of-squares partials, issued while the first weights are on their way
     typename Epi::Pre pre;
-    float ssp = 0.f;
-    constexpr bool PARTIAL = MODE == 1;
-    if (!PARTIAL) {
-        if (wave == 0) pre = epi.pre(pair, 0, lane);
-        if constexpr (Epi::kNeedsRs) {
-            ssp = sum_ss(epi.ss, epi.nch, epi.m_pad, lane & 15, wave * 4 + (lane >> 4), W * 4);
+    SsLoads ssl;
+    constexpr bool PARTIAL = MODE == 1, EARLY = Epi::kSync && MODE == 0;
+    f32x4 sla = {0.f, 0.f, 0.f, 0.f}, slb = sla, bsa = sla, bsb = sla;
+    stream_tiles<GemvSet<SPLIT>::kRing, GemvSet<SPLIT>>(k1 - k0, load, consume, [&]() {
+        // loads that do not depend on the stream: the epilogue's inputs (first wave) and this wave's
+        // share of the sum-of-squares partials, issued while the first weights are on their way
+        if (!PARTIAL) {
+            if (wave == 0) pre = epi.pre(pair, 0, lane);
+            if constexpr (EARLY) {
+                // wave s takes slot s, the own slot's wave the base
+                const SyncSum sy = epi.sync();
+                if (wave < SYNC_EARLY) {
+                    const int sl = wave < sy.tp ? wave : sy.tp - 1;
+                    const float *p = (sl == sy.rank ? sy.base : sy.slots + (size_t)sl * sy.slot_stride) + sy.at(pair, 0, lane);
+                    sla = *(const f32x4 *)p;
+                    slb = *(const f32x4 *)(p + 16);
+                }
+                if (sy.rank >= SYNC_EARLY && wave == 0) {
+                    const float *p = sy.base + sy.at(pair, 0, lane);
+                    bsa = *(const f32x4 *)p;
+                    bsb = *(const f32x4 *)(p + 16);
+                }
+            }
+            if constexpr (Epi::kNeedsRs) {
+                ssl.load(epi.ss, epi.nch, epi.m_pad, lane & 15, wave * 4 + (lane >> 4), W * 4);
+            }
         }
-    }
-
-    // two register buffers, used alternately: the loads of one batch are in flight while the other
-    // batch feeds the MFMAs
-    GemvBatch<U, SPLIT> oth;
-    auto batch_k = [&](int i) { return k0 + i * U; };
-    int i = 0;
-    for (; i + 2 < nfull; i += 2) {      // steady state: no branch between the loads and their use
-        load(oth, batch_k(i + 1));
-        consume(cur);
-        load(cur, batch_k(i + 2));
-        consume(oth);
-    }
-    if (i + 1 < nfull) {
-        load(oth, batch_k(i + 1));
-        consume(cur);
-        consume(oth);
-    } else if (i < nfull) {
-        consume(cur);
-    }
-    for (int kt = k0 + nfull * U; kt < k1; ++kt) {
-        const bf16x8 fa = __builtin_nontemporal_load(wa + (size_t)kt * kstr);
-        const bf16x8 fb = __builtin_nontemporal_load(wb + (size_t)kt * kstr);
-        const bf16x8 fh = xh[(size_t)kt * 64];
-        a = MFMA16(fa, fh, a);
-        b = MFMA16(fb, fh, b);
-        if (SPLIT) {
-            const bf16x8 fl = xl[(size_t)kt * 64];
-            a = MFMA16(fa, fl, a);
-            b = MFMA16(fb, fl, b);
-        }
-    }
+    });
     __shared__ f32x4 red[W][2][64];
     __shared__ float red_ss[W][64];
+    __shared__ f32x4 peers[EARLY ? SYNC_EARLY + 1 : 1][2][64];
     red[wave][0][lane] = a;
     red[wave][1][lane] = b;
-    red_ss[wave][lane] = ssp;
+    if constexpr (Epi::kNeedsRs && !PARTIAL) red_ss[wave][lane] = ssl.sum(epi.ss, epi.nch, epi.m_pad, lane & 15, wave * 4 + (lane >> 4), W * 4);
+    if constexpr (EARLY) {
+        if (wave < SYNC_EARLY) {
+            peers[wave][0][lane] = sla;
+            peers[wave][1][lane] = slb;
+        }
+        if (wave == 0) {
+            peers[SYNC_EARLY][0][lane] = bsa;
+            peers[SYNC_EARLY][1][lane] = bsb;
+        }
+    }
     __syncthreads();
     if (wave != 0) return;
     a = red[0][0][lane];
@@ -1003,8 +1148,13 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
         sq += shfl_xor_f(sq, 32);
         rs = 1.0f / sqrtf(sq / (float)epi.h + epi.eps);
     }
-    if constexpr (MODE == 2) epi.slice(pair, ks, 0, a, b, lane, rs, pre);
-    else epi(pair, 0, a, b, lane, rs, pre);
+    if constexpr (MODE == 2) {
+        epi.slice(pair, ks, 0, a, b, lane, rs, pre);
+    } else if constexpr (EARLY) {
+        epi(pair, 0, a, b, lane, rs, pre, SyncLds{&peers[0][0][lane], epi.sync().rank});
+    } else {
+        epi(pair, 0, a, b, lane, rs, pre);
+    }
 }
 
 // Adds the KS partial tiles of a pair in slice order and runs the epilogue.  grid = pairs,
@@ -1960,9 +2110,13 @@ __global__ void __launch_bounds__(256) k_attn_decode(const __bf16 *__restrict__ 
         int j = 0;
         for (; j + 2 < nw; j += 2) {
             attn_block<DT>(st, qf, f0, blk(j), cvalid ? n_keys : 0, scale, lane);
+            SPD_SCHED_BARRIER();
             load_kv<DT>(f0, kbase, vbase, blk(j + 2), d, lane);
+            SPD_SCHED_BARRIER();
             attn_block<DT>(st, qf, f1, blk(j + 1), cvalid ? n_keys : 0, scale, lane);
+            SPD_SCHED_BARRIER();
             load_kv<DT>(f1, kbase, vbase, blk(j + 3), d, lane);
+            SPD_SCHED_BARRIER();
         }
         attn_block<DT>(st, qf, f0, blk(j), cvalid ? n_keys : 0, scale, lane);
         attn_block<DT>(st, qf, f1, blk(j + 1), (cvalid && j + 1 < nw) ? n_keys : 0, scale, lane);
@@ -2215,26 +2369,26 @@ hipError_t launch_gemv(const spd_call &c, const __bf16 *Wp, const __bf16 *Xhi, c
     if (gemv_whole(n_pairs, KT)) {
         // one workgroup per pair, no slices
         if (KT >= 32) {
-            // 16 waves share 512 VGPRs per lane and SIMD: two batches of 2 k-tiles fit.  With as few as
+            // 16 waves share 512 VGPRs per lane and SIMD.  With as few as
             // 2 k-tiles per wave everything is requested at once, which is what a short kernel wants.
-            constexpr int W = 16, U = 2;
-            hipLaunchKernelGGL((k_gemv<W, U, SPLIT, 0, Epi>), dim3(n_pairs, 1), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT,
+            constexpr int W = 16;
+            hipLaunchKernelGGL((k_gemv<W, SPLIT, 0, Epi>), dim3(n_pairs, 1), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT,
                                1, kpart, rows, epi);
         } else {
-            constexpr int W = 8, U = 2;
-            hipLaunchKernelGGL((k_gemv<W, U, SPLIT, 0, Epi>), dim3(n_pairs, 1), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT,
+            constexpr int W = 8;
+            hipLaunchKernelGGL((k_gemv<W, SPLIT, 0, Epi>), dim3(n_pairs, 1), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT,
                                1, kpart, rows, epi);
         }
         return hipGetLastError();
     }
-    constexpr int W = GEMV_SLICE_W, U = 2;
+    constexpr int W = GEMV_SLICE_W;
     const int KS = gemv_slices(n_pairs, KT);
     if (KS <= 1) {
-        hipLaunchKernelGGL((k_gemv<W, U, SPLIT, 0, Epi>), dim3(n_pairs, 1), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT, 1,
+        hipLaunchKernelGGL((k_gemv<W, SPLIT, 0, Epi>), dim3(n_pairs, 1), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT, 1,
                            kpart, rows, epi);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL((k_gemv<W, U, SPLIT, 1, Epi>), dim3(n_pairs, KS), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT, KS,
+    hipLaunchKernelGGL((k_gemv<W, SPLIT, 1, Epi>), dim3(n_pairs, KS), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT, KS,
                        kpart, rows, epi);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -2248,13 +2402,13 @@ constexpr int QKV_SLICE_W = 16;
 template <class Epi>
 hipError_t launch_gemv_sliced(const spd_call &c, bool split, const __bf16 *Wp, const __bf16 *Xhi, size_t plane, int n_pairs,
                               int KT, int KS, const Epi &epi) {
-    constexpr int W = QKV_SLICE_W, U = 2;
+    constexpr int W = QKV_SLICE_W;
     const __bf16 *Xlo = Xhi + plane;
     if (split)
-        hipLaunchKernelGGL((k_gemv<W, U, true, 2, Epi>), dim3(n_pairs, KS), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT, KS,
+        hipLaunchKernelGGL((k_gemv<W, true, 2, Epi>), dim3(n_pairs, KS), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT, KS,
                            (float *)nullptr, 16, epi);
     else
-        hipLaunchKernelGGL((k_gemv<W, U, false, 2, Epi>), dim3(n_pairs, KS), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT, KS,
+        hipLaunchKernelGGL((k_gemv<W, false, 2, Epi>), dim3(n_pairs, KS), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT, KS,
                            (float *)nullptr, 16, epi);
     return hipGetLastError();
 }

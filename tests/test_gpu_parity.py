@@ -298,11 +298,11 @@ def test_bf16_norm_partials_serve_every_rank(gpu, w, flag):
     case.close()
 
 
-def _one_rank_block(gpu, w, batch, q_len, positions, flag, split=B.SPD_SPLIT_AUTO, max_ctx=None, bias_std=0.0, bound_scale=1.0):
+def _one_rank_block(gpu, w, batch, q_len, positions, flag, split=B.SPD_SPLIT_AUTO, max_ctx=None, bias_std=0.0, bound_scale=1.0, rank=1):
     """One rank's block call with peer slots as inputs against the oracle: the output, the slot the rank wrote, and the
     peers' slots unchanged."""
     import torch
-    rank, M = 1, batch * q_len
+    M = batch * q_len
     case = Case(w, gpu, ranks=[rank], positions=positions, max_ctx=max_ctx or (max(positions) + q_len + 31) // 32 * 32, max_tokens=M,
                 act_split=split, bias_std=bias_std)
     X = inputs.hidden_states(w, M)
@@ -416,6 +416,34 @@ def test_bf16_kept_sync_point_of_two_ranks(gpu, w, q_len):
 @pytest.mark.parametrize("q_len", [128, 129, 300, 384, 385, 512])
 def test_bf16_kept_sync_point_of_a_medium_call(gpu, q_len, bias_std, split):
     _one_rank_block(gpu, SYNC_130, 1, q_len, [0], 0, split, bias_std=bias_std)
+
+
+# the weight-streaming kernel's ring of k-tiles: shares of a wave shorter than the ring, of one and of several turns, with every number of k-tiles
+# left over (down: 33, 81, 100 and 145 k-tiles over 16 waves in one launch, 1 in a wave each; gate/up: 192, in slices)
+@pytest.mark.parametrize("k_tiles", [1, 33, 81, 100, 145])
+@pytest.mark.parametrize("split", [B.SPD_SPLIT_AUTO, B.SPD_SPLIT_ALWAYS], ids=["default", "all-split"])
+@pytest.mark.parametrize("flag", [1, 0], ids=["spd", "tp"])
+def test_bf16_decode_contraction_lengths(gpu, k_tiles, split, flag):
+    w = Workload(name=f"down-{k_tiles}-k-tiles", hidden=6144, n_q_heads=2, n_kv_heads=2, head_dim=32, ffn=64 * k_tiles, n_layers=1, tp=2,
+                 dtype=BF16, seed=48, batch=1, q_len=1, ctx=64, mask=(flag,))
+    _one_rank_block(gpu, w, 5, 1, [3, 0, 40, 17, 31], flag, split)
+
+
+# sync points in epilogues that ask for the first eight slots ahead of the contraction: fewer slots, as many, more, and an own slot beyond them
+@pytest.mark.parametrize("tp,rank", [(1, 0), (2, 0), (8, 7), (9, 8), (9, 3), (16, 11)])
+@pytest.mark.parametrize("batch,flag", [(3, 0), (16, 1), (24, 0), (48, 1), (64, 0)])
+def test_bf16_sync_point_of_several_ranks(gpu, tp, rank, batch, flag):
+    w = Workload(name=f"{tp}-ranks", hidden=512, n_q_heads=2 * tp, n_kv_heads=tp, head_dim=32, ffn=96 * tp, n_layers=1, tp=tp,
+                 dtype=BF16, seed=49, batch=1, q_len=1, ctx=64, mask=(flag,))
+    _one_rank_block(gpu, w, batch, 1, [(7 * i) % 61 for i in range(batch)], flag, max_ctx=64, bias_std=batch % 3 * 0.5, rank=rank)
+
+
+@pytest.mark.parametrize("tp,rank", [(1, 0), (8, 7), (9, 8), (16, 11)])
+@pytest.mark.parametrize("q_len,flag", [(100, 0), (128, 1), (200, 0)])
+def test_bf16_sync_point_of_several_ranks_short_prompt(gpu, tp, rank, q_len, flag):
+    w = Workload(name=f"{tp}-ranks", hidden=512, n_q_heads=2 * tp, n_kv_heads=tp, head_dim=32, ffn=96 * tp, n_layers=1, tp=tp,
+                 dtype=BF16, seed=49, batch=1, q_len=1, ctx=64, mask=(flag,))
+    _one_rank_block(gpu, w, 1, q_len, [0], flag, rank=rank)
 
 
 # fp32 path at the edges of its small-product kernel (at most 64 rows and 1024 contraction elements, rotation inside it when the
