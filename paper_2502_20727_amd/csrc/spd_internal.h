@@ -25,8 +25,8 @@
 //
 // A weight matrix W [K, N] (y = x W) is cut into n-tiles of 16 output columns and k-tiles
 // of 32 inputs; fragment (nt, kt) sits at ((nt * KT) + kt) * 512 elements, row = column
-// n0(nt) + l % 16 of W, contraction element = input kt*32 + 8*(l/16) + j.  Row-major
-// activations [M, K] use the same scheme with m-tiles in place of n-tiles.
+// n0(nt) + l % 16 of W, contraction element = input kt*32 + 8*(l/16) + j.  Activations [M, K] are made
+// of the same fragments with m-tiles in place of n-tiles, in another order: spd_act_index().
 // ------------------------------------------------------------------------------------------
 
 constexpr int SPD_FRAG_ELEMS = 512;   // 16 x 32
@@ -39,6 +39,19 @@ constexpr int SPD_MID_KPART = 2304 * 8;   // ... and a call of more than 16 toke
 
 SPD_HD size_t spd_frag_index(int tile, int ktile, int n_ktiles) {
     return ((size_t)tile * (size_t)n_ktiles + (size_t)ktile) * SPD_FRAG_ELEMS;
+}
+// Packed activations: groups of 8 m-tiles (the last one as many as are left), and in a group all m-tiles of k-tile 0, then
+// all of k-tile 1, ...  What a workgroup multiplies with one weight fragment is then one piece of up to 8 KiB, and
+// what it reads over K is one stream.  With the k-tiles of an m-tile following each other instead the 8 or 16 fragments of a step were
+// KT KiB apart, for most contractions a multiple of 4 KiB, so that they all came from the same few of an L2's channels.
+constexpr int SPD_ACT_GROUP = 8;
+SPD_HD int spd_act_width(int mt, int n_mtiles) {       // m-tiles in the group of m-tile mt
+    const int rest = n_mtiles - (mt & ~(SPD_ACT_GROUP - 1));
+    return rest < SPD_ACT_GROUP ? rest : SPD_ACT_GROUP;
+}
+SPD_HD size_t spd_act_index(int mt, int ktile, int n_ktiles, int n_mtiles) {
+    const int g = mt & ~(SPD_ACT_GROUP - 1);
+    return ((size_t)g * (size_t)n_ktiles + (size_t)ktile * (size_t)spd_act_width(mt, n_mtiles) + (size_t)(mt - g)) * SPD_FRAG_ELEMS;
 }
 // element offset inside a fragment of (row r in 0..15, contraction index c in 0..31)
 SPD_HD int spd_frag_elem(int r, int c) { return ((r + 16 * (c >> 3)) << 3) + (c & 7); }

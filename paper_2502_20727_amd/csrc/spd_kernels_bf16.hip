@@ -215,7 +215,7 @@ __global__ void __launch_bounds__(256) k_prep(const float *__restrict__ base, co
                     xl[i] = act_one(p - act_back(x[i]));
                 }
             }
-            const size_t fo = spd_frag_index(mt, kt, KT) + lane * 8;
+            const size_t fo = spd_act_index(mt, kt, KT, (M + 15) >> 4) + lane * 8;
             *(bf16x8 *)(xhat + fo) = x;
             if (xlo) *(bf16x8 *)(xlo + fo) = xl;
         }
@@ -336,7 +336,7 @@ __global__ void __launch_bounds__(256) k_prep_rows(const float *__restrict__ bas
 #pragma unroll
     for (int f = 0; f < 2 * NP; ++f) {
         const int kt = 2 * NP * wave + f, r = lane & 15, g = lane >> 4;
-        const size_t fo = spd_frag_index(mt, chunk0 * 8 + kt, KT) + lane * 8;
+        const size_t fo = spd_act_index(mt, chunk0 * 8 + kt, KT, (M + 15) >> 4) + lane * 8;
         *(bf16x8 *)(xhat + fo) = *(const bf16x8 *)&tile[0][r][kt * 32 + g * 8];
         if (xlo) *(bf16x8 *)(xlo + fo) = *(const bf16x8 *)&tile[1][r][kt * 32 + g * 8];
     }
@@ -412,7 +412,7 @@ __global__ void __launch_bounds__(1024) k_prep_cu(const float *__restrict__ base
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
             // wave w writes k-tile w % 8 of plane w / 8: 1 KiB, lane = (row, group of 8 features)
             const int plane = wave >> 3, kt = wave & 7, r = lane & 15, g = lane >> 4;
-            const size_t fo = spd_frag_index(mt, chunk * 8 + kt, KT) + lane * 8;
+            const size_t fo = spd_act_index(mt, chunk * 8 + kt, KT, (M + 15) >> 4) + lane * 8;
             const bf16x8 f = *(const bf16x8 *)&tile[buf][plane][r][kt * 32 + g * 8];
             if (plane == 0) *(bf16x8 *)(xhat + fo) = f;
             else if (xlo) *(bf16x8 *)(xlo + fo) = f;
@@ -777,7 +777,7 @@ struct EpiOT {
         }
         const bf16x4 xa = cvt4h(pa[0], pa[1], pa[2], pa[3]), xb = cvt4h(pb[0], pb[1], pb[2], pb[3]);
         // the pair's 32 features are k-tile `pair` of the next contraction
-        const size_t fo = spd_frag_index(mt, pair, h >> 5);
+        const size_t fo = spd_act_index(mt, pair, h >> 5, (M + 15) >> 4);
         const int ea = spd_frag_elem(r, 4 * g), eb = spd_frag_elem(r, 16 + 4 * g);
         *(bf16x4 *)(xhat2 + fo + ea) = xa;
         *(bf16x4 *)(xhat2 + fo + eb) = xb;
@@ -829,7 +829,7 @@ struct EpiGU {
             for (int i = 0; i < 4; ++i) {
                 const int col = pair * cols + 4 * g + i;
                 if (4 * g + i < cols && col < f_pad) {
-                    const size_t fo = spd_frag_index(mt, col >> 5, f_pad >> 5) + spd_frag_elem(r, col & 31);
+                    const size_t fo = spd_act_index(mt, col >> 5, f_pad >> 5, (M + 15) >> 4) + spd_frag_elem(r, col & 31);
                     uhat[fo] = u[i];
                     if (ulo) ulo[fo] = lo[i];
                 }
@@ -837,7 +837,7 @@ struct EpiGU {
             return;
         }
         // gate/up pair p covers FFN columns [16p, 16p+16): half of k-tile p/2 of the down projection
-        const size_t fo = spd_frag_index(mt, pair >> 1, f_pad >> 5) + spd_frag_elem(r, 16 * (pair & 1) + 4 * g);
+        const size_t fo = spd_act_index(mt, pair >> 1, f_pad >> 5, (M + 15) >> 4) + spd_frag_elem(r, 16 * (pair & 1) + 4 * g);
         *(bf16x4 *)(uhat + fo) = u;
         if (ulo) *(bf16x4 *)(ulo + fo) = cvt4h_lo(o[0], o[1], o[2], o[3], u);
     }
@@ -917,7 +917,7 @@ struct EpiDownT {
             qb[0] = xb.x * p.gb.x; qb[1] = xb.y * p.gb.y; qb[2] = xb.z * p.gb.z; qb[3] = xb.w * p.gb.w;
         }
         const bf16x4 ha = cvt4h(qa[0], qa[1], qa[2], qa[3]), hb = cvt4h(qb[0], qb[1], qb[2], qb[3]);
-        const size_t fo = spd_frag_index(mt, pair, h >> 5);
+        const size_t fo = spd_act_index(mt, pair, h >> 5, (M + 15) >> 4);
         const int ea = spd_frag_elem(r, 4 * g), eb = spd_frag_elem(r, 16 + 4 * g);
         *(bf16x4 *)(xhat + fo + ea) = ha;
         *(bf16x4 *)(xhat + fo + eb) = hb;
@@ -1221,15 +1221,16 @@ __global__ void __launch_bounds__(256) k_gemv_finish(const float *__restrict__ k
 //   MODE 0: whole K (KS = 1), Epi::operator();  MODE 2: K slices, Epi::slice (linear epilogues)
 // ------------------------------------------------------------------------------------------
 template <int MT, bool SPLIT>
-struct SkinnyBatch {
+struct SkinnySet {
     bf16x8 fa, fb, fh[MT], fl[SPLIT ? MT : 1];
+    static constexpr int kRing = MT == 2 ? (SPLIT ? 3 : 4) : 2;
 };
 
 template <int W, int MT, bool SPLIT, int MODE, class Epi>
 __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp, const __bf16 *__restrict__ Xhi,
                                                     const __bf16 *__restrict__ Xlo, int KT, int KS, int n_mtiles, unsigned rot_step, Epi epi) {
     extern __shared__ __attribute__((aligned(16))) char sk_lds[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int pair = blockIdx.x, ks = blockIdx.y, mt0 = blockIdx.z * MT;
     const int kb0 = (int)(((long)ks * KT) / KS), kb1 = (int)(((long)(ks + 1) * KT) / KS);
     const int nk = kb1 - kb0;
@@ -1237,26 +1238,27 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
     f32x4 acc[MT][2];
 #pragma unroll
     for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const bf16x8 *wa = (const bf16x8 *)(Wp + spd_frag_index(2 * pair, 0, KT)) + lane;
-    const bf16x8 *wb = (const bf16x8 *)(Wp + spd_frag_index(2 * pair + 1, 0, KT)) + lane;
-    // m-tiles past the call's last one repeat it (their results are dropped)
-    const bf16x8 *xh[MT], *xl[MT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-        const int mt = mt0 + i < n_mtiles ? mt0 + i : n_mtiles - 1;
-        xh[i] = (const bf16x8 *)(Xhi + spd_frag_index(mt, 0, KT)) + lane;
-        xl[i] = (const bf16x8 *)(Xlo + spd_frag_index(mt, 0, KT)) + lane;
-    }
-    auto load = [&](SkinnyBatch<MT, SPLIT> &B, int kt) {
-        B.fa = __builtin_nontemporal_load(wa + (size_t)kt * 64);
-        B.fb = __builtin_nontemporal_load(wb + (size_t)kt * 64);
+    const char *wa = (const char *)(Wp + spd_frag_index(2 * pair, 0, KT)), *wb = (const char *)(Wp + spd_frag_index(2 * pair + 1, 0, KT));
+    // (MT divides a group's 8 m-tiles; m-tiles past the call's last one are zeros)
+    const char *xh = (const char *)(Xhi + spd_act_index(mt0, 0, KT, n_mtiles)), *xl = (const char *)(Xlo + spd_act_index(mt0, 0, KT, n_mtiles));
+    const unsigned xstr = 1024u * spd_act_width(mt0, n_mtiles), l16 = lane * 16;
+    const int n = k1 - k0;
+    // Each workgroup starts at its own k-tile (rot_step, see launch_skinny_mt()), so that an XCD's compute units don't all ask
+    // one L2 channel for the same activations.
+    const int rot = n > 0 ? (int)((unsigned)pair * rot_step % (unsigned)n) : 0;
+    auto load = [&](SkinnySet<MT, SPLIT> &B, int q) {
+        const unsigned wn = 1024, xn = xstr;
+        q += rot;
+        const size_t kt = k0 + (q >= n ? q - n : q);
+        B.fa = frag<true>(wa + kt * 1024, wn, l16);
+        B.fb = frag<true>(wb + kt * 1024, wn, l16);
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
-            B.fh[i] = xh[i][(size_t)kt * 64];
-            if (SPLIT) B.fl[i] = xl[i][(size_t)kt * 64];
+            B.fh[i] = frag<false>(xh + kt * xstr, xn, l16 + i * 1024);
+            if (SPLIT) B.fl[i] = frag<false>(xl + kt * xstr, xn, l16 + i * 1024);
         }
     };
-    auto consume = [&](const SkinnyBatch<MT, SPLIT> &B) {
+    auto consume = [&](const SkinnySet<MT, SPLIT> &B) {
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
             acc[i][0] = MFMA16(B.fa, B.fh[i], acc[i][0]);
@@ -1267,39 +1269,28 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
             }
         }
     };
-    const int n = k1 - k0;
-    // Each workgroup starts at its own k-tile (rot_step, see launch_skinny_mt()), so that an XCD's compute units don't all ask
-    // one L2 channel for the same activations.
-    const int rot = n > 0 ? (int)((unsigned)pair * rot_step % (unsigned)n) : 0;
-    auto at = [&](int q) {
-        q += rot;
-        return k0 + (q >= n ? q - n : q);
-    };
-    SkinnyBatch<MT, SPLIT> cur, oth;
-    if (n > 0) load(cur, at(0));
     // the norm statistics by all threads while the first weights are on their way: at the end, a wave per m-tile, they were
     // eight dependent rounds of loads for 256 partials per token
     __shared__ float early_ss[Epi::kNeedsRs ? W * 64 : 1];
     constexpr int RS_PARTS = W * 4 / MT;               // threads per token
-    if constexpr (Epi::kNeedsRs) {
-        int m = mt0 * 16 + (int)threadIdx.x % (MT * 16);
-        m = m < n_mtiles * 16 ? m : n_mtiles * 16 - 1;
-        early_ss[threadIdx.x] = sum_ss(epi.ss, epi.nch, epi.m_pad, m, (int)threadIdx.x / (MT * 16), RS_PARTS);
-    }
-    int i = 0;
-    for (; i + 2 < n; i += 2) {          // steady state: no branch between the loads and their use
-        load(oth, at(i + 1));
-        consume(cur);
-        load(cur, at(i + 2));
-        consume(oth);
-    }
-    if (i + 1 < n) {
-        load(oth, at(i + 1));
-        consume(cur);
-        consume(oth);
-    } else if (i < n) {
-        consume(cur);
-    }
+    // wave w finishes m-tile w: what its epilogue reads is requested now
+    static_assert(MT <= W, "a wave per m-tile");
+    const bool fin = wave < MT && mt0 + wave < n_mtiles;
+    typename Epi::Pre pre;
+    constexpr bool EARLY = Epi::kSync && !(SPLIT && MT == 8);      // (the registers for 8 m-tiles of pairs are all taken)
+    SyncRegs peers;
+    stream_tiles<SkinnySet<MT, SPLIT>::kRing, SkinnySet<MT, SPLIT>>(n, load, consume, [&]() {
+        if (fin) pre = epi.pre(pair, mt0 + wave, lane);
+        if constexpr (EARLY) {
+            const SyncSum sy = epi.sync();
+            if (fin) sy.load(peers, sy.at(pair, mt0 + wave, lane));
+        }
+        if constexpr (Epi::kNeedsRs) {
+            int m = mt0 * 16 + (int)threadIdx.x % (MT * 16);
+            m = m < n_mtiles * 16 ? m : n_mtiles * 16 - 1;
+            early_ss[threadIdx.x] = sum_ss(epi.ss, epi.nch, epi.m_pad, m, (int)threadIdx.x / (MT * 16), RS_PARTS);
+        }
+    });
     f32x4 *red = (f32x4 *)sk_lds;        // [W][MT][2][64]
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
@@ -1307,25 +1298,24 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
         red[((wave * MT + t) * 2 + 1) * 64 + lane] = acc[t][1];
     }
     __syncthreads();
-    for (int t = wave; t < MT; t += W) {
-        const int mt = mt0 + t;
-        if (mt >= n_mtiles) break;
-        f32x4 a = red[((0 * MT + t) * 2 + 0) * 64 + lane], b = red[((0 * MT + t) * 2 + 1) * 64 + lane];
+    if (!fin) return;
+    const int t = wave, mt = mt0 + t;
+    f32x4 a = red[((0 * MT + t) * 2 + 0) * 64 + lane], b = red[((0 * MT + t) * 2 + 1) * 64 + lane];
 #pragma unroll
-        for (int w = 1; w < W; ++w) {
-            a += red[((w * MT + t) * 2 + 0) * 64 + lane];
-            b += red[((w * MT + t) * 2 + 1) * 64 + lane];
-        }
-        float rs = 1.f;
-        if constexpr (Epi::kNeedsRs) {
-            float q = 0.f;
-#pragma unroll
-            for (int part = 0; part < RS_PARTS; ++part) q += early_ss[part * MT * 16 + t * 16 + (lane & 15)];
-            rs = 1.0f / sqrtf(q / (float)epi.h + epi.eps);
-        }
-        if constexpr (MODE == 2) epi.slice(pair, ks, mt, a, b, lane, rs, epi.pre(pair, mt, lane));
-        else epi(pair, mt, a, b, lane, rs, epi.pre(pair, mt, lane));
+    for (int w = 1; w < W; ++w) {
+        a += red[((w * MT + t) * 2 + 0) * 64 + lane];
+        b += red[((w * MT + t) * 2 + 1) * 64 + lane];
     }
+    float rs = 1.f;
+    if constexpr (Epi::kNeedsRs) {
+        float q = 0.f;
+#pragma unroll
+        for (int part = 0; part < RS_PARTS; ++part) q += early_ss[part * MT * 16 + t * 16 + (lane & 15)];
+        rs = 1.0f / sqrtf(q / (float)epi.h + epi.eps);
+    }
+    if constexpr (MODE == 2) epi.slice(pair, ks, mt, a, b, lane, rs, pre);
+    else if constexpr (EARLY) epi(pair, mt, a, b, lane, rs, pre, peers);
+    else epi(pair, mt, a, b, lane, rs, pre);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1376,7 +1366,7 @@ __global__ void __launch_bounds__(MID_PAIRS * 64) k_mid(const __bf16 *__restrict
 #pragma unroll
     for (int i = 0; i < XPW; ++i) {
         const int mt = ((wave * XPW + i) % NFRAG) / MID_KB;
-        xoff[i] = spd_frag_index(mt < n_mtiles ? mt : n_mtiles - 1, 0, KT) + (size_t)lane * 8;
+        xoff[i] = spd_act_index(mt < n_mtiles ? mt : n_mtiles - 1, 0, KT, n_mtiles) + (size_t)lane * 8;
     }
     f32x4 acc[MT][2];
 #pragma unroll
@@ -1387,7 +1377,7 @@ __global__ void __launch_bounds__(MID_PAIRS * 64) k_mid(const __bf16 *__restrict
 #pragma unroll
         for (int i = 0; i < XPW; ++i) {
             const int kt = kt0 + ((wave * XPW + i) % NFRAG) % MID_KB;
-            const size_t o = xoff[i] + (size_t)(kt < KT ? kt : KT - 1) * 512;
+            const size_t o = xoff[i] + (size_t)(kt < KT ? kt : KT - 1) * n_mtiles * SPD_FRAG_ELEMS;      // (one group)
             S.x[i] = *(const bf16x8 *)(Xp + o);
         }
 #pragma unroll
@@ -1612,10 +1602,13 @@ __global__ void __launch_bounds__(G::WN *G::WM * 64, 1)
     const int l16 = lane * 16;
     const unsigned pitch = (unsigned)KT * 1024;  // bytes between two tiles of a panel
     const int n_rows = n_ntiles - nt0 < BN ? n_ntiles - nt0 : BN, m_rows = n_mtiles - mt0 < BM ? n_mtiles - mt0 : BM;
+    // (the activations' panels begin and end with a group of m-tiles)
+    const int mg0 = mt0 & ~(SPD_ACT_GROUP - 1), mlast = mt0 + m_rows - 1,
+              mg_rows = (mlast & ~(SPD_ACT_GROUP - 1)) + spd_act_width(mlast, n_mtiles) - mg0;
     const __amdgpu_buffer_rsrc_t wbuf = panel((const char *)Wp + (size_t)nt0 * pitch, n_rows * pitch),
-                                 xbuf = panel((const char *)Xp + (size_t)mt0 * pitch, m_rows * pitch),
-                                 lbuf = panel((const char *)(XS ? Xlo : Xp) + (size_t)mt0 * pitch, m_rows * pitch);
-    unsigned wsrc[CW], xsrc[CX];                 // (wave-uniform)
+                                 xbuf = panel((const char *)Xp + (size_t)mg0 * pitch, mg_rows * pitch),
+                                 lbuf = panel((const char *)(XS ? Xlo : Xp) + (size_t)mg0 * pitch, mg_rows * pitch);
+    unsigned wsrc[CW], xsrc[CX], xstr[CX];       // (wave-uniform)
     int wdst[CW];
 #pragma unroll
     for (int n = 0; n < CW; ++n) {
@@ -1628,7 +1621,9 @@ __global__ void __launch_bounds__(G::WN *G::WM * 64, 1)
 #pragma unroll
     for (int n = 0; n < CX; ++n) {
         const int t = (wave * CX + n) >> 1;
-        xsrc[n] = (unsigned)(t < m_rows ? t : m_rows - 1) * pitch + kt_first * 1024;
+        const int mt = mt0 + (t < m_rows ? t : m_rows - 1), mg = mt & ~(SPD_ACT_GROUP - 1);
+        xstr[n] = (unsigned)spd_act_width(mt, n_mtiles) * 1024;
+        xsrc[n] = (unsigned)(mg - mg0) * pitch + (unsigned)(mt - mg) * 1024 + kt_first * xstr[n];
     }
     // Where the registers allow, the lo plane's products are summed on their own: half as many roundings of the large sums.
     constexpr bool LO_ACC = XS && TI * TJ <= 16;
@@ -1653,7 +1648,7 @@ __global__ void __launch_bounds__(G::WN *G::WM * 64, 1)
             kt = kt < nk ? kt : nk - 1;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(XS && (c & 1) ? lbuf : xbuf,
                                                      (__attribute__((address_space(3))) void *)(lds + slot * STAGE + W_BYTES + c * 1024),
-                                                     16, l16, (int)(xsrc[n - CW] + kt * 1024), 0, 0);
+                                                     16, l16, (int)(xsrc[n - CW] + kt * xstr[n - CW]), 0, 0);
         }
     };
     const char *a_base = lds + wn * TI * KW * 1024 + l16, *b_base = lds + W_BYTES + wm * TJ * 2048 + l16;
@@ -2210,7 +2205,7 @@ __global__ void __launch_bounds__(256) k_attn_combine(const float *__restrict__ 
     }
     const float val = num / den;
     const int kidx = (kvh * group + c) * d + dd;
-    const size_t o = spd_frag_index(b >> 4, kidx >> 5, qd >> 5) + spd_frag_elem(b & 15, kidx & 31);
+    const size_t o = spd_act_index(b >> 4, kidx >> 5, qd >> 5, ((int)gridDim.y + 15) >> 4) + spd_frag_elem(b & 15, kidx & 31);
     const __bf16 hi = act_one(val);
     ahat[o] = hi;
     if (alo) alo[o] = act_one(val - act_back(hi));
@@ -2316,7 +2311,7 @@ __global__ void __launch_bounds__(256) k_attn_prefill(const __bf16 *__restrict__
         const int kidx = hd[c] * d + dt * 16 + 4 * g;
         const float o0 = num[0] * inv, o1 = num[1] * inv, o2 = num[2] * inv, o3 = num[3] * inv;
         const bf16x4 v = cvt4h(o0, o1, o2, o3);
-        const size_t o = spd_frag_index(mt, kidx >> 5, qd >> 5) + spd_frag_elem(r, kidx & 31);
+        const size_t o = spd_act_index(mt, kidx >> 5, qd >> 5, ((int)gridDim.z * q_len + 15) >> 4) + spd_frag_elem(r, kidx & 31);
         *(bf16x4 *)(ahat + o) = v;
         if (alo) *(bf16x4 *)(alo + o) = cvt4h_lo(o0, o1, o2, o3, v);
     }
@@ -2330,7 +2325,7 @@ __global__ void k_unpack_act(const __bf16 *__restrict__ src, const __bf16 *__res
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (int64_t)M * K_out) return;
     const int m = (int)(i / K_out), k = (int)(i % K_out);
-    const size_t o = spd_frag_index(m >> 4, k >> 5, K_packed >> 5) + spd_frag_elem(m & 15, k & 31);
+    const size_t o = spd_act_index(m >> 4, k >> 5, K_packed >> 5, (M + 15) >> 4) + spd_frag_elem(m & 15, k & 31);
     dst[i] = act_back(src[o]) + (lo ? act_back(lo[o]) : 0.f);
 }
 __global__ void k_bf16_to_f32(const __bf16 *__restrict__ src, const __bf16 *__restrict__ lo, float *__restrict__ dst,
