@@ -137,6 +137,31 @@ int block_core(const spd_ctx *ctx, spd_call &c, int spd, int32_t rank, const cha
     return SPD_OK;
 }
 
+// fp32 path, small calls: n_layers blocks with all ranks of the call in each launch, and every sum over the ranks but the last one in
+// the launch that reads it.  Returns through *done whether the call is of that kind.
+// The residual stream moves between rbuf and x_out: a sum is written where no workgroup of its launch reads.
+int f32_ranks_side_by_side(const spd_call &c, const uint8_t *mask, int n_layers, int32_t rank, const void *const *layer_weights,
+                           void *const *layer_kv, const float *x_in, float *slots, float *x_out, bool *done) {
+    const spd_dims &D = *c.D;
+    const bool all = rank == SPD_ALL_RANKS;
+    const int n = all ? D.tp : 1;
+    *done = D.dtype == SPD_F32 && !c.taps && !c.timer && c.stages == SPD_ALL_STAGES && spd_f32::ranks_fit(c, n);
+    if (!*done) return SPD_OK;
+    float *rbuf = (float *)(c.ws + D.ws_r);
+    const float *cur = x_in;                  // the stream's present place (x_in may be x_out)
+    auto next = [&]() { return cur == rbuf ? x_out : rbuf; };
+    spd_f32::spd_sum x = {x_in, nullptr, 0, nullptr, nullptr};
+    for (int l = 0; l < n_layers; ++l) {
+        const char *w = (const char *)layer_weights[l];
+        if (x.n) cur = x.out = next();
+        SPD_HIP(spd_f32::block_ranks(c, w, (char *)layer_kv[l], n, mask[l], slots + (all ? 0 : (size_t)rank * c.slot_stride), slots, &x, next(),
+                                     D.o_bias ? (const float *)(w + D.w_bo) : nullptr));
+        cur = x.base;
+    }
+    SPD_HIP(spd_common::rank_sum(x.base, slots, D.tp, (int64_t)c.slot_stride, x_out, c.s, x.bias, D.h));
+    return SPD_OK;
+}
+
 // The helper stream of the two-chain model forward and the events that fork to it and join from it: one
 // set per device, created on first use with that device current (default priority, non-blocking), never
 // destroyed.
@@ -190,6 +215,12 @@ int block_forward_impl(const spd_ctx *ctx, int32_t layer, int32_t spd_flag, int3
     if (D.dtype == SPD_BF16) {
         SPD_HIP(spd_bf16::prep(c, x_in, nullptr, 0, nullptr, (const float *)(w + D.w_g1), true, 0));
         c.nch1 = spd_bf16::prep_chunks(c);
+    }
+    {
+        const uint8_t mask = (uint8_t)spd_flag;
+        bool done = false;
+        const int rc1 = f32_ranks_side_by_side(c, &mask, 1, rank, &packed_weights, &kv_cache, x_in, slots, x_out, &done);
+        if (rc1 != SPD_OK || done) return rc1;
     }
     const float *base = nullptr, *bias = nullptr;
     int64_t syncs = 0;
@@ -260,6 +291,17 @@ int spd_model_forward_staged(const spd_ctx *ctx, const uint8_t *spd_mask, int32_
     clear_stale_hip_error();
     const bool bf = D.dtype == SPD_BF16;
     int64_t syncs = 0;
+
+    if (!layer_out) {
+        bool done = false;
+        const int rc1 = f32_ranks_side_by_side(c, spd_mask, L, rank, layer_weights, layer_kv, x_in, slots, x_out, &done);
+        if (rc1 != SPD_OK) return rc1;
+        if (done) {
+            for (int l = 0; l < L; ++l) syncs += spd_mask[l] ? 1 : 2;
+            if (n_rank_sums) *n_rank_sums = syncs;
+            return SPD_OK;
+        }
+    }
 
     // One chain of launches per half of the sequences, or a single chain for the whole call.  A prefill is
     // independent from sequence to sequence all the way through the model, and a chain alternates between

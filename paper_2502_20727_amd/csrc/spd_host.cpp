@@ -170,6 +170,17 @@ void compute_dims(const spd_config &c, spd_dims &D) {
         D.ws_ahat = o; o = spd_align256(o + M * qd * 4);
         D.ws_gu = o; o = spd_align256(o + M * 2 * f * 4);
         D.ws_uhat = o; o = spd_align256(o + M * f * 4);
+        // Small calls run the ranks they emulate side by side, each with buffers of its own.  Left out where they would be large, or
+        // take a workspace beyond what spd_block_forward_static() accepts: the ranks then run one after the other.
+        const size_t rows = std::min<size_t>(M, 64);
+        const size_t a = spd_align256(D.tp * rows * (size_t)D.nqkv * 4), b = spd_align256(D.tp * rows * qd * 4), g = spd_align256(D.tp * rows * f * 4);
+        const bool keeps = o > (size_t)SPD_STATIC_WORKSPACE_BYTES || o + a + b + g <= (size_t)SPD_STATIC_WORKSPACE_BYTES;
+        if (D.tp > 1 && D.tp <= 1024 && a + b + g <= ((size_t)16 << 20) && keeps) {
+            D.rk_ranks = D.tp;
+            D.rk_rows = (int)rows;
+            D.ws_rk_qkv = o; D.ws_rk_ahat = o + a; D.ws_rk_uhat = o + a + b;
+            o += a + b + g;
+        }
     }
     D.ws_single = o;
     D.ws_dual = bf && c.max_batch >= 2 && c.max_tokens / 2 >= SPD_DUAL_MIN_TOKENS;

@@ -169,6 +169,9 @@ struct spd_dims {
     // workspace (bytes)
     size_t ws_cos, ws_sin, ws_xhat, ws_xhat2, ws_q, ws_ahat, ws_y, ws_r, ws_ss1, ws_ss2, ws_uhat,
         ws_apart, ws_kpart, ws_qkv, ws_gu, workspace_bytes;
+    // fp32 path: buffers of all ranks of a call that emulates them side by side, rk_ranks (0: none) of rk_rows tokens each
+    int rk_ranks, rk_rows;
+    size_t ws_rk_qkv, ws_rk_ahat, ws_rk_uhat;
     // a context for long prefills of several sequences lays out two such workspaces back to back (ws_single bytes
     // each), one per chain of the two-chain model forward
     int ws_dual;
@@ -250,6 +253,17 @@ hipError_t copy2d(const float *src, int lds, float *dst, int ldd, int rows, int 
 }
 
 namespace spd_f32 {
+// small calls, several ranks side by side: the block's input as the sum at the sync point before it, base + (slot_0 + ...) [+ bias] -> out,
+// or, with n = 0, base itself
+struct spd_sum {
+    const float *base, *slots;
+    int n;
+    const float *bias;
+    float *out;
+};
+bool ranks_fit(const spd_call &c, int n_ranks);
+hipError_t block_ranks(const spd_call &c, const char *w, char *kvc, int n_ranks, int spd, float *slot0, const float *slots, spd_sum *x, float *R,
+                       const float *bo);
 // attention half of a rank's share: X -> Y_r (into ybuf or the slot), fp32 path; r_out (may be NULL) <- X + Y_r [+ bias]
 hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const float *x, float *y_out, float *r_out, const float *bias);
 // MLP half: r_in -> Z_r, out[m][n] = (add ? add[m][n] : 0) + Z_r

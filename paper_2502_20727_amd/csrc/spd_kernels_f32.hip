@@ -134,125 +134,202 @@ __global__ void k_rope_append(float *__restrict__ qkv, float *__restrict__ kc, f
 }
 
 // Small products (at most ROWS_MAX_M rows, ROWS_MAX_K contraction elements): bound by latency, not by work, so a kernel does
-// as much as it can between two launches.  A workgroup of 16 waves owns 8 rows of A and 64 columns of W: it loads
+// as much as it can between two launches.  A workgroup of 16 waves owns 1 to 8 rows of A and 64 columns of W: it loads
 // its rows once (optionally applying the RMS norm: the whole row is there), wave w contracts the w-th sixteenth of K
 // with lane = column, the waves' sums meet in LDS in wave order and an epilogue finishes the tile.  Toy model (hidden
-// 256), one rank and layer, us for 1 / 32 tokens: norm + QKV + rotation 27 / 35 -> 7 / 8 (three launches before), O + fold 21-27 / 38 -> 5,
-// norm + gate + up + SwiGLU 47 / 60 -> 9 / 11 (four launches before), down 23 / 33 -> 7 / 8.
-constexpr int RW = 16, RM = 8, RN = 64;
+// 256, two ranks side by side), us for 1 / 32 tokens: norm + QKV + rotation 5.2 / 5.9, O 3.9 / 4.2, fold + norm + gate + up + SwiGLU 5.0 / 6.0,
+// down 4.8 / 5.3 (an almost empty launch 1.5; 8 rows per workgroup at any size, a row's elements apart in the LDS and the weights of K = 344
+// in two goes 7.3, 4.8, 8.6, 7.4 for one token and rank).
+constexpr int RW = 16, RN = 64;
 constexpr int ROWS_MAX_M = 64, ROWS_MAX_K = 1024;
 // Every group of 8 rows reads the weights again, so a very wide product is left to the 32 x 32 tiles.  hidden 1024, two layers,
 // us, tiles / rows by workgroups of the gate/up launch: 64 rows 1024 2119 / 1752, 2048 3605 / 3323, 4096 8422 / 8457, 8192 16821 / 17845;
 // 32 rows 2048 8537 / 8280, 3072 12412 / 12626; hidden 256: 64 rows 2048 3157 / 3108, 4096 6358 / 6394
 constexpr int ROWS_MAX_WGS = 2048;
 
+// What the rows of a product are made of: a[m][k], or a sum over ranks on top of it, a + (slot_0 + slot_1 + ...) [+ bias], which the first
+// column block of the first rank leaves in `out` (no workgroup of the launch reads `out`).  So a sync point, and the SPD block's
+// local fold X + Y_r [+ b] (one slot, the rank's own), need no launch of their own.  grid.z is the rank: all ranks a call
+// emulates run side by side, `*_rank` being the distances between their buffers.
+struct RowsIn {
+    const float *a;
+    int lda;
+    size_t a_rank;
+    const float *gain;           // RMS norm of the row with this gain, or NULL
+    float eps;
+    size_t w_rank;               // distance between two ranks' weights (gain included)
+    const float *slots = nullptr;
+    size_t slot_stride = 0, slot_rank = 0;
+    int n_slots = 0;
+    const float *bias = nullptr;
+    float *out = nullptr;
+};
+
+// Epilogues: one thread per element.  What does not depend on the product is requested ahead of it, by where() before the weights and by
+// pre() (what needs where()'s result) behind them.
 struct RowsQKV {       // queries and keys rotated, keys and values appended to the cache; needs whole heads per tile (64 % d == 0)
     static constexpr bool kDual = false;
     float *qkv, *kc, *vc;
+    size_t qkv_rank, kv_rank;
     const float *cosT, *sinT;
     int q_len, q, kv, d, nqkv, max_ctx;
     spd_positions P;
-    __device__ __forceinline__ void operator()(const float *tile, const float *, int r, int cl, int m, int n) const {
+    struct Pre { float c, s; int b, pos; };
+    __device__ __forceinline__ int where(int m) const { return P.pos[m / q_len]; }
+    __device__ __forceinline__ Pre pre(int first, int, int m, int n) const {
+        const int half = d >> 1, j = n % d, jj = j < half ? j : j - half;
+        Pre p;
+        p.b = m / q_len;
+        p.pos = first + (m % q_len);
+        p.c = cosT[(size_t)p.pos * half + jj];
+        p.s = sinT[(size_t)p.pos * half + jj];
+        return p;
+    }
+    __device__ __forceinline__ void operator()(const float *tile, const float *, int r, int cl, int m, int n, int z, const Pre &p) const {
         const int half = d >> 1, head = n / d, j = n % d;
-        const int b = m / q_len, pos = P.pos[b] + (m % q_len);
         float v = tile[r * RN + cl];
         if (head < q + kv) {
-            const int jj = j < half ? j : j - half;
-            const float c = cosT[(size_t)pos * half + jj], sn = sinT[(size_t)pos * half + jj];
             const float o = tile[r * RN + (j < half ? cl + half : cl - half)];
-            v = j < half ? v * c - o * sn : v * c + o * sn;
+            v = j < half ? v * p.c - o * p.s : v * p.c + o * p.s;
         }
         if (head < q) {
-            qkv[(size_t)m * nqkv + n] = v;
+            qkv[z * qkv_rank + (size_t)m * nqkv + n] = v;
         } else {
             const int kh = head < q + kv ? head - q : head - q - kv;
-            (head < q + kv ? kc : vc)[(((size_t)b * kv + kh) * max_ctx + pos) * d + j] = v;
+            (head < q + kv ? kc : vc)[z * kv_rank + (((size_t)p.b * kv + kh) * max_ctx + p.pos) * d + j] = v;
         }
     }
 };
 struct RowsO {         // y = the partial product; r_out (optional) = x + y [+ bias], the SPD block's local fold
     static constexpr bool kDual = false;
     float *y, *r_out;
+    size_t y_rank;
     const float *x, *bias;
     int ld;
-    __device__ __forceinline__ void operator()(const float *tile, const float *, int r, int cl, int m, int n) const {
+    struct Pre { float x, b; };
+    __device__ __forceinline__ int where(int) const { return 0; }
+    __device__ __forceinline__ Pre pre(int, int, int m, int n) const {
+        return Pre{r_out ? x[(size_t)m * ld + n] : 0.f, r_out && bias ? bias[n] : 0.f};
+    }
+    __device__ __forceinline__ void operator()(const float *tile, const float *, int r, int cl, int m, int n, int z, const Pre &p) const {
         const size_t o = (size_t)m * ld + n;
         const float v = tile[r * RN + cl];
-        y[o] = v;
-        if (r_out) r_out[o] = bias ? (x[o] + v) + bias[n] : x[o] + v;
+        y[z * y_rank + o] = v;
+        if (r_out) r_out[o] = bias ? (p.x + v) + p.b : p.x + v;
     }
 };
 struct RowsGU {        // silu(gate) * up
     static constexpr bool kDual = true;
     float *u;
+    size_t u_rank;
     int ld;
-    __device__ __forceinline__ void operator()(const float *tile, const float *tile2, int r, int cl, int m, int n) const {
+    struct Pre {};
+    __device__ __forceinline__ int where(int) const { return 0; }
+    __device__ __forceinline__ Pre pre(int, int, int, int) const { return Pre(); }
+    __device__ __forceinline__ void operator()(const float *tile, const float *tile2, int r, int cl, int m, int n, int z, const Pre &) const {
         const float x = tile[r * RN + cl];
-        u[(size_t)m * ld + n] = x / (1.0f + expf(-x)) * tile2[r * RN + cl];
+        u[z * u_rank + (size_t)m * ld + n] = x / (1.0f + expf(-x)) * tile2[r * RN + cl];
     }
 };
-struct RowsDown {      // out = [add +] z
+struct RowsDown {      // out = [add +] z  (add may be out itself)
     static constexpr bool kDual = false;
     float *out;
     const float *add;
+    size_t out_rank;   // also the distance between two ranks' `add`
     int ld;
-    __device__ __forceinline__ void operator()(const float *tile, const float *, int r, int cl, int m, int n) const {
-        const size_t o = (size_t)m * ld + n;
+    struct Pre { float a; };
+    __device__ __forceinline__ int where(int) const { return 0; }
+    __device__ __forceinline__ Pre pre(int, int z, int m, int n) const { return Pre{add ? add[z * out_rank + (size_t)m * ld + n] : 0.f}; }
+    __device__ __forceinline__ void operator()(const float *tile, const float *, int r, int cl, int m, int n, int z, const Pre &p) const {
         const float v = tile[r * RN + cl];
-        out[o] = add ? add[o] + v : v;
+        out[z * out_rank + (size_t)m * ld + n] = add ? p.a + v : v;
     }
 };
 
-template <class Epi>
-__global__ void __launch_bounds__(RW * 64) k_rows(const float *__restrict__ A, int lda, const float *__restrict__ gain, float eps,
-                                                  const float *__restrict__ W, const float *__restrict__ W2, int ldw, int M, int N,
+template <int RM>
+struct alignas(RM * 4 < 16 ? RM * 4 : 16) RowsOf { float v[RM]; };
+
+template <int RM, int KMAX, class Epi>      // RM rows of at most KMAX elements per workgroup
+__global__ void __launch_bounds__(RW * 64) k_rows(RowsIn in, const float *__restrict__ W, const float *__restrict__ W2, int ldw, int M, int N,
                                                   int K, Epi epi) {
     constexpr int NB = Epi::kDual ? 2 : 1;
-    extern __shared__ float rows_lds[];                 // rows [RM][K], then the waves' sums [NB][RW][RM][RN]
-    __shared__ float ssq[RM][2];
+    constexpr int P = RW / RM;                          // waves that load a row together
+    constexpr int V = KMAX / P > 64 ? KMAX / P / 64 : 1;      // pieces of 64 elements of a wave's part of a row
+    constexpr int U = KMAX / RW < 32 ? KMAX / RW : 32;  // weight rows that a wave requests at once
+    // rows, transposed: [K][RM], so that what a wave multiplies with one weight is side by side; then the waves' sums
+    // [NB][RW][RM][RN]
+    extern __shared__ __attribute__((aligned(16))) float rows_lds[];
+    __shared__ float ssq[RM][P];
     __shared__ float tile[NB][RM * RN];
     float *xs = rows_lds, *red = rows_lds + RM * K;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n0 = blockIdx.x * RN, m0 = blockIdx.y * RM;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n0 = blockIdx.x * RN, m0 = blockIdx.y * RM, z = blockIdx.z;
     const int n = n0 + lane < N ? n0 + lane : N - 1;    // (columns past the matrix repeat its last one and are dropped)
-    // this wave's share of the weights does not depend on the rows: the first of them are requested ahead of everything
+    // Everything a workgroup reads is requested up front: a launch of this kind is its start and one trip to the memory.
+    // rows: wave w takes part w % P of row w / P (past its end the last element again, not used)
+    const int row = wave / P, hk = (K + P - 1) / P, rb = (wave % P) * hk, re = rb + hk < K ? rb + hk : K;
+    const bool valid = m0 + row < M;
+    float v[V], gn[V], bs[V], sl[V];
+    size_t ro[V];
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+        const int k = rb + t * 64 + lane;
+        ro[t] = k < re ? k : K - 1;
+        gn[t] = in.gain ? in.gain[z * in.w_rank + ro[t]] : 1.f;
+        bs[t] = in.bias ? in.bias[ro[t]] : 0.f;
+        ro[t] += (size_t)(valid ? m0 + row : 0) * in.lda;
+        v[t] = in.a[z * in.a_rank + ro[t]];
+    }
+    const float *slots = in.slots + z * in.slot_rank;
+#pragma unroll
+    for (int t = 0; t < V; ++t) sl[t] = in.n_slots > 0 ? slots[ro[t]] : 0.f;
+    const int er = (threadIdx.x / RN) % RM, em = m0 + er, en = n0 + (int)threadIdx.x % RN;
+    const bool elem = threadIdx.x < RM * RN && em < M && en < N;
+    const int first = epi.where(em < M ? em : M - 1);
     const int k0 = (wave * K) / RW, k1 = ((wave + 1) * K) / RW, klast = k1 > k0 ? k1 - 1 : k0;
-    constexpr int U = 16;
     float w0[U], w1[NB == 2 ? U : 1];
     auto load = [&](int kb) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int k = kb + u < klast ? kb + u : klast;
-            w0[u] = W[(size_t)k * ldw + n];
-            if constexpr (NB == 2) w1[u] = W2[(size_t)k * ldw + n];
+            w0[u] = W[z * in.w_rank + (size_t)k * ldw + n];
+            if constexpr (NB == 2) w1[u] = W2[z * in.w_rank + (size_t)k * ldw + n];
         }
     };
     load(k0);
-    {   // rows: wave w takes half w % 2 of row w / 2
-        const int r = wave >> 1, hk = (K + 1) / 2, kb = (wave & 1) * hk, ke = kb + hk < K ? kb + hk : K;
-        const bool valid = m0 + r < M;
-        const float *src = A + (size_t)(valid ? m0 + r : 0) * lda;
-        constexpr int V = (ROWS_MAX_K / 2 + 63) / 64;
-        float v[V], sq = 0.f;
+    typename Epi::Pre pre;
+    {
+        // the slots in ascending order, then what they join, then the bias
+        for (int s = 1; s < in.n_slots; ++s) {
+#pragma unroll
+            for (int t = 0; t < V; ++t) sl[t] += slots[s * in.slot_stride + ro[t]];
+        }
+        float sq = 0.f;
 #pragma unroll
         for (int t = 0; t < V; ++t) {
-            const int k = kb + t * 64 + lane;
-            v[t] = valid && k < ke ? src[k] : 0.f;
+            const int k = rb + t * 64 + lane;
+            if (in.n_slots > 0) v[t] += sl[t];
+            if (in.bias) v[t] += bs[t];
+            if (in.out && blockIdx.x == 0 && z == 0 && valid && k < re) in.out[ro[t]] = v[t];
+            if (!valid || k >= re) v[t] = 0.f;
+            sq += v[t] * v[t];
         }
+        if (elem) pre = epi.pre(first, z, em, en);
         float rs = 1.f;
-        if (gain) {
-#pragma unroll
-            for (int t = 0; t < V; ++t) sq += v[t] * v[t];
+        if (in.gain) {
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
-            if (lane == 0) ssq[r][wave & 1] = sq;
+            if (lane == 0) ssq[row][wave % P] = sq;
             __syncthreads();
-            rs = 1.0f / sqrtf((ssq[r][0] + ssq[r][1]) / (float)K + eps);
+            sq = ssq[row][0];
+#pragma unroll
+            for (int i = 1; i < P; ++i) sq += ssq[row][i];
+            rs = 1.0f / sqrtf(sq / (float)K + in.eps);
         }
 #pragma unroll
         for (int t = 0; t < V; ++t) {
-            const int k = kb + t * 64 + lane;
-            if (k < ke) xs[r * K + k] = gain ? v[t] * rs * gain[k] : v[t];
+            const int k = rb + t * 64 + lane;
+            if (k < re) xs[k * RM + row] = in.gain ? v[t] * rs * gn[t] : v[t];
         }
     }
     __syncthreads();
@@ -263,15 +340,24 @@ __global__ void __launch_bounds__(RW * 64) k_rows(const float *__restrict__ A, i
         for (int r = 0; r < RM; ++r) acc[b][r] = 0.f;
     for (int kb = k0; kb < k1; kb += U) {
         if (kb > k0) load(kb);
+        auto use = [&](int u) {
+            const RowsOf<RM> x = *(const RowsOf<RM> *)&xs[(kb + u) * RM];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (kb + u < k1) {                          // (uniform)
+            for (int r = 0; r < RM; ++r) {
+                acc[0][r] += x.v[r] * w0[u];
+                if constexpr (NB == 2) acc[1][r] += x.v[r] * w1[u];
+            }
+        };
+        // (uniform branches, four rows' reads from the LDS between two of them)
 #pragma unroll
-                for (int r = 0; r < RM; ++r) {
-                    const float x = xs[r * K + kb + u];
-                    acc[0][r] += x * w0[u];
-                    if constexpr (NB == 2) acc[1][r] += x * w1[u];
-                }
+        for (int u0 = 0; u0 < U; u0 += 4) {
+            if (kb + u0 + 4 <= k1) {
+#pragma unroll
+                for (int u = u0; u < u0 + 4; ++u) use(u);
+            } else {
+#pragma unroll
+                for (int u = u0; u < u0 + 3; ++u)
+                    if (kb + u < k1) use(u);
             }
         }
     }
@@ -280,7 +366,7 @@ __global__ void __launch_bounds__(RW * 64) k_rows(const float *__restrict__ A, i
 #pragma unroll
         for (int r = 0; r < RM; ++r) red[((b * RW + wave) * RM + r) * RN + lane] = acc[b][r];
     __syncthreads();
-    if (threadIdx.x < NB * RM * RN) {
+    if (threadIdx.x < NB * RM * RN) {                   // (at most all 1024 threads)
         const int b = threadIdx.x / (RM * RN), e = threadIdx.x % (RM * RN);
         float t = red[(b * RW) * RM * RN + e];
 #pragma unroll
@@ -288,36 +374,56 @@ __global__ void __launch_bounds__(RW * 64) k_rows(const float *__restrict__ A, i
         tile[b][e] = t;
     }
     __syncthreads();
-    if (threadIdx.x < RM * RN) {
-        const int r = threadIdx.x / RN, cl = threadIdx.x % RN;
-        if (m0 + r < M && n0 + cl < N) epi(tile[0], tile[NB - 1], r, cl, m0 + r, n0 + cl);
-    }
+    if (elem) epi(tile[0], tile[NB - 1], er, en - n0, em, en, z, pre);
 }
 
 bool rows_fit(int M, int N, int K) {
-    return M <= ROWS_MAX_M && K <= ROWS_MAX_K && K >= 1 && (int64_t)((N + RN - 1) / RN) * ((M + RM - 1) / RM) <= ROWS_MAX_WGS;
+    return M <= ROWS_MAX_M && K <= ROWS_MAX_K && K >= 1 && (int64_t)((N + RN - 1) / RN) * ((M + 7) / 8) <= ROWS_MAX_WGS;
 }
 
-template <class Epi>
-hipError_t launch_rows(hipStream_t s, const float *A, int lda, const float *gain, float eps, const float *W, const float *W2, int ldw,
-                       int M, int N, int K, const Epi &epi) {
+template <int RM, int KMAX, class Epi>
+hipError_t launch_rows_as(hipStream_t s, const RowsIn &in, const float *W, const float *W2, int ldw, int M, int N, int K, const Epi &epi,
+                          int n_ranks) {
     constexpr int RED = (Epi::kDual ? 2 : 1) * RW * RM * RN * 4;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute((const void *)k_rows<Epi>, hipFuncAttributeMaxDynamicSharedMemorySize, RED + RM * ROWS_MAX_K * 4);
+        attr_err = hipFuncSetAttribute((const void *)k_rows<RM, KMAX, Epi>, hipFuncAttributeMaxDynamicSharedMemorySize, RED + RM * KMAX * 4);
     });
     if (attr_err != hipSuccess) return attr_err;
-    hipLaunchKernelGGL((k_rows<Epi>), dim3((N + RN - 1) / RN, (M + RM - 1) / RM), dim3(RW * 64), RED + RM * K * 4, s, A, lda, gain, eps, W,
+    hipLaunchKernelGGL((k_rows<RM, KMAX, Epi>), dim3((N + RN - 1) / RN, (M + RM - 1) / RM, n_ranks), dim3(RW * 64), RED + RM * K * 4, s, in, W,
                        W2, ldw, M, N, K, epi);
     return hipGetLastError();
+}
+template <int RM, class Epi>
+hipError_t launch_rows_rm(hipStream_t s, const RowsIn &in, const float *W, const float *W2, int ldw, int M, int N, int K, const Epi &epi,
+                          int n_ranks) {
+    if (K <= 256) return launch_rows_as<RM, 256>(s, in, W, W2, ldw, M, N, K, epi, n_ranks);
+    if (K <= 512) return launch_rows_as<RM, 512>(s, in, W, W2, ldw, M, N, K, epi, n_ranks);
+    return launch_rows_as<RM, ROWS_MAX_K>(s, in, W, W2, ldw, M, N, K, epi, n_ranks);
+}
+// The fewest rows per workgroup with which the launch is one round of the chip: a workgroup's vector work grows with its rows (8 rows of
+// 344 elements: 1.3 us), and every group of rows reads the weights again.  Toy model, us per call, 8 rows
+// always / this: 1 token 55.8 / 48.0, 32 tokens 59.2 / 50.5.
+template <class Epi>
+hipError_t launch_rows(hipStream_t s, const RowsIn &in, const float *W, const float *W2, int ldw, int M, int N, int K, const Epi &epi,
+                       int n_ranks = 1) {
+    const int64_t cols = (int64_t)((N + RN - 1) / RN) * n_ranks;
+    if (cols * M <= 256) return launch_rows_rm<1>(s, in, W, W2, ldw, M, N, K, epi, n_ranks);
+    if (cols * ((M + 1) / 2) <= 256) return launch_rows_rm<2>(s, in, W, W2, ldw, M, N, K, epi, n_ranks);
+    if (cols * ((M + 3) / 4) <= 256) return launch_rows_rm<4>(s, in, W, W2, ldw, M, N, K, epi, n_ranks);
+    return launch_rows_rm<8>(s, in, W, W2, ldw, M, N, K, epi, n_ranks);
 }
 
 // One workgroup of 4 waves per (token, query head): causal softmax attention over the cache.  A thread takes a key at a time
 // for the scores; for the output wave w takes keys w, w + 4, ... with lane = feature, and the four sums meet in LDS.
 __global__ void __launch_bounds__(TB) k_attention(const float *__restrict__ qkv, const float *__restrict__ kc, const float *__restrict__ vc,
-                                                  float *__restrict__ out, spd_positions P, int q_len, int q, int kv, int d, int nqkv,
-                                                  int max_ctx) {
+                                                  float *__restrict__ out, size_t qkv_rank, size_t kv_rank, size_t out_rank, spd_positions P,
+                                                  int q_len, int q, int kv, int d, int nqkv, int max_ctx) {
+    qkv += blockIdx.y * qkv_rank;          // (grid.y: the rank)
+    kc += blockIdx.y * kv_rank;
+    vc += blockIdx.y * kv_rank;
+    out += blockIdx.y * out_rank;
     extern __shared__ float sc[];          // [n_keys] scores, then probabilities
     __shared__ float part[4][64];
     __shared__ float qs[256];
@@ -449,6 +555,76 @@ namespace spd_f32 {
         if (e_ != hipSuccess) return e_;  \
     } while (0)
 
+static RowsQKV rows_qkv(const spd_call &c, float *qkv, size_t qkv_rank, char *kvc) {
+    const spd_dims &D = *c.D;
+    RowsQKV e;
+    e.qkv = qkv; e.qkv_rank = qkv_rank;
+    e.kc = (float *)kvc; e.vc = (float *)(kvc + D.kv_v); e.kv_rank = D.kv_bytes / 4;
+    e.cosT = (const float *)(c.ws + D.ws_cos); e.sinT = (const float *)(c.ws + D.ws_sin);
+    e.q_len = c.q_len; e.q = D.q; e.kv = D.kv; e.d = D.d; e.nqkv = D.nqkv; e.max_ctx = D.max_ctx; e.P = c.pos;
+    return e;
+}
+static RowsIn rows_in(const spd_call &c, const float *a, int lda, size_t a_rank, const float *gain) {
+    RowsIn in;
+    in.a = a; in.lda = lda; in.a_rank = a_rank; in.gain = gain; in.eps = c.D->eps; in.w_rank = c.D->weight_bytes / 4;
+    return in;
+}
+
+bool ranks_fit(const spd_call &c, int n_ranks) {
+    const spd_dims &D = *c.D;
+    const int M = c.M, qd = D.q * D.d;
+    return rows_fit(M, D.nqkv, D.h) && RN % D.d == 0 && rows_fit(M, D.h, qd) && rows_fit(M, D.f, D.h) && rows_fit(M, D.h, D.f) &&
+           (n_ranks == 1 || (n_ranks <= D.rk_ranks && M <= D.rk_rows));
+}
+
+// One block of `n` ranks side by side in five launches (23 -> 11 of a two-layer model with two ranks).  X is x->base, or the sum
+// *x describes, which is written to x->out; the sum that ends the block is left to the reader of its slots: *x describes it
+// on return.  R: where a TP block's kept sync point puts X + sum of the slots.  Toy model (hidden 256, two layers, two ranks), us per call, one
+// rank after the other with launches of their own for the sums / side by side: 1 token 137 / 68, 32 tokens 142 / 70.
+hipError_t block_ranks(const spd_call &c, const char *w, char *kvc, int n, int spd, float *slot0, const float *slots, spd_sum *x, float *R,
+                       const float *bo) {
+    const spd_dims &D = *c.D;
+    const int M = c.M, qd = D.q * D.d, f = D.f;
+    const size_t mr = n > 1 ? D.rk_rows : D.m_pad;
+    float *qkv = (float *)(c.ws + (n > 1 ? D.ws_rk_qkv : D.ws_qkv)), *att = (float *)(c.ws + (n > 1 ? D.ws_rk_ahat : D.ws_ahat)),
+          *u = (float *)(c.ws + (n > 1 ? D.ws_rk_uhat : D.ws_uhat));
+    const size_t slot_n = c.slot_stride;
+
+    RowsIn in = rows_in(c, x->base, D.h, 0, (const float *)(w + D.w_g1));
+    in.slots = x->slots; in.slot_stride = slot_n; in.n_slots = x->n; in.bias = x->bias; in.out = x->out;
+    SPD_TRY(launch_rows(c.s, in, (const float *)(w + D.w_qkv), nullptr, D.nqkv, M, D.nqkv, D.h, rows_qkv(c, qkv, mr * D.nqkv, kvc), n));
+    const float *X = x->n ? x->out : x->base;
+
+    hipLaunchKernelGGL(k_attention, dim3(M * D.q, n), dim3(TB), (size_t)c.max_pos_end * sizeof(float), c.s, qkv, (const float *)kvc,
+                       (const float *)(kvc + D.kv_v), att, mr * D.nqkv, D.kv_bytes / 4, mr * qd, c.pos, c.q_len, D.q, D.kv, D.d, D.nqkv,
+                       D.max_ctx);
+    SPD_TRY(hipGetLastError());
+
+    RowsO eo;                              // Y_r into the rank's slot
+    eo.y = slot0; eo.y_rank = slot_n; eo.r_out = nullptr; eo.x = nullptr; eo.bias = nullptr; eo.ld = D.h;
+    SPD_TRY(launch_rows(c.s, rows_in(c, att, qd, mr * qd, nullptr), (const float *)(w + D.w_o), nullptr, D.h, M, D.h, qd, eo, n));
+
+    in = rows_in(c, X, D.h, 0, (const float *)(w + D.w_g2));
+    in.bias = bo;
+    if (spd) {                             // R_r = X + Y_r [+ b] (Sec. 4.1.1), needed by this product only
+        in.slots = slot0; in.slot_rank = slot_n; in.n_slots = 1;
+    } else {                               // the kept sync point
+        in.slots = slots; in.slot_stride = slot_n; in.n_slots = D.tp; in.out = R;
+    }
+    RowsGU eg;
+    eg.u = u; eg.u_rank = mr * f; eg.ld = f;
+    SPD_TRY(launch_rows(c.s, in, (const float *)(w + D.w_g), (const float *)(w + D.w_u), f, M, f, D.h, eg, n));
+
+    RowsDown ed;                           // slot = Z_r, or Y_r + Z_r
+    ed.out = slot0; ed.add = spd ? slot0 : nullptr; ed.out_rank = slot_n; ed.ld = D.h;
+    SPD_TRY(launch_rows(c.s, rows_in(c, u, f, mr * f, nullptr), (const float *)(w + D.w_d), nullptr, D.h, M, D.h, f, ed, n));
+    x->base = spd ? X : R;
+    x->slots = slots;
+    x->n = D.tp;
+    x->bias = spd ? bo : nullptr;
+    return hipSuccess;
+}
+
 // r_out (may be NULL) <- x + Y_r [+ bias], the local fold of an SPD block
 hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const float *x, float *y_out, float *r_out, const float *bias) {
     const spd_dims &D = *c.D;
@@ -457,10 +633,8 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
     const float *cosT = (const float *)(c.ws + D.ws_cos), *sinT = (const float *)(c.ws + D.ws_sin);
     float *kc = (float *)kvc, *vc = (float *)(kvc + D.kv_v);
     if (rows_fit(M, D.nqkv, D.h) && RN % D.d == 0) {
-        RowsQKV e;
-        e.qkv = qkv; e.kc = kc; e.vc = vc; e.cosT = cosT; e.sinT = sinT;
-        e.q_len = c.q_len; e.q = D.q; e.kv = D.kv; e.d = D.d; e.nqkv = D.nqkv; e.max_ctx = D.max_ctx; e.P = c.pos;
-        SPD_TRY(launch_rows(c.s, x, D.h, (const float *)(w + D.w_g1), D.eps, (const float *)(w + D.w_qkv), nullptr, D.nqkv, M, D.nqkv, D.h, e));
+        SPD_TRY(launch_rows(c.s, rows_in(c, x, D.h, 0, (const float *)(w + D.w_g1)), (const float *)(w + D.w_qkv), nullptr, D.nqkv, M, D.nqkv,
+                            D.h, rows_qkv(c, qkv, 0, kvc)));
     } else {
         hipLaunchKernelGGL(k_rmsnorm, dim3(M), dim3(TB), 0, c.s, x, (const float *)(w + D.w_g1), xn, D.h, D.eps);
         SPD_TRY(hipGetLastError());
@@ -471,12 +645,12 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
         SPD_TRY(hipGetLastError());
     }
     hipLaunchKernelGGL(k_attention, dim3(M * D.q), dim3(TB), (size_t)c.max_pos_end * sizeof(float), c.s, qkv, kc, vc,
-                       att, c.pos, c.q_len, D.q, D.kv, D.d, D.nqkv, D.max_ctx);
+                       att, (size_t)0, (size_t)0, (size_t)0, c.pos, c.q_len, D.q, D.kv, D.d, D.nqkv, D.max_ctx);
     SPD_TRY(hipGetLastError());
     if (rows_fit(M, D.h, qd)) {
         RowsO e;
-        e.y = y_out; e.r_out = r_out; e.x = x; e.bias = bias; e.ld = D.h;
-        SPD_TRY(launch_rows(c.s, att, qd, nullptr, 0.f, (const float *)(w + D.w_o), nullptr, D.h, M, D.h, qd, e));
+        e.y = y_out; e.y_rank = 0; e.r_out = r_out; e.x = x; e.bias = bias; e.ld = D.h;
+        SPD_TRY(launch_rows(c.s, rows_in(c, att, qd, 0, nullptr), (const float *)(w + D.w_o), nullptr, D.h, M, D.h, qd, e));
     } else {
         SPD_TRY(gemm(att, qd, (const float *)(w + D.w_o), D.h, nullptr, y_out, D.h, M, D.h, qd, c.s));
         if (r_out) SPD_TRY(spd_common::rank_sum(x, y_out, 1, (int64_t)M * D.h, r_out, c.s, bias, D.h));
@@ -495,9 +669,9 @@ hipError_t mlp_half(const spd_call &c, const char *w, const float *r_in, const f
     float *xn = (float *)(c.ws + D.ws_xhat), *gu = (float *)(c.ws + D.ws_gu), *u = (float *)(c.ws + D.ws_uhat);
     if (rows_fit(M, f, D.h)) {
         RowsGU e;
-        e.u = u; e.ld = f;
-        SPD_TRY(launch_rows(c.s, r_in, D.h, (const float *)(w + D.w_g2), D.eps, (const float *)(w + D.w_g), (const float *)(w + D.w_u), f, M, f,
-                            D.h, e));
+        e.u = u; e.u_rank = 0; e.ld = f;
+        SPD_TRY(launch_rows(c.s, rows_in(c, r_in, D.h, 0, (const float *)(w + D.w_g2)), (const float *)(w + D.w_g), (const float *)(w + D.w_u),
+                            f, M, f, D.h, e));
     } else {
         hipLaunchKernelGGL(k_rmsnorm, dim3(M), dim3(TB), 0, c.s, r_in, (const float *)(w + D.w_g2), xn, D.h, D.eps);
         SPD_TRY(hipGetLastError());
@@ -509,8 +683,8 @@ hipError_t mlp_half(const spd_call &c, const char *w, const float *r_in, const f
     }
     if (rows_fit(M, D.h, f)) {
         RowsDown e;
-        e.out = out; e.add = add; e.ld = D.h;
-        SPD_TRY(launch_rows(c.s, u, f, nullptr, 0.f, (const float *)(w + D.w_d), nullptr, D.h, M, D.h, f, e));
+        e.out = out; e.add = add; e.out_rank = 0; e.ld = D.h;
+        SPD_TRY(launch_rows(c.s, rows_in(c, u, f, 0, nullptr), (const float *)(w + D.w_d), nullptr, D.h, M, D.h, f, e));
     } else {
         SPD_TRY(gemm(u, f, (const float *)(w + D.w_d), D.h, add, out, D.h, M, D.h, f, c.s));
     }

@@ -478,6 +478,35 @@ def test_fp32_small_products(gpu, w, flag, batch, q_len, positions):
     case.close()
 
 
+# Small fp32 calls run the ranks side by side, one to eight rows of up to 256, 512 or 1024 elements per workgroup, and perform every sum over
+# the ranks but the last in the launch that reads it.  A call that wants every block's output runs them one after the other with launches of
+# their own for the sums: the same numbers in another order of fp32 sums over K <= 520 (1e-5 of the largest).
+@pytest.mark.parametrize("hidden,ffn", [(96, 1560), (257, 768), (768, 90)], ids=["k520", "k257", "k768"])
+@pytest.mark.parametrize("rank", [None, 1], ids=["all-ranks", "one-rank"])
+@pytest.mark.parametrize("batch,q_len,positions", [(1, 1, [31]), (5, 1, [0, 9, 30, 2, 31]), (1, 33, [3]), (2, 32, [0, 32])], ids=["1", "5", "33", "64"])
+def test_fp32_ranks_side_by_side(gpu, hidden, ffn, rank, batch, q_len, positions):
+    import torch
+    w = Workload(name=f"f32-side-{hidden}-{ffn}", hidden=hidden, n_q_heads=6, n_kv_heads=3, head_dim=32, ffn=ffn, n_layers=4, tp=3, dtype=F32,
+                 seed=46, batch=1, q_len=1, ctx=64, mask=(1, 0, 0, 1))
+    M = batch * q_len
+    X, peers = inputs.hidden_states(w, M), inputs.peer_slots(w, M)
+    say(f"fp32 side by side: {w.name} rank={rank} {M} tokens")
+    got = []
+    for layer_out in (False, True):
+        case = Case(w, gpu, ranks=range(w.tp) if rank is None else [rank], positions=positions, max_ctx=64, max_tokens=M, bias_std=1.0)
+        slots = case.to_dev(peers).reshape(w.tp, M, w.hidden)
+        x = case.to_dev(X)                       # the output takes the input's place
+        taps = torch.zeros((w.n_layers, M, w.hidden), dtype=torch.float32, device=gpu) if layer_out else None
+        syncs = B.spd_model_forward_staged(case.dev.ctx, w.mask, case.dev.rank_arg(), case.dev.weights, case.dev.kv, positions, batch, q_len, x,
+                                           slots, x, case.dev.workspace, layer_out=taps)
+        torch.cuda.synchronize()
+        assert syncs == 6
+        got.append([x, slots] + [k.view(torch.float32) for k in case.dev.kv])
+        case.close()
+    for a, b in zip(*got):
+        assert float((a - b).abs().max()) <= 1e-5 * float(b.abs().max())
+
+
 # fp32 attention where a thread takes a second key (256 keys and more), the waves' shares end unevenly and the output needs a
 # second and a fourth pass of 64 features
 @pytest.mark.parametrize("head_dim", [2, 64, 66, 128, 256])
