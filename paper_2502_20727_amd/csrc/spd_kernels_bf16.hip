@@ -1223,7 +1223,7 @@ __global__ void __launch_bounds__(256) k_gemv_finish(const float *__restrict__ k
 template <int MT, bool SPLIT>
 struct SkinnySet {
     bf16x8 fa, fb, fh[MT], fl[SPLIT ? MT : 1];
-    static constexpr int kRing = MT == 2 ? (SPLIT ? 3 : 4) : 2;
+        static constexpr int kRing = MT == 2 ? (SPLIT ? 3 : 4) : 2;      // (three or four sets of 8 m-tiles: 70B 128 tokens 103 -> 124, 136 us)
 };
 
 template <int W, int MT, bool SPLIT, int MODE, class Epi>
@@ -1443,31 +1443,40 @@ __global__ void __launch_bounds__(MID_PAIRS * 64) k_mid(const __bf16 *__restrict
     }
 }
 
-// Adds the KS partial tiles of (pair, m-tile) in slice order and runs the epilogue; one wave per
-// pair, the 8 pairs of a k_mid workgroup per workgroup.  grid = (groups of 8 pairs, m-tiles).
+// Adds the KS partial tiles of (pair, m-tile) and runs the epilogue.  A workgroup of 8 waves takes PP pairs, 8 / PP waves each: wave q of
+// a pair adds the slices q, q + 8 / PP, ... and the pair's first wave the waves' sums, in that order.  grid = (groups of PP pairs, m-tiles).
 // The norm scale of the m-tile's 16 tokens is computed once per workgroup: thread t adds the
 // partial sums of squares t/16, t/16 + 32, ... of token t%16, then 16 threads add the 32 results
 // in order.
-template <class Epi>
-__global__ void __launch_bounds__(MID_PAIRS * 64) k_mid_finish(const f32x4 *__restrict__ kpart, int KS, int n_pairs, int n_mtiles,
-                                                               Epi epi) {
+constexpr int FIN_WAVES = 8;
+template <int PP, class Epi>
+__global__ void __launch_bounds__(FIN_WAVES * 64) k_mid_finish(const f32x4 *__restrict__ kpart, int KS, int n_pairs, int n_mtiles, Epi epi) {
+    // the QKV projection's slices are added in 64 bits: its keys and values are rounded to bf16 next, and the sums over up to
+    // 16 slices are the larger part of what decides the last place of a near tie
+    typedef typename std::conditional<Epi::kWideSum, double, float>::type Sum;
+    constexpr int NQ = FIN_WAVES / PP;                   // waves per pair
+    constexpr int NL = NQ <= 2 ? 8 : 4;                   // slices a wave requests at once
     __shared__ float red[32][16];
     __shared__ float rs_row[16];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int pair = blockIdx.x * MID_PAIRS + wave, mt = blockIdx.y;
+    __shared__ Sum sums[NQ > 1 ? NQ - 1 : 1][NQ > 1 ? PP : 1][8][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q = wave % NQ;
+    const int pair = blockIdx.x * PP + wave / NQ, mt = blockIdx.y;
     const bool live = pair < n_pairs;
     typename Epi::Pre pre;
-    if (live) pre = epi.pre(pair, mt, lane);
-    // the first eight slices are requested before the norm statistics are dealt with, the others eight at a time
+    if (live && q == 0) pre = epi.pre(pair, mt, lane);
+    // the first slices are requested before the norm statistics are dealt with
     const f32x4 *src = kpart + (((size_t)(live ? pair : n_pairs - 1) * KS * n_mtiles + mt) * 2) * 64 + lane;
     const size_t sstr = (size_t)n_mtiles * 128;
-    f32x4 ta[8], tb[8];
+    f32x4 ta[NL], tb[NL];
+    auto load = [&](int s0) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int sl = j < KS ? j : KS - 1;
-        ta[j] = src[(size_t)sl * sstr];
-        tb[j] = src[(size_t)sl * sstr + 64];
-    }
+        for (int j = 0; j < NL; ++j) {
+            const int sl = s0 + NQ * j < KS ? s0 + NQ * j : KS - 1;
+            ta[j] = src[(size_t)sl * sstr];
+            tb[j] = src[(size_t)sl * sstr + 64];
+        }
+    };
+    load(q);
     float rs = 1.f;
     if constexpr (Epi::kNeedsRs) {
         if (epi.nch == 0) {                  // the factor itself (k_row_scale)
@@ -1479,41 +1488,58 @@ __global__ void __launch_bounds__(MID_PAIRS * 64) k_mid_finish(const f32x4 *__re
             if (threadIdx.x < 16) {
                 float t = 0.f;
 #pragma unroll
-                for (int q = 0; q < 32; ++q) t += red[q][threadIdx.x];
+                for (int i = 0; i < 32; ++i) t += red[i][threadIdx.x];
                 rs_row[threadIdx.x] = 1.0f / sqrtf(t / (float)epi.h + epi.eps);
             }
             __syncthreads();
             rs = rs_row[lane & 15];
         }
     }
-    if (!live) return;
-    // the QKV projection's slices are added in 64 bits: its keys and values are rounded to bf16 next, and the sums over up to
-    // 16 slices are the larger part of what decides the last place of a near tie
-    typedef typename std::conditional<Epi::kWideSum, double, float>::type Sum;
-    Sum sa[4] = {0, 0, 0, 0}, sb[4] = {0, 0, 0, 0};
-    auto add = [&](int j) {
+    if (NQ == 1 && !live) return;
+    Sum s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int s0 = q; s0 < KS; s0 += NL * NQ) {
+        if (s0 != q) load(s0);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            sa[e] += (Sum)ta[j][e];
-            sb[e] += (Sum)tb[j][e];
-        }
-    };
+        for (int j = 0; j < NL; ++j)
+            if (s0 + NQ * j < KS) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (j < KS) add(j);
-    for (int s0 = 8; s0 < KS; s0 += 8) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int sl = s0 + j < KS ? s0 + j : KS - 1;
-            ta[j] = src[(size_t)sl * sstr];
-            tb[j] = src[(size_t)sl * sstr + 64];
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (s0 + j < KS) add(j);
+                for (int e = 0; e < 4; ++e) {
+                    s[e] += (Sum)ta[j][e];
+                    s[4 + e] += (Sum)tb[j][e];
+                }
+            }
     }
-    const f32x4 a = {(float)sa[0], (float)sa[1], (float)sa[2], (float)sa[3]}, b = {(float)sb[0], (float)sb[1], (float)sb[2], (float)sb[3]};
+    if constexpr (NQ > 1) {
+        const int p = wave / NQ;
+        if (q > 0) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sums[q - 1][p][e][lane] = s[e];
+        }
+        __syncthreads();
+        if (!live || q > 0) return;
+#pragma unroll
+        for (int i = 0; i < NQ - 1; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s[e] += sums[i][p][e][lane];
+    }
+    const f32x4 a = {(float)s[0], (float)s[1], (float)s[2], (float)s[3]}, b = {(float)s[4], (float)s[5], (float)s[6], (float)s[7]};
     epi(pair, mt, a, b, lane, rs, pre);
+}
+// Pairs per workgroup: 8 from 128 workgroups on, fewer below, so that a narrow projection's sums are not left to a few compute units, one
+// wave's loads after the other.  us per call, always 8 / 4 from 64 and 2 below: 7B 24 tokens (12 and 22 workgroups of 8 pairs) 44.9 / 41.6, 64
+// (24, 44) 51.8 / 46.8; 70B 40 tokens (15, 84) 76.5 / 72.6, 128 (40, 224) 101.6 / 98.8; 13B 100 (105, 189) 66.5 / 64.3.  The lines at 160 and
+// 80 and at 257 and 128: 13B 180 tokens (180, 324) 89.2 / 90.8 against 89.1, 7B 200 (78, 143) 73.4 both against 72.6; with 4 or 2 pairs at
+// any size 512 tokens of 70B (160, 896 and 1024) 244 -> 252 and 254, the norm's statistics being summed once per workgroup.
+template <class Epi>
+hipError_t launch_mid_finish(hipStream_t s, const f32x4 *kpart, int KS, int n_pairs, int n_mtiles, const Epi &epi) {
+    const int n8 = (n_pairs + 7) / 8 * n_mtiles;
+#define SPD_FIN(PP) \
+    hipLaunchKernelGGL((k_mid_finish<PP, Epi>), dim3((n_pairs + PP - 1) / PP, n_mtiles), dim3(FIN_WAVES * 64), 0, s, kpart, KS, n_pairs, n_mtiles, epi)
+    if (n8 >= 128) SPD_FIN(8);
+    else if (n8 >= 64) SPD_FIN(4);
+    else SPD_FIN(2);
+#undef SPD_FIN
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2480,9 +2506,8 @@ hipError_t launch_mid(const spd_call &c, const __bf16 *Wp, const __bf16 *X, int 
     else if (n_mtiles <= 4) hipLaunchKernelGGL((k_mid<4>), grid, wg, 0, c.s, Wp, X, KT, KS, n_pairs, n_mtiles, kpart);
     else hipLaunchKernelGGL((k_mid<8>), grid, wg, 0, c.s, Wp, X, KT, KS, n_pairs, n_mtiles, kpart);
     SPD_TRY(hipGetLastError());
-    hipLaunchKernelGGL((k_mid_finish<Epi>), dim3(groups, n_mtiles), dim3(MID_PAIRS * 64), 0, c.s, kpart, KS, n_pairs, n_mtiles, epi);
     *done = true;
-    return hipGetLastError();
+    return launch_mid_finish(c.s, kpart, KS, n_pairs, n_mtiles, epi);
 }
 
 // Projection in K slices: the LDS-tiled GEMM in one launch of (tiles x slices) workgroups, at most one per compute unit,
@@ -2518,9 +2543,7 @@ hipError_t launch_sliced(const spd_call &c, bool split, const __bf16 *Wp, const 
     else if (kind == 1) SPD_SLICED(GemmSquare);
     else SPD_SLICED(GemmHalf);
 #undef SPD_SLICED
-    hipLaunchKernelGGL((k_mid_finish<Epi>), dim3((n_pairs + MID_PAIRS - 1) / MID_PAIRS, n_mtiles), dim3(MID_PAIRS * 64), 0, c.s,
-                       (const f32x4 *)park.kpart, KS, n_pairs, n_mtiles, epi);
-    return hipGetLastError();
+    return launch_mid_finish(c.s, (const f32x4 *)park.kpart, KS, n_pairs, n_mtiles, epi);
 }
 
 // 17 .. 512 tokens, short contractions: the skinny kernel with the whole epilogue is done before K slices and the launch that

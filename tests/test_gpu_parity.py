@@ -373,6 +373,17 @@ def test_bf16_short_and_sliced_contractions(gpu, w, split, q_len):
     _one_rank_block(gpu, w, 1, q_len, [0], q_len % 2, split)
 
 
+# the kernel that adds the slices takes 2, 4 or 8 pairs of n-tiles per workgroup, by the number of groups of 8 times m-tiles (lines at 64 and
+# 128): gate/up of 66 pairs (9 groups) on either side of both lines, QKV of 7 pairs
+FIN_66 = Workload(name="66-and-7-pairs", hidden=3232, n_q_heads=10, n_kv_heads=2, head_dim=32, ffn=2112, n_layers=1, tp=2, dtype=BF16,
+                  seed=47, batch=1, q_len=1, ctx=64, mask=(1,))
+
+
+@pytest.mark.parametrize("q_len", [17, 112, 113, 224, 225])
+def test_bf16_slices_added_by_few_and_many_workgroups(gpu, q_len):
+    _one_rank_block(gpu, FIN_66, 1, q_len, [0], q_len % 2)
+
+
 @pytest.mark.parametrize("q_len,flag", [(17, 1), (40, 0), (100, 1)])
 def test_bf16_short_call_of_a_wide_model(gpu, q_len, flag):
     """More pairs of n-tiles (520 in the O and down projections) than compute units, and two sync-point epilogues on them."""
