@@ -952,6 +952,64 @@ struct EpiPark {
 };
 
 // ------------------------------------------------------------------------------------------
+// Partial softmax states of a decode step's attention, one per (sequence, KV head = "unit"; split of the context; query head c of the
+// group): d unnormalised sums, maximum and sum of the exponentials.  [unit][split][c][d] first, then [unit][split][2][c]: only the
+// group's real heads (1 of an MFMA's 16 columns in multi-head attention), a head's features side by side.  (Whole tiles of 16 columns
+// before: us per layer 70B 16 sequences of 4096 63.8 -> 62.6, 13B 8 of 4096 56.3 -> 54.8, 7B 1 of 2048 40.4 -> 38.8.)
+// ------------------------------------------------------------------------------------------
+struct AttnParts {
+    float *o;
+    int units, n_splits, group, d;
+    __device__ __forceinline__ float *sums(int u, int split, int c) const { return o + (((size_t)u * n_splits + split) * group + c) * d; }
+    __device__ __forceinline__ float *max_sum(int u, int split, int c) const {       // maximum; `group` floats further the sum
+        return o + (size_t)units * n_splits * group * d + ((size_t)u * n_splits + split) * 2 * group + c;
+    }
+};
+// CH splits of four features, requested together
+template <int CH>
+struct MergeLoads {
+    float m[CH], l[CH];
+    float4 o[CH];
+    __device__ __forceinline__ void load(const AttnParts &P, int u, int c, int quad, int s0) {
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            const int sp = s0 + j < P.n_splits ? s0 + j : P.n_splits - 1;
+            const float *ml = P.max_sum(u, sp, c);
+            m[j] = ml[0];
+            l[j] = ml[P.group];
+            o[j] = *(const float4 *)(P.sums(u, sp, c) + 4 * quad);
+        }
+    }
+};
+// The merge of the splits in ascending order, CH at a time: the normalised output of four features.  `first` holds the first CH.
+template <int CH>
+__device__ __forceinline__ float4 merge_splits(const AttnParts &P, int u, int c, int quad, MergeLoads<CH> first) {
+    float M = -INFINITY, den = 0.f;
+    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s0 = 0; s0 < P.n_splits; s0 += CH) {
+        if (s0) first.load(P, u, c, quad, s0);
+        float mc = M;
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            if (s0 + j >= P.n_splits) first.m[j] = -INFINITY;
+            mc = fmaxf(mc, first.m[j]);
+        }
+        const float keep = (M == -INFINITY) ? 0.f : __expf(M - mc);
+        num.x *= keep; num.y *= keep; num.z *= keep; num.w *= keep;
+        den *= keep;
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            if (first.m[j] == -INFINITY) continue;
+            const float sc = __expf(first.m[j] - mc);
+            num.x += first.o[j].x * sc; num.y += first.o[j].y * sc; num.z += first.o[j].z * sc; num.w += first.o[j].w * sc;
+            den += first.l[j] * sc;
+        }
+        M = mc;
+    }
+    return make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
+}
+
+// ------------------------------------------------------------------------------------------
 // GEMV-like projection for at most 16 tokens (one m-tile): bound by streaming the weights.
 //   out^T[n][m] = sum_k W[k][n] x[m][k]
 // grid = (pairs of n-tiles, KS).  A workgroup owns one pair and one of KS slices of K; its W
@@ -1028,10 +1086,15 @@ struct GemvSet {
     static constexpr int kRing = SPLIT ? 3 : 5;      // (16 waves: 128 registers each)
 };
 
-template <int W, bool SPLIT, int MODE, class Epi>     // MODE 0: whole K, 1: slices -> kpart, 2: slices -> Epi::slice
+// MERGE: the input is the attention's output, merged here from the splits' states: every workgroup merges all of it, a thread
+// four features of a (token, head), into fragments in LDS while its weights are on their way.
+struct NoParts {};
+constexpr int GEMV_MERGE_TILES = 5;      // k-tiles per wave
+template <int W, bool SPLIT, int MODE, class Epi, bool MERGE = false>     // MODE 0: whole K, 1: slices -> kpart, 2: slices -> Epi::slice
 __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, const __bf16 *__restrict__ Xhi,
                                                   const __bf16 *__restrict__ Xlo, int KT, int KS,
-                                                  float *__restrict__ kpart, int rows, Epi epi) {
+                                                  float *__restrict__ kpart, int rows, Epi epi,
+                                                  typename std::conditional<MERGE, AttnParts, NoParts>::type parts) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int pair = blockIdx.x, ks = blockIdx.y;
     const int kb0 = (int)(((long)ks * KT) / KS), kb1 = (int)(((long)(ks + 1) * KT) / KS);
@@ -1083,7 +1146,7 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
     SsLoads ssl;
     constexpr bool PARTIAL = MODE == 1, EARLY = Epi::kSync && MODE == 0;
     f32x4 sla = {0.f, 0.f, 0.f, 0.f}, slb = sla, bsa = sla, bsb = sla;
-    stream_tiles<GemvSet<SPLIT>::kRing, GemvSet<SPLIT>>(k1 - k0, load, consume, [&]() {
+    auto between = [&]() {
         // loads that do not depend on the stream: the epilogue's inputs (first wave) and this wave's
         // share of the sum-of-squares partials, issued while the first weights are on their way
         if (!PARTIAL) {
@@ -1107,7 +1170,44 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
                 ssl.load(epi.ss, epi.nch, epi.m_pad, lane & 15, wave * 4 + (lane >> 4), W * 4);
             }
         }
-    });
+    };
+    if constexpr (!MERGE) {
+        stream_tiles<GemvSet<SPLIT>::kRing, GemvSet<SPLIT>>(k1 - k0, load, consume, between);
+    } else {
+        static_assert(!SPLIT && MODE == 0, "merged input: one plane, whole K");
+        extern __shared__ __attribute__((aligned(16))) char merged[];          // [KT] fragments (rows past the call: anything)
+        constexpr int CH = 16;
+        // (states first: what returns in order behind them may take its time)
+        const int per_tok = KT * 8, n_items = epi.M * per_tok, hq = parts.d >> 2;      // (hq divides per_tok)
+        const int e = min((int)threadIdx.x, n_items - 1), tok = e / per_tok, head = (e % per_tok) / hq, quad = e % hq;
+        const int u = tok * (per_tok / hq / parts.group) + head / parts.group, c = head % parts.group;
+        MergeLoads<CH> L;
+        L.load(parts, u, c, quad, 0);
+        SPD_SCHED_BARRIER();
+        GemvSet<false> R[GEMV_MERGE_TILES];
+        const int n = k1 - k0;
+#pragma unroll
+        for (int j = 0; j < GEMV_MERGE_TILES; ++j) {
+            const size_t kt = k0 + (j < n ? j : 0);                            // (a wave's first k-tile again, not used)
+            R[j].fa = frag<true>(wa + (n > 0 ? kt : 0) * kstr, 64 * rows, wlane);
+            R[j].fb = frag<true>(wb + (n > 0 ? kt : 0) * kstr, 64 * rows, wlane);
+        }
+        SPD_SCHED_BARRIER();
+        between();
+        SPD_SCHED_BARRIER();
+        if ((int)threadIdx.x < n_items) {
+            const float4 v = merge_splits<CH>(parts, u, c, quad, L);
+            const int k = 4 * (e % per_tok);
+            *(bf16x4 *)(merged + (k >> 5) * 1024 + 2 * spd_frag_elem(tok, k & 31)) = cvt4h(v.x, v.y, v.z, v.w);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < GEMV_MERGE_TILES; ++j)
+            if (j < n) {
+                R[j].fh = *(const bf16x8 *)(merged + (k0 + j) * 1024 + lane * 16);
+                consume(R[j]);
+            }
+    }
     __shared__ f32x4 red[W][2][64];
     __shared__ float red_ss[W][64];
     __shared__ f32x4 peers[EARLY ? SYNC_EARLY + 1 : 1][2][64];
@@ -1999,7 +2099,6 @@ __device__ __forceinline__ void load_q(bf16x8 *qf, const __bf16 *__restrict__ qb
 // take the 32-key blocks of their split round-robin, the next block's fragments being loaded
 // while the current one is processed; the workgroup writes one partial (unnormalised O^T,
 // running max, running sum) per split.
-// partial layout: [seq][kvh][split][(d + 2) * 16] floats: O^T[d][16], m[16], l[16]
 //
 // FUSED: the QKV projection ran in K slices and left fp32 partial rows qkvp[slice][token][nqkv]
 // (EpiQKVPart).  Every workgroup adds the slices of its queries (ascending order), keeps them as
@@ -2010,15 +2109,16 @@ template <int DT, bool FUSED>
 __global__ void __launch_bounds__(256) k_attn_decode(const __bf16 *__restrict__ qbuf_in, const __bf16 *__restrict__ qlo_in,
                                                      const float *__restrict__ qkvp, int KS, int part_rows, int nqkv, __bf16 *__restrict__ qbuf_out,
                                                      __bf16 *__restrict__ qlo_out, __bf16 *__restrict__ kc, __bf16 *__restrict__ vc,
-                                                     float *__restrict__ part, spd_positions P, int q, int kv, int max_ctx,
-                                                     int n_splits) {
+                                                     AttnParts parts, spd_positions P, int q, int kv, int max_ctx) {
     constexpr int d = DT * 16;
-    __shared__ float sm[4][(DT * 16 + 2) * 16];
+    // the waves' states: a column's features side by side (padded, so that the 16 columns begin at different banks)
+    __shared__ __attribute__((aligned(16))) float sm[4][16][DT * 16 + 4];
+    __shared__ float sml[4][2][16];
     __shared__ __attribute__((aligned(16))) __bf16 sq[2][16 * d];      // hi / lo queries of the group's heads
     __shared__ __attribute__((aligned(16))) __bf16 snew[2][d];         // new key, new value
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
-    const int group = q / kv, qd = q * d;
+    const int group = q / kv, qd = q * d, n_splits = parts.n_splits;
     const int n_keys = FUSED ? P.pos[b] : P.pos[b] + 1;       // keys in the cache
     const int nblk = (n_keys + 31) >> 5;
     const int b0 = (int)(((long)split * nblk) / n_splits), b1 = (int)(((long)(split + 1) * nblk) / n_splits);
@@ -2158,83 +2258,55 @@ __global__ void __launch_bounds__(256) k_attn_decode(const __bf16 *__restrict__ 
         }
         attn_block<DT>(st, qf, fn, 0, cvalid ? 1 : 0, scale, lane);
     }
-    // merge the four waves
-    float *my = sm[wave];
+    // merge the four waves: a thread takes four features of a head
+    if (cvalid) {
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) my[(dt * 16 + 4 * g + i) * 16 + col] = st.o[dt][i];
-    if (g == 0) {
-        my[d * 16 + col] = st.m;
-        my[(d + 1) * 16 + col] = st.l;
+        for (int dt = 0; dt < DT; ++dt) *(f32x4 *)&sm[wave][col][dt * 16 + 4 * g] = st.o[dt];
+        if (g == 0) {
+            sml[wave][0][col] = st.m;
+            sml[wave][1][col] = st.l;
+        }
     }
     __syncthreads();
-    float *dst = part + (((size_t)b * kv + kvh) * n_splits + split) * (size_t)((d + 2) * 16);
-    for (int e = threadIdx.x; e < (d + 2) * 16; e += 256) {
-        const int c = e & 15, row = e >> 4;
-        float mm = -INFINITY;
+    const int u = b * kv + kvh;
+    for (int e = threadIdx.x; e < group * (d / 4); e += 256) {
+        const int c = e / (d / 4), f = 4 * (e % (d / 4));
+        float mm = -INFINITY, l = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) mm = fmaxf(mm, sm[w][d * 16 + c]);
-        float v;
-        if (row == d) {
-            v = mm;
-        } else {
-            v = 0.f;
+        for (int w = 0; w < 4; ++w) mm = fmaxf(mm, sml[w][0][c]);
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const float mw = sm[w][d * 16 + c];
-                const float sc = (mw == -INFINITY) ? 0.f : __expf(mw - mm);
-                v += sm[w][row * 16 + c] * sc;
-            }
+        for (int w = 0; w < 4; ++w) {
+            const float mw = sml[w][0][c];
+            const float sc = (mw == -INFINITY) ? 0.f : __expf(mw - mm);
+            v += *(const f32x4 *)&sm[w][c][f] * sc;
+            l += sml[w][1][c] * sc;
         }
-        dst[e] = v;
+        *(f32x4 *)(parts.sums(u, split, c) + f) = v;
+        if (f == 0) {
+            float *ml = parts.max_sum(u, split, c);
+            ml[0] = mm;
+            ml[group] = l;
+        }
     }
 }
 
-// merge the splits of one (sequence, KV head) and write the normalised output as packed
-// activations of the O projection: row = token, contraction index = head*d + dd.
-// grid (kv heads, sequences, d/16); thread -> (feature dd, column c).  Every thread reads the
-// running max and sum of its column itself (16 splits at a time, all loads issued together), so
-// the kernel is one memory round trip per 16 splits; the splits are merged in ascending order.
-__global__ void __launch_bounds__(256) k_attn_combine(const float *__restrict__ part, __bf16 *__restrict__ ahat,
-                                                      __bf16 *__restrict__ alo, int q, int kv, int d, int n_splits) {
-    const int kvh = blockIdx.x, b = blockIdx.y;
-    const int group = q / kv, qd = q * d;
-    const size_t pstride = (size_t)(d + 2) * 16;
-    const float *src = part + ((size_t)b * kv + kvh) * n_splits * pstride;
-    const int c = threadIdx.x & 15, dd = blockIdx.z * 16 + (threadIdx.x >> 4);
-    if (c >= group) return;
-    float M = -INFINITY, num = 0.f, den = 0.f;
-    for (int s0 = 0; s0 < n_splits; s0 += 16) {
-        float ms[16], ls[16], os[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const bool ok = s0 + j < n_splits;
-            const float *p = src + (size_t)(ok ? s0 + j : s0) * pstride;
-            ms[j] = ok ? p[d * 16 + c] : -INFINITY;
-            ls[j] = ok ? p[(d + 1) * 16 + c] : 0.f;
-            os[j] = ok ? p[dd * 16 + c] : 0.f;
-        }
-        float mc = M;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) mc = fmaxf(mc, ms[j]);
-        const float keep = (M == -INFINITY) ? 0.f : __expf(M - mc);
-        num *= keep;
-        den *= keep;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const float sc = (ms[j] == -INFINITY) ? 0.f : __expf(ms[j] - mc);
-            num += os[j] * sc;
-            den += ls[j] * sc;
-        }
-        M = mc;
-    }
-    const float val = num / den;
-    const int kidx = (kvh * group + c) * d + dd;
-    const size_t o = spd_act_index(b >> 4, kidx >> 5, qd >> 5, ((int)gridDim.y + 15) >> 4) + spd_frag_elem(b & 15, kidx & 31);
-    const __bf16 hi = act_one(val);
-    ahat[o] = hi;
-    if (alo) alo[o] = act_one(val - act_back(hi));
+// merge the splits and write the normalised output as packed activations of the O projection: row = token, contraction index =
+// head*d + dd.  grid (quarters of 64 threads of a unit's group * d / 4 quads, units); every thread reads the maximum and sum of its
+// head itself (16 splits at a time, all loads issued together), so the kernel is one memory round trip per 16 splits.
+__global__ void __launch_bounds__(64) k_attn_combine(AttnParts parts, __bf16 *__restrict__ ahat, __bf16 *__restrict__ alo, int kv, int batch) {
+    const int hq = parts.d >> 2, u = blockIdx.y, b = u / kv, kvh = u % kv;
+    const int e = blockIdx.x * 64 + threadIdx.x;
+    if (e >= parts.group * hq) return;
+    const int c = e / hq, quad = e % hq, qd = kv * parts.group * parts.d;
+    MergeLoads<16> L;
+    L.load(parts, u, c, quad, 0);
+    const float4 v = merge_splits<16>(parts, u, c, quad, L);
+    const int kidx = (kvh * parts.group + c) * parts.d + 4 * quad;
+    const size_t o = spd_act_index(b >> 4, kidx >> 5, qd >> 5, (batch + 15) >> 4) + spd_frag_elem(b & 15, kidx & 31);
+    const bf16x4 hi = cvt4h(v.x, v.y, v.z, v.w);
+    *(bf16x4 *)(ahat + o) = hi;
+    if (alo) *(bf16x4 *)(alo + o) = cvt4h_lo(v.x, v.y, v.z, v.w, hi);
 }
 
 // Prefill (q_len > 1): grid (groups of CT column tiles, kv heads, sequences), 4 waves.  All four
@@ -2394,11 +2466,11 @@ hipError_t launch_gemv(const spd_call &c, const __bf16 *Wp, const __bf16 *Xhi, c
             // 2 k-tiles per wave everything is requested at once, which is what a short kernel wants.
             constexpr int W = 16;
             hipLaunchKernelGGL((k_gemv<W, SPLIT, 0, Epi>), dim3(n_pairs, 1), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT,
-                               1, kpart, rows, epi);
+                               1, kpart, rows, epi, NoParts());
         } else {
             constexpr int W = 8;
             hipLaunchKernelGGL((k_gemv<W, SPLIT, 0, Epi>), dim3(n_pairs, 1), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT,
-                               1, kpart, rows, epi);
+                               1, kpart, rows, epi, NoParts());
         }
         return hipGetLastError();
     }
@@ -2406,11 +2478,11 @@ hipError_t launch_gemv(const spd_call &c, const __bf16 *Wp, const __bf16 *Xhi, c
     const int KS = gemv_slices(n_pairs, KT);
     if (KS <= 1) {
         hipLaunchKernelGGL((k_gemv<W, SPLIT, 0, Epi>), dim3(n_pairs, 1), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT, 1,
-                           kpart, rows, epi);
+                           kpart, rows, epi, NoParts());
         return hipGetLastError();
     }
     hipLaunchKernelGGL((k_gemv<W, SPLIT, 1, Epi>), dim3(n_pairs, KS), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT, KS,
-                       kpart, rows, epi);
+                       kpart, rows, epi, NoParts());
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_gemv_finish<Epi>), dim3(n_pairs), dim3(256), 0, c.s, kpart, KS, epi);
@@ -2427,10 +2499,10 @@ hipError_t launch_gemv_sliced(const spd_call &c, bool split, const __bf16 *Wp, c
     const __bf16 *Xlo = Xhi + plane;
     if (split)
         hipLaunchKernelGGL((k_gemv<W, true, 2, Epi>), dim3(n_pairs, KS), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT, KS,
-                           (float *)nullptr, 16, epi);
+                           (float *)nullptr, 16, epi, NoParts());
     else
         hipLaunchKernelGGL((k_gemv<W, false, 2, Epi>), dim3(n_pairs, KS), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT, KS,
-                           (float *)nullptr, 16, epi);
+                           (float *)nullptr, 16, epi, NoParts());
     return hipGetLastError();
 }
 
@@ -2604,15 +2676,41 @@ inline bool sync_in_o(int n_pairs, int KT, int tp, int n_mtiles) {
     return n_mtiles <= 8 || (n_mtiles <= SKINNY_MAX_MTILES && n_pairs * ((n_mtiles + 7) / 8) <= 512 && KT <= 8 * tp);
 }
 
+// Does a decode step's O projection merge the attention's splits itself, instead of a kernel in between?  Every workgroup then reads
+// all states, so only where that is a quad of features per thread and 200 KB at most.  us per call, kernel of its own / in the projection: 7B 1
+// sequence of 2000 positions 38.8 / 37.5, 2: 39.3 / 37.9, 4 (512 quads, 131 KB): 41.4 / 40.5, 1 of 16000 47.3 / 45.6; 70B 1 of 4096 (32 splits,
+// 131 KB) 60.8 / 59.8; with two or three quads per thread: 7B 8 sequences 40.5 / 41.4, 13B 8 of 4096, 4 layers 219.1 / 225.7.
+constexpr int GEMV_MERGE_W = 8;
+inline bool merge_in_o(const spd_call &c, int n_pairs, int KT, int n_splits) {
+    const int quads = c.M * KT * 8;
+    if (c.M > 16 || c.sp_a || c.taps || !c.on(SPD_STAGE_ATTN) || !c.on(SPD_STAGE_O)) return false;
+    if (KT > GEMV_MERGE_W * GEMV_MERGE_TILES || n_pairs < 96 || quads > GEMV_MERGE_W * 64) return false;
+    return (int64_t)quads * n_splits * 16 <= 200 * 1024;
+}
+
 // The output projection's contraction is short (a rank's heads): up to 128 tokens the skinny kernel with the whole epilogue
 // beats slices and their finishing kernel; beyond, 256 x 128 tiles by themselves beat both once the skinny kernel would
 // take two rounds (70B shard, main kernel, us, skinny / tiles: 192 tokens 15.8 / 14.7, 512: 30.9 / 17.2; 13B 384: 10.8 / 11.4, 512:
 // 16.1 / 12.0).  With a kept sync point in its epilogue (MID) always the skinny kernel.
+// `merge`: the splits' states of a decode step whose O projection merges them itself (see merge_in_o()).
 template <bool MID>
 hipError_t launch_o(const spd_call &c, bool split, const __bf16 *Wp, const __bf16 *Xhi, size_t plane, int n_pairs, int KT,
-                    const EpiOT<MID> &epi) {
+                    const EpiOT<MID> &epi, const AttnParts &merge) {
     const int n_mtiles = (c.M + 15) / 16, zg = (n_mtiles + 7) / 8;
     const __bf16 *Xlo = Xhi + plane;
+    if (n_mtiles == 1 && merge.o) {
+        constexpr int W = GEMV_MERGE_W;
+        static std::once_flag once;
+        static hipError_t attr_err = hipSuccess;
+        std::call_once(once, [] {
+            attr_err = hipFuncSetAttribute((const void *)k_gemv<W, false, 0, EpiOT<MID>, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           W * GEMV_MERGE_TILES * 1024);
+        });
+        if (attr_err != hipSuccess) return attr_err;
+        hipLaunchKernelGGL((k_gemv<W, false, 0, EpiOT<MID>, true>), dim3(n_pairs, 1), dim3(W * 64), KT * 1024, c.s, Wp, Xhi, Xlo, KT, 1,
+                           (float *)nullptr, 16, epi, merge);
+        return hipGetLastError();
+    }
     if (n_mtiles == 1)
         return split ? launch_gemv<true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi) : launch_gemv<false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
     if (n_mtiles <= 8 || (n_mtiles <= SKINNY_MAX_MTILES && (MID || n_pairs * zg < 512)) || !spd_gemm_fits(KT))
@@ -2760,6 +2858,8 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
     spd_stage_begin(c, SPD_STAGE_EMPTY);      // (timers only) an empty bracket between two kernels of the block
     spd_stage_end(c, SPD_STAGE_EMPTY);
     const int DT = D.d / 16;
+    AttnParts parts = {};
+    bool merge_o = false;
     spd_stage_begin(c, SPD_STAGE_ATTN);
     if (!c.on(SPD_STAGE_ATTN)) {
         // skipped
@@ -2780,16 +2880,17 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
                 splits = sp;
             }
         }
-        float *part = (float *)(c.ws + D.ws_apart);
+        parts.o = (float *)(c.ws + D.ws_apart);
+        parts.units = units; parts.n_splits = splits; parts.group = D.group; parts.d = D.d;
         const dim3 grid(splits, D.kv, c.batch);
 #define SPD_DECODE(DTV)                                                                                              \
     if (fused_q)                                                                                                     \
         hipLaunchKernelGGL((k_attn_decode<DTV, true>), grid, dim3(256), 0, c.s, (const __bf16 *)nullptr,             \
-                           (const __bf16 *)nullptr, qkvp, qkv_slices, 16 * n_mtiles, D.nqkv, qbuf, qlo, kc, vc, part, c.pos, D.q, D.kv, \
-                           D.max_ctx, splits);                                                                       \
+                           (const __bf16 *)nullptr, qkvp, qkv_slices, 16 * n_mtiles, D.nqkv, qbuf, qlo, kc, vc, parts, c.pos, D.q, D.kv, \
+                           D.max_ctx);                                                                               \
     else                                                                                                             \
         hipLaunchKernelGGL((k_attn_decode<DTV, false>), grid, dim3(256), 0, c.s, qbuf, qlo, (const float *)nullptr, 1, 16,   \
-                           D.nqkv, (__bf16 *)nullptr, (__bf16 *)nullptr, kc, vc, part, c.pos, D.q, D.kv, D.max_ctx, splits)
+                           D.nqkv, (__bf16 *)nullptr, (__bf16 *)nullptr, kc, vc, parts, c.pos, D.q, D.kv, D.max_ctx)
         switch (DT) {
             case 2: SPD_DECODE(2); break;
             case 4: SPD_DECODE(4); break;
@@ -2799,9 +2900,11 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
         }
 #undef SPD_DECODE
         SPD_TRY(hipGetLastError());
-        hipLaunchKernelGGL(k_attn_combine, dim3(D.kv, c.batch, D.d / 16), dim3(256), 0, c.s, part, ahat, alo, D.q, D.kv,
-                           D.d, splits);
-        SPD_TRY(hipGetLastError());
+        merge_o = merge_in_o(c, D.h / 32, qd / 32, splits);
+        if (!merge_o) {
+            hipLaunchKernelGGL(k_attn_combine, dim3(cdiv(D.group * D.d / 4, 64), units), dim3(64), 0, c.s, parts, ahat, alo, D.kv, c.batch);
+            SPD_TRY(hipGetLastError());
+        }
     } else {
         const int n_ct = (c.q_len * D.group + 15) / 16;
         // Two column tiles per workgroup read each key and value once for both; up to two rounds of such workgroups, one
@@ -2856,11 +2959,11 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
             fill_o(e2);
             e2.spd = 2;
             e2.slots = mid->slots; e2.slot_stride = c.slot_stride; e2.tp = mid->tp; e2.rank = mid->rank; e2.rbuf = mid->rbuf;
-            SPD_TRY(launch_o(c, c.sp_a, wo.w, ahat, D.pl_a, D.h / 32, qd / 32, e2));
+            SPD_TRY(launch_o(c, c.sp_a, wo.w, ahat, D.pl_a, D.h / 32, qd / 32, e2, merge_o ? parts : AttnParts()));
         } else {
             EpiOT<false> e2;
             fill_o(e2);
-            SPD_TRY(launch_o(c, c.sp_a, wo.w, ahat, D.pl_a, D.h / 32, qd / 32, e2));
+            SPD_TRY(launch_o(c, c.sp_a, wo.w, ahat, D.pl_a, D.h / 32, qd / 32, e2, merge_o ? parts : AttnParts()));
         }
     }
 

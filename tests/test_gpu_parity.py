@@ -390,6 +390,19 @@ def test_bf16_short_call_of_a_wide_model(gpu, q_len, flag):
     _one_rank_block(gpu, ROWS_65, 1, q_len, [0], flag)
 
 
+# decode steps whose O projection merges the attention's splits itself (at most 512 quads of features, 40 k-tiles) and the first beyond: one k-tile
+# (waves without any), 9, 32, 40 and 41; groups of 1, 3 and 4 heads; an empty cache, and more than 16 splits
+@pytest.mark.parametrize("heads,kv_heads,head_dim,batches", [(2, 2, 32, (1, 16)), (6, 2, 96, (7, 8)), (16, 4, 128, (2, 3)), (80, 80, 32, (1, 2)),
+                                                             (82, 82, 32, (1,))], ids=["1-k-tile", "9", "32", "40", "41"])
+@pytest.mark.parametrize("flag", [1, 0], ids=["spd", "tp"])
+def test_bf16_decode_merge_of_splits(gpu, heads, kv_heads, head_dim, batches, flag):
+    w = Workload(name=f"merge-{heads}x{head_dim}", hidden=3072, n_q_heads=heads, n_kv_heads=kv_heads, head_dim=head_dim, ffn=256, n_layers=1,
+                 tp=2, dtype=BF16, seed=48, batch=1, q_len=1, ctx=64, mask=(flag,))
+    for b in batches:
+        _one_rank_block(gpu, w, b, 1, [(i * 211) % 700 for i in range(b)], flag)
+    _one_rank_block(gpu, w, 1, 1, [2300], flag)
+
+
 # decode QKV projections of 192 pairs and more, which the attention kernel does not add up: one launch up to 160 k-tiles
 QKV_192 = Workload(name="qkv-192-pairs", hidden=5120, n_q_heads=32, n_kv_heads=32, head_dim=128, ffn=256, n_layers=1, tp=2, dtype=BF16,
                    seed=40, batch=1, q_len=1, ctx=64, mask=(1,))
