@@ -1669,6 +1669,9 @@ struct GemmHalf {     // 256 x 128: three stages of 48 KiB, four of 32 KiB (a st
 struct GemmTall {     // 128 x 384: for few n-tiles, where 256 x 256 tiles leave compute units idle
     static constexpr int WN = 2, WM = 4, TI = 4, TJ = 6, NST = 2, NSTX = 2;
 };
+struct GemmThird {    // 128 x 192, three stages of 40 KiB (split: four of 32 KiB): where 256 x 128 tiles leave compute units idle (see launch_gemm_lds())
+    static constexpr int WN = 2, WM = 4, TI = 4, TJ = 3, NST = 3, NSTX = 4;
+};
 struct GemmWide {     // 160 x 256, every wave all 10 n-tiles of 2 m-tiles: for split activations and few n-tiles
     static constexpr int WN = 1, WM = 8, TI = 10, TJ = 2, NST = 2, NSTX = 3;      // (80 n-tiles x 512 m-tiles = exactly 256 tiles)
 };
@@ -1965,6 +1968,12 @@ hipError_t launch_gemm_lds(const spd_call &c, const __bf16 *Wp, const __bf16 *Xp
         // the other shapes
         const int halves = ((2 * n_pairs + 15) / 16) * ((n_mtiles + 7) / 8);
         const int other = (big < 224 && tall <= 256 && tall > big) ? tall : big;
+        // 128 x 192 tiles, three quarters of a half tile's work, where they still come to one round: us per call, half / these: 7B 1100
+        // tokens 192.5 / 183.3, 1500: 237.5 / 218.6, 2048 (gate/up 176 / 242 tiles) 335.5 / 325.0; 13B 800 195.7 / 184.2, 1400 285.3 / 269.0; 70B
+        // 550 293.7 / 256.4, 760 (gate/up 168 / 224) 325.4 / 280.1; calls of two chains equal (70B) to - 4 % (13B 2 x 1500)
+        const int thirds = ((2 * n_pairs + 7) / 8) * ((n_mtiles + 11) / 12);
+        if (big <= 128 && halves <= 256 && thirds <= 256 && thirds > halves)
+            return launch_gemm_lds_cfg<GemmThird, XS>(c, Wp, Xp, Xlo, n_pairs, KT, epi);
         if (big <= 128 && halves <= 256 && halves > other)
             return launch_gemm_lds_cfg<GemmHalf, XS>(c, Wp, Xp, Xlo, n_pairs, KT, epi, 0, 2, big);
     }

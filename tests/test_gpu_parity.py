@@ -265,6 +265,13 @@ def test_bf16_gemm_contraction_lengths(gpu, w, flag, split, q_len):
     case.close()
 
 
+# 128 x 192 tiles begin in the middle of a group of eight m-tiles: last tiles of 1, 2, 5 and 12 m-tiles, even and odd numbers of k-tiles
+@pytest.mark.parametrize("split", [B.SPD_SPLIT_AUTO, B.SPD_SPLIT_ALWAYS], ids=["default", "all-split"])
+@pytest.mark.parametrize("q_len", [577, 608, 656, 768])
+def test_bf16_gemm_tiles_across_groups(gpu, split, q_len):
+    _one_rank_block(gpu, KT_ODD, 1, q_len, [0], q_len % 2, split)
+
+
 # 65 partial sums of squares per token after a kept attention sync point of more than 512 tokens (hidden sizes that the row-wise
 # and the tile-wise preparation kernel serve): one preparation for all emulated ranks, whose partial sums every rank's
 # gate/up projection needs whole
