@@ -60,6 +60,7 @@ int check_call(const spd_ctx *ctx, int32_t rank, const int32_t *positions, int32
         c->sp_m = always;
     }
     c->nch1 = 0;
+    c->raw_x = nullptr;
     std::memset(&c->pos, 0, sizeof(c->pos));
     for (int b = 0; b < batch; ++b) {
         if (positions[b] < 0 || (int64_t)positions[b] + q_len > D.max_ctx) return SPD_EINVAL;
@@ -162,6 +163,16 @@ int f32_ranks_side_by_side(const spd_call &c, const uint8_t *mask, int n_layers,
     return SPD_OK;
 }
 
+// bf16 path: the first norm of the call's first block, left to its QKV projection or prepared by a launch of its own
+hipError_t first_norm(spd_call &c, const float *x_in, const char *w) {
+    if (spd_bf16::qkv_reads_x(c)) {
+        c.raw_x = x_in;
+        return hipSuccess;
+    }
+    c.nch1 = spd_bf16::prep_chunks(c);
+    return spd_bf16::prep(c, x_in, nullptr, 0, nullptr, (const float *)(w + c.D->w_g1), true, 0);
+}
+
 // The helper stream of the two-chain model forward and the events that fork to it and join from it: one
 // set per device, created on first use with that device current (default priority, non-blocking), never
 // destroyed.
@@ -212,10 +223,7 @@ int block_forward_impl(const spd_ctx *ctx, int32_t layer, int32_t spd_flag, int3
     const spd_dims &D = ctx->D;
     c.taps = taps;
     const char *w = (const char *)packed_weights;
-    if (D.dtype == SPD_BF16) {
-        SPD_HIP(spd_bf16::prep(c, x_in, nullptr, 0, nullptr, (const float *)(w + D.w_g1), true, 0));
-        c.nch1 = spd_bf16::prep_chunks(c);
-    }
+    if (D.dtype == SPD_BF16) SPD_HIP(first_norm(c, x_in, w));
     {
         const uint8_t mask = (uint8_t)spd_flag;
         bool done = false;
@@ -355,11 +363,7 @@ int spd_model_forward_staged(const spd_ctx *ctx, const uint8_t *spd_mask, int32_
     for (int k = 0; k < n_chains; ++k) {
         Chain &h = ch[k];
         h.layer_out = layer_out;
-        if (bf) {
-            SPD_HIP(spd_bf16::prep(h.c, h.x_in, nullptr, 0, nullptr, (const float *)((const char *)layer_weights[0] + D.w_g1),
-                                   true, 0));
-            h.c.nch1 = spd_bf16::prep_chunks(h.c);
-        }
+        if (bf) SPD_HIP(first_norm(h.c, h.x_in, (const char *)layer_weights[0]));
     }
     for (int l = 0; l < L; ++l) {
         const bool more = l + 1 < L;
@@ -372,6 +376,7 @@ int spd_model_forward_staged(const spd_ctx *ctx, const uint8_t *spd_mask, int32_
             const int rc2 = block_core(ctx, h.c, spd_mask[l], rank, (const char *)layer_weights[l],
                                        (char *)layer_kv[l] + h.kv_off, h.x, h.slots, &base, &bias, &kept, h.x_out, g1, &end_done);
             if (rc2 != SPD_OK) return rc2;
+            h.c.raw_x = nullptr;                       // (the first block's)
             if (k == 0) syncs += kept;
             // end-of-block sync point; in the bf16 path it also prepares the next block's first norm
             if (end_done) {

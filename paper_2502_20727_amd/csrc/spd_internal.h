@@ -219,6 +219,7 @@ struct spd_call {
     bool sp_a;                // attention output (input of the O projection)
     bool sp_m;                // second norm's output and SwiGLU output (inputs of the MLP's projections)
     int nch1;                 // number of sum-of-squares partials per token waiting in ss1
+    const float *raw_x;       // this block's QKV projection reads the residual stream itself, or NULL: the first norm is prepared
     char *ws;                 // workspace
     const spd_taps *taps;
     bool chained;             // one of the two chains of a long prefill: its kernels share the chip with the other chain's
@@ -312,4 +313,5 @@ struct spd_end_sync {
 hipError_t mlp_half(const spd_call &c, const char *w, int spd, float *slot, const spd_end_sync *fuse, bool *fused,
                     bool ss_per_pair);
 int prep_chunks(const spd_call &c);
+bool qkv_reads_x(const spd_call &c);      // can the block's QKV projection do the first norm itself (spd_call::raw_x)?
 }

@@ -1086,15 +1086,29 @@ struct GemvSet {
     static constexpr int kRing = SPLIT ? 3 : 5;      // (16 waves: 128 registers each)
 };
 
-// MERGE: the input is the attention's output, merged here from the splits' states: every workgroup merges all of it, a thread
+// SRC_MERGE: the input is the attention's output, merged here from the splits' states: every workgroup merges all of it, a thread
 // four features of a (token, head), into fragments in LDS while its weights are on their way.
+// SRC_X: the input is the residual stream itself, the first norm's elementwise part done on the way; every slice leaves its sums of squares
+// in ss[slice][16], and whoever adds the slices applies the factor.
 struct NoParts {};
+struct RawX {
+    const float *x, *gain;
+    float *ss;
+};
+struct GemvSetX {
+    bf16x8 fa, fb;
+    float4 x0, x1, g0, g1;
+};
 constexpr int GEMV_MERGE_TILES = 5;      // k-tiles per wave
-template <int W, bool SPLIT, int MODE, class Epi, bool MERGE = false>     // MODE 0: whole K, 1: slices -> kpart, 2: slices -> Epi::slice
+enum { SRC_PACKED, SRC_MERGE, SRC_X };
+template <int SRC> struct GemvSrc { typedef NoParts type; };
+template <> struct GemvSrc<SRC_MERGE> { typedef AttnParts type; };
+template <> struct GemvSrc<SRC_X> { typedef RawX type; };
+template <int W, bool SPLIT, int MODE, class Epi, int SRC = SRC_PACKED>     // MODE 0: whole K, 1: slices -> kpart, 2: slices -> Epi::slice
 __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, const __bf16 *__restrict__ Xhi,
                                                   const __bf16 *__restrict__ Xlo, int KT, int KS,
                                                   float *__restrict__ kpart, int rows, Epi epi,
-                                                  typename std::conditional<MERGE, AttnParts, NoParts>::type parts) {
+                                                  typename GemvSrc<SRC>::type parts) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int pair = blockIdx.x, ks = blockIdx.y;
     const int kb0 = (int)(((long)ks * KT) / KS), kb1 = (int)(((long)(ks + 1) * KT) / KS);
@@ -1166,13 +1180,56 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
                     bsb = *(const f32x4 *)(p + 16);
                 }
             }
-            if constexpr (Epi::kNeedsRs) {
+            if constexpr (Epi::kNeedsRs && SRC != SRC_X) {
                 ssl.load(epi.ss, epi.nch, epi.m_pad, lane & 15, wave * 4 + (lane >> 4), W * 4);
             }
         }
     };
-    if constexpr (!MERGE) {
+    float xsq = 0.f;
+    if constexpr (SRC == SRC_PACKED) {
         stream_tiles<GemvSet<SPLIT>::kRing, GemvSet<SPLIT>>(k1 - k0, load, consume, between);
+    } else if constexpr (SRC == SRC_X) {
+        static_assert(!SPLIT && MODE == 2, "raw input: one plane, K slices");
+        const int m = (lane & 15) < epi.M ? (lane & 15) : epi.M - 1;           // (rows past the call: its last one)
+        const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc((void *)parts.x, 0, epi.M * epi.h * 4, 0x00020000),
+                                     gbuf = __builtin_amdgcn_make_buffer_rsrc((void *)parts.gain, 0, epi.h * 4, 0x00020000);
+        const int grow = (lane >> 4) * 32, xrow = m * epi.h * 4 + grow;
+        auto at = [](__amdgpu_buffer_rsrc_t r, int off, int soff) {
+            return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
+        };
+        auto loadx = [&](GemvSetX &B, int i) {
+            const int kt = k0 + i;
+            B.fa = frag<true>(wa + (size_t)kt * kstr, 64 * rows, wlane);
+            B.fb = frag<true>(wb + (size_t)kt * kstr, 64 * rows, wlane);
+            B.x0 = at(xbuf, xrow, kt * 128);
+            B.x1 = at(xbuf, xrow + 16, kt * 128);
+            B.g0 = at(gbuf, grow, kt * 128);
+            B.g1 = at(gbuf, grow + 16, kt * 128);
+        };
+        auto usex = [&](const GemvSetX &B) {
+            const bf16x4 lo = cvt4h(B.x0.x * B.g0.x, B.x0.y * B.g0.y, B.x0.z * B.g0.z, B.x0.w * B.g0.w),
+                         hi = cvt4h(B.x1.x * B.g1.x, B.x1.y * B.g1.y, B.x1.z * B.g1.z, B.x1.w * B.g1.w);
+            const bf16x8 f = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            a = MFMA16(B.fa, f, a);
+            b = MFMA16(B.fb, f, b);
+            xsq += B.x0.x * B.x0.x + B.x0.y * B.x0.y + B.x0.z * B.x0.z + B.x0.w * B.x0.w;
+            xsq += B.x1.x * B.x1.x + B.x1.y * B.x1.y + B.x1.z * B.x1.z + B.x1.w * B.x1.w;
+        };
+        // (two or three k-tiles per wave, mostly: everything at once; a ring of this much per k-tile spills)
+        constexpr int NB = 3;
+        GemvSetX R[NB];
+        const int n = k1 - k0;
+        for (int i = 0; i < n || i == 0; i += NB) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                if (i + j < n) loadx(R[j], i + j);
+            SPD_SCHED_BARRIER();
+            if (i == 0) between();
+            SPD_SCHED_BARRIER();
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                if (i + j < n) usex(R[j]);
+        }
     } else {
         static_assert(!SPLIT && MODE == 0, "merged input: one plane, whole K");
         extern __shared__ __attribute__((aligned(16))) char merged[];          // [KT] fragments (rows past the call: anything)
@@ -1213,7 +1270,8 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
     __shared__ f32x4 peers[EARLY ? SYNC_EARLY + 1 : 1][2][64];
     red[wave][0][lane] = a;
     red[wave][1][lane] = b;
-    if constexpr (Epi::kNeedsRs && !PARTIAL) red_ss[wave][lane] = ssl.sum(epi.ss, epi.nch, epi.m_pad, lane & 15, wave * 4 + (lane >> 4), W * 4);
+    if constexpr (SRC == SRC_X) red_ss[wave][lane] = xsq;
+    else if constexpr (Epi::kNeedsRs && !PARTIAL) red_ss[wave][lane] = ssl.sum(epi.ss, epi.nch, epi.m_pad, lane & 15, wave * 4 + (lane >> 4), W * 4);
     if constexpr (EARLY) {
         if (wave < SYNC_EARLY) {
             peers[wave][0][lane] = sla;
@@ -1228,7 +1286,8 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
     if (wave != 0) return;
     a = red[0][0][lane];
     b = red[0][1][lane];
-#pragma unroll
+    constexpr int UN = SRC == SRC_X ? 5 : W;      // (with all waves' sums on their way at once SRC_X would spill)
+#pragma unroll UN
     for (int w = 1; w < W; ++w) {
         a += red[w][0][lane];
         b += red[w][1][lane];
@@ -1246,7 +1305,11 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
         for (int w = 1; w < W; ++w) sq += red_ss[w][lane];
         sq += shfl_xor_f(sq, 16);
         sq += shfl_xor_f(sq, 32);
-        rs = 1.0f / sqrtf(sq / (float)epi.h + epi.eps);
+        if constexpr (SRC == SRC_X) {
+            if (pair == 0 && lane < 16) parts.ss[ks * 16 + lane] = sq;
+        } else {
+            rs = 1.0f / sqrtf(sq / (float)epi.h + epi.eps);
+        }
     }
     if constexpr (MODE == 2) {
         epi.slice(pair, ks, 0, a, b, lane, rs, pre);
@@ -2116,7 +2179,8 @@ __device__ __forceinline__ void load_q(bf16x8 *qf, const __bf16 *__restrict__ qb
 // cache's bf16, appends them to the cache and attends to them as one more (single-key) block.
 template <int DT, bool FUSED>
 __global__ void __launch_bounds__(256) k_attn_decode(const __bf16 *__restrict__ qbuf_in, const __bf16 *__restrict__ qlo_in,
-                                                     const float *__restrict__ qkvp, int KS, int part_rows, int nqkv, __bf16 *__restrict__ qbuf_out,
+                                                     const float *__restrict__ qkvp, int KS, int part_rows, int nqkv,
+                                                     const float *__restrict__ xss, float xh, float xeps, __bf16 *__restrict__ qbuf_out,
                                                      __bf16 *__restrict__ qlo_out, __bf16 *__restrict__ kc, __bf16 *__restrict__ vc,
                                                      AttnParts parts, spd_positions P, int q, int kv, int max_ctx) {
     constexpr int d = DT * 16;
@@ -2178,6 +2242,12 @@ __global__ void __launch_bounds__(256) k_attn_decode(const __bf16 *__restrict__ 
     }
     bf16x8 qf[DT];
     if constexpr (FUSED) {
+        float xrs = 1.f;
+        if (xss) {
+            float t = xss[b];
+            for (int j = 1; j < KS; ++j) t += xss[j * 16 + b];
+            xrs = 1.0f / sqrtf(t / xh + xeps);
+        }
         auto add_slices = [&](const float4 *v) {
             float4 acc = v[0];
 #pragma unroll
@@ -2185,6 +2255,7 @@ __global__ void __launch_bounds__(256) k_attn_decode(const __bf16 *__restrict__ 
                 const float on = j < KS ? 1.f : 0.f;      // a clamped repeat of the last slice counts for nothing
                 acc.x += on * v[j].x; acc.y += on * v[j].y; acc.z += on * v[j].z; acc.w += on * v[j].w;
             }
+            if (xss) { acc.x *= xrs; acc.y *= xrs; acc.z *= xrs; acc.w *= xrs; }
             return acc;
         };
 #pragma unroll
@@ -2503,10 +2574,13 @@ hipError_t launch_gemv(const spd_call &c, const __bf16 *Wp, const __bf16 *Xhi, c
 constexpr int QKV_SLICE_W = 16;
 template <class Epi>
 hipError_t launch_gemv_sliced(const spd_call &c, bool split, const __bf16 *Wp, const __bf16 *Xhi, size_t plane, int n_pairs,
-                              int KT, int KS, const Epi &epi) {
+                              int KT, int KS, const Epi &epi, const RawX &raw) {
     constexpr int W = QKV_SLICE_W;
     const __bf16 *Xlo = Xhi + plane;
-    if (split)
+    if (raw.x)
+        hipLaunchKernelGGL((k_gemv<W, false, 2, Epi, SRC_X>), dim3(n_pairs, KS), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT, KS,
+                           (float *)nullptr, 16, epi, raw);
+    else if (split)
         hipLaunchKernelGGL((k_gemv<W, true, 2, Epi>), dim3(n_pairs, KS), dim3(W * 64), 0, c.s, Wp, Xhi, Xlo, KT, KS,
                            (float *)nullptr, 16, epi, NoParts());
     else
@@ -2712,11 +2786,11 @@ hipError_t launch_o(const spd_call &c, bool split, const __bf16 *Wp, const __bf1
         static std::once_flag once;
         static hipError_t attr_err = hipSuccess;
         std::call_once(once, [] {
-            attr_err = hipFuncSetAttribute((const void *)k_gemv<W, false, 0, EpiOT<MID>, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            attr_err = hipFuncSetAttribute((const void *)k_gemv<W, false, 0, EpiOT<MID>, SRC_MERGE>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            W * GEMV_MERGE_TILES * 1024);
         });
         if (attr_err != hipSuccess) return attr_err;
-        hipLaunchKernelGGL((k_gemv<W, false, 0, EpiOT<MID>, true>), dim3(n_pairs, 1), dim3(W * 64), KT * 1024, c.s, Wp, Xhi, Xlo, KT, 1,
+        hipLaunchKernelGGL((k_gemv<W, false, 0, EpiOT<MID>, SRC_MERGE>), dim3(n_pairs, 1), dim3(W * 64), KT * 1024, c.s, Wp, Xhi, Xlo, KT, 1,
                            (float *)nullptr, 16, epi, merge);
         return hipGetLastError();
     }
@@ -2798,7 +2872,37 @@ inline ProjW proj_weights(const spd_call &c, const char *w, int i) {
     p.wsc = (const float *)(w + D.w_scale) + i;
     return p;
 }
+// K slices of the QKV projection that the attention kernel adds up itself, 1: none.
+// A decode step whose QKV projection has too few column tiles to occupy the chip: K slices with the linear epilogue (at
+// most SPD_MAX_QKV_SLICES), whose partial rows the attention kernel adds itself.  Up to 16 sequences about 240
+// workgroups of 16 waves, at least two k-tiles per wave; more of them, about 480 of the skinny kernel's 8 waves (two fit a compute unit).
+// (Also where gemv_whole() would contract K in one launch: the slices cost no second kernel here.  hidden 2048, 96 pairs,
+// slices / whole, us per layer: 4 sequences of 4000 positions 52 / 53.6, 8: 67.5 / 70, 16: 102 / 104.5.)
+int decode_qkv_slices(const spd_call &c) {
+    const spd_dims &D = *c.D;
+    const int n_mtiles = (c.M + 15) / 16, qkv_pairs = D.nqkv / 32;
+    int qkv_slices = 1;
+    if (c.q_len == 1 && n_mtiles <= 4 && qkv_pairs < GEMV_MANY_PAIRS) {
+        const int want = n_mtiles == 1 ? (240 + qkv_pairs - 1) / qkv_pairs : 480 / qkv_pairs;
+        qkv_slices = want < 2 ? 2 : (want > SPD_MAX_QKV_SLICES ? SPD_MAX_QKV_SLICES : want);
+        const int most = D.h / 32 / (2 * (n_mtiles == 1 ? QKV_SLICE_W : SKINNY_W));
+        if (qkv_slices > most) qkv_slices = most;
+        while (qkv_slices > 1 && (size_t)qkv_slices * 16 * n_mtiles * D.nqkv > (size_t)SPD_MAX_KPART * 512) --qkv_slices;
+    }
+    return qkv_slices;
+}
 }  // namespace
+
+// A decode step of up to 16 sequences in slices can take the residual stream itself: no launch for the first norm's elementwise part, for
+// twice the activation bytes.  us per call of one layer, launch / this: 7B 1 sequence 37.6 / 35.5, 4: 40.5 / 38.1, 16: 40.7 / 39.4; 13B 8: 44.4 / 42.9; 70B 1: 57.6 /
+// 55.7, 16: 60.7 / 59.7.
+// Up to 8 sequences (with weights from HBM 16 of 70B, 4 layers, lost 252.1 / 253.8) and one round of the chip (7B 4-way, 288 workgroups, 4: 51.6 / 52.1, 8:
+// 55.3 / 57.0).
+bool qkv_reads_x(const spd_call &c) {
+    if (c.q_len != 1 || c.M > 8 || c.sp_x || c.stages != SPD_ALL_STAGES || c.timer) return false;
+    const int KS = decode_qkv_slices(c);
+    return KS > 1 && KS * (c.D->nqkv / 32) <= 256;
+}
 
 hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const float *x, int spd, float *slot,
                           const spd_mid_sync *mid, bool *mid_done) {
@@ -2812,23 +2916,15 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
     float *ybuf = (float *)(c.ws + D.ws_y);
     const ProjW wqkv = proj_weights(c, w, 0), wo = proj_weights(c, w, 1);
 
-    // A decode step whose QKV projection has too few column tiles to occupy the chip: K slices with the linear epilogue (at
-    // most SPD_MAX_QKV_SLICES), whose partial rows the attention kernel adds itself.  Up to 16 sequences about 240
-    // workgroups of 16 waves, at least two k-tiles per wave; more of them, about 480 of the skinny kernel's 8 waves (two fit a compute unit).
-    // (Also where gemv_whole() would contract K in one launch: the slices cost no second kernel here.  hidden 2048, 96 pairs,
-    // slices / whole, us per layer: 4 sequences of 4000 positions 52 / 53.6, 8: 67.5 / 70, 16: 102 / 104.5.)
-    const int n_mtiles = (M + 15) / 16, qkv_pairs = D.nqkv / 32;
-    int qkv_slices = 1;
-    if (c.q_len == 1 && n_mtiles <= 4 && qkv_pairs < GEMV_MANY_PAIRS) {
-        const int want = n_mtiles == 1 ? (240 + qkv_pairs - 1) / qkv_pairs : 480 / qkv_pairs;
-        qkv_slices = want < 2 ? 2 : (want > SPD_MAX_QKV_SLICES ? SPD_MAX_QKV_SLICES : want);
-        const int most = D.h / 32 / (2 * (n_mtiles == 1 ? QKV_SLICE_W : SKINNY_W));
-        if (qkv_slices > most) qkv_slices = most;
-        while (qkv_slices > 1 && (size_t)qkv_slices * 16 * n_mtiles * D.nqkv > (size_t)SPD_MAX_KPART * 512) --qkv_slices;
-    }
+    const int n_mtiles = (M + 15) / 16, qkv_pairs = D.nqkv / 32, qkv_slices = decode_qkv_slices(c);
     const bool fused_q = qkv_slices > 1;
     float *qkvp = (float *)(c.ws + D.ws_kpart);
+    RawX raw = {};
     if (fused_q) {
+        if (c.raw_x) {
+            raw.x = c.raw_x; raw.gain = (const float *)(w + D.w_g1);
+            raw.ss = (float *)(c.ws + D.ws_ss1);           // (h / 32 rows of at least 16 tokens: room for the slices)
+        }
         EpiQKVPart e1;
         e1.M = M; e1.q_len = c.q_len; e1.q = D.q; e1.kv = D.kv; e1.d = D.d; e1.h = D.h; e1.nqkv = D.nqkv;
         e1.nch = c.nch1; e1.m_pad = D.m_pad; e1.part_rows = 16 * n_mtiles; e1.eps = D.eps;
@@ -2839,7 +2935,7 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
         if (c.on(SPD_STAGE_QKV)) {
             spd_stage_scope prof(c, SPD_STAGE_QKV);
             if (n_mtiles == 1)
-                SPD_TRY(launch_gemv_sliced(c, c.sp_x, wqkv.w, xhat, D.pl_x, qkv_pairs, D.h / 32, qkv_slices, e1));
+                SPD_TRY(launch_gemv_sliced(c, c.sp_x, wqkv.w, xhat, D.pl_x, qkv_pairs, D.h / 32, qkv_slices, e1, raw));
             else
                 SPD_TRY(launch_skinny<2>(c, c.sp_x, wqkv.w, xhat, D.pl_x, qkv_pairs, D.h / 32, e1, qkv_slices));
         }
@@ -2895,11 +2991,11 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
 #define SPD_DECODE(DTV)                                                                                              \
     if (fused_q)                                                                                                     \
         hipLaunchKernelGGL((k_attn_decode<DTV, true>), grid, dim3(256), 0, c.s, (const __bf16 *)nullptr,             \
-                           (const __bf16 *)nullptr, qkvp, qkv_slices, 16 * n_mtiles, D.nqkv, qbuf, qlo, kc, vc, parts, c.pos, D.q, D.kv, \
+                           (const __bf16 *)nullptr, qkvp, qkv_slices, 16 * n_mtiles, D.nqkv, raw.ss, (float)D.h, D.eps, qbuf, qlo, kc, vc, parts, c.pos, D.q, D.kv, \
                            D.max_ctx);                                                                               \
     else                                                                                                             \
         hipLaunchKernelGGL((k_attn_decode<DTV, false>), grid, dim3(256), 0, c.s, qbuf, qlo, (const float *)nullptr, 1, 16,   \
-                           D.nqkv, (__bf16 *)nullptr, (__bf16 *)nullptr, kc, vc, parts, c.pos, D.q, D.kv, D.max_ctx)
+                           D.nqkv, (const float *)nullptr, 1.f, 0.f, (__bf16 *)nullptr, (__bf16 *)nullptr, kc, vc, parts, c.pos, D.q, D.kv, D.max_ctx)
         switch (DT) {
             case 2: SPD_DECODE(2); break;
             case 4: SPD_DECODE(4); break;

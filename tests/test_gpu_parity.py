@@ -410,6 +410,30 @@ def test_bf16_decode_merge_of_splits(gpu, heads, kv_heads, head_dim, batches, fl
     _one_rank_block(gpu, w, 1, 1, [2300], flag)
 
 
+# decode steps whose QKV projection reads the residual stream itself (up to 8 sequences, slices in one round of the chip): waves with one to six of its
+# k-tiles (161 in two slices; 64 in two), the first number of sequences beyond; the output in the input's place
+QKV_161 = Workload(name="qkv-161-k-tiles", hidden=5152, n_q_heads=20, n_kv_heads=20, head_dim=128, ffn=64, n_layers=1, tp=2, dtype=BF16,
+                   seed=50, batch=1, q_len=1, ctx=64, mask=(1,))
+
+
+@pytest.mark.parametrize("w", [QKV_161, QKV_96], ids=lambda w: w.name)
+@pytest.mark.parametrize("flag", [1, 0], ids=["spd", "tp"])
+@pytest.mark.parametrize("batch", [1, 5, 8, 9])
+def test_bf16_decode_first_norm_in_qkv(gpu, w, flag, batch):
+    import torch
+    positions = [(11 * i) % 61 for i in range(batch)]
+    _one_rank_block(gpu, w, batch, 1, positions, flag, max_ctx=64)
+    case = Case(w, gpu, ranks=range(w.tp), positions=positions, max_ctx=64, max_tokens=batch)
+    X = inputs.hidden_states(w, batch)
+    x, slots = case.to_dev(X), torch.zeros((w.tp, batch, w.hidden), dtype=torch.float32, device=gpu)
+    B.spd_block_forward(case.dev.ctx, 0, flag, B.SPD_ALL_RANKS, case.dev.weights[0], case.dev.kv[0], positions, batch, 1, x, slots, x,
+                        case.dev.workspace)
+    torch.cuda.synchronize()
+    want, _ = O.block_all_ranks(case.sh, X, case.shards[0], case.caches[0], positions, batch, 1, flag, {})
+    assert_close(x.cpu().numpy(), want, w, "block output, all ranks")
+    case.close()
+
+
 # decode QKV projections of 192 pairs and more, which the attention kernel does not add up: one launch up to 160 k-tiles
 QKV_192 = Workload(name="qkv-192-pairs", hidden=5120, n_q_heads=32, n_kv_heads=32, head_dim=128, ffn=256, n_layers=1, tp=2, dtype=BF16,
                    seed=40, batch=1, q_len=1, ctx=64, mask=(1,))
