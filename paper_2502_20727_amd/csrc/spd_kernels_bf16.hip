@@ -1087,7 +1087,8 @@ struct GemvSet {
 };
 
 // SRC_MERGE: the input is the attention's output, merged here from the splits' states: every workgroup merges all of it, a thread
-// four features of a (token, head), into fragments in LDS while its weights are on their way.
+// four features of a (token, head), into fragments in LDS while its weights are on their way.  SRC_MERGE3: up to three such quads per thread and
+// 8 splits; the splits' factors of a (token, head) are computed once, by one thread, and go through LDS.
 // SRC_X: the input is the residual stream itself, the first norm's elementwise part done on the way; every slice leaves its sums of squares
 // in ss[slice][16], and whoever adds the slices applies the factor.
 struct NoParts {};
@@ -1100,9 +1101,10 @@ struct GemvSetX {
     float4 x0, x1, g0, g1;
 };
 constexpr int GEMV_MERGE_TILES = 5;      // k-tiles per wave
-enum { SRC_PACKED, SRC_MERGE, SRC_X };
+enum { SRC_PACKED, SRC_MERGE, SRC_X, SRC_MERGE3 };
 template <int SRC> struct GemvSrc { typedef NoParts type; };
 template <> struct GemvSrc<SRC_MERGE> { typedef AttnParts type; };
+template <> struct GemvSrc<SRC_MERGE3> { typedef AttnParts type; };
 template <> struct GemvSrc<SRC_X> { typedef RawX type; };
 template <int W, bool SPLIT, int MODE, class Epi, int SRC = SRC_PACKED>     // MODE 0: whole K, 1: slices -> kpart, 2: slices -> Epi::slice
 __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, const __bf16 *__restrict__ Xhi,
@@ -1233,13 +1235,34 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
     } else {
         static_assert(!SPLIT && MODE == 0, "merged input: one plane, whole K");
         extern __shared__ __attribute__((aligned(16))) char merged[];          // [KT] fragments (rows past the call: anything)
-        constexpr int CH = 16;
+        constexpr bool ONE = SRC == SRC_MERGE;
+        constexpr int CH = ONE ? 16 : 8, NI = ONE ? 1 : 3;
         // (states first: what returns in order behind them may take its time)
-        const int per_tok = KT * 8, n_items = epi.M * per_tok, hq = parts.d >> 2;      // (hq divides per_tok)
-        const int e = min((int)threadIdx.x, n_items - 1), tok = e / per_tok, head = (e % per_tok) / hq, quad = e % hq;
-        const int u = tok * (per_tok / hq / parts.group) + head / parts.group, c = head % parts.group;
+        const int per_tok = KT * 8, n_items = epi.M * per_tok, hq = parts.d >> 2, heads = per_tok / hq;      // (hq divides per_tok)
+        auto unit = [&](int th) { return th / heads * (heads / parts.group) + th % heads / parts.group; };    // of (token, head) th
+        auto column = [&](int th) { return th % heads % parts.group; };
         MergeLoads<CH> L;
-        L.load(parts, u, c, quad, 0);
+        float4 o[ONE ? 1 : NI][CH];
+        const int e = min((int)threadIdx.x, n_items - 1), n_th = epi.M * heads;
+        __shared__ __attribute__((aligned(16))) float fac[ONE ? 1 : W * 64][CH];
+        if constexpr (ONE) {
+            L.load(parts, unit(e / hq), column(e / hq), e % hq, 0);
+        } else {
+            const int th = min((int)threadIdx.x, n_th - 1);
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                const float *ml = parts.max_sum(unit(th), min(j, parts.n_splits - 1), column(th));
+                L.m[j] = ml[0];
+                L.l[j] = ml[parts.group];
+            }
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const int ei = min(e + i * W * 64, n_items - 1);
+#pragma unroll
+                for (int j = 0; j < CH; ++j)
+                    o[i][j] = *(const float4 *)(parts.sums(unit(ei / hq), min(j, parts.n_splits - 1), column(ei / hq)) + 4 * (ei % hq));
+            }
+        }
         SPD_SCHED_BARRIER();
         GemvSet<false> R[GEMV_MERGE_TILES];
         const int n = k1 - k0;
@@ -1252,10 +1275,41 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
         SPD_SCHED_BARRIER();
         between();
         SPD_SCHED_BARRIER();
-        if ((int)threadIdx.x < n_items) {
-            const float4 v = merge_splits<CH>(parts, u, c, quad, L);
-            const int k = 4 * (e % per_tok);
-            *(bf16x4 *)(merged + (k >> 5) * 1024 + 2 * spd_frag_elem(tok, k & 31)) = cvt4h(v.x, v.y, v.z, v.w);
+        auto put = [&](int item, float4 v) {
+            const int k = 4 * (item % per_tok);
+            *(bf16x4 *)(merged + (k >> 5) * 1024 + 2 * spd_frag_elem(item / per_tok, k & 31)) = cvt4h(v.x, v.y, v.z, v.w);
+        };
+        if constexpr (ONE) {
+            if ((int)threadIdx.x < n_items) put(e, merge_splits<CH>(parts, unit(e / hq), column(e / hq), e % hq, L));
+        } else {
+            float mc = -INFINITY, den = 0.f;
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                if (j >= parts.n_splits) L.m[j] = -INFINITY;
+                mc = fmaxf(mc, L.m[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                L.m[j] = L.m[j] == -INFINITY ? 0.f : __expf(L.m[j] - mc);
+                den += L.l[j] * L.m[j];
+            }
+            if ((int)threadIdx.x < n_th) {
+#pragma unroll
+                for (int j = 0; j < CH; ++j) fac[threadIdx.x][j] = L.m[j] / den;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const int ei = (int)threadIdx.x + i * W * 64;
+                if (ei >= n_items) break;
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                for (int j = 0; j < CH; ++j) {
+                    const float f = fac[ei / hq][j];
+                    v.x += o[i][j].x * f; v.y += o[i][j].y * f; v.z += o[i][j].z * f; v.w += o[i][j].w * f;
+                }
+                put(ei, v);
+            }
         }
         __syncthreads();
 #pragma unroll
@@ -2760,14 +2814,16 @@ inline bool sync_in_o(int n_pairs, int KT, int tp, int n_mtiles) {
 }
 
 // Does a decode step's O projection merge the attention's splits itself, instead of a kernel in between?  Every workgroup then reads
-// all states, so only where that is a quad of features per thread and 200 KB at most.  us per call, kernel of its own / in the projection: 7B 1
-// sequence of 2000 positions 38.8 / 37.5, 2: 39.3 / 37.9, 4 (512 quads, 131 KB): 41.4 / 40.5, 1 of 16000 47.3 / 45.6; 70B 1 of 4096 (32 splits,
-// 131 KB) 60.8 / 59.8; with two or three quads per thread: 7B 8 sequences 40.5 / 41.4, 13B 8 of 4096, 4 layers 219.1 / 225.7.
+// all states, so only where that is 200 KB at most: a quad of features per thread, or up to three of up to 8 splits.  us per call, kernel of its
+// own / in the projection: 7B 1 sequence of 2000 positions 38.8 / 37.5, 2: 39.3 / 37.9, 4 (512 quads, 131 KB): 41.4 / 40.5, 1 of 16000 47.3 / 45.6; 70B 1 of
+// 4096 (32 splits, 131 KB) 60.8 / 59.8; three quads: 13B 8 of 4096, 4 layers 216.0 / 213.5, 7B 6 of 3000 42.7 / 42.0, 70B 4 of 1000 57.5 / 56.6 (every
+// thread with the factors of its own quads: 219.1 / 225.7, 8 sequences of 7B 40.5 / 41.4).
 constexpr int GEMV_MERGE_W = 8;
 inline bool merge_in_o(const spd_call &c, int n_pairs, int KT, int n_splits) {
     const int quads = c.M * KT * 8;
     if (c.M > 16 || c.sp_a || c.taps || !c.on(SPD_STAGE_ATTN) || !c.on(SPD_STAGE_O)) return false;
-    if (KT > GEMV_MERGE_W * GEMV_MERGE_TILES || n_pairs < 96 || quads > GEMV_MERGE_W * 64) return false;
+    if (KT > GEMV_MERGE_W * GEMV_MERGE_TILES || n_pairs < 96) return false;
+    if (quads > GEMV_MERGE_W * 64 && (quads > 3 * GEMV_MERGE_W * 64 || n_splits > 8)) return false;
     return (int64_t)quads * n_splits * 16 <= 200 * 1024;
 }
 
@@ -2786,12 +2842,17 @@ hipError_t launch_o(const spd_call &c, bool split, const __bf16 *Wp, const __bf1
         static std::once_flag once;
         static hipError_t attr_err = hipSuccess;
         std::call_once(once, [] {
-            attr_err = hipFuncSetAttribute((const void *)k_gemv<W, false, 0, EpiOT<MID>, SRC_MERGE>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           W * GEMV_MERGE_TILES * 1024);
+            for (const void *k : {(const void *)k_gemv<W, false, 0, EpiOT<MID>, SRC_MERGE>, (const void *)k_gemv<W, false, 0, EpiOT<MID>, SRC_MERGE3>})
+                if (attr_err == hipSuccess)
+                    attr_err = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, W * GEMV_MERGE_TILES * 1024);
         });
         if (attr_err != hipSuccess) return attr_err;
-        hipLaunchKernelGGL((k_gemv<W, false, 0, EpiOT<MID>, SRC_MERGE>), dim3(n_pairs, 1), dim3(W * 64), KT * 1024, c.s, Wp, Xhi, Xlo, KT, 1,
-                           (float *)nullptr, 16, epi, merge);
+        if (c.M * KT * 8 <= W * 64)
+            hipLaunchKernelGGL((k_gemv<W, false, 0, EpiOT<MID>, SRC_MERGE>), dim3(n_pairs, 1), dim3(W * 64), KT * 1024, c.s, Wp, Xhi, Xlo, KT, 1,
+                               (float *)nullptr, 16, epi, merge);
+        else
+            hipLaunchKernelGGL((k_gemv<W, false, 0, EpiOT<MID>, SRC_MERGE3>), dim3(n_pairs, 1), dim3(W * 64), KT * 1024, c.s, Wp, Xhi, Xlo, KT, 1,
+                               (float *)nullptr, 16, epi, merge);
         return hipGetLastError();
     }
     if (n_mtiles == 1)

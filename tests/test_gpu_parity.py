@@ -397,9 +397,10 @@ def test_bf16_short_call_of_a_wide_model(gpu, q_len, flag):
     _one_rank_block(gpu, ROWS_65, 1, q_len, [0], flag)
 
 
-# decode steps whose O projection merges the attention's splits itself (at most 512 quads of features, 40 k-tiles) and the first beyond: one k-tile
+# decode steps whose O projection merges the attention's splits itself (one or up to three quads of features per thread, 512 and 1536 of them; 40 k-tiles)
+# and the first beyond: one k-tile
 # (waves without any), 9, 32, 40 and 41; groups of 1, 3 and 4 heads; an empty cache, and more than 16 splits
-@pytest.mark.parametrize("heads,kv_heads,head_dim,batches", [(2, 2, 32, (1, 16)), (6, 2, 96, (7, 8)), (16, 4, 128, (2, 3)), (80, 80, 32, (1, 2)),
+@pytest.mark.parametrize("heads,kv_heads,head_dim,batches", [(2, 2, 32, (1, 16)), (6, 2, 96, (7, 8, 16)), (16, 4, 128, (2, 3, 6, 7)), (80, 80, 32, (1, 2)),
                                                              (82, 82, 32, (1,))], ids=["1-k-tile", "9", "32", "40", "41"])
 @pytest.mark.parametrize("flag", [1, 0], ids=["spd", "tp"])
 def test_bf16_decode_merge_of_splits(gpu, heads, kv_heads, head_dim, batches, flag):
