@@ -435,6 +435,31 @@ def test_bf16_decode_first_norm_in_qkv(gpu, w, flag, batch):
     case.close()
 
 
+# The first norm's product x * gain is rounded to fp16 once, in the QKV projection (up to 8 sequences) as in the preparation's launch: every second
+# element is (1 + 2^-12)^2, a little above a tie of fp16, the others are 1 and counted with the other sign.  The values are then
+# the sum of 1024 times 2^-10; of products rounded to 32 bits first, which are ties and become 1, they are 0.
+@pytest.mark.parametrize("batch", [1, 8, 9])
+def test_bf16_decode_first_norm_rounds_once(gpu, batch):
+    import torch
+    w = Workload(name="round-once", hidden=2048, n_q_heads=4, n_kv_heads=2, head_dim=64, ffn=64, n_layers=1, tp=1, dtype=BF16, seed=51,
+                 batch=1, q_len=1, ctx=32, mask=(1,))
+    shard = B.DeviceShard(w, [0], gpu, max_ctx=32, max_tokens=batch, max_batch=batch)
+    s = inputs.layer_shard(w, 0, 0)
+    s["g1"] = np.ones(w.hidden, np.float32)
+    s["g1"][::2] += 2.0 ** -12
+    s["wv"] = np.full_like(s["wv"], 1.0)
+    s["wv"][1::2] = -1.0
+    shard.load_layer(0, [s])
+    x = torch.from_numpy(np.tile(s["g1"], (batch, 1))).to(gpu)
+    slots, out = torch.zeros((1, batch, w.hidden), dtype=torch.float32, device=gpu), torch.empty_like(x)
+    B.spd_block_forward(shard.ctx, 0, 1, 0, shard.weights[0], shard.kv[0], [0] * batch, batch, 1, x, slots, out, shard.workspace)
+    torch.cuda.synchronize()
+    _, v = B.spd_kv_unpack(shard.ctx, shard.kv[0].cpu().numpy(), batch, 1, w.kv_per_rank, w.head_dim)
+    # 2^-8 relative: the value's rounding to bf16; the norm's factor differs from 1 by 3e-4
+    assert np.all(np.abs(np.asarray(v) - 1.0) <= 2.0 ** -8 + 1e-3), np.asarray(v).ravel()[:4]
+    shard.close()
+
+
 # decode QKV projections of 192 pairs and more, which the attention kernel does not add up: one launch up to 160 k-tiles
 QKV_192 = Workload(name="qkv-192-pairs", hidden=5120, n_q_heads=32, n_kv_heads=32, head_dim=128, ffn=256, n_layers=1, tp=2, dtype=BF16,
                    seed=40, batch=1, q_len=1, ctx=64, mask=(1,))
