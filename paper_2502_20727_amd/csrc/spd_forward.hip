@@ -163,12 +163,8 @@ int f32_ranks_side_by_side(const spd_call &c, const uint8_t *mask, int n_layers,
     return SPD_OK;
 }
 
-// bf16 path: the first norm of the call's first block, left to its QKV projection or prepared by a launch of its own
+// bf16 path: the first norm of the call's first block
 hipError_t first_norm(spd_call &c, const float *x_in, const char *w) {
-    if (spd_bf16::qkv_reads_x(c)) {
-        c.raw_x = x_in;
-        return hipSuccess;
-    }
     c.nch1 = spd_bf16::prep_chunks(c);
     return spd_bf16::prep(c, x_in, nullptr, 0, nullptr, (const float *)(w + c.D->w_g1), true, 0);
 }
@@ -223,7 +219,10 @@ int block_forward_impl(const spd_ctx *ctx, int32_t layer, int32_t spd_flag, int3
     const spd_dims &D = ctx->D;
     c.taps = taps;
     const char *w = (const char *)packed_weights;
-    if (D.dtype == SPD_BF16) SPD_HIP(first_norm(c, x_in, w));
+    if (D.dtype == SPD_BF16) {
+        if (spd_bf16::qkv_reads_x(c)) c.raw_x = x_in;
+        else SPD_HIP(first_norm(c, x_in, w));
+    }
     {
         const uint8_t mask = (uint8_t)spd_flag;
         bool done = false;
@@ -376,7 +375,6 @@ int spd_model_forward_staged(const spd_ctx *ctx, const uint8_t *spd_mask, int32_
             const int rc2 = block_core(ctx, h.c, spd_mask[l], rank, (const char *)layer_weights[l],
                                        (char *)layer_kv[l] + h.kv_off, h.x, h.slots, &base, &bias, &kept, h.x_out, g1, &end_done);
             if (rc2 != SPD_OK) return rc2;
-            h.c.raw_x = nullptr;                       // (the first block's)
             if (k == 0) syncs += kept;
             // end-of-block sync point; in the bf16 path it also prepares the next block's first norm
             if (end_done) {

@@ -2962,13 +2962,17 @@ int decode_qkv_slices(const spd_call &c) {
 }
 }  // namespace
 
-// A decode step of up to 16 sequences in slices can take the residual stream itself: no launch for the first norm's elementwise part, for
-// twice the activation bytes.  us per call of one layer, launch / this: 7B 1 sequence 37.6 / 35.5, 4: 40.5 / 38.1, 16: 40.7 / 39.4; 13B 8: 44.4 / 42.9; 70B 1: 57.6 /
-// 55.7, 16: 60.7 / 59.7.
-// Up to 8 sequences (with weights from HBM 16 of 70B, 4 layers, lost 252.1 / 253.8) and one round of the chip (7B 4-way, 288 workgroups, 4: 51.6 / 52.1, 8:
-// 55.3 / 57.0).
+// A block call of a decode step of up to 8 sequences whose QKV projection runs in slices takes the residual stream itself: no launch for
+// the first norm's elementwise part, for twice the activation bytes.  us per call, launch / this: 7B 1 sequence 37.6 / 35.5, 4: 40.5 / 38.1; 13B 8: 44.4 /
+// 42.9, 4-way 65.5 / 64.1; 70B 1: 57.6 / 55.7, 4-way 91.8 / 89.6.
+// Not beyond 8 sequences (with weights from HBM 16 of 70B, 4 layers, 252.1 / 253.8), nor beyond one round of the chip (7B 4-way, 288
+// workgroups, 4: 51.6 / 52.1, 8: 55.3 / 57.0).
+// Not in a model call, whose other blocks get their first norm from the block before: 2 us once, and the norm's factor, applied to the slices'
+// sum instead of every slice, is another order of 32-bit operations, which through the fp16 activations of the blocks that follow
+// changes the call's output by as much as its rounding (13B, 8 sequences, four layers, slots: 6.5e-4 of an error of 7.4e-4
+// on either side).
 bool qkv_reads_x(const spd_call &c) {
-    if (c.q_len != 1 || c.M > 8 || c.sp_x || c.stages != SPD_ALL_STAGES || c.timer) return false;
+    if (c.q_len != 1 || c.M > 8 || c.sp_x) return false;
     const int KS = decode_qkv_slices(c);
     return KS > 1 && KS * (c.D->nqkv / 32) <= 256;
 }

@@ -435,6 +435,30 @@ def test_bf16_decode_first_norm_in_qkv(gpu, w, flag, batch):
     case.close()
 
 
+# A timer on a stage, or the blocks' outputs asked for, leave a call's launches as they are: the same bits
+@pytest.mark.parametrize("batch", [1, 5, 8, 9])
+def test_bf16_timed_call_is_the_ordinary_call(gpu, batch):
+    import torch
+    w = Workload(name="timed", hidden=2048, n_q_heads=16, n_kv_heads=16, head_dim=128, ffn=256, n_layers=2, tp=2, dtype=BF16, seed=52, batch=1,
+                 q_len=1, ctx=64, mask=(1, 0))
+    positions = [(13 * i + 9) % 61 for i in range(batch)]
+    case = Case(w, gpu, ranks=[1], positions=positions, max_ctx=64, max_tokens=batch)
+    x, peers = case.to_dev(inputs.hidden_states(w, batch)), case.to_dev(inputs.peer_slots(w, batch)).reshape(w.tp, batch, w.hidden)
+    got = []
+    for stage in [None, "layer_out"] + list(range(B.SPD_ALL_STAGES.bit_length())):
+        timer = B.spd_stage_timer_create(stage, 8) if isinstance(stage, int) else None
+        slots, out = peers.clone(), torch.empty_like(x)
+        kw = {} if stage is None else {"timer": timer} if timer else {"layer_out": torch.empty((2, batch, w.hidden), device=gpu)}
+        f = B.spd_model_forward if stage is None else B.spd_model_forward_staged
+        f(case.dev.ctx, w.mask, 1, case.dev.weights, case.dev.kv, positions, batch, 1, x, slots, out, case.dev.workspace, **kw)
+        torch.cuda.synchronize()
+        if timer:
+            B.spd_stage_timer_destroy(timer)
+        got.append((out, slots))
+        assert torch.equal(out, got[0][0]) and torch.equal(slots, got[0][1]), stage
+    case.close()
+
+
 # The first norm's product x * gain is rounded to fp16 once, in the QKV projection (up to 8 sequences) as in the preparation's launch: every second
 # element is (1 + 2^-12)^2, a little above a tie of fp16, the others are 1 and counted with the other sign.  The values are then
 # the sum of 1024 times 2^-10; of products rounded to 32 bits first, which are ties and become 1, they are 0.
