@@ -1097,7 +1097,8 @@ struct GemvSet {
 
 // SRC_MERGE: the input is the attention's output, merged here from the splits' states: every workgroup merges all of it, a thread
 // four features of a (token, head), into fragments in LDS while its weights are on their way.  SRC_MERGE3: up to three such quads per thread and
-// 8 splits; the splits' factors of a (token, head) are computed once, by one thread, and go through LDS.
+// 8 splits; the splits' factors of a (token, head) and their sum are computed once, by one thread, and go through LDS.  The arithmetic is
+// k_attn_combine's for as many splits, operation for operation.
 // SRC_X: the input is the residual stream itself, the first norm's elementwise part done on the way; every slice leaves its sums of squares
 // in ss[slice][16], and whoever adds the slices applies the factor.
 struct NoParts {};
@@ -1253,6 +1254,7 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
         float4 o[ONE ? 1 : NI][CH];
         const int e = min((int)threadIdx.x, n_items - 1), n_th = epi.M * heads;
         __shared__ __attribute__((aligned(16))) float fac[ONE ? 1 : W * 64][CH];
+        __shared__ float2 dens[ONE ? 1 : W * 64];
         if constexpr (ONE) {
             L.load(parts, unit(e / hq), column(e / hq), e % hq, 0);
         } else {
@@ -1303,7 +1305,8 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
             }
             if ((int)threadIdx.x < n_th) {
 #pragma unroll
-                for (int j = 0; j < CH; ++j) fac[threadIdx.x][j] = L.m[j] / den;
+                for (int j = 0; j < CH; ++j) fac[threadIdx.x][j] = L.m[j];
+                dens[threadIdx.x] = make_float2(den, 1.0f / den);
             }
             __syncthreads();
 #pragma unroll
@@ -1316,7 +1319,13 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
                     const float f = fac[ei / hq][j];
                     v.x += o[i][j].x * f; v.y += o[i][j].y * f; v.z += o[i][j].z * f; v.w += o[i][j].w * f;
                 }
-                put(ei, v);
+                // v / den as a division rounds it: the quotient by the reciprocal, corrected by its remainder
+                const float2 dn = dens[ei / hq];
+                auto quotient = [&](float n) {
+                    const float q = n * dn.y, r = __builtin_fmaf(-dn.x, q, n);
+                    return __builtin_isfinite(q) ? __builtin_fmaf(r, dn.y, q) : q;
+                };
+                put(ei, make_float4(quotient(v.x), quotient(v.y), quotient(v.z), quotient(v.w)));
             }
         }
         __syncthreads();
@@ -2829,7 +2838,7 @@ inline bool sync_in_o(int n_pairs, int KT, int tp, int n_mtiles) {
 constexpr int GEMV_MERGE_W = 8;
 inline bool merge_in_o(const spd_call &c, int n_pairs, int KT, int n_splits) {
     const int quads = c.M * KT * 8;
-    if (c.M > 16 || c.sp_a || c.taps || !c.on(SPD_STAGE_ATTN) || !c.on(SPD_STAGE_O)) return false;
+    if (c.M > 16 || c.sp_a) return false;
     if (KT > GEMV_MERGE_W * GEMV_MERGE_TILES || n_pairs < 96) return false;
     if (quads > GEMV_MERGE_W * 64 && (quads > 3 * GEMV_MERGE_W * 64 || n_splits > 8)) return false;
     return (int64_t)quads * n_splits * 16 <= 200 * 1024;
@@ -3038,10 +3047,7 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
     const int DT = D.d / 16;
     AttnParts parts = {};
     bool merge_o = false;
-    spd_stage_begin(c, SPD_STAGE_ATTN);
-    if (!c.on(SPD_STAGE_ATTN)) {
-        // skipped
-    } else if (c.q_len == 1) {
+    if (c.q_len == 1) {
         // key blocks per workgroup (4 waves, so multiples of 4): the number of rounds the launch takes
         // on 256 compute units times the length of a round, a round costing about 5 blocks' worth of
         // start-up besides its blocks
@@ -3060,7 +3066,13 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
         }
         parts.o = (float *)(c.ws + D.ws_apart);
         parts.units = units; parts.n_splits = splits; parts.group = D.group; parts.d = D.d;
-        const dim3 grid(splits, D.kv, c.batch);
+        merge_o = merge_in_o(c, D.h / 32, qd / 32, splits);
+    }
+    spd_stage_begin(c, SPD_STAGE_ATTN);
+    if (!c.on(SPD_STAGE_ATTN)) {
+        // skipped
+    } else if (c.q_len == 1) {
+        const dim3 grid(parts.n_splits, D.kv, c.batch);
 #define SPD_DECODE(DTV)                                                                                              \
     if (fused_q)                                                                                                     \
         hipLaunchKernelGGL((k_attn_decode<DTV, true>), grid, dim3(256), 0, c.s, (const __bf16 *)nullptr,             \
@@ -3078,9 +3090,8 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
         }
 #undef SPD_DECODE
         SPD_TRY(hipGetLastError());
-        merge_o = merge_in_o(c, D.h / 32, qd / 32, splits);
-        if (!merge_o) {
-            hipLaunchKernelGGL(k_attn_combine, dim3(cdiv(D.group * D.d / 4, 64), units), dim3(64), 0, c.s, parts, ahat, alo, D.kv, c.batch);
+        if (!merge_o || c.taps) {      // (a tapped call also wants what the O projection would keep to itself)
+            hipLaunchKernelGGL(k_attn_combine, dim3(cdiv(D.group * D.d / 4, 64), parts.units), dim3(64), 0, c.s, parts, ahat, alo, D.kv, c.batch);
             SPD_TRY(hipGetLastError());
         }
     } else {

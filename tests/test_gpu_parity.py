@@ -411,6 +411,57 @@ def test_bf16_decode_merge_of_splits(gpu, heads, kv_heads, head_dim, batches, fl
     _one_rank_block(gpu, w, 1, 1, [2300], flag)
 
 
+# Taps leave the launches as they are where the O projection merges the splits (the tapped attention output comes from the merging kernel's launch
+# beside it): the same bits with and without taps.  One, two and three quads per thread, and more splits than the first chunk of 16.
+@pytest.mark.parametrize("heads,batch,pos", [(2, 3, 700), (8, 4, 500), (8, 6, 900), (8, 1, 3000)])
+def test_bf16_tapped_call_is_the_ordinary_call(gpu, heads, batch, pos):
+    import torch
+    w = Workload(name="tapped", hidden=3072, n_q_heads=heads, n_kv_heads=heads // 2, head_dim=128, ffn=256, n_layers=1, tp=1, dtype=BF16, seed=53,
+                 batch=1, q_len=1, ctx=64, mask=(1,))
+    for seed in range(4):
+        positions = [pos - 97 * ((i + seed) % 5) for i in range(batch)]
+        case = Case(w, gpu, ranks=[0], positions=positions, max_ctx=(pos + 32) // 32 * 32, max_tokens=batch)
+        X = inputs.hidden_states(w, batch) * (1 + seed)
+        got = []
+        for tapped in (False, True):
+            slots = torch.zeros((1, batch, w.hidden), dtype=torch.float32, device=gpu)
+            x = case.to_dev(X)
+            if tapped:
+                got.append((_block_with_taps(case, 0, 1, 0, x, slots, batch, 1, positions)[0], slots))
+            else:
+                out = torch.empty_like(x)
+                B.spd_block_forward(case.dev.ctx, 0, 1, 0, case.dev.weights[0], case.dev.kv[0], positions, batch, 1, x, slots, out, case.dev.workspace)
+                got.append((out, slots))
+            torch.cuda.synchronize()
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), seed
+        case.close()
+
+
+# A call with only the O projection's stage launches what the ordinary call launches, on what that call left: its partial sums come out again
+@pytest.mark.parametrize("heads,batch,pos", [(4, 3, 700), (16, 6, 900), (16, 16, 900)])
+def test_bf16_o_stage_alone(gpu, heads, batch, pos):
+    import torch
+    w = Workload(name="o-alone", hidden=3072, n_q_heads=heads, n_kv_heads=heads // 2, head_dim=128, ffn=256, n_layers=1, tp=2, dtype=BF16, seed=54,
+                 batch=1, q_len=1, ctx=64, mask=(0,))
+    positions = [pos - 97 * (i % 5) for i in range(batch)]
+    x = torch.from_numpy(inputs.hidden_states(w, batch)).to(gpu)
+    got = []
+    for ahat_of in (0, 1):               # another call in between, whose attention output must not be what the O projection reads
+        case = Case(w, gpu, ranks=[0], positions=positions, max_ctx=(pos + 32) // 32 * 32, max_tokens=batch)
+        peers = case.to_dev(inputs.peer_slots(w, batch)).reshape(w.tp, batch, w.hidden)
+        args = lambda xx, sl: (case.dev.ctx, w.mask, 0, case.dev.weights, case.dev.kv, positions, batch, 1, xx, sl, torch.empty_like(xx), case.dev.workspace)
+        if ahat_of:
+            B.spd_model_forward(*args(x * -2.0 + 1.0, peers.clone()))
+        B.spd_model_forward(*args(x, peers.clone()))
+        slots = peers.clone()
+        B.spd_model_forward_staged(*args(x, slots), stage_mask=1 << 3)
+        torch.cuda.synchronize()
+        got.append(slots[0])
+        case.close()
+    assert torch.isfinite(got[0]).all() and float(got[0].abs().max()) > 0
+    assert torch.equal(got[0], got[1])
+
+
 # decode steps whose QKV projection reads the residual stream itself (up to 8 sequences, slices in one round of the chip): waves with one to six of its
 # k-tiles (161 in two slices; 64 in two), the first number of sequences beyond; the output in the input's place
 QKV_161 = Workload(name="qkv-161-k-tiles", hidden=5152, n_q_heads=20, n_kv_heads=20, head_dim=128, ffn=64, n_layers=1, tp=2, dtype=BF16,
