@@ -46,8 +46,12 @@ void spd_stage_timer_destroy(spd_stage_timer *timer);
  *               call.  With a single bit a whole-model call becomes a train of launches of one
  *               stage's kernel over every layer's distinct weights (its inputs are whatever an
  *               earlier full call left in the workspace, its outputs are meaningless): the way to
- *               time a kernel on its own without the whole layer fitting a cache.
- *   timer       NULL, or a timer whose stage's launches are to be bracketed by events.
+ *               time a kernel on its own without the whole layer fitting a cache.  An operation that a
+ *               launch does besides its own stage's (a sum over the ranks on the way in, the merge of
+ *               the attention's splits) belongs to that launch's stage.  fp32 calls too large to run their
+ *               ranks side by side launch every kernel but the sums that end the blocks, and time nothing.
+ *   timer       NULL, or a timer whose stage's launches are to be bracketed by events.  Neither it nor
+ *               layer_out nor taps (spd.h) change which kernels compute the outputs.
  *   layer_out   NULL, or device fp32 [n_layers][batch*q_len, hidden]: receives every block's output (a
  *               device-to-device copy after each block), so that a test can check a deep model block by block.
  * SPD_EINVAL for bits beyond SPD_ALL_STAGES; otherwise as spd_model_forward(). */

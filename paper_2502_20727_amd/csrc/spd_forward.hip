@@ -138,28 +138,36 @@ int block_core(const spd_ctx *ctx, spd_call &c, int spd, int32_t rank, const cha
     return SPD_OK;
 }
 
-// fp32 path, small calls: n_layers blocks with all ranks of the call in each launch, and every sum over the ranks but the last one in
-// the launch that reads it.  Returns through *done whether the call is of that kind.
+// fp32 path, small calls: n_layers blocks with all ranks of the call in each launch, and the sums over the ranks but the last one mostly in
+// the launch that reads them.  Returns through *done whether the call is of that kind.
 // The residual stream moves between rbuf and x_out: a sum is written where no workgroup of its launch reads.
 int f32_ranks_side_by_side(const spd_call &c, const uint8_t *mask, int n_layers, int32_t rank, const void *const *layer_weights,
-                           void *const *layer_kv, const float *x_in, float *slots, float *x_out, bool *done) {
+                           void *const *layer_kv, const float *x_in, float *slots, float *x_out, float *layer_out, bool *done) {
     const spd_dims &D = *c.D;
     const bool all = rank == SPD_ALL_RANKS;
     const int n = all ? D.tp : 1;
-    *done = D.dtype == SPD_F32 && !c.taps && !c.timer && c.stages == SPD_ALL_STAGES && spd_f32::ranks_fit(c, n);
+    *done = D.dtype == SPD_F32 && spd_f32::ranks_fit(c, n);
     if (!*done) return SPD_OK;
     float *rbuf = (float *)(c.ws + D.ws_r);
     const float *cur = x_in;                  // the stream's present place (x_in may be x_out)
     auto next = [&]() { return cur == rbuf ? x_out : rbuf; };
+    auto tap = [&](int l, const float *x) {   // test tap: every block's output
+        return layer_out ? hipMemcpyAsync(layer_out + l * c.slot_stride, x, c.slot_stride * 4, hipMemcpyDeviceToDevice, c.s) : hipSuccess;
+    };
     spd_f32::spd_sum x = {x_in, nullptr, 0, nullptr, nullptr};
     for (int l = 0; l < n_layers; ++l) {
         const char *w = (const char *)layer_weights[l];
         if (x.n) cur = x.out = next();
         SPD_HIP(spd_f32::block_ranks(c, w, (char *)layer_kv[l], n, mask[l], slots + (all ? 0 : (size_t)rank * c.slot_stride), slots, &x, next(),
                                      D.o_bias ? (const float *)(w + D.w_bo) : nullptr));
+        if (l) SPD_HIP(tap(l - 1, cur));
         cur = x.base;
     }
-    SPD_HIP(spd_common::rank_sum(x.base, slots, D.tp, (int64_t)c.slot_stride, x_out, c.s, x.bias, D.h));
+    if (c.on(SPD_STAGE_PREP)) {
+        spd_stage_scope prof(c, SPD_STAGE_PREP);
+        SPD_HIP(spd_common::rank_sum(x.base, slots, D.tp, (int64_t)c.slot_stride, x_out, c.s, x.bias, D.h));
+    }
+    SPD_HIP(tap(n_layers - 1, x_out));
     return SPD_OK;
 }
 
@@ -226,7 +234,7 @@ int block_forward_impl(const spd_ctx *ctx, int32_t layer, int32_t spd_flag, int3
     {
         const uint8_t mask = (uint8_t)spd_flag;
         bool done = false;
-        const int rc1 = f32_ranks_side_by_side(c, &mask, 1, rank, &packed_weights, &kv_cache, x_in, slots, x_out, &done);
+        const int rc1 = f32_ranks_side_by_side(c, &mask, 1, rank, &packed_weights, &kv_cache, x_in, slots, x_out, nullptr, &done);
         if (rc1 != SPD_OK || done) return rc1;
     }
     const float *base = nullptr, *bias = nullptr;
@@ -299,9 +307,9 @@ int spd_model_forward_staged(const spd_ctx *ctx, const uint8_t *spd_mask, int32_
     const bool bf = D.dtype == SPD_BF16;
     int64_t syncs = 0;
 
-    if (!layer_out) {
+    {
         bool done = false;
-        const int rc1 = f32_ranks_side_by_side(c, spd_mask, L, rank, layer_weights, layer_kv, x_in, slots, x_out, &done);
+        const int rc1 = f32_ranks_side_by_side(c, spd_mask, L, rank, layer_weights, layer_kv, x_in, slots, x_out, layer_out, &done);
         if (rc1 != SPD_OK) return rc1;
         if (done) {
             for (int l = 0; l < L; ++l) syncs += spd_mask[l] ? 1 : 2;

@@ -580,7 +580,7 @@ bool ranks_fit(const spd_call &c, int n_ranks) {
 // One block of `n` ranks side by side in five launches (23 -> 11 of a two-layer model with two ranks).  X is x->base, or the sum
 // *x describes, which is written to x->out; the sum that ends the block is left to the reader of its slots: *x describes it
 // on return.  R: where a TP block's kept sync point puts X + sum of the slots.  Toy model (hidden 256, two layers, two ranks), us per call, one
-// rank after the other with launches of their own for the sums / side by side: 1 token 137 / 68, 32 tokens 142 / 70.
+// rank after the other with launches of their own for the sums / side by side: 1 token 137 / 50, 32 tokens 142 / 51.
 hipError_t block_ranks(const spd_call &c, const char *w, char *kvc, int n, int spd, float *slot0, const float *slots, spd_sum *x, float *R,
                        const float *bo) {
     const spd_dims &D = *c.D;
@@ -589,35 +589,53 @@ hipError_t block_ranks(const spd_call &c, const char *w, char *kvc, int n, int s
     float *qkv = (float *)(c.ws + (n > 1 ? D.ws_rk_qkv : D.ws_qkv)), *att = (float *)(c.ws + (n > 1 ? D.ws_rk_ahat : D.ws_ahat)),
           *u = (float *)(c.ws + (n > 1 ? D.ws_rk_uhat : D.ws_uhat));
     const size_t slot_n = c.slot_stride;
-
-    RowsIn in = rows_in(c, x->base, D.h, 0, (const float *)(w + D.w_g1));
-    in.slots = x->slots; in.slot_stride = slot_n; in.n_slots = x->n; in.bias = x->bias; in.out = x->out;
-    SPD_TRY(launch_rows(c.s, in, (const float *)(w + D.w_qkv), nullptr, D.nqkv, M, D.nqkv, D.h, rows_qkv(c, qkv, mr * D.nqkv, kvc), n));
     const float *X = x->n ? x->out : x->base;
 
-    hipLaunchKernelGGL(k_attention, dim3(M * D.q, n), dim3(TB), (size_t)c.max_pos_end * sizeof(float), c.s, qkv, (const float *)kvc,
-                       (const float *)(kvc + D.kv_v), att, mr * D.nqkv, D.kv_bytes / 4, mr * qd, c.pos, c.q_len, D.q, D.kv, D.d, D.nqkv,
-                       D.max_ctx);
-    SPD_TRY(hipGetLastError());
-
-    RowsO eo;                              // Y_r into the rank's slot
-    eo.y = slot0; eo.y_rank = slot_n; eo.r_out = nullptr; eo.x = nullptr; eo.bias = nullptr; eo.ld = D.h;
-    SPD_TRY(launch_rows(c.s, rows_in(c, att, qd, mr * qd, nullptr), (const float *)(w + D.w_o), nullptr, D.h, M, D.h, qd, eo, n));
-
-    in = rows_in(c, X, D.h, 0, (const float *)(w + D.w_g2));
-    in.bias = bo;
-    if (spd) {                             // R_r = X + Y_r [+ b] (Sec. 4.1.1), needed by this product only
-        in.slots = slot0; in.slot_rank = slot_n; in.n_slots = 1;
-    } else {                               // the kept sync point
-        in.slots = slots; in.slot_stride = slot_n; in.n_slots = D.tp; in.out = R;
+    if (c.on(SPD_STAGE_QKV)) {
+        RowsIn in = rows_in(c, x->base, D.h, 0, (const float *)(w + D.w_g1));
+        in.slots = x->slots; in.slot_stride = slot_n; in.n_slots = x->n; in.bias = x->bias; in.out = x->out;
+        spd_stage_scope prof(c, SPD_STAGE_QKV);
+        SPD_TRY(launch_rows(c.s, in, (const float *)(w + D.w_qkv), nullptr, D.nqkv, M, D.nqkv, D.h, rows_qkv(c, qkv, mr * D.nqkv, kvc), n));
     }
-    RowsGU eg;
-    eg.u = u; eg.u_rank = mr * f; eg.ld = f;
-    SPD_TRY(launch_rows(c.s, in, (const float *)(w + D.w_g), (const float *)(w + D.w_u), f, M, f, D.h, eg, n));
-
-    RowsDown ed;                           // slot = Z_r, or Y_r + Z_r
-    ed.out = slot0; ed.add = spd ? slot0 : nullptr; ed.out_rank = slot_n; ed.ld = D.h;
-    SPD_TRY(launch_rows(c.s, rows_in(c, u, f, mr * f, nullptr), (const float *)(w + D.w_d), nullptr, D.h, M, D.h, f, ed, n));
+    if (c.on(SPD_STAGE_ATTN)) {
+        spd_stage_scope prof(c, SPD_STAGE_ATTN);
+        hipLaunchKernelGGL(k_attention, dim3(M * D.q, n), dim3(TB), (size_t)c.max_pos_end * sizeof(float), c.s, qkv, (const float *)kvc,
+                           (const float *)(kvc + D.kv_v), att, mr * D.nqkv, D.kv_bytes / 4, mr * qd, c.pos, c.q_len, D.q, D.kv, D.d, D.nqkv,
+                           D.max_ctx);
+        SPD_TRY(hipGetLastError());
+    }
+    if (c.on(SPD_STAGE_O)) {
+        RowsO eo;                          // Y_r into the rank's slot
+        eo.y = slot0; eo.y_rank = slot_n; eo.r_out = nullptr; eo.x = nullptr; eo.bias = nullptr; eo.ld = D.h;
+        spd_stage_scope prof(c, SPD_STAGE_O);
+        SPD_TRY(launch_rows(c.s, rows_in(c, att, qd, mr * qd, nullptr), (const float *)(w + D.w_o), nullptr, D.h, M, D.h, qd, eo, n));
+    }
+    if (c.taps) {                          // (of several ranks the last one's)
+        const size_t r = n - 1;
+        if (c.taps->q) SPD_TRY(spd_common::copy2d(qkv + r * mr * D.nqkv, D.nqkv, c.taps->q, qd, M, qd, c.s));
+        if (c.taps->attn) SPD_TRY(spd_common::copy2d(att + r * mr * qd, qd, c.taps->attn, qd, M, qd, c.s));
+        if (c.taps->y) SPD_TRY(spd_common::copy2d(slot0 + r * slot_n, D.h, c.taps->y, D.h, M, D.h, c.s));
+    }
+    if (c.on(SPD_STAGE_GATEUP)) {
+        RowsIn in = rows_in(c, X, D.h, 0, (const float *)(w + D.w_g2));
+        in.bias = bo;
+        if (spd) {                         // R_r = X + Y_r [+ b] (Sec. 4.1.1), needed by this product only
+            in.slots = slot0; in.slot_rank = slot_n; in.n_slots = 1;
+        } else {                           // the kept sync point
+            in.slots = slots; in.slot_stride = slot_n; in.n_slots = D.tp; in.out = R;
+        }
+        RowsGU eg;
+        eg.u = u; eg.u_rank = mr * f; eg.ld = f;
+        spd_stage_scope prof(c, SPD_STAGE_GATEUP);
+        SPD_TRY(launch_rows(c.s, in, (const float *)(w + D.w_g), (const float *)(w + D.w_u), f, M, f, D.h, eg, n));
+    }
+    if (c.taps && c.taps->u) SPD_TRY(spd_common::copy2d(u + (size_t)(n - 1) * mr * f, f, c.taps->u, f, M, f, c.s));
+    if (c.on(SPD_STAGE_DOWN)) {
+        RowsDown ed;                       // slot = Z_r, or Y_r + Z_r
+        ed.out = slot0; ed.add = spd ? slot0 : nullptr; ed.out_rank = slot_n; ed.ld = D.h;
+        spd_stage_scope prof(c, SPD_STAGE_DOWN);
+        SPD_TRY(launch_rows(c.s, rows_in(c, u, f, mr * f, nullptr), (const float *)(w + D.w_d), nullptr, D.h, M, D.h, f, ed, n));
+    }
     x->base = spd ? X : R;
     x->slots = slots;
     x->n = D.tp;

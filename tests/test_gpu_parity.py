@@ -634,9 +634,9 @@ def test_fp32_small_products(gpu, w, flag, batch, q_len, positions):
     case.close()
 
 
-# Small fp32 calls run the ranks side by side, one to eight rows of up to 256, 512 or 1024 elements per workgroup, and perform every sum over
-# the ranks but the last in the launch that reads it.  A call that wants every block's output runs them one after the other with launches of
-# their own for the sums: the same numbers in another order of fp32 sums over K <= 520 (1e-5 of the largest).
+# Small fp32 calls run the ranks side by side, one to eight rows of up to 256, 512 or 1024 elements per workgroup, and perform the sums over
+# the ranks but the last mostly in the launch that reads them: every block against the oracle on the input it had (sums over at most 768 elements in 32
+# bits: 1e-5 of the largest), and the same bits whether the blocks' outputs, a stage's time or nothing is asked for.
 @pytest.mark.parametrize("hidden,ffn", [(96, 1560), (257, 768), (768, 90)], ids=["k520", "k257", "k768"])
 @pytest.mark.parametrize("rank", [None, 1], ids=["all-ranks", "one-rank"])
 @pytest.mark.parametrize("batch,q_len,positions", [(1, 1, [31]), (5, 1, [0, 9, 30, 2, 31]), (1, 33, [3]), (2, 32, [0, 32])], ids=["1", "5", "33", "64"])
@@ -648,19 +648,55 @@ def test_fp32_ranks_side_by_side(gpu, hidden, ffn, rank, batch, q_len, positions
     X, peers = inputs.hidden_states(w, M), inputs.peer_slots(w, M)
     say(f"fp32 side by side: {w.name} rank={rank} {M} tokens")
     got = []
-    for layer_out in (False, True):
+    for how in ("plain", "layer_out", "timer"):
         case = Case(w, gpu, ranks=range(w.tp) if rank is None else [rank], positions=positions, max_ctx=64, max_tokens=M, bias_std=1.0)
         slots = case.to_dev(peers).reshape(w.tp, M, w.hidden)
         x = case.to_dev(X)                       # the output takes the input's place
-        taps = torch.zeros((w.n_layers, M, w.hidden), dtype=torch.float32, device=gpu) if layer_out else None
-        syncs = B.spd_model_forward_staged(case.dev.ctx, w.mask, case.dev.rank_arg(), case.dev.weights, case.dev.kv, positions, batch, q_len, x,
-                                           slots, x, case.dev.workspace, layer_out=taps)
+        outs = torch.zeros((w.n_layers, M, w.hidden), dtype=torch.float32, device=gpu)
+        timer = B.spd_stage_timer_create(4, 16) if how == "timer" else None
+        args = (case.dev.ctx, w.mask, case.dev.rank_arg(), case.dev.weights, case.dev.kv, positions, batch, q_len, x, slots, x, case.dev.workspace)
+        if how == "plain":
+            syncs = B.spd_model_forward(*args)
+        else:
+            syncs = B.spd_model_forward_staged(*args, **({"timer": timer} if timer else {"layer_out": outs}))
         torch.cuda.synchronize()
         assert syncs == 6
+        if timer:
+            assert B.spd_stage_timer_read(timer)[0] == w.n_layers
+            B.spd_stage_timer_destroy(timer)
         got.append([x, slots] + [k.view(torch.float32) for k in case.dev.kv])
+        for a, b in zip(got[0], got[-1]):
+            assert torch.equal(a, b), how
+        if how == "layer_out":
+            outs, xb = outs.cpu().numpy().astype(np.float64), X
+            assert np.array_equal(outs[-1], x.cpu().numpy())
+            for l, flag in enumerate(w.mask):
+                if rank is None:
+                    want, _ = O.block_all_ranks(case.sh, xb, case.shards[l], case.caches[l], positions, batch, q_len, flag, {})
+                else:
+                    want = O.block_single_rank(case.sh, xb, case.shards[l][0], case.caches[l][0], positions, batch, q_len, flag, rank,
+                                               peers.reshape(w.tp, M, w.hidden).astype(np.float64))
+                assert np.max(np.abs(outs[l] - want)) <= 1e-5 * np.max(np.abs(want)), l
+                xb = outs[l].astype(np.float32)
         case.close()
-    for a, b in zip(*got):
-        assert float((a - b).abs().max()) <= 1e-5 * float(b.abs().max())
+
+
+# A block call with taps takes the ordinary call's launches too: the same bits, and the taps against the oracle
+@pytest.mark.parametrize("flag", [1, 0], ids=["spd", "tp"])
+@pytest.mark.parametrize("q_len", [1, 33])
+def test_fp32_tapped_call_is_the_ordinary_call(gpu, flag, q_len):
+    import torch
+    w = workloads.TOY
+    case = Case(w, gpu, ranks=range(w.tp), positions=[5], max_ctx=64, max_tokens=q_len)
+    x = case.to_dev(inputs.hidden_states(w, q_len))
+    slots = torch.zeros((w.tp, q_len, w.hidden), dtype=torch.float32, device=gpu)
+    slots2, out2 = slots.clone(), torch.empty_like(x)
+    out, _ = _block_with_taps(case, 0, flag, B.SPD_ALL_RANKS, x, slots, 1, q_len, [5])
+    B.spd_block_forward(case.dev.ctx, 0, flag, B.SPD_ALL_RANKS, case.dev.weights[0], case.dev.kv[0], [5], 1, q_len, x, slots2, out2,
+                        case.dev.workspace)
+    torch.cuda.synchronize()
+    assert torch.equal(out, out2) and torch.equal(slots, slots2)
+    case.close()
 
 
 # fp32 attention where a thread takes a second key (256 keys and more), the waves' shares end unevenly and the output needs a
