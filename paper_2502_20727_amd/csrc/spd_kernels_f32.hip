@@ -577,6 +577,30 @@ bool ranks_fit(const spd_call &c, int n_ranks) {
            (n_ranks == 1 || (n_ranks <= D.rk_ranks && M <= D.rk_rows));
 }
 
+// A sum over the ranks that a product's rows are made of: in the product's launch, whose every column block then reads the slots of
+// its rows, one slot after the other, or, where that is too much, by a launch of its own ahead of it (the same additions in the same order).
+// us per call of two layers with both sync points, sums in the products / ahead of them: up to 4 MiB of slots read by a launch the first
+// gains (2 ranks, hidden 256, 1 token 48.0 / 49.5; 16, hidden 1024, 4 tokens 72.7 / 77.9; 256, hidden 64, 4 tokens 138 / 155), at
+// 8 to 16 MiB with up to 32 slots too (8, hidden 1024, 16 tokens 72.0 / 77.5; 16 MiB of 8 ranks side by side 103.8 / 110.5), with
+// more of them no longer (64, hidden 1024, 6 MiB 96.9 / 89.4; 128, 8 MiB 143 / 117); from 24 MiB on it loses (16, 24 MiB 82.1 /
+// 79.7; 16 side by side 256 MiB 427 / 249, 1 GiB 1370 / 675).
+constexpr int64_t SUM_INSIDE = (int64_t)16 << 20, SUM_INSIDE_MANY = (int64_t)4 << 20;
+constexpr int SUM_MANY_SLOTS = 32;
+static hipError_t sum_ahead(const spd_call &c, RowsIn &in, int N, int n_ranks) {
+    const spd_dims &D = *c.D;
+    const int64_t bytes = (int64_t)((N + RN - 1) / RN) * n_ranks * in.n_slots * c.M * D.h * 4;
+    if (bytes <= (in.n_slots <= SUM_MANY_SLOTS ? SUM_INSIDE : SUM_INSIDE_MANY)) return hipSuccess;
+    if (c.on(SPD_STAGE_PREP)) {
+        spd_stage_scope prof(c, SPD_STAGE_PREP);
+        SPD_TRY(spd_common::rank_sum(in.a, in.slots, in.n_slots, (int64_t)in.slot_stride, in.out, c.s, in.bias, D.h));
+    }
+    in.a = in.out;
+    in.n_slots = 0;
+    in.slots = in.bias = nullptr;
+    in.out = nullptr;
+    return hipSuccess;
+}
+
 // One block of `n` ranks side by side in five launches (23 -> 11 of a two-layer model with two ranks).  X is x->base, or the sum
 // *x describes, which is written to x->out; the sum that ends the block is left to the reader of its slots: *x describes it
 // on return.  R: where a TP block's kept sync point puts X + sum of the slots.  Toy model (hidden 256, two layers, two ranks), us per call, one
@@ -591,9 +615,10 @@ hipError_t block_ranks(const spd_call &c, const char *w, char *kvc, int n, int s
     const size_t slot_n = c.slot_stride;
     const float *X = x->n ? x->out : x->base;
 
+    RowsIn in = rows_in(c, x->base, D.h, 0, (const float *)(w + D.w_g1));
+    in.slots = x->slots; in.slot_stride = slot_n; in.n_slots = x->n; in.bias = x->bias; in.out = x->out;
+    SPD_TRY(sum_ahead(c, in, D.nqkv, n));
     if (c.on(SPD_STAGE_QKV)) {
-        RowsIn in = rows_in(c, x->base, D.h, 0, (const float *)(w + D.w_g1));
-        in.slots = x->slots; in.slot_stride = slot_n; in.n_slots = x->n; in.bias = x->bias; in.out = x->out;
         spd_stage_scope prof(c, SPD_STAGE_QKV);
         SPD_TRY(launch_rows(c.s, in, (const float *)(w + D.w_qkv), nullptr, D.nqkv, M, D.nqkv, D.h, rows_qkv(c, qkv, mr * D.nqkv, kvc), n));
     }
@@ -616,14 +641,15 @@ hipError_t block_ranks(const spd_call &c, const char *w, char *kvc, int n, int s
         if (c.taps->attn) SPD_TRY(spd_common::copy2d(att + r * mr * qd, qd, c.taps->attn, qd, M, qd, c.s));
         if (c.taps->y) SPD_TRY(spd_common::copy2d(slot0 + r * slot_n, D.h, c.taps->y, D.h, M, D.h, c.s));
     }
+    in = rows_in(c, X, D.h, 0, (const float *)(w + D.w_g2));
+    in.bias = bo;
+    if (spd) {                             // R_r = X + Y_r [+ b] (Sec. 4.1.1), needed by this product only
+        in.slots = slot0; in.slot_rank = slot_n; in.n_slots = 1;
+    } else {                               // the kept sync point
+        in.slots = slots; in.slot_stride = slot_n; in.n_slots = D.tp; in.out = R;
+        SPD_TRY(sum_ahead(c, in, f, n));
+    }
     if (c.on(SPD_STAGE_GATEUP)) {
-        RowsIn in = rows_in(c, X, D.h, 0, (const float *)(w + D.w_g2));
-        in.bias = bo;
-        if (spd) {                         // R_r = X + Y_r [+ b] (Sec. 4.1.1), needed by this product only
-            in.slots = slot0; in.slot_rank = slot_n; in.n_slots = 1;
-        } else {                           // the kept sync point
-            in.slots = slots; in.slot_stride = slot_n; in.n_slots = D.tp; in.out = R;
-        }
         RowsGU eg;
         eg.u = u; eg.u_rank = mr * f; eg.ld = f;
         spd_stage_scope prof(c, SPD_STAGE_GATEUP);

@@ -681,6 +681,36 @@ def test_fp32_ranks_side_by_side(gpu, hidden, ffn, rank, batch, q_len, positions
         case.close()
 
 
+# Where a sum over the ranks is done: in the launch of the product that reads it up to 4 MiB of slots read (16 MiB with up to 32 slots), by a launch of
+# its own beyond (counted by a timer on its stage).  Two layers, the kept sync point and the end of the first block on either side of the lines.
+@pytest.mark.parametrize("tp,rank,M,ffn,launches", [(34, 1, 30, 64, 1), (34, 1, 40, 64, 2), (34, 1, 64, 64, 3), (32, 1, 64, 256, 1), (32, 1, 64, 320, 2),
+                                                    (8, None, 64, 128, 1), (8, None, 64, 192, 2)])
+def test_fp32_sums_over_many_ranks(gpu, tp, rank, M, ffn, launches):
+    import torch
+    w = Workload(name=f"f32-sums-{tp}", hidden=512, n_q_heads=tp, n_kv_heads=tp, head_dim=32, ffn=ffn * tp, n_layers=2, tp=tp, dtype=F32, seed=55,
+                 batch=1, q_len=1, ctx=64, mask=(0, 1))
+    X, peers = inputs.hidden_states(w, M), inputs.peer_slots(w, M)
+    timer = B.spd_stage_timer_create(0, 16)
+    for t in (timer, None):
+        case = Case(w, gpu, ranks=range(tp) if rank is None else [rank], positions=[0], max_ctx=64, max_tokens=M, bias_std=1.0)
+        slots, out = case.to_dev(peers).reshape(tp, M, w.hidden), torch.empty((M, w.hidden), device=gpu)
+        B.spd_model_forward_staged(case.dev.ctx, w.mask, case.dev.rank_arg(), case.dev.weights, case.dev.kv, [0], 1, M, case.to_dev(X), slots, out,
+                                   case.dev.workspace, timer=t)
+        torch.cuda.synchronize()
+        if t:
+            assert B.spd_stage_timer_read(timer)[0] == launches
+        if rank is None:
+            want, _ = O.model_all_ranks(case.sh, X, case.shards, case.caches, [0], 1, M, w.mask)
+        else:
+            p64, want = peers.reshape(tp, M, w.hidden).astype(np.float64), X
+            for l, flag in enumerate(w.mask):
+                want = O.block_single_rank(case.sh, want, case.shards[l][0], case.caches[l][0], [0], 1, M, flag, rank, p64)
+        # (two layers in 32 bits, sums over 512 elements)
+        assert np.max(np.abs(out.cpu().numpy() - want)) <= 2e-5 * np.max(np.abs(want))
+        case.close()
+    B.spd_stage_timer_destroy(timer)
+
+
 # A block call with taps takes the ordinary call's launches too: the same bits, and the taps against the oracle
 @pytest.mark.parametrize("flag", [1, 0], ids=["spd", "tp"])
 @pytest.mark.parametrize("q_len", [1, 33])
