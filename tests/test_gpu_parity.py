@@ -265,11 +265,18 @@ def test_bf16_gemm_contraction_lengths(gpu, w, flag, split, q_len):
     case.close()
 
 
-# 128 x 192 tiles begin in the middle of a group of eight m-tiles: last tiles of 1, 2, 5 and 12 m-tiles, even and odd numbers of k-tiles
+# 128 x 192 tiles begin in the middle of a group of eight m-tiles: last tiles of 1, 2, 5 and 12 m-tiles in the O projection, which is never
+# sliced beyond 512 tokens (66 pairs of n-tiles), with fewer k-tiles than stages (2) and several turns of them, odd and even (15, 16)
+def _long_o(heads):
+    return Workload(name=f"o-{heads}-k-tiles", hidden=2112, n_q_heads=2 * heads, n_kv_heads=2, head_dim=32, ffn=128, n_layers=1, tp=2, dtype=BF16,
+                    seed=56, batch=1, q_len=1, ctx=64, mask=(1,))
+
+
+@pytest.mark.parametrize("w", [KT_ODD, _long_o(15), _long_o(16)], ids=lambda w: w.name)
 @pytest.mark.parametrize("split", [B.SPD_SPLIT_AUTO, B.SPD_SPLIT_ALWAYS], ids=["default", "all-split"])
 @pytest.mark.parametrize("q_len", [577, 608, 656, 768])
-def test_bf16_gemm_tiles_across_groups(gpu, split, q_len):
-    _one_rank_block(gpu, KT_ODD, 1, q_len, [0], q_len % 2, split)
+def test_bf16_gemm_tiles_across_groups(gpu, w, split, q_len):
+    _one_rank_block(gpu, w, 1, q_len, [0], q_len % 2, split)
 
 
 # 65 partial sums of squares per token after a kept attention sync point of more than 512 tokens (hidden sizes that the row-wise
