@@ -2443,10 +2443,10 @@ __global__ void __launch_bounds__(256) k_attn_decode(const __bf16 *__restrict__ 
 }
 
 // merge the splits and write the normalised output as packed activations of the O projection: row = token, contraction index =
-// head*d + dd.  grid (quarters of 64 threads of a unit's group * d / 4 quads, units); every thread reads the maximum and sum of its
+// head*d + dd.  grid (groups of 64 of a unit's group * d / 4 quads, KV heads, sequences); every thread reads the maximum and sum of its
 // head itself (16 splits at a time, all loads issued together), so the kernel is one memory round trip per 16 splits.
-__global__ void __launch_bounds__(64) k_attn_combine(AttnParts parts, __bf16 *__restrict__ ahat, __bf16 *__restrict__ alo, int kv, int batch) {
-    const int hq = parts.d >> 2, u = blockIdx.y, b = u / kv, kvh = u % kv;
+__global__ void __launch_bounds__(64) k_attn_combine(AttnParts parts, __bf16 *__restrict__ ahat, __bf16 *__restrict__ alo) {
+    const int hq = parts.d >> 2, kvh = blockIdx.y, b = blockIdx.z, kv = gridDim.y, batch = gridDim.z, u = b * kv + kvh;
     const int e = blockIdx.x * 64 + threadIdx.x;
     if (e >= parts.group * hq) return;
     const int c = e / hq, quad = e % hq, qd = kv * parts.group * parts.d;
@@ -3091,7 +3091,7 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
 #undef SPD_DECODE
         SPD_TRY(hipGetLastError());
         if (!merge_o || c.taps) {      // (a tapped call also wants what the O projection would keep to itself)
-            hipLaunchKernelGGL(k_attn_combine, dim3(cdiv(D.group * D.d / 4, 64), parts.units), dim3(64), 0, c.s, parts, ahat, alo, D.kv, c.batch);
+            hipLaunchKernelGGL(k_attn_combine, dim3(cdiv(D.group * D.d / 4, 64), D.kv, c.batch), dim3(64), 0, c.s, parts, ahat, alo);
             SPD_TRY(hipGetLastError());
         }
     } else {

@@ -444,6 +444,13 @@ def test_bf16_tapped_call_is_the_ordinary_call(gpu, heads, batch, pos):
         case.close()
 
 
+# more (sequence, KV head) pairs than a launch takes along one dimension of its grid (65536): the merging kernel's is over heads and sequences
+def test_bf16_decode_many_heads_and_sequences(gpu):
+    w = Workload(name="1040-heads", hidden=64, n_q_heads=1040, n_kv_heads=1040, head_dim=32, ffn=32, n_layers=1, tp=1, dtype=BF16, seed=57,
+                 batch=1, q_len=1, ctx=64, mask=(1,))
+    _one_rank_block(gpu, w, 64, 1, [i % 3 for i in range(64)], 1, max_ctx=32, rank=0)
+
+
 # A call with only the O projection's stage launches what the ordinary call launches, on what that call left: its partial sums come out again
 @pytest.mark.parametrize("heads,batch,pos", [(4, 3, 700), (16, 6, 900), (16, 16, 900)])
 def test_bf16_o_stage_alone(gpu, heads, batch, pos):
