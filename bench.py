@@ -85,40 +85,75 @@ def profiled_duration(workload: str, stage: str, kernel: str):
     return None, None, "no DURATION line for this workload and stage"
 
 
+KPART_TILES = 2304 * 8      # partial tiles a workspace holds (SPD_MID_KPART)
+
+
+def cdiv(a, b):
+    return -(-a // b)
+
+
+def finish_kernel(pairs, mt):
+    """The kernel that adds K slices: pairs of n-tiles per workgroup."""
+    n8 = cdiv(pairs, 8) * mt
+    return f"k_mid_finish<{8 if n8 >= 128 else 4 if n8 >= 64 else 2},EpiGU>"
+
+
+def slices(tiles, most, pairs, mt):
+    ks = min(256 // tiles, most)
+    while ks > 1 and pairs * ks * mt > KPART_TILES:
+        ks -= 1
+    return ks
+
+
 def stage_kernel(w, stage: str) -> str:
     """Label of the kernel(s) the library launches for `stage` at this call size (mirrors its dispatch)."""
-    M = w.batch * w.q_len
-    f_pairs = (w.ffn_per_rank + 31) // 32 * 32 // 16
+    if stage != "gateup":
+        return stage
+    M, kt = w.batch * w.q_len, w.hidden // 32
+    pairs = (w.ffn_per_rank + 31) // 32 * 32 // 16
     two_chains = w.q_len > 1 and w.batch >= 2 and (w.batch // 2) * w.q_len >= 1024
-    if stage == "gateup":
-        if M > 512:
-            n16, mt = (2 * f_pairs + 15) // 16, ((M // 2 if two_chains else M) + 15) // 16
-            tiles, halves, tall = n16 * ((mt + 15) // 16), n16 * ((mt + 7) // 8), ((2 * f_pairs + 7) // 8) * ((mt + 23) // 24)
-            use_tall = tiles < 224 and tall <= 256 and tall > tiles
-            if tiles <= 128 and halves <= 256 and halves > (tall if use_tall else tiles):
-                one = "k_gemm_lds<EpiGU,GemmHalf,false>"
-            elif use_tall:
-                one = "k_gemm_lds<EpiGU,GemmTall,false>"
-            else:
-                one = "k_gemm_lds<EpiGU,GemmBig,false>"
-                if tiles > 256 and 0 < tiles % 256 <= 128:
-                    one += "+k_gemm_lds<EpiGU,GemmHalf,false>"
-            return one + ("x2" if two_chains else "")          # x2: one launch per chain of a two-chain prefill
-        if M > 16:
-            kt, mt = w.hidden // 32, (M + 15) // 16
-            tiles, wgs = f_pairs * kt, f_pairs * ((mt + 7) // 8)
-            if M <= 128 and (tiles >= 40 * 1024 or (M > 64 and f_pairs >= 128 and tiles >= 20 * 1024)):
-                return f"k_mid<{2 if M <= 32 else 4 if M <= 64 else 8}>+k_mid_finish<EpiGU>"
-            if (kt <= 128 or (kt <= 160 and f_pairs >= 128) if mt <= 2 else kt <= 32 or (kt <= 64 and f_pairs >= 48) if mt <= 4 else
-                    kt <= 32 if mt <= 8 else (kt <= 48 and wgs <= 512) or (kt <= 96 and 128 <= wgs <= 256)):
-                return f"k_skinny<8,{2 if M <= 32 else 4 if M <= 64 else 8},false,0,EpiGU>"
-            half = M > 128 and (f_pairs >= 64 or (2 * f_pairs + 15) // 16 * ((M + 127) // 128) >= 32)
-            shape = "GemmSmall" if M <= 64 else "GemmHalf" if half else "GemmSquare"
-            return f"k_gemm_lds<EpiPark,{shape},false>+k_mid_finish<EpiGU>"
-        if f_pairs >= 192 or (f_pairs >= 64 and f_pairs % 256 != 0):
-            return "k_gemv<16,2,false,0,EpiGU>"            # 16-column tiles, or the decode-only copy with narrow groups
-        return "k_gemv<8,2,false,1,EpiGU>+k_gemv_finish<EpiGU>"
-    return stage
+    mt = cdiv((w.batch + 1) // 2 * w.q_len if two_chains else M, 16)
+    if M <= 16:
+        want = 256 * cdiv(pairs, 256)
+        cols = cdiv(pairs * 16, want)
+        if pairs >= 64 and want != pairs and cols < 16:      # the decode-only copy with narrow groups
+            pairs = cdiv(pairs * 16, cols)
+        if pairs >= 192 or (pairs >= 96 and 32 <= kt <= 64):
+            return f"k_gemv<{16 if kt >= 32 else 8},false,0,EpiGU,0>"
+        if min(cdiv(512, pairs), max(kt // 16, 1)) <= 1:
+            return "k_gemv<8,false,0,EpiGU,0>"
+        return "k_gemv<8,false,1,EpiGU,0>+k_gemv_finish<EpiGU>"
+    if M <= 128 and (pairs * kt >= 40 * 1024 or (mt > 4 and pairs >= 128 and pairs * kt >= 20 * 1024)):
+        if slices(cdiv(pairs, 8), cdiv(kt, 4) // 4, pairs, mt) >= 2:
+            return f"k_mid<{2 if mt <= 2 else 4 if mt <= 4 else 8}>+" + finish_kernel(pairs, mt)
+    skinny = f"k_skinny<8,{2 if mt <= 2 else 4 if mt <= 4 else 8},false,0,EpiGU>"
+    n16, n8 = cdiv(2 * pairs, 16), cdiv(2 * pairs, 8)
+    halves = n16 * cdiv(mt, 8)
+    if M <= 512:
+        wgs = pairs * cdiv(mt, 8)
+        if (kt <= 128 or (kt <= 160 and pairs >= 128) if mt <= 2 else kt <= 32 or (kt <= 64 and pairs >= 48) if mt <= 4 else
+                kt <= 32 if mt <= 8 else (kt <= 48 and wgs <= 512) or (kt <= 96 and 128 <= wgs <= 256)):
+            return skinny
+    if not two_chains:
+        shape = "GemmSmall" if mt <= 4 else "GemmHalf" if mt > 8 and (pairs >= 64 or halves >= 32) else "GemmSquare"
+        tiles = halves if shape == "GemmHalf" else n8 * cdiv(mt, 4 if shape == "GemmSmall" else 8)
+        if slices(tiles, min(16, kt // 8), pairs, mt) > 1:
+            return f"k_gemm_lds<EpiPark,{shape},false>+" + finish_kernel(pairs, mt)
+    if M <= 512:
+        return "k_gemm_lds<EpiGU,GemmHalf,false>" if mt > 8 and halves >= 128 else skinny
+    big, tall, thirds = n16 * cdiv(mt, 16), n8 * cdiv(mt, 24), n8 * cdiv(mt, 12)
+    use_tall = big < 224 and tall <= 256 and tall > big
+    if big <= 128 and halves <= 256 and thirds <= 256 and thirds > halves:
+        one = "k_gemm_lds<EpiGU,GemmThird,false>"
+    elif big <= 128 and halves <= 256 and halves > (tall if use_tall else big):
+        one = "k_gemm_lds<EpiGU,GemmHalf,false>"
+    elif use_tall:
+        one = "k_gemm_lds<EpiGU,GemmTall,false>"
+    else:
+        one = "k_gemm_lds<EpiGU,GemmBig,false>"
+        if big > 256 and 0 < big % 256 <= 128:
+            one += "+k_gemm_lds<EpiGU,GemmHalf,false>"
+    return one + ("x2" if two_chains else "")          # x2: one launch per chain of a two-chain prefill
 
 
 # ------------------------------------------------------------------------------------------------

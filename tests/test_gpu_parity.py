@@ -1374,6 +1374,61 @@ def test_bf16_two_chain_prefill(gpu):
 
 
 # ------------------------------------------------------------------------------------------------
+# bench.py names the kernels of the gate/up stage it times (and takes their traffic and durations from profiles/ by that name): the names against
+# those of the launches, as a profiler sees them, on every model's shard from one token to two chains
+def _kernel_label(name):
+    """k_name<arguments> of a kernel's mangled or demangled name."""
+    import re
+    m = re.match(r"_ZN12_GLOBAL__N_1(\d+)", name)
+    if not m:
+        return re.sub(r"\(anonymous namespace\)::|^void | ", "", name).split("(")[0]
+    n = int(m[1])
+    base, rest, args = name[m.end():m.end() + n], name[m.end() + n + 1:], []
+    while (t := re.match(r"Li(\d+)E|Lb([01])E|NS_(\d+)", rest)):
+        rest = rest[t.end():]
+        if t[3]:
+            args.append(rest[:int(t[3])])
+            rest = rest[int(t[3]) + 1:]
+        else:
+            args.append(t[1] or ("true" if t[2] == "1" else "false"))
+    return f"{base}<{','.join(args)}>"
+
+
+@pytest.mark.parametrize("model", ["7b-decode", "13b-decode", "70b-decode", "7b-tp4-decode", "13b-tp4-decode"])
+def test_bench_names_the_kernels_it_times(gpu, model):
+    import torch
+    from dataclasses import replace
+    from torch.profiler import ProfilerActivity, profile
+
+    import bench
+    base = workloads.get(model)
+    shapes = [(1, 1), (16, 1), (17, 1), (64, 1)] + [(1, n) for n in (24, 48, 100, 128, 129, 200, 333, 512, 513, 600, 760, 1000, 1500, 2048, 3000, 4096)]
+    shapes += [(2, 1024), (4, 2048)]
+    most = max(b * q for b, q in shapes)
+    shard = B.DeviceShard(replace(base, n_layers=1, mask=(1,)), [0], gpu, max_ctx=4096, max_tokens=most, max_batch=64)
+    shard.weights[0].zero_()
+    x = torch.zeros((most, base.hidden), dtype=torch.float32, device=gpu)
+    slots, out = torch.zeros((base.tp, most, base.hidden), dtype=torch.float32, device=gpu), torch.empty_like(x)
+
+    def call(b, q):
+        B.spd_model_forward_staged(shard.ctx, (1,), 0, shard.weights, shard.kv, [0] * b, b, q, x[:b * q], slots.view(-1)[:base.tp * b * q * base.hidden],
+                                   out[:b * q], shard.workspace, stage_mask=1 << B.STAGES["gateup"])
+
+    call(1, 1)
+    torch.cuda.synchronize()
+    for b, q in shapes:
+        with profile(activities=[ProfilerActivity.CUDA, ProfilerActivity.CPU]) as prof:
+            for _ in range(3):           # (the profiler loses a launch now and then)
+                call(b, q)
+            torch.cuda.synchronize()
+        names = [_kernel_label(e.name) for e in prof.events() if e.device_type != torch.autograd.DeviceType.CPU]
+        names = {n for n in names if n.startswith(("k_gemv", "k_mid", "k_skinny", "k_gemm_lds"))}
+        label = bench.stage_kernel(replace(base, batch=b, q_len=q), "gateup")
+        say(f"{model} {b} x {q}: {label}")
+        assert names == set(label.replace("x2", "").split("+")), (model, b, q, names, label)
+    shard.close()
+
+
 # the launch configuration bench.py times: the whole-model forward replayed from a HIP graph
 # ------------------------------------------------------------------------------------------------
 def _capture(torch, fn):
