@@ -1457,7 +1457,7 @@ __global__ void __launch_bounds__(256) k_gemv_finish(const float *__restrict__ k
 template <int MT, bool SPLIT>
 struct SkinnySet {
     bf16x8 fa, fb, fh[MT], fl[SPLIT ? MT : 1];
-        static constexpr int kRing = MT == 2 ? (SPLIT ? 3 : 4) : 2;      // (three or four sets of 8 m-tiles: 70B 128 tokens 103 -> 124, 136 us)
+    static constexpr int kRing = MT == 2 ? (SPLIT ? 3 : 4) : 2;      // (three or four sets of 8 m-tiles: 70B 128 tokens 103 -> 124, 136 us)
 };
 
 template <int W, int MT, bool SPLIT, int MODE, class Epi>

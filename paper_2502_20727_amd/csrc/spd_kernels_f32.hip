@@ -321,10 +321,16 @@ __global__ void __launch_bounds__(RW * 64) k_rows(RowsIn in, const float *__rest
             for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
             if (lane == 0) ssq[row][wave % P] = sq;
             __syncthreads();
-            sq = ssq[row][0];
+            // (the parts in pairs: the factor is common to the whole row, and with the parts of one token one after the other its rounding
+            // showed in the results, 2.29e-7 instead of 2.16e-7 from 64 bits)
+            float part[P];
 #pragma unroll
-            for (int i = 1; i < P; ++i) sq += ssq[row][i];
-            rs = 1.0f / sqrtf(sq / (float)K + in.eps);
+            for (int i = 0; i < P; ++i) part[i] = ssq[row][i];
+#pragma unroll
+            for (int n = P / 2; n > 0; n /= 2)
+#pragma unroll
+                for (int i = 0; i < n; ++i) part[i] += part[i + n];
+            rs = 1.0f / sqrtf(part[0] / (float)K + in.eps);
         }
 #pragma unroll
         for (int t = 0; t < V; ++t) {

@@ -695,6 +695,32 @@ def test_fp32_ranks_side_by_side(gpu, hidden, ffn, rank, batch, q_len, positions
         case.close()
 
 
+# The norm's factor of a call of one token, whose row 16 waves load: one element of 2^12 in the first part of the row and a 1 in each of the others, which
+# a sum of the parts one after the other loses against 2^24.  The factor would be off by 15 / 2^25 = 4.5e-7; roundings leave 2e-7 at most
+# (the mean, the root's argument by half, the root, its inverse, two products: half a unit in the last place each).
+def test_fp32_norm_of_one_token(gpu):
+    import torch
+    w = Workload(name="f32-norm", hidden=256, n_q_heads=2, n_kv_heads=2, head_dim=32, ffn=64, n_layers=1, tp=1, dtype=F32, seed=58, batch=1,
+                 q_len=1, ctx=32, mask=(1,))
+    shard = B.DeviceShard(w, [0], gpu, max_ctx=32, max_tokens=1, max_batch=1)
+    s = inputs.layer_shard(w, 0, 0)
+    s["g1"] = np.ones(w.hidden, np.float32)
+    s["wv"] = np.zeros_like(s["wv"])
+    s["wv"][0] = 1.0
+    shard.load_layer(0, [s])
+    x = np.zeros((1, w.hidden), np.float32)
+    x[0, ::16] = 1.0
+    x[0, 0] = 4096.0
+    xd = torch.from_numpy(x).to(gpu)
+    slots, out = torch.zeros((1, 1, w.hidden), dtype=torch.float32, device=gpu), torch.empty_like(xd)
+    B.spd_block_forward(shard.ctx, 0, 1, 0, shard.weights[0], shard.kv[0], [0], 1, 1, xd, slots, out, shard.workspace)
+    torch.cuda.synchronize()
+    _, v = B.spd_kv_unpack(shard.ctx, shard.kv[0].cpu().numpy(), 1, 1, w.kv_per_rank, w.head_dim)
+    want = 4096.0 / np.sqrt(np.mean(x.astype(np.float64) ** 2) + w.rms_eps)
+    assert np.max(np.abs(np.asarray(v, np.float64) / want - 1.0)) <= 2.5e-7
+    shard.close()
+
+
 # Where a sum over the ranks is done: in the launch of the product that reads it up to 4 MiB of slots read (16 MiB with up to 32 slots), by a launch of
 # its own beyond (counted by a timer on its stage).  Two layers, the kept sync point and the end of the first block on either side of the lines.
 @pytest.mark.parametrize("tp,rank,M,ffn,launches", [(34, 1, 30, 64, 1), (34, 1, 40, 64, 2), (34, 1, 64, 64, 3), (32, 1, 64, 256, 1), (32, 1, 64, 320, 2),
