@@ -2249,11 +2249,11 @@ __device__ __forceinline__ void load_q(bf16x8 *qf, const __bf16 *__restrict__ qb
 // workgroup of the last split adds the new token: it sums its key and value, rounds them to the
 // cache's bf16, appends them to the cache and attends to them as one more (single-key) block.
 template <int DT, bool FUSED>
-__global__ void __launch_bounds__(256) k_attn_decode(const __bf16 *__restrict__ qbuf_in, const __bf16 *__restrict__ qlo_in,
-                                                     const float *__restrict__ qkvp, int KS, int part_rows, int nqkv,
-                                                     const float *__restrict__ xss, float xh, float xeps, __bf16 *__restrict__ qbuf_out,
-                                                     __bf16 *__restrict__ qlo_out, __bf16 *__restrict__ kc, __bf16 *__restrict__ vc,
-                                                     AttnParts parts, spd_positions P, int q, int kv, int max_ctx) {
+__global__ void __launch_bounds__(256) k_attn_decode(__bf16 *__restrict__ kc, __bf16 *__restrict__ vc, const float *__restrict__ qkvp, int q, int kv,
+                                                     int max_ctx, int KS, int part_rows, int nqkv, const __bf16 *__restrict__ qbuf_in,
+                                                     const __bf16 *__restrict__ qlo_in, const float *__restrict__ xss, float xh, float xeps,
+                                                     __bf16 *__restrict__ qbuf_out, __bf16 *__restrict__ qlo_out, AttnParts parts,
+                                                     spd_positions P) {
     constexpr int d = DT * 16;
     // the waves' states: a column's features side by side (padded, so that the 16 columns begin at different banks)
     __shared__ __attribute__((aligned(16))) float sm[4][16][DT * 16 + 4];
@@ -2445,7 +2445,9 @@ __global__ void __launch_bounds__(256) k_attn_decode(const __bf16 *__restrict__ 
 // merge the splits and write the normalised output as packed activations of the O projection: row = token, contraction index =
 // head*d + dd.  grid (groups of 64 of a unit's group * d / 4 quads, KV heads, sequences); every thread reads the maximum and sum of its
 // head itself (16 splits at a time, all loads issued together), so the kernel is one memory round trip per 16 splits.
-__global__ void __launch_bounds__(64) k_attn_combine(AttnParts parts, __bf16 *__restrict__ ahat, __bf16 *__restrict__ alo) {
+__global__ void __launch_bounds__(64) k_attn_combine(float *po, int units, int n_splits, int group, int d, __bf16 *__restrict__ ahat,
+                                                     __bf16 *__restrict__ alo) {
+    const AttnParts parts = {po, units, n_splits, group, d};
     const int hq = parts.d >> 2, kvh = blockIdx.y, b = blockIdx.z, kv = gridDim.y, batch = gridDim.z, u = b * kv + kvh;
     const int e = blockIdx.x * 64 + threadIdx.x;
     if (e >= parts.group * hq) return;
@@ -2467,9 +2469,8 @@ __global__ void __launch_bounds__(64) k_attn_combine(AttnParts parts, __bf16 *__
 // every wave finishes a quarter of the (tile, 16-feature slice) outputs.
 template <int DT, int CT>
 __global__ void __launch_bounds__(256) k_attn_prefill(const __bf16 *__restrict__ qbuf, const __bf16 *__restrict__ qlo, const __bf16 *__restrict__ kc,
-                                                      const __bf16 *__restrict__ vc, __bf16 *__restrict__ ahat,
-                                                      __bf16 *__restrict__ alo, spd_positions P, int q_len, int q, int kv,
-                                                      int max_ctx) {
+                                                      const __bf16 *__restrict__ vc, int q_len, int q, int kv, int max_ctx,
+                                                      __bf16 *__restrict__ ahat, __bf16 *__restrict__ alo, spd_positions P) {
     constexpr int d = DT * 16;
     extern __shared__ __attribute__((aligned(16))) char ap_lds[];
     f32x4 *so = (f32x4 *)ap_lds;                                   // [4 waves][CT][DT][64 lanes]
@@ -3075,12 +3076,11 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
         const dim3 grid(parts.n_splits, D.kv, c.batch);
 #define SPD_DECODE(DTV)                                                                                              \
     if (fused_q)                                                                                                     \
-        hipLaunchKernelGGL((k_attn_decode<DTV, true>), grid, dim3(256), 0, c.s, (const __bf16 *)nullptr,             \
-                           (const __bf16 *)nullptr, qkvp, qkv_slices, 16 * n_mtiles, D.nqkv, raw.ss, (float)D.h, D.eps, qbuf, qlo, kc, vc, parts, c.pos, D.q, D.kv, \
-                           D.max_ctx);                                                                               \
+        hipLaunchKernelGGL((k_attn_decode<DTV, true>), grid, dim3(256), 0, c.s, kc, vc, qkvp, D.q, D.kv, D.max_ctx, qkv_slices, 16 * n_mtiles, \
+                           D.nqkv, (const __bf16 *)nullptr, (const __bf16 *)nullptr, raw.ss, (float)D.h, D.eps, qbuf, qlo, parts, c.pos);     \
     else                                                                                                             \
-        hipLaunchKernelGGL((k_attn_decode<DTV, false>), grid, dim3(256), 0, c.s, qbuf, qlo, (const float *)nullptr, 1, 16,   \
-                           D.nqkv, (const float *)nullptr, 1.f, 0.f, (__bf16 *)nullptr, (__bf16 *)nullptr, kc, vc, parts, c.pos, D.q, D.kv, D.max_ctx)
+        hipLaunchKernelGGL((k_attn_decode<DTV, false>), grid, dim3(256), 0, c.s, kc, vc, (const float *)nullptr, D.q, D.kv, D.max_ctx, 1, 16,  \
+                           D.nqkv, qbuf, qlo, (const float *)nullptr, 1.f, 0.f, (__bf16 *)nullptr, (__bf16 *)nullptr, parts, c.pos)
         switch (DT) {
             case 2: SPD_DECODE(2); break;
             case 4: SPD_DECODE(4); break;
@@ -3091,7 +3091,8 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
 #undef SPD_DECODE
         SPD_TRY(hipGetLastError());
         if (!merge_o || c.taps) {      // (a tapped call also wants what the O projection would keep to itself)
-            hipLaunchKernelGGL(k_attn_combine, dim3(cdiv(D.group * D.d / 4, 64), D.kv, c.batch), dim3(64), 0, c.s, parts, ahat, alo);
+            hipLaunchKernelGGL(k_attn_combine, dim3(cdiv(D.group * D.d / 4, 64), D.kv, c.batch), dim3(64), 0, c.s, parts.o, parts.units, parts.n_splits,
+                               parts.group, parts.d, ahat, alo);
             SPD_TRY(hipGetLastError());
         }
     } else {
@@ -3110,8 +3111,8 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
             attr_err = hipFuncSetAttribute((const void *)k_attn_prefill<DTV, CT>, hipFuncAttributeMaxDynamicSharedMemorySize, lds); \
         });                                                                                                                \
         SPD_TRY(attr_err);                                                                                                 \
-        hipLaunchKernelGGL((k_attn_prefill<DTV, CT>), grid, dim3(256), lds, c.s, qbuf, qlo, kc, vc, ahat, alo, c.pos, c.q_len, \
-                           D.q, D.kv, D.max_ctx);                                                                          \
+        hipLaunchKernelGGL((k_attn_prefill<DTV, CT>), grid, dim3(256), lds, c.s, qbuf, qlo, kc, vc, c.q_len, D.q, D.kv,  \
+                           D.max_ctx, ahat, alo, c.pos);                                                                   \
     }
 #define SPD_PREFILL(DTV)           \
     if (one) SPD_PREFILL_CT(DTV, 1) \
