@@ -151,13 +151,13 @@ constexpr int ROWS_MAX_WGS = 2048;
 // column block of the first rank leaves in `out` (no workgroup of the launch reads `out`).  So a sync point, and the SPD block's
 // local fold X + Y_r [+ b] (one slot, the rank's own), need no launch of their own.  grid.z is the rank: all ranks a call
 // emulates run side by side, `*_rank` being the distances between their buffers.
+// (Rows of A and W follow each other without gaps.)
 struct RowsIn {
     const float *a;
-    int lda;
-    size_t a_rank;
+    int a_rank;
     const float *gain;           // RMS norm of the row with this gain, or NULL
     float eps;
-    size_t w_rank;               // distance between two ranks' weights (gain included)
+    int w_rank;                  // distance between two ranks' weights (gain included)
     const float *slots = nullptr;
     size_t slot_stride = 0, slot_rank = 0;
     int n_slots = 0;
@@ -249,96 +249,14 @@ struct RowsDown {      // out = [add +] z  (add may be out itself)
 template <int RM>
 struct alignas(RM * 4 < 16 ? RM * 4 : 16) RowsOf { float v[RM]; };
 
-template <int RM, int KMAX, class Epi>      // RM rows of at most KMAX elements per workgroup
-__global__ void __launch_bounds__(RW * 64) k_rows(RowsIn in, const float *__restrict__ W, const float *__restrict__ W2, int ldw, int M, int N,
-                                                  int K, Epi epi) {
+// The product of a workgroup's rows in the LDS, xs [K][RM], with its 64 columns and the epilogue: wave w contracts k0 .. k1 - 1 (the first U
+// weights are on their way, `load` requests U more), the waves' sums meet in `red`, [NB][RW][RM][RN].
+template <int RM, int U, class Epi, int U2, class Load>
+__device__ __forceinline__ void rows_product(const float *xs, float *red, float (*tile)[RM * RN], int k0, int k1, float (&w0)[U], float (&w1)[U2],
+                                             const Load &load, const Epi &epi, bool elem, int er, int cl, int em, int en, int z,
+                                             const typename Epi::Pre &pre) {
     constexpr int NB = Epi::kDual ? 2 : 1;
-    constexpr int P = RW / RM;                          // waves that load a row together
-    constexpr int V = KMAX / P > 64 ? KMAX / P / 64 : 1;      // pieces of 64 elements of a wave's part of a row
-    constexpr int U = KMAX / RW < 32 ? KMAX / RW : 32;  // weight rows that a wave requests at once
-    // rows, transposed: [K][RM], so that what a wave multiplies with one weight is side by side; then the waves' sums
-    // [NB][RW][RM][RN]
-    extern __shared__ __attribute__((aligned(16))) float rows_lds[];
-    __shared__ float ssq[RM][P];
-    __shared__ float tile[NB][RM * RN];
-    float *xs = rows_lds, *red = rows_lds + RM * K;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n0 = blockIdx.x * RN, m0 = blockIdx.y * RM, z = blockIdx.z;
-    const int n = n0 + lane < N ? n0 + lane : N - 1;    // (columns past the matrix repeat its last one and are dropped)
-    // Everything a workgroup reads is requested up front: a launch of this kind is its start and one trip to the memory.
-    // rows: wave w takes part w % P of row w / P (past its end the last element again, not used)
-    const int row = wave / P, hk = (K + P - 1) / P, rb = (wave % P) * hk, re = rb + hk < K ? rb + hk : K;
-    const bool valid = m0 + row < M;
-    float v[V], gn[V], bs[V], sl[V];
-    size_t ro[V];
-#pragma unroll
-    for (int t = 0; t < V; ++t) {
-        const int k = rb + t * 64 + lane;
-        ro[t] = k < re ? k : K - 1;
-        gn[t] = in.gain ? in.gain[z * in.w_rank + ro[t]] : 1.f;
-        bs[t] = in.bias ? in.bias[ro[t]] : 0.f;
-        ro[t] += (size_t)(valid ? m0 + row : 0) * in.lda;
-        v[t] = in.a[z * in.a_rank + ro[t]];
-    }
-    const float *slots = in.slots + z * in.slot_rank;
-#pragma unroll
-    for (int t = 0; t < V; ++t) sl[t] = in.n_slots > 0 ? slots[ro[t]] : 0.f;
-    const int er = (threadIdx.x / RN) % RM, em = m0 + er, en = n0 + (int)threadIdx.x % RN;
-    const bool elem = threadIdx.x < RM * RN && em < M && en < N;
-    const int first = epi.where(em < M ? em : M - 1);
-    const int k0 = (wave * K) / RW, k1 = ((wave + 1) * K) / RW, klast = k1 > k0 ? k1 - 1 : k0;
-    float w0[U], w1[NB == 2 ? U : 1];
-    auto load = [&](int kb) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = kb + u < klast ? kb + u : klast;
-            w0[u] = W[z * in.w_rank + (size_t)k * ldw + n];
-            if constexpr (NB == 2) w1[u] = W2[z * in.w_rank + (size_t)k * ldw + n];
-        }
-    };
-    load(k0);
-    typename Epi::Pre pre;
-    {
-        // the slots in ascending order, then what they join, then the bias
-        for (int s = 1; s < in.n_slots; ++s) {
-#pragma unroll
-            for (int t = 0; t < V; ++t) sl[t] += slots[s * in.slot_stride + ro[t]];
-        }
-        float sq = 0.f;
-#pragma unroll
-        for (int t = 0; t < V; ++t) {
-            const int k = rb + t * 64 + lane;
-            if (in.n_slots > 0) v[t] += sl[t];
-            if (in.bias) v[t] += bs[t];
-            if (in.out && blockIdx.x == 0 && z == 0 && valid && k < re) in.out[ro[t]] = v[t];
-            if (!valid || k >= re) v[t] = 0.f;
-            sq += v[t] * v[t];
-        }
-        if (elem) pre = epi.pre(first, z, em, en);
-        float rs = 1.f;
-        if (in.gain) {
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
-            if (lane == 0) ssq[row][wave % P] = sq;
-            __syncthreads();
-            // (the parts in pairs: the factor is common to the whole row, and with the parts of one token one after the other its rounding
-            // showed in the results, 2.29e-7 instead of 2.16e-7 from 64 bits)
-            float part[P];
-#pragma unroll
-            for (int i = 0; i < P; ++i) part[i] = ssq[row][i];
-#pragma unroll
-            for (int n = P / 2; n > 0; n /= 2)
-#pragma unroll
-                for (int i = 0; i < n; ++i) part[i] += part[i + n];
-            rs = 1.0f / sqrtf(part[0] / (float)K + in.eps);
-        }
-#pragma unroll
-        for (int t = 0; t < V; ++t) {
-            const int k = rb + t * 64 + lane;
-            if (k < re) xs[k * RM + row] = in.gain ? v[t] * rs * gn[t] : v[t];
-        }
-    }
-    __syncthreads();
     float acc[NB][RM];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
@@ -380,7 +298,102 @@ __global__ void __launch_bounds__(RW * 64) k_rows(RowsIn in, const float *__rest
         tile[b][e] = t;
     }
     __syncthreads();
-    if (elem) epi(tile[0], tile[NB - 1], er, en - n0, em, en, z, pre);
+    if (elem) epi(tile[0], tile[NB - 1], er, cl, em, en, z, pre);
+}
+
+// (What the first loads need comes as arguments of its own, which are in registers when a kernel starts: see build.py.  `in` for the rest.)
+template <int RM, int KMAX, class Epi>      // RM rows of at most KMAX elements per workgroup
+__global__ void __launch_bounds__(RW * 64) k_rows(const float *__restrict__ a, const float *__restrict__ W, const float *__restrict__ W2,
+                                                  const float *__restrict__ gain, int K, int N, int M, int n_slots, int a_rank, int w_rank,
+                                                  RowsIn in, Epi epi) {
+    constexpr int NB = Epi::kDual ? 2 : 1;
+    constexpr int P = RW / RM;                          // waves that load a row together
+    constexpr int V = KMAX / P > 64 ? KMAX / P / 64 : 1;      // pieces of 64 elements of a wave's part of a row
+    constexpr int U = KMAX / RW < 32 ? KMAX / RW : 32;  // weight rows that a wave requests at once
+    // rows, transposed: [K][RM], so that what a wave multiplies with one weight is side by side; then the waves' sums
+    // [NB][RW][RM][RN]
+    extern __shared__ __attribute__((aligned(16))) float rows_lds[];
+    __shared__ float ssq[RM][P];
+    __shared__ float tile[NB][RM * RN];
+    float *xs = rows_lds, *red = rows_lds + RM * K;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n0 = blockIdx.x * RN, m0 = blockIdx.y * RM, z = blockIdx.z;
+    const int n = n0 + lane < N ? n0 + lane : N - 1;    // (columns past the matrix repeat its last one and are dropped)
+    // Everything a workgroup reads is requested up front: a launch of this kind is its start and one trip to the memory.
+    // rows: wave w takes part w % P of row w / P (past its end the last element again, not used)
+    const int row = wave / P, hk = (K + P - 1) / P, rb = (wave % P) * hk, re = rb + hk < K ? rb + hk : K;
+    const bool valid = m0 + row < M;
+    float v[V], gn[V], bs[V], sl[V];
+    size_t ro[V];
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+        const int k = rb + t * 64 + lane;
+        ro[t] = k < re ? k : K - 1;
+        gn[t] = gain ? gain[(size_t)z * w_rank + ro[t]] : 1.f;
+        bs[t] = in.bias ? in.bias[ro[t]] : 0.f;
+        ro[t] += (size_t)(valid ? m0 + row : 0) * K;
+        v[t] = a[(size_t)z * a_rank + ro[t]];
+    }
+    const float *slots = in.slots + z * in.slot_rank;
+#pragma unroll
+    for (int t = 0; t < V; ++t) sl[t] = n_slots > 0 ? slots[ro[t]] : 0.f;
+    const int er = (threadIdx.x / RN) % RM, em = m0 + er, en = n0 + (int)threadIdx.x % RN;
+    const bool elem = threadIdx.x < RM * RN && em < M && en < N;
+    const int first = epi.where(em < M ? em : M - 1);
+    const int k0 = (wave * K) / RW, k1 = ((wave + 1) * K) / RW, klast = k1 > k0 ? k1 - 1 : k0;
+    float w0[U], w1[NB == 2 ? U : 1];
+    auto load = [&](int kb) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = kb + u < klast ? kb + u : klast;
+            w0[u] = W[(size_t)z * w_rank + (size_t)k * N + n];
+            if constexpr (NB == 2) w1[u] = W2[(size_t)z * w_rank + (size_t)k * N + n];
+        }
+    };
+    load(k0);
+    typename Epi::Pre pre;
+    {
+        // the slots in ascending order, then what they join, then the bias
+        for (int s = 1; s < n_slots; ++s) {
+#pragma unroll
+            for (int t = 0; t < V; ++t) sl[t] += slots[s * in.slot_stride + ro[t]];
+        }
+        float sq = 0.f;
+#pragma unroll
+        for (int t = 0; t < V; ++t) {
+            const int k = rb + t * 64 + lane;
+            if (n_slots > 0) v[t] += sl[t];
+            if (in.bias) v[t] += bs[t];
+            if (in.out && blockIdx.x == 0 && z == 0 && valid && k < re) in.out[ro[t]] = v[t];
+            if (!valid || k >= re) v[t] = 0.f;
+            sq += v[t] * v[t];
+        }
+        if (elem) pre = epi.pre(first, z, em, en);
+        float rs = 1.f;
+        if (gain) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
+            if (lane == 0) ssq[row][wave % P] = sq;
+            __syncthreads();
+            // (the parts in pairs: the factor is common to the whole row, and with the parts of one token one after the other its rounding
+            // showed in the results, 2.29e-7 instead of 2.16e-7 from 64 bits)
+            float part[P];
+#pragma unroll
+            for (int i = 0; i < P; ++i) part[i] = ssq[row][i];
+#pragma unroll
+            for (int n = P / 2; n > 0; n /= 2)
+#pragma unroll
+                for (int i = 0; i < n; ++i) part[i] += part[i + n];
+            rs = 1.0f / sqrtf(part[0] / (float)K + in.eps);
+        }
+#pragma unroll
+        for (int t = 0; t < V; ++t) {
+            const int k = rb + t * 64 + lane;
+            if (k < re) xs[k * RM + row] = gain ? v[t] * rs * gn[t] : v[t];
+        }
+    }
+    __syncthreads();
+    rows_product<RM, U>(xs, red, tile, k0, k1, w0, w1, load, epi, elem, er, en - n0, em, en, z, pre);
 }
 
 bool rows_fit(int M, int N, int K) {
@@ -388,7 +401,7 @@ bool rows_fit(int M, int N, int K) {
 }
 
 template <int RM, int KMAX, class Epi>
-hipError_t launch_rows_as(hipStream_t s, const RowsIn &in, const float *W, const float *W2, int ldw, int M, int N, int K, const Epi &epi,
+hipError_t launch_rows_as(hipStream_t s, const RowsIn &in, const float *W, const float *W2, int M, int N, int K, const Epi &epi,
                           int n_ranks) {
     constexpr int RED = (Epi::kDual ? 2 : 1) * RW * RM * RN * 4;
     static std::once_flag once;
@@ -397,35 +410,142 @@ hipError_t launch_rows_as(hipStream_t s, const RowsIn &in, const float *W, const
         attr_err = hipFuncSetAttribute((const void *)k_rows<RM, KMAX, Epi>, hipFuncAttributeMaxDynamicSharedMemorySize, RED + RM * KMAX * 4);
     });
     if (attr_err != hipSuccess) return attr_err;
-    hipLaunchKernelGGL((k_rows<RM, KMAX, Epi>), dim3((N + RN - 1) / RN, (M + RM - 1) / RM, n_ranks), dim3(RW * 64), RED + RM * K * 4, s, in, W,
-                       W2, ldw, M, N, K, epi);
+    hipLaunchKernelGGL((k_rows<RM, KMAX, Epi>), dim3((N + RN - 1) / RN, (M + RM - 1) / RM, n_ranks), dim3(RW * 64), RED + RM * K * 4, s, in.a, W,
+                       W2, in.gain, K, N, M, in.n_slots, in.a_rank, in.w_rank, in, epi);
     return hipGetLastError();
 }
 template <int RM, class Epi>
-hipError_t launch_rows_rm(hipStream_t s, const RowsIn &in, const float *W, const float *W2, int ldw, int M, int N, int K, const Epi &epi,
+hipError_t launch_rows_rm(hipStream_t s, const RowsIn &in, const float *W, const float *W2, int M, int N, int K, const Epi &epi,
                           int n_ranks) {
-    if (K <= 256) return launch_rows_as<RM, 256>(s, in, W, W2, ldw, M, N, K, epi, n_ranks);
-    if (K <= 512) return launch_rows_as<RM, 512>(s, in, W, W2, ldw, M, N, K, epi, n_ranks);
-    return launch_rows_as<RM, ROWS_MAX_K>(s, in, W, W2, ldw, M, N, K, epi, n_ranks);
+    if (K <= 256) return launch_rows_as<RM, 256>(s, in, W, W2, M, N, K, epi, n_ranks);
+    if (K <= 512) return launch_rows_as<RM, 512>(s, in, W, W2, M, N, K, epi, n_ranks);
+    return launch_rows_as<RM, ROWS_MAX_K>(s, in, W, W2, M, N, K, epi, n_ranks);
 }
 // The fewest rows per workgroup with which the launch is one round of the chip: a workgroup's vector work grows with its rows (8 rows of
 // 344 elements: 1.3 us), and every group of rows reads the weights again.  Toy model, us per call, 8 rows
 // always / this: 1 token 55.8 / 48.0, 32 tokens 59.2 / 50.5.
-template <class Epi>
-hipError_t launch_rows(hipStream_t s, const RowsIn &in, const float *W, const float *W2, int ldw, int M, int N, int K, const Epi &epi,
-                       int n_ranks = 1) {
+int rows_per_wg(int M, int N, int n_ranks) {
     const int64_t cols = (int64_t)((N + RN - 1) / RN) * n_ranks;
-    if (cols * M <= 256) return launch_rows_rm<1>(s, in, W, W2, ldw, M, N, K, epi, n_ranks);
-    if (cols * ((M + 1) / 2) <= 256) return launch_rows_rm<2>(s, in, W, W2, ldw, M, N, K, epi, n_ranks);
-    if (cols * ((M + 3) / 4) <= 256) return launch_rows_rm<4>(s, in, W, W2, ldw, M, N, K, epi, n_ranks);
-    return launch_rows_rm<8>(s, in, W, W2, ldw, M, N, K, epi, n_ranks);
+    return cols * M <= 256 ? 1 : (cols * ((M + 1) / 2) <= 256 ? 2 : (cols * ((M + 3) / 4) <= 256 ? 4 : 8));
+}
+template <class Epi>
+hipError_t launch_rows(hipStream_t s, const RowsIn &in, const float *W, const float *W2, int M, int N, int K, const Epi &epi,
+                       int n_ranks = 1) {
+    switch (rows_per_wg(M, N, n_ranks)) {
+        case 1: return launch_rows_rm<1>(s, in, W, W2, M, N, K, epi, n_ranks);
+        case 2: return launch_rows_rm<2>(s, in, W, W2, M, N, K, epi, n_ranks);
+        case 4: return launch_rows_rm<4>(s, in, W, W2, M, N, K, epi, n_ranks);
+        default: return launch_rows_rm<8>(s, in, W, W2, M, N, K, epi, n_ranks);
+    }
+}
+
+// The O projection of rows whose attention fits a workgroup: it does that attention itself, for its RM rows and all heads of the rank, instead
+// of a launch in between (every block of 64 columns again).  The 16 waves share out the (row, head) items, `wpi` waves an item; eight lanes
+// take a key, D / 8 features each, up to ROWS_ATT_PASSES keys per group of lanes, and everything is requested up front, the weights included.  The waves' softmax
+// states meet in the LDS.  Toy model (two layers, two ranks, 11 -> 9 launches), us per call, launch of its own / this: 1 token 47.4 / 42.5, 32 tokens
+// 48.7 / 45.8.
+constexpr int ROWS_ATT_PASSES = 2;
+template <int RM, int KMAX, int D>
+__global__ void __launch_bounds__(RW * 64) k_rows_att(const float *__restrict__ qkv, const float *__restrict__ kc, const float *__restrict__ vc,
+                                                      const float *__restrict__ W, int q, int q_len, int kv, int nqkv, int max_ctx, int M, int N,
+                                                      int wpi, int qkv_rank, int w_rank, size_t kv_rank, spd_positions P, RowsO epi) {
+    constexpr int NP = ROWS_ATT_PASSES, F = D / 8;
+    constexpr int U = KMAX / RW < 32 ? KMAX / RW : 32;
+    __shared__ float xs[KMAX * RM], red[RW * RM * RN];
+    __shared__ float tile[1][RM * RN];
+    __shared__ float so[RW][D], sml[RW][2];
+    const int K = q * D;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n0 = blockIdx.x * RN, m0 = blockIdx.y * RM, z = blockIdx.z;
+    const int n = n0 + lane < N ? n0 + lane : N - 1;
+    const int item = wave / wpi < RM * q ? wave / wpi : RM * q - 1, part = wave % wpi;      // (a wave too many repeats the last item and is not used)
+    const int row = item / q, head = item % q, m = m0 + row < M ? m0 + row : M - 1, b = m / q_len;
+    const int n_keys = P.pos[b] + m % q_len + 1;                                             // causal
+    const size_t c0 = z * kv_rank + ((size_t)b * kv + head / (q / kv)) * max_ctx * D + (lane & 7) * F;
+    struct Piece { float v[F]; };
+    auto piece = [](const float *p) { Piece r; __builtin_memcpy(&r, p, sizeof(r)); return r; };       // (the cache is aligned to its elements only)
+    const Piece qv = piece(qkv + (size_t)z * qkv_rank + (size_t)m * nqkv + head * D + (lane & 7) * F);
+    Piece kk[NP], vv[NP];
+    bool live[NP];
+#pragma unroll
+    for (int t = 0; t < NP; ++t) {
+        const int key = (t * wpi + part) * 8 + (lane >> 3);
+        live[t] = key < n_keys;
+        const size_t o = c0 + (size_t)(live[t] ? key : n_keys - 1) * D;
+        kk[t] = piece(kc + o);
+        vv[t] = piece(vc + o);
+    }
+    const int er = (threadIdx.x / RN) % RM, em = m0 + er, en = n0 + (int)threadIdx.x % RN;
+    const bool elem = threadIdx.x < RM * RN && em < M && en < N;
+    const int k0 = (wave * K) / RW, k1 = ((wave + 1) * K) / RW, klast = k1 > k0 ? k1 - 1 : k0;
+    float w0[U], w1[1];
+    auto load = [&](int kb) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) w0[u] = W[(size_t)z * w_rank + (size_t)(kb + u < klast ? kb + u : klast) * N + n];
+    };
+    load(k0);
+    RowsO::Pre pre;
+    if (elem) pre = epi.pre(0, z, em, en);
+    const float scale = 1.0f / sqrtf((float)D);
+    float s[NP], mx = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < NP; ++t) {
+        s[t] = 0.f;
+#pragma unroll
+        for (int f = 0; f < F; ++f) s[t] += qv.v[f] * kk[t].v[f];
+#pragma unroll
+        for (int o = 1; o < 8; o <<= 1) s[t] += __shfl_xor(s[t], o, 64);
+        s[t] = live[t] ? s[t] * scale : -INFINITY;
+        mx = fmaxf(mx, s[t]);
+    }
+#pragma unroll
+    for (int o = 8; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    float sum = 0.f, out[F];
+#pragma unroll
+    for (int f = 0; f < F; ++f) out[f] = 0.f;
+#pragma unroll
+    for (int t = 0; t < NP; ++t) {
+        const float p = live[t] ? expf(s[t] - mx) : 0.f;
+        sum += p;
+#pragma unroll
+        for (int f = 0; f < F; ++f) out[f] += live[t] ? p * vv[t].v[f] : 0.f;
+    }
+#pragma unroll
+    for (int o = 8; o < 64; o <<= 1) {
+        sum += __shfl_xor(sum, o, 64);
+#pragma unroll
+        for (int f = 0; f < F; ++f) out[f] += __shfl_xor(out[f], o, 64);
+    }
+    if (lane < 8) {
+#pragma unroll
+        for (int f = 0; f < F; ++f) so[wave][lane * F + f] = out[f];
+    }
+    if (lane == 0) {
+        sml[wave][0] = mx;
+        sml[wave][1] = sum;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < RM * K; e += RW * 64) {
+        const int it = e / D, f = e % D;
+        float mm = -INFINITY, den = 0.f, num = 0.f;
+        for (int w = it * wpi; w < (it + 1) * wpi; ++w) mm = fmaxf(mm, sml[w][0]);
+        for (int w = it * wpi; w < (it + 1) * wpi; ++w) {
+            if (sml[w][0] == -INFINITY && mm != -INFINITY) continue;             // (no key of its own)
+            const float sc = expf(sml[w][0] - mm);
+            den += sml[w][1] * sc;
+            num += so[w][f] * sc;
+        }
+        xs[(it % q * D + f) * RM + it / q] = num / den;
+    }
+    __syncthreads();
+    rows_product<RM, U>(xs, red, tile, k0, k1, w0, w1, load, epi, elem, er, en - n0, em, en, z, pre);
 }
 
 // One workgroup of 4 waves per (token, query head): causal softmax attention over the cache.  A thread takes a key at a time
 // for the scores; for the output wave w takes keys w, w + 4, ... with lane = feature, and the four sums meet in LDS.
 __global__ void __launch_bounds__(TB) k_attention(const float *__restrict__ qkv, const float *__restrict__ kc, const float *__restrict__ vc,
-                                                  float *__restrict__ out, size_t qkv_rank, size_t kv_rank, size_t out_rank, spd_positions P,
-                                                  int q_len, int q, int kv, int d, int nqkv, int max_ctx) {
+                                                  int q_len, int q, int kv, int d, int nqkv, int max_ctx, float *__restrict__ out,
+                                                  size_t qkv_rank, size_t kv_rank, size_t out_rank, spd_positions P) {
     qkv += blockIdx.y * qkv_rank;          // (grid.y: the rank)
     kc += blockIdx.y * kv_rank;
     vc += blockIdx.y * kv_rank;
@@ -570,9 +690,9 @@ static RowsQKV rows_qkv(const spd_call &c, float *qkv, size_t qkv_rank, char *kv
     e.q_len = c.q_len; e.q = D.q; e.kv = D.kv; e.d = D.d; e.nqkv = D.nqkv; e.max_ctx = D.max_ctx; e.P = c.pos;
     return e;
 }
-static RowsIn rows_in(const spd_call &c, const float *a, int lda, size_t a_rank, const float *gain) {
+static RowsIn rows_in(const spd_call &c, const float *a, size_t a_rank, const float *gain) {
     RowsIn in;
-    in.a = a; in.lda = lda; in.a_rank = a_rank; in.gain = gain; in.eps = c.D->eps; in.w_rank = c.D->weight_bytes / 4;
+    in.a = a; in.a_rank = (int)a_rank; in.gain = gain; in.eps = c.D->eps; in.w_rank = (int)(c.D->weight_bytes / 4);      // (of a few rows: see rows_fit())
     return in;
 }
 
@@ -607,6 +727,40 @@ static hipError_t sum_ahead(const spd_call &c, RowsIn &in, int N, int n_ranks) {
     return hipSuccess;
 }
 
+// Does the O projection of a small call do the attention itself?  Heads of 32 or 64 features, at most 16 (row, head) items a workgroup and as
+// many keys as its lanes take in ROWS_ATT_PASSES rounds.  Returns the waves per item, 0 for a launch of its own.
+static int att_in_o(const spd_call &c, int n_ranks) {
+    const spd_dims &D = *c.D;
+    const int items = rows_per_wg(c.M, D.h, n_ranks) * D.q;
+    if ((D.d != 32 && D.d != 64) || items > RW) return 0;
+    return c.max_pos_end <= RW / items * 8 * ROWS_ATT_PASSES ? RW / items : 0;
+}
+template <int RM>
+static hipError_t launch_rows_att_rm(const spd_call &c, const float *qkv, size_t qkv_rank, const char *kvc, const char *w, const RowsO &epi,
+                                     int n, int wpi) {
+    const spd_dims &D = *c.D;
+    const dim3 grid((D.h + RN - 1) / RN, (c.M + RM - 1) / RM, n);
+#define SPD_ROWS_ATT(KMAX, DD)                                                                                                              \
+    hipLaunchKernelGGL((k_rows_att<RM, KMAX, DD>), grid, dim3(RW * 64), 0, c.s, qkv, (const float *)kvc, (const float *)(kvc + D.kv_v),      \
+                       (const float *)(w + D.w_o), D.q, c.q_len, D.kv, D.nqkv, D.max_ctx, c.M, D.h, wpi, (int)qkv_rank,                      \
+                       (int)(D.weight_bytes / 4), D.kv_bytes / 4, c.pos, epi)
+    // (at most 16 / RM heads)
+    if (D.d == 32) SPD_ROWS_ATT(RW / RM * 32, 32);
+    else if (D.q * 64 <= 256 || RM > 2) SPD_ROWS_ATT(256, 64);
+    else SPD_ROWS_ATT(RW / RM * 64, 64);
+#undef SPD_ROWS_ATT
+    return hipGetLastError();
+}
+static hipError_t launch_rows_att(const spd_call &c, const float *qkv, size_t qkv_rank, const char *kvc, const char *w, const RowsO &epi, int n,
+                                  int wpi) {
+    switch (rows_per_wg(c.M, c.D->h, n)) {
+        case 1: return launch_rows_att_rm<1>(c, qkv, qkv_rank, kvc, w, epi, n, wpi);
+        case 2: return launch_rows_att_rm<2>(c, qkv, qkv_rank, kvc, w, epi, n, wpi);
+        case 4: return launch_rows_att_rm<4>(c, qkv, qkv_rank, kvc, w, epi, n, wpi);
+        default: return launch_rows_att_rm<8>(c, qkv, qkv_rank, kvc, w, epi, n, wpi);
+    }
+}
+
 // One block of `n` ranks side by side in five launches (23 -> 11 of a two-layer model with two ranks).  X is x->base, or the sum
 // *x describes, which is written to x->out; the sum that ends the block is left to the reader of its slots: *x describes it
 // on return.  R: where a TP block's kept sync point puts X + sum of the slots.  Toy model (hidden 256, two layers, two ranks), us per call, one
@@ -621,25 +775,29 @@ hipError_t block_ranks(const spd_call &c, const char *w, char *kvc, int n, int s
     const size_t slot_n = c.slot_stride;
     const float *X = x->n ? x->out : x->base;
 
-    RowsIn in = rows_in(c, x->base, D.h, 0, (const float *)(w + D.w_g1));
+    RowsIn in = rows_in(c, x->base, 0, (const float *)(w + D.w_g1));
     in.slots = x->slots; in.slot_stride = slot_n; in.n_slots = x->n; in.bias = x->bias; in.out = x->out;
     SPD_TRY(sum_ahead(c, in, D.nqkv, n));
     if (c.on(SPD_STAGE_QKV)) {
         spd_stage_scope prof(c, SPD_STAGE_QKV);
-        SPD_TRY(launch_rows(c.s, in, (const float *)(w + D.w_qkv), nullptr, D.nqkv, M, D.nqkv, D.h, rows_qkv(c, qkv, mr * D.nqkv, kvc), n));
+        SPD_TRY(launch_rows(c.s, in, (const float *)(w + D.w_qkv), nullptr, M, D.nqkv, D.h, rows_qkv(c, qkv, mr * D.nqkv, kvc), n));
     }
-    if (c.on(SPD_STAGE_ATTN)) {
+    // (a call of one of the two stages alone keeps a launch for each)
+    const int wpi = att_in_o(c, n);
+    const bool fused = wpi > 0 && c.on(SPD_STAGE_ATTN) && c.on(SPD_STAGE_O);
+    if (c.on(SPD_STAGE_ATTN) && (!fused || c.taps)) {      // (a tapped call also wants what the O projection would keep to itself)
         spd_stage_scope prof(c, SPD_STAGE_ATTN);
         hipLaunchKernelGGL(k_attention, dim3(M * D.q, n), dim3(TB), (size_t)c.max_pos_end * sizeof(float), c.s, qkv, (const float *)kvc,
-                           (const float *)(kvc + D.kv_v), att, mr * D.nqkv, D.kv_bytes / 4, mr * qd, c.pos, c.q_len, D.q, D.kv, D.d, D.nqkv,
-                           D.max_ctx);
+                           (const float *)(kvc + D.kv_v), c.q_len, D.q, D.kv, D.d, D.nqkv, D.max_ctx, att, mr * D.nqkv, D.kv_bytes / 4, mr * qd,
+                           c.pos);
         SPD_TRY(hipGetLastError());
     }
     if (c.on(SPD_STAGE_O)) {
         RowsO eo;                          // Y_r into the rank's slot
         eo.y = slot0; eo.y_rank = slot_n; eo.r_out = nullptr; eo.x = nullptr; eo.bias = nullptr; eo.ld = D.h;
         spd_stage_scope prof(c, SPD_STAGE_O);
-        SPD_TRY(launch_rows(c.s, rows_in(c, att, qd, mr * qd, nullptr), (const float *)(w + D.w_o), nullptr, D.h, M, D.h, qd, eo, n));
+        if (fused) SPD_TRY(launch_rows_att(c, qkv, mr * D.nqkv, kvc, w, eo, n, wpi));
+        else SPD_TRY(launch_rows(c.s, rows_in(c, att, mr * qd, nullptr), (const float *)(w + D.w_o), nullptr, M, D.h, qd, eo, n));
     }
     if (c.taps) {                          // (of several ranks the last one's)
         const size_t r = n - 1;
@@ -647,7 +805,7 @@ hipError_t block_ranks(const spd_call &c, const char *w, char *kvc, int n, int s
         if (c.taps->attn) SPD_TRY(spd_common::copy2d(att + r * mr * qd, qd, c.taps->attn, qd, M, qd, c.s));
         if (c.taps->y) SPD_TRY(spd_common::copy2d(slot0 + r * slot_n, D.h, c.taps->y, D.h, M, D.h, c.s));
     }
-    in = rows_in(c, X, D.h, 0, (const float *)(w + D.w_g2));
+    in = rows_in(c, X, 0, (const float *)(w + D.w_g2));
     in.bias = bo;
     if (spd) {                             // R_r = X + Y_r [+ b] (Sec. 4.1.1), needed by this product only
         in.slots = slot0; in.slot_rank = slot_n; in.n_slots = 1;
@@ -659,14 +817,14 @@ hipError_t block_ranks(const spd_call &c, const char *w, char *kvc, int n, int s
         RowsGU eg;
         eg.u = u; eg.u_rank = mr * f; eg.ld = f;
         spd_stage_scope prof(c, SPD_STAGE_GATEUP);
-        SPD_TRY(launch_rows(c.s, in, (const float *)(w + D.w_g), (const float *)(w + D.w_u), f, M, f, D.h, eg, n));
+        SPD_TRY(launch_rows(c.s, in, (const float *)(w + D.w_g), (const float *)(w + D.w_u), M, f, D.h, eg, n));
     }
     if (c.taps && c.taps->u) SPD_TRY(spd_common::copy2d(u + (size_t)(n - 1) * mr * f, f, c.taps->u, f, M, f, c.s));
     if (c.on(SPD_STAGE_DOWN)) {
         RowsDown ed;                       // slot = Z_r, or Y_r + Z_r
         ed.out = slot0; ed.add = spd ? slot0 : nullptr; ed.out_rank = slot_n; ed.ld = D.h;
         spd_stage_scope prof(c, SPD_STAGE_DOWN);
-        SPD_TRY(launch_rows(c.s, rows_in(c, u, f, mr * f, nullptr), (const float *)(w + D.w_d), nullptr, D.h, M, D.h, f, ed, n));
+        SPD_TRY(launch_rows(c.s, rows_in(c, u, mr * f, nullptr), (const float *)(w + D.w_d), nullptr, M, D.h, f, ed, n));
     }
     x->base = spd ? X : R;
     x->slots = slots;
@@ -683,8 +841,8 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
     const float *cosT = (const float *)(c.ws + D.ws_cos), *sinT = (const float *)(c.ws + D.ws_sin);
     float *kc = (float *)kvc, *vc = (float *)(kvc + D.kv_v);
     if (rows_fit(M, D.nqkv, D.h) && RN % D.d == 0) {
-        SPD_TRY(launch_rows(c.s, rows_in(c, x, D.h, 0, (const float *)(w + D.w_g1)), (const float *)(w + D.w_qkv), nullptr, D.nqkv, M, D.nqkv,
-                            D.h, rows_qkv(c, qkv, 0, kvc)));
+        SPD_TRY(launch_rows(c.s, rows_in(c, x, 0, (const float *)(w + D.w_g1)), (const float *)(w + D.w_qkv), nullptr, M, D.nqkv, D.h,
+                            rows_qkv(c, qkv, 0, kvc)));
     } else {
         hipLaunchKernelGGL(k_rmsnorm, dim3(M), dim3(TB), 0, c.s, x, (const float *)(w + D.w_g1), xn, D.h, D.eps);
         SPD_TRY(hipGetLastError());
@@ -694,13 +852,13 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
                            c.q_len, D.q, D.kv, D.d, D.nqkv, D.max_ctx);
         SPD_TRY(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_attention, dim3(M * D.q), dim3(TB), (size_t)c.max_pos_end * sizeof(float), c.s, qkv, kc, vc,
-                       att, (size_t)0, (size_t)0, (size_t)0, c.pos, c.q_len, D.q, D.kv, D.d, D.nqkv, D.max_ctx);
+    hipLaunchKernelGGL(k_attention, dim3(M * D.q), dim3(TB), (size_t)c.max_pos_end * sizeof(float), c.s, qkv, kc, vc, c.q_len, D.q, D.kv, D.d,
+                       D.nqkv, D.max_ctx, att, (size_t)0, (size_t)0, (size_t)0, c.pos);
     SPD_TRY(hipGetLastError());
     if (rows_fit(M, D.h, qd)) {
         RowsO e;
         e.y = y_out; e.y_rank = 0; e.r_out = r_out; e.x = x; e.bias = bias; e.ld = D.h;
-        SPD_TRY(launch_rows(c.s, rows_in(c, att, qd, 0, nullptr), (const float *)(w + D.w_o), nullptr, D.h, M, D.h, qd, e));
+        SPD_TRY(launch_rows(c.s, rows_in(c, att, 0, nullptr), (const float *)(w + D.w_o), nullptr, M, D.h, qd, e));
     } else {
         SPD_TRY(gemm(att, qd, (const float *)(w + D.w_o), D.h, nullptr, y_out, D.h, M, D.h, qd, c.s));
         if (r_out) SPD_TRY(spd_common::rank_sum(x, y_out, 1, (int64_t)M * D.h, r_out, c.s, bias, D.h));
@@ -720,8 +878,8 @@ hipError_t mlp_half(const spd_call &c, const char *w, const float *r_in, const f
     if (rows_fit(M, f, D.h)) {
         RowsGU e;
         e.u = u; e.u_rank = 0; e.ld = f;
-        SPD_TRY(launch_rows(c.s, rows_in(c, r_in, D.h, 0, (const float *)(w + D.w_g2)), (const float *)(w + D.w_g), (const float *)(w + D.w_u),
-                            f, M, f, D.h, e));
+        SPD_TRY(launch_rows(c.s, rows_in(c, r_in, 0, (const float *)(w + D.w_g2)), (const float *)(w + D.w_g), (const float *)(w + D.w_u),
+                            M, f, D.h, e));
     } else {
         hipLaunchKernelGGL(k_rmsnorm, dim3(M), dim3(TB), 0, c.s, r_in, (const float *)(w + D.w_g2), xn, D.h, D.eps);
         SPD_TRY(hipGetLastError());
@@ -734,7 +892,7 @@ hipError_t mlp_half(const spd_call &c, const char *w, const float *r_in, const f
     if (rows_fit(M, D.h, f)) {
         RowsDown e;
         e.out = out; e.add = add; e.out_rank = 0; e.ld = D.h;
-        SPD_TRY(launch_rows(c.s, rows_in(c, u, f, 0, nullptr), (const float *)(w + D.w_d), nullptr, D.h, M, D.h, f, e));
+        SPD_TRY(launch_rows(c.s, rows_in(c, u, 0, nullptr), (const float *)(w + D.w_d), nullptr, M, D.h, f, e));
     } else {
         SPD_TRY(gemm(u, f, (const float *)(w + D.w_d), D.h, add, out, D.h, M, D.h, f, c.s));
     }

@@ -769,6 +769,42 @@ def test_fp32_tapped_call_is_the_ordinary_call(gpu, flag, q_len):
     case.close()
 
 
+# The O projection of a small call does the attention itself for up to 16 (row, head) items a workgroup (1, 2, 4 or 8 rows) and 16 keys per wave of an
+# item, a launch of its own beyond (counted by a timer on its stage): against the oracle, and against that launch, which a call of one stage
+# after the other takes (sums over at most 256 keys in 32 bits: 1e-5 of the largest).
+@pytest.mark.parametrize("hidden,tp,q,kv,d,batch,q_len,positions,fused", [
+    (64, 1, 16, 16, 32, 1, 1, [15], True), (64, 1, 16, 4, 32, 1, 1, [16], False), (64, 1, 17, 17, 32, 1, 1, [0], False),
+    (96, 1, 3, 1, 64, 2, 1, [79, 3], True), (96, 1, 3, 3, 64, 2, 1, [3, 80], False), (64, 2, 1, 1, 64, 1, 1, [255], True),
+    (64, 1, 1, 1, 64, 1, 1, [256], False), (64, 1, 1, 1, 16, 1, 1, [3], False), (1024, 1, 2, 2, 64, 1, 32, [32], True),
+    (1024, 1, 2, 1, 32, 4, 16, [0, 3, 1, 16], True), (1024, 1, 1, 1, 64, 3, 11, [0, 53, 7], True), (1024, 2, 2, 2, 64, 4, 16, [0] * 4, True)])
+def test_fp32_attention_in_the_output_projection(gpu, hidden, tp, q, kv, d, batch, q_len, positions, fused):
+    import torch
+    w = Workload(name=f"f32-att-{q}x{d}", hidden=hidden, n_q_heads=q * tp, n_kv_heads=kv * tp, head_dim=d, ffn=64 * tp, n_layers=1, tp=tp, dtype=F32,
+                 seed=61, batch=1, q_len=1, ctx=288, mask=(0,))
+    M, S = batch * q_len, B.STAGES
+    case = Case(w, gpu, ranks=range(tp), positions=positions, max_ctx=288, max_tokens=M)
+    X = inputs.hidden_states(w, M)
+    x, got = case.to_dev(X), []
+    timer = B.spd_stage_timer_create(S["attn"], 4)
+    for masks in ([(1 << S["qkv"]) | (1 << S["attn"]) | (1 << S["o"])], [1 << S["qkv"], 1 << S["attn"], 1 << S["o"]]):
+        slots, out = torch.zeros((tp, M, hidden), dtype=torch.float32, device=gpu), torch.empty_like(x)
+        for mask in masks:
+            B.spd_model_forward_staged(case.dev.ctx, w.mask, B.SPD_ALL_RANKS, case.dev.weights, case.dev.kv, positions, batch, q_len, x, slots, out,
+                                       case.dev.workspace, stage_mask=mask, timer=timer)
+        torch.cuda.synchronize()
+        assert B.spd_stage_timer_read(timer)[0] == (0 if fused and not got else 1)
+        got.append(slots.cpu().numpy())
+    B.spd_stage_timer_destroy(timer)
+    assert np.max(np.abs(got[0] - got[1])) <= 1e-5 * np.max(np.abs(got[1]))
+    assert fused or np.array_equal(got[0], got[1])
+    B.spd_block_forward(case.dev.ctx, 0, 0, B.SPD_ALL_RANKS, case.dev.weights[0], case.dev.kv[0], positions, batch, q_len, x, slots, out,
+                        case.dev.workspace)
+    torch.cuda.synchronize()
+    want, _ = O.block_all_ranks(case.sh, X, case.shards[0], case.caches[0], positions, batch, q_len, 0, {})
+    assert np.max(np.abs(out.cpu().numpy() - want)) <= 1e-5 * np.max(np.abs(want))
+    case.close()
+
+
 # fp32 attention where a thread takes a second key (256 keys and more), the waves' shares end unevenly and the output needs a
 # second and a fourth pass of 64 features
 @pytest.mark.parametrize("head_dim", [2, 64, 66, 128, 256])
