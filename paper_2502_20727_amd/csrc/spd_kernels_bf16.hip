@@ -2790,6 +2790,19 @@ inline bool skinny_first(int n_pairs, int KT, bool split, int n_mtiles) {
     return (kp <= 48 && wgs <= 512) || (kp <= 96 && wgs >= 128 && wgs <= 256);
 }
 
+inline int square_tiles(int n_pairs, int n_mtiles) { return (2 * n_pairs + 7) / 8 * ((n_mtiles + 7) / 8); }      // of 128 x 128
+
+// The down projection of 257 to 512 tokens, where it is not the skinny kernel's: 128 x 128 tiles over the whole of K, and the closing sync point a launch
+// of its own, instead of slices and a sync point in the launch that adds them: a slice's rows are written and read once more.  At
+// most one round of the chip and at least a third of one.  us per call, slices / this: 70B 300 tokens 176.2 / 174.3, 400 behind 1000 positions
+// 213.5 / 206.7, 512 behind 1536 237.4 / 235.6; 13B 333 122.3 / 119.1 (sync point kept 133.0 / 131.2), 500 152.8 / 148.6; 7B 4-way 400 145.7 / 142.2; four
+// layers of 13B, 400 tokens 526 / 511.  (200 tokens of 70B 156.4 / 161.4; instead of the skinny kernel, 7B 300 and 500: 87.1 / 89.6, 121.1 / 124.0.)
+inline bool down_whole(int n_pairs, int KT, bool split, int n_mtiles) {
+    const int tiles = square_tiles(n_pairs, n_mtiles);
+    return n_mtiles > 16 && n_mtiles <= SKINNY_MAX_MTILES && tiles >= 96 && tiles <= 256 && spd_gemm_fits(KT) &&
+           !skinny_first(n_pairs, KT, split, n_mtiles);
+}
+
 // Projection of a call of any size: the weight-streaming kernel up to 16 tokens; up to 512 tokens the skinny kernel for short
 // contractions and K slices of the LDS-tiled GEMM for the others; slices beyond for a call of one chain whose tiles leave half of the compute units idle (the QKV projection of the
 // 70B shard, 1000 tokens: 6 slices 37 us, 160 x 256 tiles in 8 slices 58); one launch of the GEMM otherwise.  The skinny
@@ -2848,7 +2861,9 @@ inline bool merge_in_o(const spd_call &c, int n_pairs, int KT, int n_splits) {
 // The output projection's contraction is short (a rank's heads): up to 128 tokens the skinny kernel with the whole epilogue
 // beats slices and their finishing kernel; beyond, 256 x 128 tiles by themselves beat both once the skinny kernel would
 // take two rounds (70B shard, main kernel, us, skinny / tiles: 192 tokens 15.8 / 14.7, 512: 30.9 / 17.2; 13B 384: 10.8 / 11.4, 512:
-// 16.1 / 12.0).  With a kept sync point in its epilogue (MID) always the skinny kernel.
+// 16.1 / 12.0), and tiles of 128 x 128 beat those as long as they come to one round (such a launch is its reads of X and its writes, which a
+// compute unit makes at 50 GB/s; us per call, 256 x 128 / 128 x 128: 70B 300 tokens 185.6 / 176.2, 512 behind 1536 positions 245.0 / 237.4, 13B 500
+// 159.2 / 152.8, 7B 2 x 200 112.7 / 106.2, 4-way 400 155.1 / 145.7).  With a kept sync point in its epilogue (MID) always the skinny kernel.
 // `merge`: the splits' states of a decode step whose O projection merges them itself (see merge_in_o()).
 template <bool MID>
 hipError_t launch_o(const spd_call &c, bool split, const __bf16 *Wp, const __bf16 *Xhi, size_t plane, int n_pairs, int KT,
@@ -2880,6 +2895,9 @@ hipError_t launch_o(const spd_call &c, bool split, const __bf16 *Wp, const __bf1
     if constexpr (MID) {
         return hipErrorInvalidValue;         // (see sync_in_o())
     } else {
+        if (n_mtiles <= SKINNY_MAX_MTILES && square_tiles(n_pairs, n_mtiles) <= 256)
+            return split ? launch_gemm_lds_cfg<GemmSquare, true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi)
+                         : launch_gemm_lds_cfg<GemmSquare, false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
         if (n_mtiles <= SKINNY_MAX_MTILES)
             return split ? launch_gemm_lds_cfg<GemmHalf, true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi)
                          : launch_gemm_lds_cfg<GemmHalf, false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
@@ -3218,11 +3236,12 @@ hipError_t mlp_half(const spd_call &c, const char *w, int spd, float *slot, cons
         }
     }
 
-    // the closing sync point rides in the down projection's epilogue up to 512 tokens: that of the weight-streaming kernels, of the
-    // kernel that adds K slices, or of one launch of 256 x 128 tiles.  In a long call's GEMM it gains nothing: measured on the 70B prefill shape, the
+    // the closing sync point rides in the down projection's epilogue up to 512 tokens (but see down_whole()): that of the
+    // weight-streaming kernels, of the kernel that adds K slices, or of one launch of 256 x 128 tiles.  In a long call's GEMM it gains nothing: measured on the 70B prefill shape, the
     // workgroups of a compute unit reach their epilogues together, so the slot reads do not overlap with
     // anybody's contraction and the fused kernel takes exactly as long as GEMM + rank-sum kernel.
-    const bool do_fuse = fuse && M <= 16 * SKINNY_MAX_MTILES;
+    const bool whole = down_whole(D.h / 32, D.f_pad / 32, c.sp_m, (M + 15) / 16);
+    const bool do_fuse = fuse && M <= 16 * SKINNY_MAX_MTILES && !whole;
     if (fused) *fused = do_fuse;
     auto fill = [&](auto &e2) {
         e2.M = M; e2.h = D.h; e2.spd = spd;
@@ -3251,7 +3270,11 @@ hipError_t mlp_half(const spd_call &c, const char *w, int spd, float *slot, cons
         } else {
             EpiDownT<false> e2;
             fill(e2);
-            SPD_TRY(launch_proj(c, c.sp_m, wdn.w, uhat, D.pl_u, D.h / 32, D.f_pad / 32, e2));
+            const __bf16 *lo = uhat + D.pl_u;
+            if (whole)
+                SPD_TRY((c.sp_m ? launch_gemm_lds_cfg<GemmSquare, true>(c, wdn.w, uhat, lo, D.h / 32, D.f_pad / 32, e2)
+                                : launch_gemm_lds_cfg<GemmSquare, false>(c, wdn.w, uhat, lo, D.h / 32, D.f_pad / 32, e2)));
+            else SPD_TRY(launch_proj(c, c.sp_m, wdn.w, uhat, D.pl_u, D.h / 32, D.f_pad / 32, e2));
         }
     }
 

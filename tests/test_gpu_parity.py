@@ -387,6 +387,40 @@ def test_bf16_short_and_sliced_contractions(gpu, w, split, q_len):
     _one_rank_block(gpu, w, 1, q_len, [0], q_len % 2, split)
 
 
+# 257 to 512 tokens: down projection in tiles of 128 x 128 over the whole of K with the closing sync point behind it (from 96 tiles on: 25 m-tiles
+# of 105 pairs, 17 of 129, none below), O projection in such tiles from 512 workgroups of the skinny kernel on (129 pairs: 25 m-tiles); n-tiles that end
+# inside a tile, an odd number of k-tiles
+DOWN_129 = Workload(name="129-pairs-51-k-tiles", hidden=4128, n_q_heads=10, n_kv_heads=2, head_dim=32, ffn=3232, n_layers=2, tp=2, dtype=BF16,
+                    seed=62, batch=1, q_len=1, ctx=64, mask=(1, 0))
+DOWN_105 = Workload(name="105-pairs-51-k-tiles", hidden=3360, n_q_heads=10, n_kv_heads=2, head_dim=32, ffn=3232, n_layers=2, tp=2, dtype=BF16,
+                    seed=63, batch=1, q_len=1, ctx=64, mask=(0, 1))
+
+
+@pytest.mark.parametrize("w", [DOWN_129, DOWN_105], ids=lambda w: w.name)
+@pytest.mark.parametrize("q_len,flag,split", [(256, 1, 0), (257, 0, 0), (257, 1, 1), (384, 1, 0), (385, 0, 0), (400, 1, 1), (512, 0, 0), (512, 1, 2)])
+def test_bf16_medium_call_in_square_tiles(gpu, w, q_len, flag, split):
+    _one_rank_block(gpu, w, 1, q_len, [0], flag, split, bias_std=0.1 * (q_len % 2))
+
+
+# ... and in a model call, where the launch behind it also prepares the next block's first norm: every block against the oracle on the input it had
+@pytest.mark.parametrize("w", [DOWN_129, DOWN_105], ids=lambda w: w.name)
+def test_bf16_medium_model_call_in_square_tiles(gpu, w):
+    import torch
+    M, rank = 390, 1
+    case = Case(w, gpu, ranks=[rank], positions=[0], max_ctx=416, max_tokens=M, bias_std=0.1)
+    X, peers = inputs.hidden_states(w, M), inputs.peer_slots(w, M)
+    outs, x = torch.zeros((2, M, w.hidden), dtype=torch.float32, device=gpu), case.to_dev(X)
+    B.spd_model_forward_staged(case.dev.ctx, w.mask, rank, case.dev.weights, case.dev.kv, [0], 1, M, x, case.to_dev(peers).reshape(w.tp, M, w.hidden),
+                               torch.empty_like(x), case.dev.workspace, layer_out=outs)
+    torch.cuda.synchronize()
+    for l, flag in enumerate(w.mask):
+        want = O.block_single_rank(case.sh, X, case.shards[l][0], case.caches[l][0], [0], 1, M, flag, rank,
+                                   peers.reshape(w.tp, M, w.hidden).astype(np.float64))
+        X = outs[l].cpu().numpy()
+        assert_close(X, want, w, f"block {l}")
+    case.close()
+
+
 # the kernel that adds the slices takes 2, 4 or 8 pairs of n-tiles per workgroup, by the number of groups of 8 times m-tiles (lines at 64 and
 # 128): gate/up of 66 pairs (9 groups) on either side of both lines, QKV of 7 pairs
 FIN_66 = Workload(name="66-and-7-pairs", hidden=3232, n_q_heads=10, n_kv_heads=2, head_dim=32, ffn=2112, n_layers=1, tp=2, dtype=BF16,
