@@ -506,6 +506,9 @@ struct SyncLds {           // ... in LDS, [slot][half][lane]; the base in the ow
     __device__ __forceinline__ float4 at_base(int half) const { return slot(rank < SYNC_EARLY ? rank : SYNC_EARLY, half); }
 };
 struct SyncNone {};        // nothing requested yet
+struct SyncDone {          // the sum is there: the own partial and the result in LDS, [half][lane] each
+    const f32x4 *own, *x;
+};
 struct SyncSum {           // the sync point an epilogue performs
     const float *slots, *base, *bias;
     size_t slot_stride;
@@ -555,6 +558,28 @@ struct SyncSum {           // the sync point an epilogue performs
         rank_sum_pair(slots, slot_stride, tp, rank, base, o, own_a, own_b, ra, rb);
         add_bias(na, ra, rb);
     }
+    __device__ __forceinline__ void sum(const SyncDone &t, size_t, int, float4, float4, float4 &ra, float4 &rb) const {
+        ra = __builtin_bit_cast(float4, t.x[0]);
+        rb = __builtin_bit_cast(float4, t.x[64]);
+    }
+    // element e = 256 half + 4 lane + i of the tile pair's sum, in the same order; slots and base as SyncLds holds them.  Up to SYNC_EARLY ranks.
+    __device__ __forceinline__ float element(const float *peers, int e, float own, float bs) const {
+        float acc = own;
+#pragma unroll
+        for (int s = 0; s < SYNC_EARLY; ++s) {
+            if (s >= tp) break;
+            const float v = s == rank ? own : peers[s * 512 + e];
+            acc = s == 0 ? v : acc + v;
+        }
+        const float r = peers[(rank < SYNC_EARLY ? rank : SYNC_EARLY) * 512 + e] + acc;
+        return bias ? r + bs : r;
+    }
+    // where element e lies in a [tokens][h] buffer (rows past the call: its last one), and its column
+    __device__ __forceinline__ int col(int pair, int e) const { return pair * 32 + (e >> 8) * 16 + 4 * ((e & 255) >> 6) + (e & 3); }
+    __device__ __forceinline__ size_t at_element(int pair, int e) const {
+        const int m = (e >> 2) & 15;
+        return (size_t)(m < M ? m : M - 1) * h + col(pair, e);
+    }
     __device__ __forceinline__ void add_bias(int na, float4 &ra, float4 &rb) const {
         if (!bias) return;
         const float4 ba = *(const float4 *)(bias + na), bb = *(const float4 *)(bias + na + 16);
@@ -569,9 +594,11 @@ struct SyncSum {           // the sync point an epilogue performs
 // ------------------------------------------------------------------------------------------
 // Every epilogue has two parts: pre() issues the loads that do not depend on the accumulators
 // (so that they can be started before the weights are streamed), operator() finishes the tile.
+// (The matrix's factor among them: read where it is used, it was a trip to the memory of 1.2 us at the end of every launch of a decode step.)
 // kNeedsRs: the tile must be scaled by 1/sqrt(mean(x^2)+eps) of the token, which the caller
 // computes from the partial sums of squares ss[nch][m_pad].
 struct EpiQKV {
+    static constexpr bool kByElement = false;
     static constexpr bool kSync = false;
     static constexpr bool kLong = true;        // used by calls of any length
     static constexpr bool kWideSum = true;     // K slices are added in 64 bits
@@ -585,11 +612,13 @@ struct EpiQKV {
     spd_positions P;
     struct Pre {
         float4 c, s;
+        float sc;
     };
 
     __device__ __forceinline__ Pre pre(int pair, int mt, int lane) const {
         Pre p;
         p.c = p.s = make_float4(0.f, 0.f, 0.f, 0.f);
+        p.sc = *wsc;
         const int m = mt * 16 + (lane & 15), g = lane >> 4;
         const int tph = d >> 4, half = d >> 1;
         const int head = (2 * pair) / tph;
@@ -610,7 +639,7 @@ struct EpiQKV {
         const int bseq = m / q_len, pos = P.pos[bseq] + (m % q_len);
         const int ca = spd_qkv_tile_col0(2 * pair, q, kv, d) - head * d + 4 * g;       // column inside the head
         const int cb = spd_qkv_tile_col0(2 * pair + 1, q, kv, d) - head * d + 4 * g;
-        rs *= *wsc;
+        rs *= p.sc;
         a *= rs;
         b *= rs;
         if (head < q + kv) {
@@ -648,6 +677,7 @@ struct EpiQKV {
 // part[slice][token][column] (columns in natural order: head * d + j).  The attention kernel adds
 // the slices in ascending order, rounds, and appends the new key and value to the cache.
 struct EpiQKVPart {
+    static constexpr bool kByElement = false;
     static constexpr bool kSync = false;
     static constexpr bool kNeedsRs = true;
     int M, q_len, q, kv, d, h, nqkv, nch, m_pad;
@@ -662,6 +692,7 @@ struct EpiQKVPart {
     __device__ __forceinline__ Pre pre(int pair, int mt, int lane) const {
         Pre p;
         p.c = p.s = make_float4(0.f, 0.f, 0.f, 0.f);
+        p.sc = *wsc;
         const int m = mt * 16 + (lane & 15), g = lane >> 4;
         const int tph = d >> 4, half = d >> 1;
         const int head = (2 * pair) / tph;
@@ -681,7 +712,7 @@ struct EpiQKVPart {
         const int head = (2 * pair) / tph;
         const int ca = spd_qkv_tile_col0(2 * pair, q, kv, d) + 4 * g;
         const int cb = spd_qkv_tile_col0(2 * pair + 1, q, kv, d) + 4 * g;
-        rs *= *wsc;
+        rs *= p.sc;
         a *= rs;
         b *= rs;
         float4 lo = make_float4(a[0], a[1], a[2], a[3]), hi = make_float4(b[0], b[1], b[2], b[3]);
@@ -698,6 +729,7 @@ struct EpiQKVPart {
 
 template <bool MID>      // MID: the epilogue can also perform the kept attention sync point (spd = 2)
 struct EpiOT {
+    static constexpr bool kByElement = false;
     static constexpr bool kSync = MID;         // can perform a sync point (one rank, the peers' partial sums are inputs)
     static constexpr bool kWideSum = false;
     static constexpr bool kNeedsRs = false;
@@ -715,13 +747,16 @@ struct EpiOT {
     int tp = 0, rank = 0;
     float *rbuf = nullptr;
     __device__ __forceinline__ SyncSum sync() const { return SyncSum{slots, x, bo, slot_stride, tp, rank, M, h}; }
+    __device__ __forceinline__ const float *joins_own() const { return nullptr; }      // what is added to the own partial before the sum
     struct Pre {
         float4 x0, x1, ga, gb;
+        float sc;
     };
 
     __device__ __forceinline__ Pre pre(int pair, int mt, int lane) const {
         Pre p;
         p.x0 = p.x1 = p.ga = p.gb = make_float4(0.f, 0.f, 0.f, 0.f);
+        p.sc = *wsc;
         const int m = mt * 16 + (lane & 15), g = lane >> 4;
         const int na = pair * 32 + 4 * g, nb = na + 16;
         if (MID && spd == 2 && m < M) {      // the sum loads X itself
@@ -748,10 +783,12 @@ struct EpiOT {
         const int r = lane & 15, m = mt * 16 + r, g = lane >> 4;
         const int na = pair * 32 + 4 * g, nb = na + 16;
         const bool valid = m < M;
-        {
-            const float sc = *wsc;
-            a *= sc;
-            b *= sc;
+        if constexpr (std::is_same<Peers, SyncDone>::value) {
+            a = peers.own[0];
+            b = peers.own[64];
+        } else {
+            a *= p.sc;
+            b *= p.sc;
         }
         if (!spd) {
             if (valid) {
@@ -804,6 +841,7 @@ struct EpiOT {
 };
 
 struct EpiGU {
+    static constexpr bool kByElement = true;
     static constexpr bool kSync = false;
     static constexpr bool kLong = true;
     static constexpr bool kWideSum = false;
@@ -815,14 +853,30 @@ struct EpiGU {
     const float *ss;
     const float *wsc;
     __bf16 *uhat, *ulo;        // ulo may be NULL
-    struct Pre {};
+    struct Pre {
+        float sc;
+    };
 
-    __device__ __forceinline__ Pre pre(int, int, int) const { return Pre(); }
+    __device__ __forceinline__ Pre pre(int, int, int) const { return Pre{*wsc}; }
 
-    __device__ __forceinline__ void operator()(int pair, int mt, f32x4 a, f32x4 b, int lane, float rs, const Pre &) const {
+    // narrow groups: feature i of a lane is FFN column cols * pair + 4 g + i, stored by itself
+    __device__ __forceinline__ bool by_element() const { return cols != 16; }
+    __device__ __forceinline__ void element(int pair, int i, float a, float b, int lane, float rs, const Pre &p) const {
+        const int r = lane & 15, row = 4 * (lane >> 4) + i, col = pair * cols + row;
+        if (row >= cols || col >= f_pad) return;
+        rs *= p.sc;
+        const float gt = a * rs, up = b * rs;
+        const float o = r < M ? gt / (1.0f + __expf(-gt)) * up : 0.f;
+        const __bf16 u = act_one(o);
+        const size_t fo = spd_act_index(0, col >> 5, f_pad >> 5, 1) + spd_frag_elem(r, col & 31);
+        uhat[fo] = u;
+        if (ulo) ulo[fo] = act_one(o - act_back(u));
+    }
+
+    __device__ __forceinline__ void operator()(int pair, int mt, f32x4 a, f32x4 b, int lane, float rs, const Pre &p) const {
         const int r = lane & 15, m = mt * 16 + r, g = lane >> 4;
         float o[4] = {0.f, 0.f, 0.f, 0.f};
-        rs *= *wsc;
+        rs *= p.sc;
         if (m < M) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -831,20 +885,6 @@ struct EpiGU {
             }
         }
         const bf16x4 u = cvt4h(o[0], o[1], o[2], o[3]);
-        if (cols != 16) {
-            // narrow group: rows 4g .. 4g+3 are FFN columns cols*pair + 4g + i, stored one by one
-            const bf16x4 lo = cvt4h_lo(o[0], o[1], o[2], o[3], u);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int col = pair * cols + 4 * g + i;
-                if (4 * g + i < cols && col < f_pad) {
-                    const size_t fo = spd_act_index(mt, col >> 5, f_pad >> 5, (M + 15) >> 4) + spd_frag_elem(r, col & 31);
-                    uhat[fo] = u[i];
-                    if (ulo) ulo[fo] = lo[i];
-                }
-            }
-            return;
-        }
         // gate/up pair p covers FFN columns [16p, 16p+16): half of k-tile p/2 of the down projection
         const size_t fo = spd_act_index(mt, pair >> 1, f_pad >> 5, (M + 15) >> 4) + spd_frag_elem(r, 16 * (pair & 1) + 4 * g);
         *(bf16x4 *)(uhat + fo) = u;
@@ -854,6 +894,7 @@ struct EpiGU {
 
 template <bool FUSED>
 struct EpiDownT {
+    static constexpr bool kByElement = false;
     static constexpr bool kSync = FUSED;
     static constexpr bool kLong = !FUSED;
     static constexpr bool kWideSum = false;
@@ -872,13 +913,16 @@ struct EpiDownT {
     float *x_out, *ss1;
     __bf16 *xhat, *xlo;        // next block's first-norm activations (xhat NULL: last block)
     __device__ __forceinline__ SyncSum sync() const { return SyncSum{slots, base, bias, slot_stride, tp, rank, M, h}; }
+    __device__ __forceinline__ const float *joins_own() const { return spd ? ybuf : nullptr; }
     struct Pre {
         float4 ya, yb, ga, gb;
+        float sc;
     };
 
     __device__ __forceinline__ Pre pre(int pair, int mt, int lane) const {
         Pre p;
         p.ya = p.yb = p.ga = p.gb = make_float4(0.f, 0.f, 0.f, 0.f);
+        p.sc = *wsc;
         const int m = mt * 16 + (lane & 15), g = lane >> 4;
         if (FUSED && xhat) {
             p.ga = *(const float4 *)(g1 + pair * 32 + 4 * g);
@@ -898,14 +942,17 @@ struct EpiDownT {
         const int r = lane & 15, m = mt * 16 + r, g = lane >> 4;
         const bool valid = m < M;
         const size_t oa = (size_t)m * h + pair * 32 + 4 * g, ob = oa + 16;
-        {
-            const float sc = *wsc;
-            a *= sc;
-            b *= sc;
-        }
         // SPD block: Y_r joins the partial sum before the sync point (Sec. 4.1.1); p.y* are zero otherwise
-        const float4 pa = make_float4(a[0] + p.ya.x, a[1] + p.ya.y, a[2] + p.ya.z, a[3] + p.ya.w);
-        const float4 pb = make_float4(b[0] + p.yb.x, b[1] + p.yb.y, b[2] + p.yb.z, b[3] + p.yb.w);
+        float4 pa, pb;
+        if constexpr (std::is_same<Peers, SyncDone>::value) {
+            pa = __builtin_bit_cast(float4, peers.own[0]);
+            pb = __builtin_bit_cast(float4, peers.own[64]);
+        } else {
+            a *= p.sc;
+            b *= p.sc;
+            pa = make_float4(a[0] + p.ya.x, a[1] + p.ya.y, a[2] + p.ya.z, a[3] + p.ya.w);
+            pb = make_float4(b[0] + p.yb.x, b[1] + p.yb.y, b[2] + p.yb.z, b[3] + p.yb.w);
+        }
         if (valid) {
             *(float4 *)(slot + oa) = pa;
             *(float4 *)(slot + ob) = pb;
@@ -1172,11 +1219,12 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
     SsLoads ssl;
     constexpr bool PARTIAL = MODE == 1, EARLY = Epi::kSync && MODE == 0;
     f32x4 sla = {0.f, 0.f, 0.f, 0.f}, slb = sla, bsa = sla, bsb = sla;
+    float el_y = 0.f, el_b = 0.f, el_sc = 1.f;
     auto between = [&]() {
         // loads that do not depend on the stream: the epilogue's inputs (first wave) and this wave's
         // share of the sum-of-squares partials, issued while the first weights are on their way
         if (!PARTIAL) {
-            if (wave == 0) pre = epi.pre(pair, 0, lane);
+            if (wave == 0 || (Epi::kByElement && wave < 4)) pre = epi.pre(pair, 0, lane);
             if constexpr (EARLY) {
                 // wave s takes slot s, the own slot's wave the base
                 const SyncSum sy = epi.sync();
@@ -1190,6 +1238,11 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
                     const float *p = sy.base + sy.at(pair, 0, lane);
                     bsa = *(const f32x4 *)p;
                     bsb = *(const f32x4 *)(p + 16);
+                }
+                if (threadIdx.x < 512 && sy.tp <= SYNC_EARLY) {
+                    if (epi.joins_own()) el_y = epi.joins_own()[sy.at_element(pair, threadIdx.x)];
+                    if (sy.bias) el_b = sy.bias[sy.col(pair, threadIdx.x)];
+                    el_sc = *epi.wsc;
                 }
             }
             if constexpr (Epi::kNeedsRs && SRC != SRC_X) {
@@ -1338,7 +1391,7 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
     }
     __shared__ f32x4 red[W][2][64];
     __shared__ float red_ss[W][64];
-    __shared__ f32x4 peers[EARLY ? SYNC_EARLY + 1 : 1][2][64];
+    __shared__ f32x4 peers[EARLY ? SYNC_EARLY + 1 : 1][2][64], xsum[EARLY ? 2 : 1][64];
     red[wave][0][lane] = a;
     red[wave][1][lane] = b;
     if constexpr (SRC == SRC_X) red_ss[wave][lane] = xsq;
@@ -1354,38 +1407,61 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
         }
     }
     __syncthreads();
+    // Eight waves add an element a thread over the waves (in place: nobody else reads that column), and one the sums of squares; by the first
+    // wave alone these were half of the 400 instructions behind the last weights.
+    static_assert(W >= 8, "an element a thread");
+    {
+        float *sum = (float *)&red[0][0][0] + threadIdx.x;
+        if (threadIdx.x < 512) {
+            float v = sum[0];
+#pragma unroll
+            for (int w = 1; w < W; ++w) v += sum[w * 512];
+            if (PARTIAL) {
+                kpart[((size_t)pair * KS + ks) * 512 + threadIdx.x] = v;
+                return;
+            }
+            if constexpr (EARLY) {
+                const SyncSum sy = epi.sync();
+                if (sy.tp <= SYNC_EARLY) {
+                    v = epi.joins_own() ? v * el_sc + el_y : v * el_sc;
+                    ((float *)xsum)[threadIdx.x] = sy.element((const float *)peers, threadIdx.x, v, el_b);
+                }
+            }
+            sum[0] = v;
+        }
+        if (PARTIAL) return;
+    }
+    if constexpr (Epi::kNeedsRs) {
+        if (wave == W - 1) {
+            float sq = red_ss[0][lane];
+#pragma unroll
+            for (int w = 1; w < W; ++w) sq += red_ss[w][lane];
+            sq += shfl_xor_f(sq, 16);
+            sq += shfl_xor_f(sq, 32);
+            if constexpr (SRC == SRC_X) {
+                if (pair == 0 && lane < 16) parts.ss[ks * 16 + lane] = sq;
+            } else {
+                red_ss[0][lane] = 1.0f / sqrtf(sq / (float)epi.h + epi.eps);
+            }
+        }
+    }
+    __syncthreads();
+    const float rs = Epi::kNeedsRs && SRC != SRC_X ? red_ss[0][lane] : 1.f;
+    if constexpr (Epi::kByElement) {
+        if (epi.by_element()) {          // a wave takes one of the four features of every lane
+            const float *sum = (const float *)&red[0][0][0] + lane * 4 + wave;
+            if (wave < 4) epi.element(pair, wave, sum[0], sum[256], lane, rs, pre);
+            return;
+        }
+    }
     if (wave != 0) return;
     a = red[0][0][lane];
     b = red[0][1][lane];
-    constexpr int UN = SRC == SRC_X ? 5 : W;      // (with all waves' sums on their way at once SRC_X would spill)
-#pragma unroll UN
-    for (int w = 1; w < W; ++w) {
-        a += red[w][0][lane];
-        b += red[w][1][lane];
-    }
-    if (PARTIAL) {
-        float *mine = kpart + ((size_t)pair * KS + ks) * 512 + lane * 4;
-        *(f32x4 *)mine = a;
-        *(f32x4 *)(mine + 256) = b;
-        return;
-    }
-    float rs = 1.f;
-    if constexpr (Epi::kNeedsRs) {
-        float sq = red_ss[0][lane];
-#pragma unroll
-        for (int w = 1; w < W; ++w) sq += red_ss[w][lane];
-        sq += shfl_xor_f(sq, 16);
-        sq += shfl_xor_f(sq, 32);
-        if constexpr (SRC == SRC_X) {
-            if (pair == 0 && lane < 16) parts.ss[ks * 16 + lane] = sq;
-        } else {
-            rs = 1.0f / sqrtf(sq / (float)epi.h + epi.eps);
-        }
-    }
     if constexpr (MODE == 2) {
         epi.slice(pair, ks, 0, a, b, lane, rs, pre);
     } else if constexpr (EARLY) {
-        epi(pair, 0, a, b, lane, rs, pre, SyncLds{&peers[0][0][lane], epi.sync().rank});
+        if (epi.sync().tp <= SYNC_EARLY) epi(pair, 0, a, b, lane, rs, pre, SyncDone{&red[0][0][lane], &xsum[0][lane]});
+        else epi(pair, 0, a, b, lane, rs, pre, SyncLds{&peers[0][0][lane], epi.sync().rank});
     } else {
         epi(pair, 0, a, b, lane, rs, pre);
     }
@@ -2315,8 +2391,12 @@ __global__ void __launch_bounds__(256) k_attn_decode(__bf16 *__restrict__ kc, __
     if constexpr (FUSED) {
         float xrs = 1.f;
         if (xss) {
-            float t = xss[b];
-            for (int j = 1; j < KS; ++j) t += xss[j * 16 + b];
+            float part[MAXKS];
+#pragma unroll
+            for (int j = 0; j < MAXKS; ++j) part[j] = xss[min(j, KS - 1) * 16 + b];
+            float t = part[0];
+#pragma unroll
+            for (int j = 1; j < MAXKS; ++j) t += j < KS ? part[j] : 0.f;
             xrs = 1.0f / sqrtf(t / xh + xeps);
         }
         auto add_slices = [&](const float4 *v) {
