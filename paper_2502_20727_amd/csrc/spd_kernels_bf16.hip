@@ -2336,7 +2336,7 @@ __global__ void __launch_bounds__(256) k_attn_decode(__bf16 *__restrict__ kc, __
     __shared__ float sml[4][2][16];
     __shared__ __attribute__((aligned(16))) __bf16 sq[2][16 * d];      // hi / lo queries of the group's heads
     __shared__ __attribute__((aligned(16))) __bf16 snew[2][d];         // new key, new value
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
     const int group = q / kv, qd = q * d, n_splits = parts.n_splits;
     const int n_keys = FUSED ? P.pos[b] : P.pos[b] + 1;       // keys in the cache
@@ -2380,13 +2380,11 @@ __global__ void __launch_bounds__(256) k_attn_decode(__bf16 *__restrict__ kc, __
         }
     }
     // (a wave without blocks loads a block it will not use: one code path, no waiting at a join)
+    // The first block only: a wave's second one ahead of the queries too held it at its requests until most of them had been served (4.5 of
+    // 7.7 us at 16 sequences of 4096 of the 70B shard), and everything below came after that.
     KVFrags<DT> f0, f1;
-    {
-        const int last = nblk > 0 ? nblk - 1 : 0;          // the cache holds at least one block
-        const int vb = min(b0 + wave, last), vb2 = vb + 4 < b1 ? vb + 4 : vb;
-        load_kv<DT>(f0, kbase, vbase, vb, d, lane);
-        load_kv<DT>(f1, kbase, vbase, vb2, d, lane);
-    }
+    load_kv<DT>(f0, kbase, vbase, min(b0 + wave, nblk > 0 ? nblk - 1 : 0), d, lane);      // (the cache holds at least one block)
+    SPD_SCHED_BARRIER();
     bf16x8 qf[DT];
     if constexpr (FUSED) {
         float xrs = 1.f;
@@ -2453,12 +2451,15 @@ __global__ void __launch_bounds__(256) k_attn_decode(__bf16 *__restrict__ kc, __
     } else {
         load_q<DT>(qf, qbuf_in, qlo_in, b, kvh * group + col, qd, d, cvalid, lane);
     }
-    if (has_blocks) {
-        // the wave's blocks are b0 + wave + 4 j, j < nw.  Two register buffers used alternately: while
-        // one block is processed the loads of the next but one are already in flight.  No branch
-        // between loads and use: an index past the wave's last block repeats that block, masked.
-        const int nw = (b1 - b0 - wave + 3) >> 2;
+    // The wave's blocks are b0 + wave + 4 j, j < nw.  Two register buffers used alternately: while one block is processed the loads of the
+    // next are in flight.  No branch between loads and use: an index past the wave's last block repeats that block.
+    const int nw = has_blocks ? (b1 - b0 - wave + 3) >> 2 : 0;
+    if (nw == 1) {
+        attn_block<DT>(st, qf, f0, b0 + wave, cvalid ? n_keys : 0, scale, lane);
+    } else if (nw > 1) {
         auto blk = [&](int j) { return b0 + wave + 4 * (j < nw ? j : nw - 1); };
+        load_kv<DT>(f1, kbase, vbase, blk(1), d, lane);
+        SPD_SCHED_BARRIER();
         int j = 0;
         for (; j + 2 < nw; j += 2) {
             attn_block<DT>(st, qf, f0, blk(j), cvalid ? n_keys : 0, scale, lane);
@@ -2471,7 +2472,7 @@ __global__ void __launch_bounds__(256) k_attn_decode(__bf16 *__restrict__ kc, __
             SPD_SCHED_BARRIER();
         }
         attn_block<DT>(st, qf, f0, blk(j), cvalid ? n_keys : 0, scale, lane);
-        attn_block<DT>(st, qf, f1, blk(j + 1), (cvalid && j + 1 < nw) ? n_keys : 0, scale, lane);
+        if (j + 1 < nw) attn_block<DT>(st, qf, f1, blk(j + 1), cvalid ? n_keys : 0, scale, lane);
     }
     if (newtok && wave == 0) {
         // the new token as a block whose only key is key 0: K row 0, V contraction slot 0
