@@ -94,6 +94,9 @@ __device__ __forceinline__ float quad_max(float x) {
     return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
+// Where part i of n begins among `total` things.  In 32 bits: a division in 64 is a hundred instructions, ahead of a workgroup's first load.
+__device__ __forceinline__ int part_of(int i, int total, int n) { return (int)((unsigned)i * (unsigned)total / (unsigned)n); }
+
 // sum of ss[c][m] over c = start, start + stride, ... < nch, in that order; the loads are issued
 // eight at a time so that their latencies overlap
 __device__ __forceinline__ float sum_ss(const float *__restrict__ ss, int nch, int m_pad, int m, int start, int stride) {
@@ -687,7 +690,12 @@ struct EpiQKVPart {
     const float *wsc;
     float *part;
     spd_positions P;
-    typedef EpiQKV::Pre Pre;
+    struct Pre {
+        float4 c, s;
+        float sc;
+        int ca, cb;            // the lane's first column of either tile
+        bool rot;
+    };
 
     __device__ __forceinline__ Pre pre(int pair, int mt, int lane) const {
         Pre p;
@@ -695,35 +703,34 @@ struct EpiQKVPart {
         p.sc = *wsc;
         const int m = mt * 16 + (lane & 15), g = lane >> 4;
         const int tph = d >> 4, half = d >> 1;
-        const int head = (2 * pair) / tph;
-        if (m < M && head < q + kv) {
-            const int pos = P.pos[m / q_len] + (m % q_len);
-            const int ca = spd_qkv_tile_col0(2 * pair, q, kv, d) - head * d + 4 * g;
-            p.c = *(const float4 *)(cosT + (size_t)pos * half + ca);
-            p.s = *(const float4 *)(sinT + (size_t)pos * half + ca);
+        const int head = (int)((unsigned)(2 * pair) / (unsigned)tph), w = 2 * pair - head * tph;      // (as spd_qkv_tile_col0(); tph is even)
+        p.rot = head < q + kv;
+        p.ca = head * d + (p.rot ? (w >> 1) << 4 : w << 4) + 4 * g;
+        p.cb = p.ca + (p.rot ? half : 16);
+        if (m < M && p.rot) {
+            const int pos = q_len == 1 ? P.pos[m] : P.pos[m / q_len] + (m % q_len);
+            const size_t o = (size_t)pos * half + p.ca - head * d;
+            p.c = *(const float4 *)(cosT + o);
+            p.s = *(const float4 *)(sinT + o);
         }
         return p;
     }
 
-    __device__ __forceinline__ void slice(int pair, int ks, int mt, f32x4 a, f32x4 b, int lane, float rs, const Pre &p) const {
-        const int m = mt * 16 + (lane & 15), g = lane >> 4;
+    __device__ __forceinline__ void slice(int, int ks, int mt, f32x4 a, f32x4 b, int lane, float rs, const Pre &p) const {
+        const int m = mt * 16 + (lane & 15);
         if (m >= M) return;
-        const int tph = d >> 4;
-        const int head = (2 * pair) / tph;
-        const int ca = spd_qkv_tile_col0(2 * pair, q, kv, d) + 4 * g;
-        const int cb = spd_qkv_tile_col0(2 * pair + 1, q, kv, d) + 4 * g;
         rs *= p.sc;
         a *= rs;
         b *= rs;
         float4 lo = make_float4(a[0], a[1], a[2], a[3]), hi = make_float4(b[0], b[1], b[2], b[3]);
-        if (head < q + kv) {
+        if (p.rot) {
             const float4 c = p.c, s = p.s;
             lo = make_float4(a[0] * c.x - b[0] * s.x, a[1] * c.y - b[1] * s.y, a[2] * c.z - b[2] * s.z, a[3] * c.w - b[3] * s.w);
             hi = make_float4(b[0] * c.x + a[0] * s.x, b[1] * c.y + a[1] * s.y, b[2] * c.z + a[2] * s.z, b[3] * c.w + a[3] * s.w);
         }
         float *dst = part + ((size_t)ks * part_rows + m) * nqkv;
-        *(float4 *)(dst + ca) = lo;
-        *(float4 *)(dst + cb) = hi;
+        *(float4 *)(dst + p.ca) = lo;
+        *(float4 *)(dst + p.cb) = hi;
     }
 };
 
@@ -1013,9 +1020,17 @@ struct EpiPark {
 // group's real heads (1 of an MFMA's 16 columns in multi-head attention), a head's features side by side.  (Whole tiles of 16 columns
 // before: us per layer 70B 16 sequences of 4096 63.8 -> 62.6, 13B 8 of 4096 56.3 -> 54.8, 7B 1 of 2048 40.4 -> 38.8.)
 // ------------------------------------------------------------------------------------------
+// n / d for n < 2^16, d < 2^16 (the rounded-up reciprocal is off by less than 2^-32, n of it by less than 1 / d)
+struct Divider {
+    unsigned inv, d;
+    static Divider by(unsigned d) { return Divider{d > 1 ? (unsigned)((0x100000000ull + d - 1) / d) : 0u, d}; }
+    __device__ __forceinline__ int div(int n) const { return d == 1 ? n : (int)__umulhi((unsigned)n, inv); }
+    __device__ __forceinline__ int mod(int n) const { return n - div(n) * (int)d; }
+};
 struct AttnParts {
     float *o;
     int units, n_splits, group, d;
+    Divider by_quads, by_heads, by_group;      // quads of features of a head; query heads of the rank; of a KV head
     __device__ __forceinline__ float *sums(int u, int split, int c) const { return o + (((size_t)u * n_splits + split) * group + c) * d; }
     __device__ __forceinline__ float *max_sum(int u, int split, int c) const {       // maximum; `group` floats further the sum
         return o + (size_t)units * n_splits * group * d + ((size_t)u * n_splits + split) * 2 * group + c;
@@ -1170,9 +1185,9 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
                                                   typename GemvSrc<SRC>::type parts) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int pair = blockIdx.x, ks = blockIdx.y;
-    const int kb0 = (int)(((long)ks * KT) / KS), kb1 = (int)(((long)(ks + 1) * KT) / KS);
+    const int kb0 = MODE == 0 ? 0 : part_of(ks, KT, KS), kb1 = MODE == 0 ? KT : part_of(ks + 1, KT, KS);
     const int nk = kb1 - kb0;
-    const int k0 = kb0 + (wave * nk) / W, k1 = kb0 + ((wave + 1) * nk) / W;
+    const int k0 = kb0 + (int)((unsigned)(wave * nk) / W), k1 = kb0 + (int)((unsigned)((wave + 1) * nk) / W);
     f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
     // rows == 16: two n-tiles of 1 KiB fragments.  rows < 16 (narrow groups of the decode-only
     // gate/up copy): per k-tile `rows` rows of the first tile then `rows` rows of the second, 16
@@ -1300,16 +1315,17 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
         constexpr bool ONE = SRC == SRC_MERGE;
         constexpr int CH = ONE ? 16 : 8, NI = ONE ? 1 : 3;
         // (states first: what returns in order behind them may take its time)
-        const int per_tok = KT * 8, n_items = epi.M * per_tok, hq = parts.d >> 2, heads = per_tok / hq;      // (hq divides per_tok)
-        auto unit = [&](int th) { return th / heads * (heads / parts.group) + th % heads / parts.group; };    // of (token, head) th
-        auto column = [&](int th) { return th % heads % parts.group; };
+        const int per_tok = KT * 8, n_items = epi.M * per_tok, heads = parts.by_heads.d;
+        auto unit = [&](int th) { return parts.by_group.div(th); };                // of (token, head) th: KV heads have whole groups
+        auto column = [&](int th) { return parts.by_group.mod(th); };
+        auto th_of = [&](int item) { return parts.by_quads.div(item); };           // an item: four features of a (token, head)
         MergeLoads<CH> L;
         float4 o[ONE ? 1 : NI][CH];
         const int e = min((int)threadIdx.x, n_items - 1), n_th = epi.M * heads;
         __shared__ __attribute__((aligned(16))) float fac[ONE ? 1 : W * 64][CH];
         __shared__ float2 dens[ONE ? 1 : W * 64];
         if constexpr (ONE) {
-            L.load(parts, unit(e / hq), column(e / hq), e % hq, 0);
+            L.load(parts, unit(th_of(e)), column(th_of(e)), parts.by_quads.mod(e), 0);
         } else {
             const int th = min((int)threadIdx.x, n_th - 1);
 #pragma unroll
@@ -1323,7 +1339,7 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
                 const int ei = min(e + i * W * 64, n_items - 1);
 #pragma unroll
                 for (int j = 0; j < CH; ++j)
-                    o[i][j] = *(const float4 *)(parts.sums(unit(ei / hq), min(j, parts.n_splits - 1), column(ei / hq)) + 4 * (ei % hq));
+                    o[i][j] = *(const float4 *)(parts.sums(unit(th_of(ei)), min(j, parts.n_splits - 1), column(th_of(ei))) + 4 * parts.by_quads.mod(ei));
             }
         }
         SPD_SCHED_BARRIER();
@@ -1339,11 +1355,11 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
         between();
         SPD_SCHED_BARRIER();
         auto put = [&](int item, float4 v) {
-            const int k = 4 * (item % per_tok);
-            *(bf16x4 *)(merged + (k >> 5) * 1024 + 2 * spd_frag_elem(item / per_tok, k & 31)) = cvt4h(v.x, v.y, v.z, v.w);
+            const int tok = parts.by_heads.div(th_of(item)), k = 4 * (item - tok * per_tok);
+            *(bf16x4 *)(merged + (k >> 5) * 1024 + 2 * spd_frag_elem(tok, k & 31)) = cvt4h(v.x, v.y, v.z, v.w);
         };
         if constexpr (ONE) {
-            if ((int)threadIdx.x < n_items) put(e, merge_splits<CH>(parts, unit(e / hq), column(e / hq), e % hq, L));
+            if ((int)threadIdx.x < n_items) put(e, merge_splits<CH>(parts, unit(th_of(e)), column(th_of(e)), parts.by_quads.mod(e), L));
         } else {
             float mc = -INFINITY, den = 0.f;
 #pragma unroll
@@ -1369,11 +1385,11 @@ __global__ void __launch_bounds__(W * 64) k_gemv(const __bf16 *__restrict__ Wp, 
                 float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
                 for (int j = 0; j < CH; ++j) {
-                    const float f = fac[ei / hq][j];
+                    const float f = fac[th_of(ei)][j];
                     v.x += o[i][j].x * f; v.y += o[i][j].y * f; v.z += o[i][j].z * f; v.w += o[i][j].w * f;
                 }
                 // v / den as a division rounds it: the quotient by the reciprocal, corrected by its remainder
-                const float2 dn = dens[ei / hq];
+                const float2 dn = dens[th_of(ei)];
                 auto quotient = [&](float n) {
                     const float q = n * dn.y, r = __builtin_fmaf(-dn.x, q, n);
                     return __builtin_isfinite(q) ? __builtin_fmaf(r, dn.y, q) : q;
@@ -1542,9 +1558,9 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
     extern __shared__ __attribute__((aligned(16))) char sk_lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int pair = blockIdx.x, ks = blockIdx.y, mt0 = blockIdx.z * MT;
-    const int kb0 = (int)(((long)ks * KT) / KS), kb1 = (int)(((long)(ks + 1) * KT) / KS);
+    const int kb0 = MODE == 0 ? 0 : part_of(ks, KT, KS), kb1 = MODE == 0 ? KT : part_of(ks + 1, KT, KS);
     const int nk = kb1 - kb0;
-    const int k0 = kb0 + (wave * nk) / W, k1 = kb0 + ((wave + 1) * nk) / W;
+    const int k0 = kb0 + (int)((unsigned)(wave * nk) / W), k1 = kb0 + (int)((unsigned)((wave + 1) * nk) / W);
     f32x4 acc[MT][2];
 #pragma unroll
     for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -1662,7 +1678,7 @@ __global__ void __launch_bounds__(MID_PAIRS * 64) k_mid(const __bf16 *__restrict
     if (!live) pair = n_pairs - 1;        // a spare wave repeats the last pair and drops the result
     const int ks = blockIdx.y;
     const int nst = (KT + MID_KB - 1) / MID_KB;                  // stages in all of K
-    const int sb0 = (int)(((long)ks * nst) / KS), sb1 = (int)(((long)(ks + 1) * nst) / KS);
+    const int sb0 = part_of(ks, nst, KS), sb1 = part_of(ks + 1, nst, KS);
     const int ns = sb1 - sb0;                                    // >= 1: the launcher keeps KS <= nst
     const int rot = (int)((blockIdx.x * 5u + blockIdx.y * 3u) % (unsigned)ns);
     auto stage_of = [&](int st) {
@@ -1931,7 +1947,7 @@ __global__ void __launch_bounds__(G::WN *G::WM * 64, 1)
         }
         spd_tile_at(ord, tile0 + idx, tn, tm);
     }
-    const int kt_first = (int)(((long)kslice * KT) / kslices), nk = (int)(((long)(kslice + 1) * KT) / kslices) - kt_first;
+    const int kt_first = part_of(kslice, KT, kslices), nk = part_of(kslice + 1, KT, kslices) - kt_first;
     const int nt0 = tn * BN, mt0 = (tm * msub + sub) * BM;
     if (mt0 >= n_mtiles) return;                 // second half of a tile whose first half holds all the rows (whole workgroup)
     // Copies go through buffer descriptors of the tile's panels: a lane's offset plus one wave-uniform offset per
@@ -2338,10 +2354,10 @@ __global__ void __launch_bounds__(256) k_attn_decode(__bf16 *__restrict__ kc, __
     __shared__ __attribute__((aligned(16))) __bf16 snew[2][d];         // new key, new value
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
-    const int group = q / kv, qd = q * d, n_splits = parts.n_splits;
+    const int group = parts.group, qd = q * d, n_splits = parts.n_splits;
     const int n_keys = FUSED ? P.pos[b] : P.pos[b] + 1;       // keys in the cache
     const int nblk = (n_keys + 31) >> 5;
-    const int b0 = (int)(((long)split * nblk) / n_splits), b1 = (int)(((long)(split + 1) * nblk) / n_splits);
+    const int b0 = part_of(split, nblk, n_splits), b1 = part_of(split + 1, nblk, n_splits);
     const int col = lane & 15, g = lane >> 4;
     const bool cvalid = col < group;
     const bool newtok = FUSED && split == n_splits - 1;
@@ -2526,13 +2542,14 @@ __global__ void __launch_bounds__(256) k_attn_decode(__bf16 *__restrict__ kc, __
 // merge the splits and write the normalised output as packed activations of the O projection: row = token, contraction index =
 // head*d + dd.  grid (groups of 64 of a unit's group * d / 4 quads, KV heads, sequences); every thread reads the maximum and sum of its
 // head itself (16 splits at a time, all loads issued together), so the kernel is one memory round trip per 16 splits.
-__global__ void __launch_bounds__(64) k_attn_combine(float *po, int units, int n_splits, int group, int d, __bf16 *__restrict__ ahat,
-                                                     __bf16 *__restrict__ alo) {
-    const AttnParts parts = {po, units, n_splits, group, d};
+__global__ void __launch_bounds__(64) k_attn_combine(float *po, int units, int n_splits, int group, int d, Divider by_quads,
+                                                     __bf16 *__restrict__ ahat, __bf16 *__restrict__ alo) {
+    AttnParts parts;
+    parts.o = po; parts.units = units; parts.n_splits = n_splits; parts.group = group; parts.d = d;
     const int hq = parts.d >> 2, kvh = blockIdx.y, b = blockIdx.z, kv = gridDim.y, batch = gridDim.z, u = b * kv + kvh;
     const int e = blockIdx.x * 64 + threadIdx.x;
     if (e >= parts.group * hq) return;
-    const int c = e / hq, quad = e % hq, qd = kv * parts.group * parts.d;
+    const int c = by_quads.div(e), quad = by_quads.mod(e), qd = kv * parts.group * parts.d;
     MergeLoads<16> L;
     L.load(parts, u, c, quad, 0);
     const float4 v = merge_splits<16>(parts, u, c, quad, L);
@@ -3166,6 +3183,7 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
         }
         parts.o = (float *)(c.ws + D.ws_apart);
         parts.units = units; parts.n_splits = splits; parts.group = D.group; parts.d = D.d;
+        parts.by_quads = Divider::by(D.d / 4); parts.by_heads = Divider::by(D.q); parts.by_group = Divider::by(D.group);
         merge_o = merge_in_o(c, D.h / 32, qd / 32, splits);
     }
     spd_stage_begin(c, SPD_STAGE_ATTN);
@@ -3191,7 +3209,7 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
         SPD_TRY(hipGetLastError());
         if (!merge_o || c.taps) {      // (a tapped call also wants what the O projection would keep to itself)
             hipLaunchKernelGGL(k_attn_combine, dim3(cdiv(D.group * D.d / 4, 64), D.kv, c.batch), dim3(64), 0, c.s, parts.o, parts.units, parts.n_splits,
-                               parts.group, parts.d, ahat, alo);
+                               parts.group, parts.d, parts.by_quads, ahat, alo);
             SPD_TRY(hipGetLastError());
         }
     } else {
