@@ -211,6 +211,7 @@ struct spd_call {
     const spd_dims *D;
     hipStream_t s;
     int batch, q_len, M;
+    int layers;               // blocks of the call: 1, or those of a model call
     size_t slot_stride;       // elements between two ranks' slots (a chain of a two-chain call keeps the whole call's)
     spd_positions pos;
     int max_pos_end;          // max over sequences of positions[b] + q_len

@@ -2231,8 +2231,8 @@ struct KVFrags {
     bf16x8 k0[DT / 2], k1[DT / 2], v[DT];
 };
 
-// all fragments of one 32-key block: 2 x 16 keys x d for K, d x 32 keys for V
-template <int DT>
+// all fragments of one 32-key block: 2 x 16 keys x d for K, d x 32 keys for V.  STREAM: not to be kept in the caches
+template <int DT, bool STREAM = false>
 __device__ __forceinline__ void load_kv(KVFrags<DT> &f, const __bf16 *__restrict__ kbase, const __bf16 *__restrict__ vbase,
                                         int vb, int d, int lane) {
     const bf16x8 *k0 = (const bf16x8 *)(kbase + (size_t)(2 * vb) * 16 * d) + lane;
@@ -2240,11 +2240,11 @@ __device__ __forceinline__ void load_kv(KVFrags<DT> &f, const __bf16 *__restrict
     const bf16x8 *vf = (const bf16x8 *)(vbase + (size_t)vb * 32 * d) + lane;
 #pragma unroll
     for (int t = 0; t < DT / 2; ++t) {
-        f.k0[t] = k0[t * 64];
-        f.k1[t] = k1[t * 64];
+        f.k0[t] = STREAM ? __builtin_nontemporal_load(k0 + t * 64) : k0[t * 64];
+        f.k1[t] = STREAM ? __builtin_nontemporal_load(k1 + t * 64) : k1[t * 64];
     }
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) f.v[dt] = vf[dt * 64];
+    for (int dt = 0; dt < DT; ++dt) f.v[dt] = STREAM ? __builtin_nontemporal_load(vf + dt * 64) : vf[dt * 64];
 }
 
 // one 32-key block: keys [vb*32, vb*32+32) of one (sequence, KV head); n_keys_col = number of
@@ -2340,7 +2340,9 @@ __device__ __forceinline__ void load_q(bf16x8 *qf, const __bf16 *__restrict__ qb
 // hi + lo bf16 pairs; the cache then holds the P.pos[b] earlier positions only, and the
 // workgroup of the last split adds the new token: it sums its key and value, rounds them to the
 // cache's bf16, appends them to the cache and attends to them as one more (single-key) block.
-template <int DT, bool FUSED>
+//
+// STREAM: caches that do not fit beside the weights in what the chip keeps from one step to the next (256 MB) are read past it.
+template <int DT, bool FUSED, bool STREAM>
 __global__ void __launch_bounds__(256) k_attn_decode(__bf16 *__restrict__ kc, __bf16 *__restrict__ vc, const float *__restrict__ qkvp, int q, int kv,
                                                      int max_ctx, int KS, int part_rows, int nqkv, const __bf16 *__restrict__ qbuf_in,
                                                      const __bf16 *__restrict__ qlo_in, const float *__restrict__ xss, float xh, float xeps,
@@ -2399,7 +2401,7 @@ __global__ void __launch_bounds__(256) k_attn_decode(__bf16 *__restrict__ kc, __
     // The first block only: a wave's second one ahead of the queries too held it at its requests until most of them had been served (4.5 of
     // 7.7 us at 16 sequences of 4096 of the 70B shard), and everything below came after that.
     KVFrags<DT> f0, f1;
-    load_kv<DT>(f0, kbase, vbase, min(b0 + wave, nblk > 0 ? nblk - 1 : 0), d, lane);      // (the cache holds at least one block)
+    load_kv<DT, STREAM>(f0, kbase, vbase, min(b0 + wave, nblk > 0 ? nblk - 1 : 0), d, lane);      // (the cache holds at least one block)
     SPD_SCHED_BARRIER();
     bf16x8 qf[DT];
     if constexpr (FUSED) {
@@ -2474,17 +2476,17 @@ __global__ void __launch_bounds__(256) k_attn_decode(__bf16 *__restrict__ kc, __
         attn_block<DT>(st, qf, f0, b0 + wave, cvalid ? n_keys : 0, scale, lane);
     } else if (nw > 1) {
         auto blk = [&](int j) { return b0 + wave + 4 * (j < nw ? j : nw - 1); };
-        load_kv<DT>(f1, kbase, vbase, blk(1), d, lane);
+        load_kv<DT, STREAM>(f1, kbase, vbase, blk(1), d, lane);
         SPD_SCHED_BARRIER();
         int j = 0;
         for (; j + 2 < nw; j += 2) {
             attn_block<DT>(st, qf, f0, blk(j), cvalid ? n_keys : 0, scale, lane);
             SPD_SCHED_BARRIER();
-            load_kv<DT>(f0, kbase, vbase, blk(j + 2), d, lane);
+            load_kv<DT, STREAM>(f0, kbase, vbase, blk(j + 2), d, lane);
             SPD_SCHED_BARRIER();
             attn_block<DT>(st, qf, f1, blk(j + 1), cvalid ? n_keys : 0, scale, lane);
             SPD_SCHED_BARRIER();
-            load_kv<DT>(f1, kbase, vbase, blk(j + 3), d, lane);
+            load_kv<DT, STREAM>(f1, kbase, vbase, blk(j + 3), d, lane);
             SPD_SCHED_BARRIER();
         }
         attn_block<DT>(st, qf, f0, blk(j), cvalid ? n_keys : 0, scale, lane);
@@ -3191,13 +3193,21 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
         // skipped
     } else if (c.q_len == 1) {
         const dim3 grid(parts.n_splits, D.kv, c.batch);
-#define SPD_DECODE(DTV)                                                                                              \
-    if (fused_q)                                                                                                     \
-        hipLaunchKernelGGL((k_attn_decode<DTV, true>), grid, dim3(256), 0, c.s, kc, vc, qkvp, D.q, D.kv, D.max_ctx, qkv_slices, 16 * n_mtiles, \
-                           D.nqkv, (const __bf16 *)nullptr, (const __bf16 *)nullptr, raw.ss, (float)D.h, D.eps, qbuf, qlo, parts, c.pos);     \
-    else                                                                                                             \
-        hipLaunchKernelGGL((k_attn_decode<DTV, false>), grid, dim3(256), 0, c.s, kc, vc, (const float *)nullptr, D.q, D.kv, D.max_ctx, 1, 16,  \
-                           D.nqkv, qbuf, qlo, (const float *)nullptr, 1.f, 0.f, (__bf16 *)nullptr, (__bf16 *)nullptr, parts, c.pos)
+        // us per call, kept / past the caches: 13B 8 of 4096 four layers 210.4 / 205.4 (4 x 84 MB), 70B 16 of 4096 four layers 246.7 / 244.6 (4 x 34 MB), 48 of
+        // 3000 90.5 / 88.0 (74 MB), 13B 16 of 4000 68.9 / 64.8 (164 MB), 7B 64 of 1000 74.3 / 66.8 (131 MB); but 7B 8 of 4000 42.4 / 43.4, 13B 8 of 2000
+        // 44.4 / 44.9, 70B 16 of 4096 in one layer 62.3 / 62.8, 48 of 375 to 1300 81.9 / 82.2 (20 to 34 MB, which a repeated call finds in the caches)
+        int64_t kv_bytes = 0;
+        for (int i = 0; i < c.batch; ++i) kv_bytes += c.pos.pos[i];
+        kv_bytes *= (int64_t)4 * D.kv * D.d * c.layers;
+        const bool stream = kv_bytes >= ((int64_t)64 << 20);
+#define SPD_DECODE_AS(DTV, FUSED_, STREAM_)                                                                                                    \
+    hipLaunchKernelGGL((k_attn_decode<DTV, FUSED_, STREAM_>), grid, dim3(256), 0, c.s, kc, vc, fused_q ? qkvp : nullptr, D.q, D.kv, D.max_ctx,  \
+                       qkv_slices, 16 * n_mtiles, D.nqkv, qbuf, qlo, raw.ss, (float)D.h, D.eps, qbuf, qlo, parts, c.pos)
+#define SPD_DECODE(DTV)                                   \
+    if (fused_q && stream) SPD_DECODE_AS(DTV, true, true);  \
+    else if (fused_q) SPD_DECODE_AS(DTV, true, false);      \
+    else if (stream) SPD_DECODE_AS(DTV, false, true);       \
+    else SPD_DECODE_AS(DTV, false, false)
         switch (DT) {
             case 2: SPD_DECODE(2); break;
             case 4: SPD_DECODE(4); break;
@@ -3206,6 +3216,7 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
             default: return hipErrorInvalidValue;
         }
 #undef SPD_DECODE
+#undef SPD_DECODE_AS
         SPD_TRY(hipGetLastError());
         if (!merge_o || c.taps) {      // (a tapped call also wants what the O projection would keep to itself)
             hipLaunchKernelGGL(k_attn_combine, dim3(cdiv(D.group * D.d / 4, 64), D.kv, c.batch), dim3(64), 0, c.s, parts.o, parts.units, parts.n_splits,
