@@ -149,8 +149,9 @@ __global__ void __launch_bounds__(512) k_row_scale(const float *__restrict__ ss,
 
 // ------------------------------------------------------------------------------------------
 // prep: out = base + (slot0 + slot1 + ...), xhat = fp16(out * gain) in packed layout (plus its
-// lo plane), and the partial sums of squares of `out` per (k-chunk, token).  One wave per
-// (m-tile, chunk of `tpw` k-tiles); lane l handles token l%16 and 8 consecutive features.
+// lo plane), and the partial sums of squares of `out` per (workgroup, token).  One wave per
+// (m-tile, chunk of `tpw` k-tiles); lane l handles token l%16 and 8 consecutive features.  (With a partial per wave the QKV projection of 48
+// sequences read 256 of them per token in four rounds, 3.7 us of its 13.)
 // ------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_prep(const float *__restrict__ base, const float *__restrict__ slots,
                                               int n_slots, size_t slot_stride, float *__restrict__ out,
@@ -234,7 +235,12 @@ __global__ void __launch_bounds__(256) k_prep(const float *__restrict__ base, co
     }
     ssum += shfl_xor_f(ssum, 16);
     ssum += shfl_xor_f(ssum, 32);
-    if (ss && g == 0 && chunk * tpw < KT) ss[(size_t)chunk * m_pad + m] = ssum;
+    if (!ss) return;
+    __shared__ float part[4][16];
+    if (g == 0) part[wave][lane] = ssum;
+    __syncthreads();
+    if (threadIdx.x < 16)
+        ss[(size_t)blockIdx.x * m_pad + m] = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
 }
 
 // prep for long calls (more than 512 tokens, hidden size a multiple of 256): the same sums in the
@@ -1790,7 +1796,6 @@ __global__ void __launch_bounds__(FIN_WAVES * 64) k_mid_finish(const f32x4 *__re
     const bool live = pair < n_pairs;
     typename Epi::Pre pre;
     if (live && q == 0) pre = epi.pre(pair, mt, lane);
-    // the first slices are requested before the norm statistics are dealt with
     const f32x4 *src = kpart + (((size_t)(live ? pair : n_pairs - 1) * KS * n_mtiles + mt) * 2) * 64 + lane;
     const size_t sstr = (size_t)n_mtiles * 128;
     f32x4 ta[NL], tb[NL];
@@ -1802,6 +1807,9 @@ __global__ void __launch_bounds__(FIN_WAVES * 64) k_mid_finish(const f32x4 *__re
             tb[j] = src[(size_t)sl * sstr + 64];
         }
     };
+    SsLoads ssl;                             // (ahead of the slices: loads return in order)
+    if constexpr (Epi::kNeedsRs)
+        if (epi.nch != 0) ssl.load(epi.ss, epi.nch, epi.m_pad, mt * 16 + (threadIdx.x & 15), threadIdx.x >> 4, 32);
     load(q);
     float rs = 1.f;
     if constexpr (Epi::kNeedsRs) {
@@ -1809,7 +1817,7 @@ __global__ void __launch_bounds__(FIN_WAVES * 64) k_mid_finish(const f32x4 *__re
             rs = epi.ss[mt * 16 + (lane & 15)];
         } else {
             const int r = threadIdx.x & 15, part = threadIdx.x >> 4;       // 32 parts
-            red[part][r] = sum_ss(epi.ss, epi.nch, epi.m_pad, mt * 16 + r, part, 32);
+            red[part][r] = ssl.sum(epi.ss, epi.nch, epi.m_pad, mt * 16 + r, part, 32);
             __syncthreads();
             if (threadIdx.x < 16) {
                 float t = 0.f;
@@ -3010,10 +3018,10 @@ constexpr int PREP_ROWS_WGS = 512;       // workgroups of the row-wise preparati
 // layer with all sync points dropped / all kept: 64: 2459 / 2790, 96: 2408 / 2702, 112: 2374 / 2699, 128: 2367 / 2552,
 // 144: 2442 / 2712, 192: 2426 / 2718; k_prep_rows: 2454 / 2690
 constexpr int PREP_CU_WGS = 128;
-// chunking of the sum-of-squares partials written by prep(): k-tiles per wave of k_prep, enough waves to occupy the chip
-// at every call size
+// chunking of the sum-of-squares partials written by prep(): k-tiles per wave of k_prep (one partial for its four waves), enough
+// waves to occupy the chip at every call size; 256 features in the row-wise kernels
 inline int prep_tpw(int M) { return M <= 64 ? 1 : (M <= 512 ? 2 : 8); }
-inline int prep_nch(int h, int M) { return (int)cdiv(h / 32, prep_tpw(M)); }
+inline int prep_nch(int h, int M) { return prep_tpw(M) == 8 && h % 256 == 0 ? h / 256 : (int)cdiv(h / 32, 4 * prep_tpw(M)); }
 
 }  // namespace
 
@@ -3048,7 +3056,7 @@ hipError_t prep(const spd_call &c, const float *base, const float *slots, int n_
                                base, slots, 0, c.slot_stride, out, gain, xhat, xlo, ss, c.M, D.h, D.m_pad, bias, n_chunks, n_items);
     }
     else
-        hipLaunchKernelGGL(k_prep, dim3(cdiv(nch, 4), cdiv(c.M, 16)), dim3(256), 0, c.s, base, slots, n_slots,
+        hipLaunchKernelGGL(k_prep, dim3(nch, cdiv(c.M, 16)), dim3(256), 0, c.s, base, slots, n_slots,
                            c.slot_stride, out, gain, xhat, xlo, ss, c.M, D.h, tpw, D.m_pad, bias);
     return hipGetLastError();
 }
@@ -3072,7 +3080,8 @@ inline ProjW proj_weights(const spd_call &c, const char *w, int i) {
 // K slices of the QKV projection that the attention kernel adds up itself, 1: none.
 // A decode step whose QKV projection has too few column tiles to occupy the chip: K slices with the linear epilogue (at
 // most SPD_MAX_QKV_SLICES), whose partial rows the attention kernel adds itself.  Up to 16 sequences about 240
-// workgroups of 16 waves, at least two k-tiles per wave; more of them, about 480 of the skinny kernel's 8 waves (two fit a compute unit).
+// workgroups of 16 waves, at least two k-tiles per wave; more of them, up to 256 of the skinny kernel's 8 waves (two fit a compute unit, but
+// with 320 of them the 64 units that had two decided: 70B 48 sequences 82.1 / 80.5, 64 79.9 / 78.4).
 // (Also where gemv_whole() would contract K in one launch: the slices cost no second kernel here.  hidden 2048, 96 pairs,
 // slices / whole, us per layer: 4 sequences of 4000 positions 52 / 53.6, 8: 67.5 / 70, 16: 102 / 104.5.)
 int decode_qkv_slices(const spd_call &c) {
@@ -3080,7 +3089,7 @@ int decode_qkv_slices(const spd_call &c) {
     const int n_mtiles = (c.M + 15) / 16, qkv_pairs = D.nqkv / 32;
     int qkv_slices = 1;
     if (c.q_len == 1 && n_mtiles <= 4 && qkv_pairs < GEMV_MANY_PAIRS) {
-        const int want = n_mtiles == 1 ? (240 + qkv_pairs - 1) / qkv_pairs : 480 / qkv_pairs;
+        const int want = n_mtiles == 1 ? (240 + qkv_pairs - 1) / qkv_pairs : 256 / qkv_pairs;
         qkv_slices = want < 2 ? 2 : (want > SPD_MAX_QKV_SLICES ? SPD_MAX_QKV_SLICES : want);
         const int most = D.h / 32 / (2 * (n_mtiles == 1 ? QKV_SLICE_W : SKINNY_W));
         if (qkv_slices > most) qkv_slices = most;
