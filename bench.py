@@ -126,7 +126,10 @@ def stage_kernel(w, stage: str) -> str:
     if M <= 128 and (pairs * kt >= 40 * 1024 or (mt > 4 and pairs >= 128 and pairs * kt >= 20 * 1024)):
         if slices(cdiv(pairs, 8), cdiv(kt, 4) // 4, pairs, mt) >= 2:
             return f"k_mid<{2 if mt <= 2 else 4 if mt <= 4 else 8}>+" + finish_kernel(pairs, mt)
-    skinny = f"k_skinny<8,{2 if mt <= 2 else 4 if mt <= 4 else 8},false,0,EpiGU>"
+    # (8 m-tiles and more of pairs in sixteens: two pairs and four m-tiles per workgroup)
+    skinny = f"k_skinny<8,{2 if mt <= 2 else 4 if mt <= 4 else 8},false,0,EpiGU,1,false>"
+    if mt >= 8 and pairs % 16 == 0:
+        skinny = f"k_skinny<8,4,false,0,EpiGU,2,{'true' if mt > 8 else 'false'}>"
     n16, n8 = cdiv(2 * pairs, 16), cdiv(2 * pairs, 8)
     halves = n16 * cdiv(mt, 8)
     if M <= 512:

@@ -1552,70 +1552,80 @@ __global__ void __launch_bounds__(256) k_gemv_finish(const float *__restrict__ k
 // m-tiles).  The W x MT partial tile pairs meet in LDS; wave w finishes m-tiles w, w + W, ...
 //   MODE 0: whole K (KS = 1), Epi::operator();  MODE 2: K slices, Epi::slice (linear epilogues)
 // ------------------------------------------------------------------------------------------
-template <int MT, bool SPLIT>
+template <int MT, bool SPLIT, int NP>
 struct SkinnySet {
-    bf16x8 fa, fb, fh[MT], fl[SPLIT ? MT : 1];
+    bf16x8 fa[NP], fb[NP], fh[MT], fl[SPLIT ? MT : 1];
     static constexpr int kRing = MT == 2 ? (SPLIT ? 3 : 4) : 2;      // (three or four sets of 8 m-tiles: 70B 128 tokens 103 -> 124, 136 us)
 };
 
-template <int W, int MT, bool SPLIT, int MODE, class Epi>
+// NP pairs of n-tiles per workgroup: 1, or 2 with 4 m-tiles (see launch_skinny()).  KEEP: the weights stay in the L2 for the other groups of m-tiles
+template <int W, int MT, bool SPLIT, int MODE, class Epi, int NP = 1, bool KEEP = false>
 __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp, const __bf16 *__restrict__ Xhi,
                                                     const __bf16 *__restrict__ Xlo, int KT, int KS, int n_mtiles, unsigned rot_step, Epi epi) {
     extern __shared__ __attribute__((aligned(16))) char sk_lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int pair = blockIdx.x, ks = blockIdx.y, mt0 = blockIdx.z * MT;
+    const int pair0 = blockIdx.x * NP, ks = blockIdx.y, mt0 = blockIdx.z * MT;
     const int kb0 = MODE == 0 ? 0 : part_of(ks, KT, KS), kb1 = MODE == 0 ? KT : part_of(ks + 1, KT, KS);
     const int nk = kb1 - kb0;
     const int k0 = kb0 + (int)((unsigned)(wave * nk) / W), k1 = kb0 + (int)((unsigned)((wave + 1) * nk) / W);
-    f32x4 acc[MT][2];
+    f32x4 acc[NP][MT][2];
 #pragma unroll
-    for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const char *wa = (const char *)(Wp + spd_frag_index(2 * pair, 0, KT)), *wb = (const char *)(Wp + spd_frag_index(2 * pair + 1, 0, KT));
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int i = 0; i < MT; ++i) acc[p][i][0] = acc[p][i][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const char *wa = (const char *)(Wp + spd_frag_index(2 * pair0, 0, KT));
+    const size_t wrow = (size_t)KT * 1024;             // bytes between two n-tiles
     // (MT divides a group's 8 m-tiles; m-tiles past the call's last one are zeros)
     const char *xh = (const char *)(Xhi + spd_act_index(mt0, 0, KT, n_mtiles)), *xl = (const char *)(Xlo + spd_act_index(mt0, 0, KT, n_mtiles));
     const unsigned xstr = 1024u * spd_act_width(mt0, n_mtiles), l16 = lane * 16;
     const int n = k1 - k0;
     // Each workgroup starts at its own k-tile (rot_step, see launch_skinny_mt()), so that an XCD's compute units don't all ask
     // one L2 channel for the same activations.
-    const int rot = n > 0 ? (int)((unsigned)pair * rot_step % (unsigned)n) : 0;
-    auto load = [&](SkinnySet<MT, SPLIT> &B, int q) {
+    const int rot = n > 0 ? (int)(blockIdx.x * rot_step % (unsigned)n) : 0;
+    auto load = [&](SkinnySet<MT, SPLIT, NP> &B, int q) {
         const unsigned wn = 1024, xn = xstr;
         q += rot;
         const size_t kt = k0 + (q >= n ? q - n : q);
-        B.fa = frag<true>(wa + kt * 1024, wn, l16);
-        B.fb = frag<true>(wb + kt * 1024, wn, l16);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            B.fa[p] = frag<!KEEP>(wa + 2 * p * wrow + kt * 1024, wn, l16);
+            B.fb[p] = frag<!KEEP>(wa + (2 * p + 1) * wrow + kt * 1024, wn, l16);
+        }
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
             B.fh[i] = frag<false>(xh + kt * xstr, xn, l16 + i * 1024);
             if (SPLIT) B.fl[i] = frag<false>(xl + kt * xstr, xn, l16 + i * 1024);
         }
     };
-    auto consume = [&](const SkinnySet<MT, SPLIT> &B) {
+    auto consume = [&](const SkinnySet<MT, SPLIT, NP> &B) {
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            acc[i][0] = MFMA16(B.fa, B.fh[i], acc[i][0]);
-            acc[i][1] = MFMA16(B.fb, B.fh[i], acc[i][1]);
-            if (SPLIT) {
-                acc[i][0] = MFMA16(B.fa, B.fl[i], acc[i][0]);
-                acc[i][1] = MFMA16(B.fb, B.fl[i], acc[i][1]);
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                acc[p][i][0] = MFMA16(B.fa[p], B.fh[i], acc[p][i][0]);
+                acc[p][i][1] = MFMA16(B.fb[p], B.fh[i], acc[p][i][1]);
+                if (SPLIT) {
+                    acc[p][i][0] = MFMA16(B.fa[p], B.fl[i], acc[p][i][0]);
+                    acc[p][i][1] = MFMA16(B.fb[p], B.fl[i], acc[p][i][1]);
+                }
             }
-        }
     };
     // the norm statistics by all threads while the first weights are on their way: at the end, a wave per m-tile, they were
     // eight dependent rounds of loads for 256 partials per token
     __shared__ float early_ss[Epi::kNeedsRs ? W * 64 : 1];
     constexpr int RS_PARTS = W * 4 / MT;               // threads per token
-    // wave w finishes m-tile w: what its epilogue reads is requested now
-    static_assert(MT <= W, "a wave per m-tile");
-    const bool fin = wave < MT && mt0 + wave < n_mtiles;
+    // wave w finishes m-tile w % MT of pair w / MT: what its epilogue reads is requested now
+    static_assert(NP * MT <= W, "a wave per m-tile and pair");
+    const int pair = pair0 + wave / MT, wmt = mt0 + wave % MT;
+    const bool fin = wave < NP * MT && wmt < n_mtiles;
     typename Epi::Pre pre;
     constexpr bool EARLY = Epi::kSync && !(SPLIT && MT == 8);      // (the registers for 8 m-tiles of pairs are all taken)
     SyncRegs peers;
-    stream_tiles<SkinnySet<MT, SPLIT>::kRing, SkinnySet<MT, SPLIT>>(n, load, consume, [&]() {
-        if (fin) pre = epi.pre(pair, mt0 + wave, lane);
+    stream_tiles<SkinnySet<MT, SPLIT, NP>::kRing, SkinnySet<MT, SPLIT, NP>>(n, load, consume, [&]() {
+        if (fin) pre = epi.pre(pair, wmt, lane);
         if constexpr (EARLY) {
             const SyncSum sy = epi.sync();
-            if (fin) sy.load(peers, sy.at(pair, mt0 + wave, lane));
+            if (fin) sy.load(peers, sy.at(pair, wmt, lane));
         }
         if constexpr (Epi::kNeedsRs) {
             int m = mt0 * 16 + (int)threadIdx.x % (MT * 16);
@@ -1623,26 +1633,27 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
             early_ss[threadIdx.x] = sum_ss(epi.ss, epi.nch, epi.m_pad, m, (int)threadIdx.x / (MT * 16), RS_PARTS);
         }
     });
-    f32x4 *red = (f32x4 *)sk_lds;        // [W][MT][2][64]
+    f32x4 *red = (f32x4 *)sk_lds;        // [W][NP * MT][2][64]
+    constexpr int NT = NP * MT;
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-        red[((wave * MT + t) * 2 + 0) * 64 + lane] = acc[t][0];
-        red[((wave * MT + t) * 2 + 1) * 64 + lane] = acc[t][1];
+    for (int t = 0; t < NT; ++t) {
+        red[((wave * NT + t) * 2 + 0) * 64 + lane] = acc[t / MT][t % MT][0];
+        red[((wave * NT + t) * 2 + 1) * 64 + lane] = acc[t / MT][t % MT][1];
     }
     __syncthreads();
     if (!fin) return;
-    const int t = wave, mt = mt0 + t;
-    f32x4 a = red[((0 * MT + t) * 2 + 0) * 64 + lane], b = red[((0 * MT + t) * 2 + 1) * 64 + lane];
+    const int t = wave, mt = wmt;
+    f32x4 a = red[((0 * NT + t) * 2 + 0) * 64 + lane], b = red[((0 * NT + t) * 2 + 1) * 64 + lane];
 #pragma unroll
     for (int w = 1; w < W; ++w) {
-        a += red[((w * MT + t) * 2 + 0) * 64 + lane];
-        b += red[((w * MT + t) * 2 + 1) * 64 + lane];
+        a += red[((w * NT + t) * 2 + 0) * 64 + lane];
+        b += red[((w * NT + t) * 2 + 1) * 64 + lane];
     }
     float rs = 1.f;
     if constexpr (Epi::kNeedsRs) {
         float q = 0.f;
 #pragma unroll
-        for (int part = 0; part < RS_PARTS; ++part) q += early_ss[part * MT * 16 + t * 16 + (lane & 15)];
+        for (int part = 0; part < RS_PARTS; ++part) q += early_ss[part * MT * 16 + t % MT * 16 + (lane & 15)];
         rs = 1.0f / sqrtf(q / (float)epi.h + epi.eps);
     }
     if constexpr (MODE == 2) epi.slice(pair, ks, mt, a, b, lane, rs, pre);
@@ -2771,21 +2782,21 @@ hipError_t launch_gemv_sliced(const spd_call &c, bool split, const __bf16 *Wp, c
 
 // 17 .. 512 tokens, short contractions: the skinny kernel, groups of MT m-tiles in grid.z.  KS > 1 only with MODE 2.
 constexpr int SKINNY_W = 8;
-template <int MT, bool SPLIT, int MODE, class Epi>
+template <int MT, bool SPLIT, int MODE, int NP = 1, bool KEEP = false, class Epi>
 hipError_t launch_skinny_mt(const spd_call &c, const __bf16 *Wp, const __bf16 *Xhi, const __bf16 *Xlo, int n_pairs, int KT,
                             int KS, int n_mtiles, const Epi &epi) {
-    constexpr int lds = SKINNY_W * MT * 2 * 1024;
+    constexpr int lds = SKINNY_W * NP * MT * 2 * 1024;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute((const void *)k_skinny<SKINNY_W, MT, SPLIT, MODE, Epi>,
+        attr_err = hipFuncSetAttribute((const void *)k_skinny<SKINNY_W, MT, SPLIT, MODE, Epi, NP, KEEP>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (attr_err != hipSuccess) return attr_err;
     // k-tiles in a rotated order, but front to back when there are more pairs than compute units (from HBM, 32 sequences: down
     // of 7B, 128 pairs x 344 k-tiles, 34.6 us front to back / 31.0 rotated, 160 x 216 24.4 / 22.2; but QKV, 384 x 128, 31.4 / 39.6)
     const unsigned rot_step = n_pairs <= 256 ? 5 : 0;
-    hipLaunchKernelGGL((k_skinny<SKINNY_W, MT, SPLIT, MODE, Epi>), dim3(n_pairs, KS, (n_mtiles + MT - 1) / MT), dim3(SKINNY_W * 64),
+    hipLaunchKernelGGL((k_skinny<SKINNY_W, MT, SPLIT, MODE, Epi, NP, KEEP>), dim3(n_pairs / NP, KS, (n_mtiles + MT - 1) / MT), dim3(SKINNY_W * 64),
                        lds, c.s, Wp, Xhi, Xlo, KT, KS, n_mtiles, rot_step, epi);
     return hipGetLastError();
 }
@@ -2800,6 +2811,16 @@ hipError_t launch_skinny(const spd_call &c, bool split, const __bf16 *Wp, const 
     if (n_mtiles <= 4)
         return split ? launch_skinny_mt<4, true, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi)
                      : launch_skinny_mt<4, false, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi);
+    // Two pairs and four m-tiles per workgroup instead of one and eight: as many workgroups, but 64 + 64 rows of operands drawn through a compute
+    // unit's load path instead of 32 + 128, which at 50 GB/s is what bounds these launches; the weights are asked for by two or more
+    // workgroups, on one XCD as long as their number per group of m-tiles is a multiple of 8.  us per call, one pair / two: 13B 333 tokens with the
+    // kept sync point 125.1 / 121.3, 7B 500 122.2 / 115.8, 270 89.4 / 86.3, 70B 160 141.5 / 139.9.  Eight m-tiles, read by two workgroups at the same time, as
+    // data that is read once: 70B 128 tokens 104.8 / 103.2 (kept sync point 107.6 / 105.1), 13B 74.4 / 71.1, 4-way 98.4 / 93.9, 7B 58.6 / 58.0.
+    // (Seven m-tiles: 70B 97.7 / 98.7, 13B 70.8 / 70.2; fewer draw more than with one pair.)
+    if constexpr (MODE == 0)
+        if (!split && n_pairs % 16 == 0 && n_mtiles >= 8)
+            return n_mtiles > 8 ? launch_skinny_mt<4, false, MODE, 2, true>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi)
+                                : launch_skinny_mt<4, false, MODE, 2, false>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi);
     return split ? launch_skinny_mt<8, true, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi)
                  : launch_skinny_mt<8, false, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi);
 }

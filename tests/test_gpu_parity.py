@@ -421,6 +421,20 @@ def test_bf16_medium_model_call_in_square_tiles(gpu, w):
     case.close()
 
 
+# the skinny kernel with two pairs of n-tiles and four m-tiles per workgroup (8 m-tiles and more, pairs in sixteens), against one pair and eight (7 m-tiles;
+# 100 pairs): O and down of 96 pairs, 12 and 39 k-tiles, m-tiles that end inside a group of four
+SKINNY_96 = Workload(name="96-pairs-39-k-tiles", hidden=3072, n_q_heads=24, n_kv_heads=4, head_dim=32, ffn=2496, n_layers=1, tp=2, dtype=BF16,
+                     seed=64, batch=1, q_len=1, ctx=64, mask=(1,))
+SKINNY_100 = Workload(name="100-pairs-39-k-tiles", hidden=3200, n_q_heads=24, n_kv_heads=4, head_dim=32, ffn=2496, n_layers=1, tp=2, dtype=BF16,
+                      seed=65, batch=1, q_len=1, ctx=64, mask=(1,))
+
+
+@pytest.mark.parametrize("w", [SKINNY_96, SKINNY_100], ids=lambda w: w.name)
+@pytest.mark.parametrize("q_len,flag", [(112, 1), (113, 0), (128, 1), (129, 0), (150, 1), (200, 0), (333, 0), (500, 1), (512, 0)])
+def test_bf16_skinny_kernel_of_two_pairs(gpu, w, q_len, flag):
+    _one_rank_block(gpu, w, 1, q_len, [0], flag, bias_std=0.1 * (q_len % 2))
+
+
 # the kernel that adds the slices takes 2, 4 or 8 pairs of n-tiles per workgroup, by the number of groups of 8 times m-tiles (lines at 64 and
 # 128): gate/up of 66 pairs (9 groups) on either side of both lines, QKV of 7 pairs
 FIN_66 = Workload(name="66-and-7-pairs", hidden=3232, n_q_heads=10, n_kv_heads=2, head_dim=32, ffn=2112, n_layers=1, tp=2, dtype=BF16,
