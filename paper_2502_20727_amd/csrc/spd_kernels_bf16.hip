@@ -2581,7 +2581,8 @@ __global__ void __launch_bounds__(64) k_attn_combine(float *po, int units, int n
     if (alo) *(bf16x4 *)(alo + o) = cvt4h_lo(v.x, v.y, v.z, v.w, hi);
 }
 
-// Prefill (q_len > 1): grid (groups of CT column tiles, kv heads, sequences), 4 waves.  All four
+// Prefill (q_len > 1): grid (groups of CT column tiles x kv heads, 1, sequences), 4 waves.  (The heads side by side: workgroups go to the XCDs in turn, so
+// that an XCD's L2 sees the keys of one or two of four heads; 2048 tokens of 7B, 4 heads, 25.0 -> 19.4 us.)  All four
 // waves work on the same CT tiles of 16 (token, head) columns and deal the causal key range
 // among themselves block by block (the latest tokens attend thousands of keys: one wave walking
 // them alone would be the critical path of the launch); their partial states meet in LDS and
@@ -2595,11 +2596,12 @@ __global__ void __launch_bounds__(256) k_attn_prefill(const __bf16 *__restrict__
     f32x4 *so = (f32x4 *)ap_lds;                                   // [4 waves][CT][DT][64 lanes]
     float *sml = (float *)(ap_lds + 4 * CT * DT * 64 * 16);        // [4 waves][CT][2][16]: running max, running sum
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int kvh = blockIdx.y, b = blockIdx.z;
+    const unsigned group0 = blockIdx.x / (unsigned)kv, n_groups = gridDim.x / (unsigned)kv;
+    const int kvh = (int)(blockIdx.x - group0 * kv), b = blockIdx.z;
     const int group = q / kv, qd = q * d;
     const int n_cols = q_len * group;
     // causal: the later a token, the more keys it attends; the long workgroups are launched first
-    const int ct0 = (gridDim.x - 1 - blockIdx.x) * CT;
+    const int ct0 = (int)(n_groups - 1 - group0) * CT;
     const int g = lane >> 4;
     const int pos0 = P.pos[b];
     bf16x8 qf[CT][DT];
@@ -3261,7 +3263,7 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
         const bool one = (int64_t)cdiv(n_ct, 2) * D.kv * c.batch <= 512;
 #define SPD_PREFILL_CT(DTV, CT)                                                                                            \
     {                                                                                                                      \
-        const dim3 grid(cdiv(n_ct, CT), D.kv, c.batch);                                                                                                                      \
+        const dim3 grid(D.kv * cdiv(n_ct, CT), 1, c.batch);                                                                  \
         constexpr int lds = 4 * CT * DTV * 64 * 16 + 4 * CT * 2 * 16 * 4;                                                  \
         static std::once_flag once;                                                                                        \
         static hipError_t attr_err = hipSuccess;                                                                           \
