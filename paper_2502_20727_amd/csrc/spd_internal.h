@@ -204,6 +204,15 @@ struct spd_stage_timer {
     std::vector<hipEvent_t> start, stop;
 };
 
+// n / d for n < 2^16, d < 2^16 (the rounded-up reciprocal is off by less than 2^-32, n of it by less than 1 / d)
+// A launch constant that kernels divide by: the division of the hardware's instruction set is some forty instructions, one after the other.
+struct Divider {
+    unsigned inv, d;
+    static Divider by(unsigned d) { return Divider{d > 1 ? (unsigned)((0x100000000ull + d - 1) / d) : 0u, d}; }
+    __device__ __forceinline__ int div(int n) const { return d == 1 ? n : (int)__umulhi((unsigned)n, inv); }
+    __device__ __forceinline__ int mod(int n) const { return n - div(n) * (int)d; }
+};
+
 // ------------------------------------------------------------------------------------------
 // Launchers (defined next to their kernels).  All enqueue on `s` and return a hipError_t.
 // ------------------------------------------------------------------------------------------

@@ -147,11 +147,13 @@ __global__ void __launch_bounds__(512) k_row_scale(const float *__restrict__ ss,
     }
 }
 
+constexpr int PREP_BY_WAVE = 16;
 // ------------------------------------------------------------------------------------------
 // prep: out = base + (slot0 + slot1 + ...), xhat = fp16(out * gain) in packed layout (plus its
-// lo plane), and the partial sums of squares of `out` per (workgroup, token).  One wave per
+// lo plane), and the partial sums of squares of `out` per (workgroup, token), up to PREP_BY_WAVE tokens per (wave, token).  One wave per
 // (m-tile, chunk of `tpw` k-tiles); lane l handles token l%16 and 8 consecutive features.  (With a partial per wave the QKV projection of 48
-// sequences read 256 of them per token in four rounds, 3.7 us of its 13.)
+// sequences read 256 of them per token in four rounds, 3.7 us of its 13.  Up to 16 tokens its 64 threads per token read them in one, and as
+// many partials as the fused epilogues leave are added in the same order.)
 // ------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_prep(const float *__restrict__ base, const float *__restrict__ slots,
                                               int n_slots, size_t slot_stride, float *__restrict__ out,
@@ -236,6 +238,10 @@ __global__ void __launch_bounds__(256) k_prep(const float *__restrict__ base, co
     ssum += shfl_xor_f(ssum, 16);
     ssum += shfl_xor_f(ssum, 32);
     if (!ss) return;
+    if (M <= PREP_BY_WAVE) {
+        if (g == 0 && chunk * tpw < KT) ss[(size_t)chunk * m_pad + m] = ssum;
+        return;
+    }
     __shared__ float part[4][16];
     if (g == 0) part[wave][lane] = ssum;
     __syncthreads();
@@ -1026,13 +1032,6 @@ struct EpiPark {
 // group's real heads (1 of an MFMA's 16 columns in multi-head attention), a head's features side by side.  (Whole tiles of 16 columns
 // before: us per layer 70B 16 sequences of 4096 63.8 -> 62.6, 13B 8 of 4096 56.3 -> 54.8, 7B 1 of 2048 40.4 -> 38.8.)
 // ------------------------------------------------------------------------------------------
-// n / d for n < 2^16, d < 2^16 (the rounded-up reciprocal is off by less than 2^-32, n of it by less than 1 / d)
-struct Divider {
-    unsigned inv, d;
-    static Divider by(unsigned d) { return Divider{d > 1 ? (unsigned)((0x100000000ull + d - 1) / d) : 0u, d}; }
-    __device__ __forceinline__ int div(int n) const { return d == 1 ? n : (int)__umulhi((unsigned)n, inv); }
-    __device__ __forceinline__ int mod(int n) const { return n - div(n) * (int)d; }
-};
 struct AttnParts {
     float *o;
     int units, n_splits, group, d;
@@ -1900,9 +1899,14 @@ hipError_t launch_mid_finish(hipStream_t s, const f32x4 *kpart, int KS, int n_pa
 // wait), and in the second one the copies of the stage NST steps ahead.  The one barrier of a step sits between its
 // sub-steps: passing it means that everybody has read both fragments of the current stage (whose place the copies
 // take) and that the next stage has landed; the copies of the stages after that stay in flight across it.
-// What bounds it: the matrix cores at the clock they hold under load, and beside them the LDS (64 bytes per clock and
-// compute unit: 12 fragment reads per 32 MFMAs).  gate/up of 4096 tokens of the 70B shard runs at 1.3 PFLOP/s, spd_mfma_probe() (the
-// same MFMAs on register-resident random data, nothing else) at 1.63 .. 1.76; matrix cores busy 70 % of the cycles.
+// What bounds it: the matrix cores at the clock they hold under load (gate/up of 4096 tokens of the 70B shard runs at 1.3 PFLOP/s, spd_mfma_probe(), the
+// same MFMAs on register-resident random data and nothing else, at 1.63 .. 1.76; matrix cores busy 70 % of the cycles), and
+// in calls of one or two rounds what a compute unit draws through its load path: loads return in order, 52 GB/s of them from the HBM, 90
+// from the last-level cache, 110 from the L2, however many are on their way.  Gate/up of 1000 tokens (256 x 128 tiles), us: the copies alone 112 with the
+// weights from the HBM and 73 from the cache, the MFMAs alone 71, MFMAs and LDS reads 95, all of it 118 and 104.  (The LDS is not it: a kernel of
+// nothing but such reads draws 212 bytes per clock and compute unit, and MFMAs with 12 reads per 32 and this barrier run as fast as MFMAs alone.
+// 32 x 32 x 16 MFMAs: 1.63 against 1.78 PFLOP/s on random data.  One of the workgroups that share a panel touching it some stages ahead: copies
+// alone 110 -> 80 us, the kernel 118 -> 115, from the cache 102 -> 106.)
 // ------------------------------------------------------------------------------------------
 // Tile shapes.  WN x WM waves, each TI n-tiles x TJ m-tiles; stages of the plain and of the split (XS) kind.
 struct GemmBig {      // 256 x 256: two stages of 64 KiB (split: three of 48 KiB)
@@ -3044,7 +3048,10 @@ constexpr int PREP_CU_WGS = 128;
 // chunking of the sum-of-squares partials written by prep(): k-tiles per wave of k_prep (one partial for its four waves), enough
 // waves to occupy the chip at every call size; 256 features in the row-wise kernels
 inline int prep_tpw(int M) { return M <= 64 ? 1 : (M <= 512 ? 2 : 8); }
-inline int prep_nch(int h, int M) { return prep_tpw(M) == 8 && h % 256 == 0 ? h / 256 : (int)cdiv(h / 32, 4 * prep_tpw(M)); }
+inline int prep_nch(int h, int M) {
+    if (M <= PREP_BY_WAVE) return (int)cdiv(h / 32, prep_tpw(M));
+    return prep_tpw(M) == 8 && h % 256 == 0 ? h / 256 : (int)cdiv(h / 32, 4 * prep_tpw(M));
+}
 
 }  // namespace
 
@@ -3079,7 +3086,7 @@ hipError_t prep(const spd_call &c, const float *base, const float *slots, int n_
                                base, slots, 0, c.slot_stride, out, gain, xhat, xlo, ss, c.M, D.h, D.m_pad, bias, n_chunks, n_items);
     }
     else
-        hipLaunchKernelGGL(k_prep, dim3(nch, cdiv(c.M, 16)), dim3(256), 0, c.s, base, slots, n_slots,
+        hipLaunchKernelGGL(k_prep, dim3(c.M <= PREP_BY_WAVE ? cdiv(nch, 4) : nch, cdiv(c.M, 16)), dim3(256), 0, c.s, base, slots, n_slots,
                            c.slot_stride, out, gain, xhat, xlo, ss, c.M, D.h, tpw, D.m_pad, bias);
     return hipGetLastError();
 }

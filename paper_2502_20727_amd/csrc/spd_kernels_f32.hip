@@ -172,21 +172,22 @@ struct RowsQKV {       // queries and keys rotated, keys and values appended to 
     float *qkv, *kc, *vc;
     size_t qkv_rank, kv_rank;
     const float *cosT, *sinT;
-    int q_len, q, kv, d, nqkv, max_ctx;
+    int q, kv, d, dlog, nqkv, max_ctx;         // d = 2^dlog (it divides 64)
+    Divider by_qlen;
     spd_positions P;
     struct Pre { float c, s; int b, pos; };
-    __device__ __forceinline__ int where(int m) const { return P.pos[m / q_len]; }
+    __device__ __forceinline__ int where(int m) const { return P.pos[by_qlen.div(m)]; }
     __device__ __forceinline__ Pre pre(int first, int, int m, int n) const {
-        const int half = d >> 1, j = n % d, jj = j < half ? j : j - half;
+        const int half = d >> 1, j = n & (d - 1), jj = j < half ? j : j - half;
         Pre p;
-        p.b = m / q_len;
-        p.pos = first + (m % q_len);
+        p.b = by_qlen.div(m);
+        p.pos = first + by_qlen.mod(m);
         p.c = cosT[(size_t)p.pos * half + jj];
         p.s = sinT[(size_t)p.pos * half + jj];
         return p;
     }
     __device__ __forceinline__ void operator()(const float *tile, const float *, int r, int cl, int m, int n, int z, const Pre &p) const {
-        const int half = d >> 1, head = n / d, j = n % d;
+        const int half = d >> 1, head = n >> dlog, j = n & (d - 1);
         float v = tile[r * RN + cl];
         if (head < q + kv) {
             const float o = tile[r * RN + (j < half ? cl + half : cl - half)];
@@ -447,8 +448,9 @@ hipError_t launch_rows(hipStream_t s, const RowsIn &in, const float *W, const fl
 constexpr int ROWS_ATT_PASSES = 2;
 template <int RM, int KMAX, int D>
 __global__ void __launch_bounds__(RW * 64) k_rows_att(const float *__restrict__ qkv, const float *__restrict__ kc, const float *__restrict__ vc,
-                                                      const float *__restrict__ W, int q, int q_len, int kv, int nqkv, int max_ctx, int M, int N,
-                                                      int wpi, int qkv_rank, int w_rank, size_t kv_rank, spd_positions P, RowsO epi) {
+                                                      const float *__restrict__ W, int q, int kv, int nqkv, int max_ctx, int M, int N,
+                                                      int wpi, int qkv_rank, int w_rank, Divider by_wpi, Divider by_q, Divider by_qlen, Divider by_group,
+                                                      size_t kv_rank, spd_positions P, RowsO epi) {
     constexpr int NP = ROWS_ATT_PASSES, F = D / 8;
     constexpr int U = KMAX / RW < 32 ? KMAX / RW : 32;
     __shared__ float xs[KMAX * RM], red[RW * RM * RN];
@@ -458,10 +460,10 @@ __global__ void __launch_bounds__(RW * 64) k_rows_att(const float *__restrict__ 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n0 = blockIdx.x * RN, m0 = blockIdx.y * RM, z = blockIdx.z;
     const int n = n0 + lane < N ? n0 + lane : N - 1;
-    const int item = wave / wpi < RM * q ? wave / wpi : RM * q - 1, part = wave % wpi;      // (a wave too many repeats the last item and is not used)
-    const int row = item / q, head = item % q, m = m0 + row < M ? m0 + row : M - 1, b = m / q_len;
-    const int n_keys = P.pos[b] + m % q_len + 1;                                             // causal
-    const size_t c0 = z * kv_rank + ((size_t)b * kv + head / (q / kv)) * max_ctx * D + (lane & 7) * F;
+    const int item = min(by_wpi.div(wave), RM * q - 1), part = by_wpi.mod(wave);      // (a wave too many repeats the last item and is not used)
+    const int row = by_q.div(item), head = by_q.mod(item), m = m0 + row < M ? m0 + row : M - 1, b = by_qlen.div(m);
+    const int n_keys = P.pos[b] + by_qlen.mod(m) + 1;                                  // causal
+    const size_t c0 = z * kv_rank + ((size_t)b * kv + by_group.div(head)) * max_ctx * D + (lane & 7) * F;
     struct Piece { float v[F]; };
     auto piece = [](const float *p) { Piece r; __builtin_memcpy(&r, p, sizeof(r)); return r; };       // (the cache is aligned to its elements only)
     const Piece qv = piece(qkv + (size_t)z * qkv_rank + (size_t)m * nqkv + head * D + (lane & 7) * F);
@@ -535,7 +537,7 @@ __global__ void __launch_bounds__(RW * 64) k_rows_att(const float *__restrict__ 
             den += sml[w][1] * sc;
             num += so[w][f] * sc;
         }
-        xs[(it % q * D + f) * RM + it / q] = num / den;
+        xs[(by_q.mod(it) * D + f) * RM + by_q.div(it)] = num / den;
     }
     __syncthreads();
     rows_product<RM, U>(xs, red, tile, k0, k1, w0, w1, load, epi, elem, er, en - n0, em, en, z, pre);
@@ -687,7 +689,7 @@ static RowsQKV rows_qkv(const spd_call &c, float *qkv, size_t qkv_rank, char *kv
     e.qkv = qkv; e.qkv_rank = qkv_rank;
     e.kc = (float *)kvc; e.vc = (float *)(kvc + D.kv_v); e.kv_rank = D.kv_bytes / 4;
     e.cosT = (const float *)(c.ws + D.ws_cos); e.sinT = (const float *)(c.ws + D.ws_sin);
-    e.q_len = c.q_len; e.q = D.q; e.kv = D.kv; e.d = D.d; e.nqkv = D.nqkv; e.max_ctx = D.max_ctx; e.P = c.pos;
+    e.by_qlen = Divider::by(c.q_len); e.q = D.q; e.kv = D.kv; e.d = D.d; e.dlog = __builtin_ctz(D.d); e.nqkv = D.nqkv; e.max_ctx = D.max_ctx; e.P = c.pos;
     return e;
 }
 static RowsIn rows_in(const spd_call &c, const float *a, size_t a_rank, const float *gain) {
@@ -742,8 +744,8 @@ static hipError_t launch_rows_att_rm(const spd_call &c, const float *qkv, size_t
     const dim3 grid((D.h + RN - 1) / RN, (c.M + RM - 1) / RM, n);
 #define SPD_ROWS_ATT(KMAX, DD)                                                                                                              \
     hipLaunchKernelGGL((k_rows_att<RM, KMAX, DD>), grid, dim3(RW * 64), 0, c.s, qkv, (const float *)kvc, (const float *)(kvc + D.kv_v),      \
-                       (const float *)(w + D.w_o), D.q, c.q_len, D.kv, D.nqkv, D.max_ctx, c.M, D.h, wpi, (int)qkv_rank,                      \
-                       (int)(D.weight_bytes / 4), D.kv_bytes / 4, c.pos, epi)
+                       (const float *)(w + D.w_o), D.q, D.kv, D.nqkv, D.max_ctx, c.M, D.h, wpi, (int)qkv_rank, (int)(D.weight_bytes / 4),    \
+                       Divider::by(wpi), Divider::by(D.q), Divider::by(c.q_len), Divider::by(D.group), D.kv_bytes / 4, c.pos, epi)
     // (at most 16 / RM heads)
     if (D.d == 32) SPD_ROWS_ATT(RW / RM * 32, 32);
     else if (D.q * 64 <= 256 || RM > 2) SPD_ROWS_ATT(256, 64);
