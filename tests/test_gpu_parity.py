@@ -435,6 +435,34 @@ def test_bf16_skinny_kernel_of_two_pairs(gpu, w, q_len, flag):
     _one_rank_block(gpu, w, 1, q_len, [0], flag, bias_std=0.1 * (q_len % 2))
 
 
+# Decode attention on caches of 64 MB per call and more (here: of all layers of a model call), which are read past the chip's caches: the same bits as a
+# block call of the first layer, whose caches are below that, with the QKV projection whole and in slices
+@pytest.mark.parametrize("head_dim,kv", [(32, 4), (64, 2), (96, 2), (128, 1)])
+@pytest.mark.parametrize("hidden", [256, 2048], ids=["whole", "sliced"])
+def test_bf16_decode_of_large_caches(gpu, head_dim, kv, hidden):
+    import torch
+    w = Workload(name=f"kv-{head_dim}", hidden=hidden, n_q_heads=4 * kv, n_kv_heads=2 * kv, head_dim=head_dim, ffn=128, n_layers=11, tp=2, dtype=BF16,
+                 seed=66, batch=12, q_len=1, ctx=1056, mask=(1, 0) * 5 + (1,))
+    positions = [1055 - 3 * i for i in range(12)]
+    assert 4 * kv * head_dim * sum(positions) < 64 << 20 <= 11 * 4 * kv * head_dim * sum(positions)
+    shard = B.DeviceShard(w, [0], gpu, max_ctx=1056, max_tokens=12, max_batch=12)
+    torch.manual_seed(66)
+    for l in range(w.n_layers):
+        shard.load_layer(l, [inputs.layer_shard(w, 0, 0)])
+        shard.kv[l].view(torch.bfloat16).normal_()
+    x, slots = torch.randn(12, hidden, device=gpu), torch.zeros(2, 12, hidden, device=gpu)
+    taps, out = torch.zeros(w.n_layers, 12, hidden, device=gpu), torch.empty_like(x)
+    kv0 = shard.kv[0].clone()
+    B.spd_block_forward(shard.ctx, 0, 1, 0, shard.weights[0], shard.kv[0], positions, 12, 1, x, slots, out, shard.workspace)
+    torch.cuda.synchronize()
+    appended, want = shard.kv[0].clone(), out.clone()
+    shard.kv[0].copy_(kv0)
+    B.spd_model_forward_staged(shard.ctx, w.mask, 0, shard.weights, shard.kv, positions, 12, 1, x, slots.zero_(), out, shard.workspace, layer_out=taps)
+    torch.cuda.synchronize()
+    assert torch.isfinite(want).all() and torch.equal(taps[0], want) and torch.equal(shard.kv[0], appended)
+    shard.close()
+
+
 # the kernel that adds the slices takes 2, 4 or 8 pairs of n-tiles per workgroup, by the number of groups of 8 times m-tiles (lines at 64 and
 # 128): gate/up of 66 pairs (9 groups) on either side of both lines, QKV of 7 pairs
 FIN_66 = Workload(name="66-and-7-pairs", hidden=3232, n_q_heads=10, n_kv_heads=2, head_dim=32, ffn=2112, n_layers=1, tp=2, dtype=BF16,
