@@ -502,12 +502,14 @@ __global__ void __launch_bounds__(RW * 64) k_rows_att(const float *__restrict__ 
     }
 #pragma unroll
     for (int o = 8; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    // (a wave without keys, or whose keys all have no score, which a maximum passes over: the state is 0 for the one and NaN for the other)
+    const float top = mx == -INFINITY ? 0.f : mx;
     float sum = 0.f, out[F];
 #pragma unroll
     for (int f = 0; f < F; ++f) out[f] = 0.f;
 #pragma unroll
     for (int t = 0; t < NP; ++t) {
-        const float p = live[t] ? expf(s[t] - mx) : 0.f;
+        const float p = live[t] ? expf(s[t] - top) : 0.f;
         sum += p;
 #pragma unroll
         for (int f = 0; f < F; ++f) out[f] += live[t] ? p * vv[t].v[f] : 0.f;
@@ -532,8 +534,7 @@ __global__ void __launch_bounds__(RW * 64) k_rows_att(const float *__restrict__ 
         float mm = -INFINITY, den = 0.f, num = 0.f;
         for (int w = it * wpi; w < (it + 1) * wpi; ++w) mm = fmaxf(mm, sml[w][0]);
         for (int w = it * wpi; w < (it + 1) * wpi; ++w) {
-            if (sml[w][0] == -INFINITY && mm != -INFINITY) continue;             // (no key of its own)
-            const float sc = expf(sml[w][0] - mm);
+            const float sc = expf(sml[w][0] - mm);               // (0 for a wave without keys)
             den += sml[w][1] * sc;
             num += so[w][f] * sc;
         }

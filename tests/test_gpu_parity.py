@@ -881,6 +881,42 @@ def test_fp32_attention_in_the_output_projection(gpu, hidden, tp, q, kv, d, batc
     case.close()
 
 
+# ... and keys without a score (NaN, inf - inf) make their sequence's row NaN, as in the attention's own launch, and leave the other row alone: all the keys
+# that a wave has (the newest one, which is alone in its wave at 9 and 17; an aligned block of eight), all of the sequence's, or one of a wave's eight
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("first,count", [(-1, 1), (0, 8), (0, 40), (3, 1)], ids=["newest", "block", "all", "one"])
+@pytest.mark.parametrize("n_keys", [9, 17, 40])
+def test_fp32_attention_in_the_output_projection_keeps_nan(gpu, n_keys, first, count, value):
+    import torch
+    w = Workload(name="f32-att-nan", hidden=64, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=64, n_layers=1, tp=1, dtype=F32, seed=67, batch=1, q_len=1,
+                 ctx=64, mask=(0,))
+    positions, S = [n_keys - 1, 20], B.STAGES
+    first = n_keys + first if first < 0 else first
+    case = Case(w, gpu, ranks=[0], positions=positions, max_ctx=64, max_tokens=2)
+    x, out, got = case.to_dev(inputs.hidden_states(w, 2)), torch.empty((2, 64), dtype=torch.float32, device=gpu), []
+    timer = B.spd_stage_timer_create(S["attn"], 4)
+
+    def call(slots, mask):
+        B.spd_model_forward_staged(case.dev.ctx, w.mask, 0, case.dev.weights, case.dev.kv, positions, 2, 1, x, slots, out, case.dev.workspace,
+                                   stage_mask=mask, timer=timer)
+
+    for masks in ([(1 << S["attn"]) | (1 << S["o"])], [1 << S["attn"], 1 << S["o"]]):
+        slots = torch.zeros((1, 2, 64), dtype=torch.float32, device=gpu)
+        call(slots, 1 << S["qkv"])
+        # (infinities of both signs, so that the score has no value in whatever order it is summed)
+        case.dev.kv[0].view(torch.float32)[:64 * 64].view(64, 64)[first:min(first + count, n_keys)] = torch.tensor([value, -value] * 32, device=gpu)
+        for mask in masks:
+            call(slots, mask)
+        torch.cuda.synchronize()
+        assert B.spd_stage_timer_read(timer)[0] == len(got)      # the fused launch first
+        got.append(slots[0].cpu().numpy())
+    B.spd_stage_timer_destroy(timer)
+    for g in got:
+        assert np.isnan(g[0]).all() and np.isfinite(g[1]).all()
+    assert np.max(np.abs(got[0][1] - got[1][1])) <= 1e-5 * np.max(np.abs(got[1][1]))
+    case.close()
+
+
 # fp32 attention where a thread takes a second key (256 keys and more), the waves' shares end unevenly and the output needs a
 # second and a fourth pass of 64 features
 @pytest.mark.parametrize("head_dim", [2, 64, 66, 128, 256])
