@@ -453,7 +453,8 @@ __global__ void __launch_bounds__(RW * 64) k_rows_att(const float *__restrict__ 
                                                       size_t kv_rank, spd_positions P, RowsO epi) {
     constexpr int NP = ROWS_ATT_PASSES, F = D / 8;
     constexpr int U = KMAX / RW < 32 ? KMAX / RW : 32;
-    __shared__ float xs[KMAX * RM], red[RW * RM * RN];
+    __shared__ __attribute__((aligned(16))) float xs[KMAX * RM];      // (read as RowsOf<RM>)
+    __shared__ float red[RW * RM * RN];
     __shared__ float tile[1][RM * RN];
     __shared__ float so[RW][D], sml[RW][2];
     const int K = q * D;
