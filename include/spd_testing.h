@@ -101,6 +101,12 @@ int spd_gemm_tile_of(int32_t TN, int32_t TM, int32_t rn, int32_t rm, int32_t til
  * largest tile does not fit 32-bit byte offsets and other kernels serve the call; SPD_EINVAL: negative.  Host only. */
 int spd_gemm_panels_fit(int32_t k_tiles);
 
+/* ---------------------------------------------------------------- K slices of a decode step
+ * The number of K slices in which a decode step (q_len = 1) of `batch` sequences runs its QKV projection: 1 when it runs whole
+ * or on the fp32 path.  A launch has this many workgroups for every 32 columns of the projection.  SPD_EINVAL: NULL, batch outside
+ * 1 .. SPD_MAX_BATCH.  Host only. */
+int spd_decode_qkv_slices(const spd_ctx *ctx, int32_t batch);
+
 #ifdef __cplusplus
 }
 #endif

@@ -618,6 +618,11 @@ extern "C" int spd_gemm_launch_size(int32_t n_tiles) {
     return spd_tile_launch_size(n_tiles);
 }
 
+extern "C" int spd_decode_qkv_slices(const spd_ctx *ctx, int32_t batch) {
+    if (!ctx || batch < 1 || batch > SPD_MAX_BATCH) return SPD_EINVAL;
+    return ctx->D.dtype == SPD_BF16 ? spd_bf16::decode_qkv_slices(ctx->D, batch) : 1;
+}
+
 extern "C" int spd_gemm_panels_fit(int32_t k_tiles) { return k_tiles < 0 ? SPD_EINVAL : (spd_gemm_fits(k_tiles) ? 1 : 0); }
 
 extern "C" int spd_gemm_tile_of(int32_t TN, int32_t TM, int32_t rn, int32_t rm, int32_t tile0, int32_t n_tiles, int32_t b,

@@ -3110,24 +3110,35 @@ inline ProjW proj_weights(const spd_call &c, const char *w, int i) {
 // K slices of the QKV projection that the attention kernel adds up itself, 1: none.
 // A decode step whose QKV projection has too few column tiles to occupy the chip: K slices with the linear epilogue (at
 // most SPD_MAX_QKV_SLICES), whose partial rows the attention kernel adds itself.  Up to 16 sequences about 240
-// workgroups of 16 waves, at least two k-tiles per wave; more of them, up to 256 of the skinny kernel's 8 waves (two fit a compute unit, but
-// with 320 of them the 64 units that had two decided: 70B 48 sequences 82.1 / 80.5, 64 79.9 / 78.4).
+// workgroups of 16 waves, at least two k-tiles per wave; more of them, workgroups of the skinny kernel's 8 waves (two fit a compute unit): as many
+// slices as fill their rounds of the chip best, up to two of them, the fewer among equals.  us per call of 24 / 48 sequences: 70B (40 pairs) 8 slices
+// (1.25 rounds) 71.1 / 76.4, 6 (0.94) 70.0 / 75.1; 7B 4-way (96) 2 (0.75) 80.3 / 85.5, 5 (1.88) 80.2 / 85.3, at 17 and 32 53.8 / 57.9 and 53.4 / 57.2;
+// 132 pairs 2 (1.03) 69.7 / 81.6, 3 (1.55) 66.2 / 77.7; 160 2 (1.25) 64.3 / 78.2, 3 (1.88) 61.3 / 74.8; level: 7B (48) 8 (1.5) / 5 (0.94), 13B (60)
+// 8 (1.88) / 4 (0.94), 4-way (120) 4 / 2, 72 pairs 3 (0.84) / 7 (1.97).
 // (Also where gemv_whole() would contract K in one launch: the slices cost no second kernel here.  hidden 2048, 96 pairs,
 // slices / whole, us per layer: 4 sequences of 4000 positions 52 / 53.6, 8: 67.5 / 70, 16: 102 / 104.5.)
-int decode_qkv_slices(const spd_call &c) {
-    const spd_dims &D = *c.D;
-    const int n_mtiles = (c.M + 15) / 16, qkv_pairs = D.nqkv / 32;
+int qkv_slices_wanted(int pairs) {
+    int best = 2;
+    auto fill = [&](int KS) { return KS * pairs / (double)((KS * pairs + 255) / 256); };        // workgroups per round
+    for (int KS = 3; KS <= SPD_MAX_QKV_SLICES && KS * pairs <= 512; ++KS)
+        if (fill(KS) > fill(best)) best = KS;
+    return best;
+}
+}  // namespace
+
+int decode_qkv_slices(const spd_dims &D, int sequences) {
+    const int n_mtiles = (sequences + 15) / 16, qkv_pairs = D.nqkv / 32;
     int qkv_slices = 1;
-    if (c.q_len == 1 && n_mtiles <= 4 && qkv_pairs < GEMV_MANY_PAIRS) {
-        const int want = n_mtiles == 1 ? (240 + qkv_pairs - 1) / qkv_pairs : 256 / qkv_pairs;
+    if (n_mtiles <= 4 && qkv_pairs < GEMV_MANY_PAIRS) {
+        const int want = n_mtiles == 1 ? (240 + qkv_pairs - 1) / qkv_pairs : qkv_slices_wanted(qkv_pairs);
         qkv_slices = want < 2 ? 2 : (want > SPD_MAX_QKV_SLICES ? SPD_MAX_QKV_SLICES : want);
         const int most = D.h / 32 / (2 * (n_mtiles == 1 ? QKV_SLICE_W : SKINNY_W));
-        if (qkv_slices > most) qkv_slices = most;
+        if (qkv_slices > most) qkv_slices = most > 1 ? most : 1;
         while (qkv_slices > 1 && (size_t)qkv_slices * 16 * n_mtiles * D.nqkv > (size_t)SPD_MAX_KPART * 512) --qkv_slices;
     }
     return qkv_slices;
 }
-}  // namespace
+static int decode_qkv_slices(const spd_call &c) { return c.q_len == 1 ? decode_qkv_slices(*c.D, c.M) : 1; }
 
 // A block call of a decode step of up to 8 sequences whose QKV projection runs in slices takes the residual stream itself: no launch for
 // the first norm's elementwise part, for twice the activation bytes.  us per call, launch / this: 7B 1 sequence 37.6 / 35.5, 4: 40.5 / 38.1; 13B 8: 44.4 /

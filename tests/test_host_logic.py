@@ -2,6 +2,7 @@
 bad arguments before touching a device, indexes ranks and counts sync points bit-exactly,
 and its packers are lossless permutations.  No compute call is made here."""
 import ctypes as C
+import dataclasses
 import os
 import re
 
@@ -535,3 +536,35 @@ def test_gemm_panels_stay_within_32_bit_offsets():
         if fits(k):      # the last byte of the last row's last fragment, as lane offset + row offset + k-tile offset
             assert 63 * 16 + 15 + 23 * k * 1024 + (k - 1) * 1024 < 2 ** 32
     assert fits(-1) == B.SPD_EINVAL
+
+
+def _qkv_slices(batch, **over):
+    cfg = dict(n_layers=1, mask=(1,), ffn=1024)
+    cfg.update(over)
+    ctx = B.spd_create(B.make_config(dataclasses.replace(workloads.LLAMA7B_DECODE, **cfg), max_batch=64, max_ctx=64, max_tokens=64))
+    n = B.lib().spd_decode_qkv_slices(ctx, batch)
+    B.spd_destroy(ctx)
+    return n
+
+
+def test_decode_qkv_slices_fill_the_chip():
+    """The QKV projection of a decode step of 17 to 64 sequences: a workgroup per pair of n-tiles and K slice, as many slices (2 to 8) as fill
+    their rounds of 256 best, up to two rounds; the shards' own, and every number of pairs below 192."""
+    shards = {"7b-decode": 5, "7b-tp4-decode": 5, "13b-decode": 4, "13b-tp4-decode": 2, "70b-decode": 6}
+    for name, want in shards.items():
+        w = workloads.get(name)
+        ctx = B.spd_create(B.make_config(w, max_batch=64, max_ctx=64, max_tokens=64))
+        assert [B.lib().spd_decode_qkv_slices(ctx, b) for b in (17, 32, 33, 48, 64)] == [want] * 5, name
+        B.spd_destroy(ctx)
+    fill = lambda n, pairs: n * pairs / (-(-n * pairs // 256) * 256)
+    for pairs in range(3, 192, 3):       # kv heads = query heads of 32: a pair each of queries, keys and values per head
+        n = _qkv_slices(48, n_q_heads=pairs // 3 * 8, n_kv_heads=pairs // 3 * 8, head_dim=32)
+        # (a number of slices is a fraction with a denominator of 256 or 512: no rounding between them)
+        fits = [k for k in range(2, 9) if k == 2 or k * pairs <= 512]
+        assert n == min(fits, key=lambda k: (-fill(k, pairs), k)), pairs
+    assert _qkv_slices(48, n_q_heads=512, n_kv_heads=512, head_dim=32) == 1          # 192 pairs
+    assert _qkv_slices(48, hidden=512, n_q_heads=64, n_kv_heads=64, head_dim=32) == 1      # a k-tile per wave and no more
+    toy = B.spd_create(B.make_config(workloads.TOY))
+    assert B.lib().spd_decode_qkv_slices(toy, 17) == 1
+    assert [B.lib().spd_decode_qkv_slices(toy, b) for b in (0, 65)] == [B.SPD_EINVAL] * 2 and B.lib().spd_decode_qkv_slices(None, 1) == B.SPD_EINVAL
+    B.spd_destroy(toy)
