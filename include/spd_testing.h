@@ -101,6 +101,12 @@ int spd_gemm_tile_of(int32_t TN, int32_t TM, int32_t rn, int32_t rm, int32_t til
  * largest tile does not fit 32-bit byte offsets and other kernels serve the call; SPD_EINVAL: negative.  Host only. */
 int spd_gemm_panels_fit(int32_t k_tiles);
 
+/* ---------------------------------------------------------------- pieces of packed activations
+ * Packed activations lie in groups of 8 m-tiles (16 tokens each), the last group as many as are left; in a group a k-tile's fragments of
+ * 1 KiB follow each other.  The bytes that a workgroup starting at m-tile mt of n_mtiles may read of a k-tile before it meets the next
+ * one's.  SPD_EINVAL: mt outside 0 .. n_mtiles - 1.  Host only. */
+int spd_act_piece_bytes(int32_t mt, int32_t n_mtiles);
+
 /* ---------------------------------------------------------------- K slices of a decode step
  * The number of K slices in which a decode step (q_len = 1) of `batch` sequences runs its QKV projection: 1 when it runs whole
  * or on the fp32 path.  A launch has this many workgroups for every 32 columns of the projection.  SPD_EINVAL: NULL, batch outside

@@ -625,6 +625,8 @@ extern "C" int spd_decode_qkv_slices(const spd_ctx *ctx, int32_t batch) {
 
 extern "C" int spd_gemm_panels_fit(int32_t k_tiles) { return k_tiles < 0 ? SPD_EINVAL : (spd_gemm_fits(k_tiles) ? 1 : 0); }
 
+extern "C" int spd_act_piece_bytes(int32_t mt, int32_t n_mtiles) { return mt < 0 || mt >= n_mtiles ? SPD_EINVAL : spd_act_bytes(mt, n_mtiles); }
+
 extern "C" int spd_gemm_tile_of(int32_t TN, int32_t TM, int32_t rn, int32_t rm, int32_t tile0, int32_t n_tiles, int32_t b,
                                 int32_t *tn, int32_t *tm) {
     if (!tn || !tm || TN <= 0 || TM <= 0 || rn <= 0 || rm <= 0 || tile0 < 0 || n_tiles < 0 || b < 0) return SPD_EINVAL;

@@ -49,6 +49,9 @@ SPD_HD int spd_act_width(int mt, int n_mtiles) {       // m-tiles in the group o
     const int rest = n_mtiles - (mt & ~(SPD_ACT_GROUP - 1));
     return rest < SPD_ACT_GROUP ? rest : SPD_ACT_GROUP;
 }
+SPD_HD int spd_act_bytes(int mt, int n_mtiles) {       // bytes of a k-tile's piece from m-tile mt to the end of its group
+    return (spd_act_width(mt, n_mtiles) - (mt & (SPD_ACT_GROUP - 1))) * SPD_FRAG_ELEMS * 2;
+}
 SPD_HD size_t spd_act_index(int mt, int ktile, int n_ktiles, int n_mtiles) {
     const int g = mt & ~(SPD_ACT_GROUP - 1);
     return ((size_t)g * (size_t)n_ktiles + (size_t)ktile * (size_t)spd_act_width(mt, n_mtiles) + (size_t)(mt - g)) * SPD_FRAG_ELEMS;

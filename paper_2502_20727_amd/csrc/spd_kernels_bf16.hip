@@ -1576,13 +1576,13 @@ __global__ void __launch_bounds__(W * 64) k_skinny(const __bf16 *__restrict__ Wp
     const size_t wrow = (size_t)KT * 1024;             // bytes between two n-tiles
     // (MT divides a group's 8 m-tiles; m-tiles past the call's last one are zeros)
     const char *xh = (const char *)(Xhi + spd_act_index(mt0, 0, KT, n_mtiles)), *xl = (const char *)(Xlo + spd_act_index(mt0, 0, KT, n_mtiles));
-    const unsigned xstr = 1024u * spd_act_width(mt0, n_mtiles), l16 = lane * 16;
+    const unsigned xstr = 1024u * spd_act_width(mt0, n_mtiles), xlen = spd_act_bytes(mt0, n_mtiles), l16 = lane * 16;
     const int n = k1 - k0;
     // Each workgroup starts at its own k-tile (rot_step, see launch_skinny_mt()), so that an XCD's compute units don't all ask
     // one L2 channel for the same activations.
     const int rot = n > 0 ? (int)(blockIdx.x * rot_step % (unsigned)n) : 0;
     auto load = [&](SkinnySet<MT, SPLIT, NP> &B, int q) {
-        const unsigned wn = 1024, xn = xstr;
+        const unsigned wn = 1024, xn = xlen;
         q += rot;
         const size_t kt = k0 + (q >= n ? q - n : q);
 #pragma unroll

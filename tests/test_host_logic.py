@@ -538,6 +538,17 @@ def test_gemm_panels_stay_within_32_bit_offsets():
     assert fits(-1) == B.SPD_EINVAL
 
 
+def test_activation_pieces_end_with_their_k_tile():
+    """A workgroup of the skinny kernel reads a k-tile's m-tiles mt .. mt + 3 or mt .. mt + 7 (mt a multiple of either): as many as there are up to the
+    group's end, zeros past them, and nothing of the next k-tile, from the group's first half and from its second."""
+    piece = B.lib().spd_act_piece_bytes
+    for n in range(1, 33):
+        for mt in range(0, n, 4):
+            end = min(mt // 8 * 8 + 8, n)              # the group's end
+            assert piece(mt, n) == (end - mt) * 1024, (mt, n)
+    assert [piece(-1, 4), piece(4, 4), piece(0, 0)] == [B.SPD_EINVAL] * 3
+
+
 def _qkv_slices(batch, **over):
     cfg = dict(n_layers=1, mask=(1,), ffn=1024)
     cfg.update(over)
