@@ -113,6 +113,12 @@ int spd_act_piece_bytes(int32_t mt, int32_t n_mtiles);
  * 1 .. SPD_MAX_BATCH.  Host only. */
 int spd_decode_qkv_slices(const spd_ctx *ctx, int32_t batch);
 
+/* ---------------------------------------------------------------- KV caches read past the chip's caches
+ * Whether a decode step behind positions[batch] reads its KV caches non-temporally: 1, or 0 (always on the fp32 path).  It depends on the
+ * context and the positions only: a model call and a block call of the same context read alike.  SPD_EINVAL: NULL, batch outside
+ * 1 .. max_batch, a position outside 0 .. max_ctx - 1.  Host only. */
+int spd_decode_past_caches(const spd_ctx *ctx, const int32_t *positions, int32_t batch);
+
 #ifdef __cplusplus
 }
 #endif

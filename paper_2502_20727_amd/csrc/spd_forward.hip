@@ -46,7 +46,6 @@ int check_call(const spd_ctx *ctx, int32_t rank, const int32_t *positions, int32
     c->ws = (char *)workspace;
     c->taps = nullptr;
     c->chained = false;
-    c->layers = 1;
     c->stages = SPD_ALL_STAGES;
     c->timer = nullptr;
     c->max_pos_end = 0;
@@ -298,7 +297,6 @@ int spd_model_forward_staged(const spd_ctx *ctx, const uint8_t *spd_mask, int32_
     c.timer = timer;
     const spd_dims &D = ctx->D;
     const int L = ctx->cfg.n_layers;
-    c.layers = L;
     for (int l = 0; l < L; ++l) {
         if (spd_mask[l] > 1) return SPD_EINVAL;
         if (!layer_weights[l] || !layer_kv[l]) return SPD_EINVAL;

@@ -98,6 +98,7 @@ void compute_dims(const spd_config &c, spd_dims &D) {
     D.max_batch = c.max_batch;
     D.max_ctx = c.max_ctx;
     D.max_tokens = c.max_tokens;
+    D.n_layers = c.n_layers;
     D.eps = c.rms_eps;
     D.rope_base = c.rope_base;
     const bool bf = c.dtype == SPD_BF16;
@@ -624,6 +625,13 @@ extern "C" int spd_decode_qkv_slices(const spd_ctx *ctx, int32_t batch) {
 }
 
 extern "C" int spd_gemm_panels_fit(int32_t k_tiles) { return k_tiles < 0 ? SPD_EINVAL : (spd_gemm_fits(k_tiles) ? 1 : 0); }
+
+extern "C" int spd_decode_past_caches(const spd_ctx *ctx, const int32_t *positions, int32_t batch) {
+    if (!ctx || !positions || batch < 1 || batch > ctx->D.max_batch) return SPD_EINVAL;
+    for (int b = 0; b < batch; ++b)
+        if (positions[b] < 0 || positions[b] >= ctx->D.max_ctx) return SPD_EINVAL;
+    return ctx->D.dtype == SPD_BF16 && spd_bf16::decode_past_caches(ctx->D, positions, batch) ? 1 : 0;
+}
 
 extern "C" int spd_act_piece_bytes(int32_t mt, int32_t n_mtiles) { return mt < 0 || mt >= n_mtiles ? SPD_EINVAL : spd_act_bytes(mt, n_mtiles); }
 

@@ -160,7 +160,7 @@ struct spd_dims {
     size_t w_gud;                 // its offset in a layer's packed weights
     int o_bias;                   // the output projection has a bias, kept at w_bo (fp32, [h])
     size_t w_bo;
-    int max_batch, max_ctx, max_tokens, m_pad;
+    int max_batch, max_ctx, max_tokens, m_pad, n_layers;
     float eps, rope_base;
     // packed shard (bytes from its start)
     size_t w_g1, w_g2, w_qkv, w_o, w_g, w_u, w_d, weight_bytes;   // w_u: f32 path only (bf16: gate/up interleaved at w_g)
@@ -223,7 +223,6 @@ struct spd_call {
     const spd_dims *D;
     hipStream_t s;
     int batch, q_len, M;
-    int layers;               // blocks of the call: 1, or those of a model call
     size_t slot_stride;       // elements between two ranks' slots (a chain of a two-chain call keeps the whole call's)
     spd_positions pos;
     int max_pos_end;          // max over sequences of positions[b] + q_len
@@ -326,6 +325,7 @@ struct spd_end_sync {
 hipError_t mlp_half(const spd_call &c, const char *w, int spd, float *slot, const spd_end_sync *fuse, bool *fused,
                     bool ss_per_pair);
 int prep_chunks(const spd_call &c);
+bool decode_past_caches(const spd_dims &D, const int32_t *positions, int sequences);      // are a decode step's KV caches read non-temporally?
 int decode_qkv_slices(const spd_dims &D, int sequences);      // K slices of a decode step's QKV projection, 1: none
 bool qkv_reads_x(const spd_call &c);      // can a block call's QKV projection do the first norm itself (spd_call::raw_x)?
 }

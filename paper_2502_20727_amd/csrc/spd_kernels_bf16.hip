@@ -3126,6 +3126,20 @@ int qkv_slices_wanted(int pairs) {
 }
 }  // namespace
 
+// A step goes through the caches of all of the context's layers before it comes to a layer's again, whether its program calls the model or walks the
+// blocks (the weights are read past the chip's caches, 256 MB, anyway).  From 256 MB on nothing is found again; us per layer, block calls walking that
+// many layers, kept / past the caches: 70B 16 of 4096, 12 layers (403 MB) 61.5 / 60.4, 7B 8 of 4000, 8 (524 MB) 43.3 / 41.8, 4 of 2048, 32 (537 MB)
+// 34.8 / 34.1, 13B 1 of 4096, 40 (419 MB) 36.9 / 35.9, 16 of 4000, 6 (983 MB) 69.4 / 66.0; level from 295 to 335 MB.  Of a context of few layers below
+// that, repeated, they are: 70B 16 of 4096, 4 (134 MB) level, 16 of 1000, 16 (131 MB) 58.9 / 59.0, 7B 1 of 2048, 32 (134 MB) 31.9 / 32.0, 32 of 500, 8 (262
+// MB) 46.2 / 47.0, 13B 8 of 4096, 3 (252 MB) 49.2 / 52.0.  But such a context stands for a slice of a model, whose caches are cold: with three such in
+// turn one layer of 70B 48 of 3000 (74 MB) 90.5 / 88.0, 13B 16 of 4000 (164 MB) 68.9 / 64.8, 7B 64 of 1000 (131 MB) 74.3 / 66.8, four of 70B 16 of 4096
+// (134 MB) 234.4 / 232.6 a call, and below 64 MB level or worse (one of 7B 8 of 4000 42.4 / 43.4, 13B 8 of 2000 44.4 / 44.9): the line lies at 64 MB.
+bool decode_past_caches(const spd_dims &D, const int32_t *positions, int sequences) {
+    int64_t keys = 0;
+    for (int i = 0; i < sequences; ++i) keys += positions[i];
+    return 4.0 * D.kv * D.d * D.n_layers * (double)keys >= 64.0 * (1 << 20);
+}
+
 int decode_qkv_slices(const spd_dims &D, int sequences) {
     const int n_mtiles = (sequences + 15) / 16, qkv_pairs = D.nqkv / 32;
     int qkv_slices = 1;
@@ -3243,13 +3257,7 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
         // skipped
     } else if (c.q_len == 1) {
         const dim3 grid(parts.n_splits, D.kv, c.batch);
-        // us per call, kept / past the caches: 13B 8 of 4096 four layers 210.4 / 205.4 (4 x 84 MB), 70B 16 of 4096 four layers 246.7 / 244.6 (4 x 34 MB), 48 of
-        // 3000 90.5 / 88.0 (74 MB), 13B 16 of 4000 68.9 / 64.8 (164 MB), 7B 64 of 1000 74.3 / 66.8 (131 MB); but 7B 8 of 4000 42.4 / 43.4, 13B 8 of 2000
-        // 44.4 / 44.9, 70B 16 of 4096 in one layer 62.3 / 62.8, 48 of 375 to 1300 81.9 / 82.2 (20 to 34 MB, which a repeated call finds in the caches)
-        int64_t kv_bytes = 0;
-        for (int i = 0; i < c.batch; ++i) kv_bytes += c.pos.pos[i];
-        kv_bytes *= (int64_t)4 * D.kv * D.d * c.layers;
-        const bool stream = kv_bytes >= ((int64_t)64 << 20);
+        const bool stream = decode_past_caches(D, c.pos.pos, c.batch);
 #define SPD_DECODE_AS(DTV, FUSED_, STREAM_)                                                                                                    \
     hipLaunchKernelGGL((k_attn_decode<DTV, FUSED_, STREAM_>), grid, dim3(256), 0, c.s, kc, vc, fused_q ? qkvp : nullptr, D.q, D.kv, D.max_ctx,  \
                        qkv_slices, 16 * n_mtiles, D.nqkv, qbuf, qlo, raw.ss, (float)D.h, D.eps, qbuf, qlo, parts, c.pos)

@@ -1,6 +1,8 @@
 """GPU parity: the HIP library, called through the C ABI, against the CPU oracle on the same
 seeded inputs.  bf16 path: max abs error 2e-2 on the fp32-stored block outputs; fp32 path:
 1e-3 relative; integer logic (sync counts, rank indexing) bit-exact."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -435,8 +437,9 @@ def test_bf16_skinny_kernel_of_two_pairs(gpu, w, q_len, flag):
     _one_rank_block(gpu, w, 1, q_len, [0], flag, bias_std=0.1 * (q_len % 2))
 
 
-# Decode attention on caches of 64 MB per call and more (here: of all layers of a model call), which are read past the chip's caches: the same bits as a
-# block call of the first layer, whose caches are below that, with the QKV projection whole and in slices
+# Decode attention on caches of 64 MB and more in all layers of the context, which are read past the chip's caches: a model call's first block and a block
+# call of that context have the same bits as a block call of a context of one layer, whose caches are below that, with the QKV projection whole
+# and in slices
 @pytest.mark.parametrize("head_dim,kv", [(32, 4), (64, 2), (96, 2), (128, 1)])
 @pytest.mark.parametrize("hidden", [256, 2048], ids=["whole", "sliced"])
 def test_bf16_decode_of_large_caches(gpu, head_dim, kv, hidden):
@@ -453,13 +456,21 @@ def test_bf16_decode_of_large_caches(gpu, head_dim, kv, hidden):
     x, slots = torch.randn(12, hidden, device=gpu), torch.zeros(2, 12, hidden, device=gpu)
     taps, out = torch.zeros(w.n_layers, 12, hidden, device=gpu), torch.empty_like(x)
     kv0 = shard.kv[0].clone()
-    B.spd_block_forward(shard.ctx, 0, 1, 0, shard.weights[0], shard.kv[0], positions, 12, 1, x, slots, out, shard.workspace)
+    one = B.DeviceShard(dataclasses.replace(w, n_layers=1, mask=(1,)), [0], gpu, max_ctx=1056, max_tokens=12, max_batch=12)
+    pos = (B.C.c_int32 * 12)(*positions)
+    assert [B.lib().spd_decode_past_caches(c, pos, 12) for c in (one.ctx, shard.ctx)] == [0, 1]
+    B.spd_block_forward(one.ctx, 0, 1, 0, shard.weights[0], shard.kv[0], positions, 12, 1, x, slots, out, one.workspace)
     torch.cuda.synchronize()
     appended, want = shard.kv[0].clone(), out.clone()
     shard.kv[0].copy_(kv0)
+    B.spd_block_forward(shard.ctx, 0, 1, 0, shard.weights[0], shard.kv[0], positions, 12, 1, x, slots.zero_(), out, shard.workspace)
+    torch.cuda.synchronize()
+    assert torch.isfinite(want).all() and torch.equal(out, want) and torch.equal(shard.kv[0], appended)
+    shard.kv[0].copy_(kv0)
     B.spd_model_forward_staged(shard.ctx, w.mask, 0, shard.weights, shard.kv, positions, 12, 1, x, slots.zero_(), out, shard.workspace, layer_out=taps)
     torch.cuda.synchronize()
-    assert torch.isfinite(want).all() and torch.equal(taps[0], want) and torch.equal(shard.kv[0], appended)
+    assert torch.equal(taps[0], want) and torch.equal(shard.kv[0], appended)
+    one.close()
     shard.close()
 
 

@@ -579,3 +579,24 @@ def test_decode_qkv_slices_fill_the_chip():
     assert B.lib().spd_decode_qkv_slices(toy, 17) == 1
     assert [B.lib().spd_decode_qkv_slices(toy, b) for b in (0, 65)] == [B.SPD_EINVAL] * 2 and B.lib().spd_decode_qkv_slices(None, 1) == B.SPD_EINVAL
     B.spd_destroy(toy)
+
+
+def test_decode_caches_read_past_the_chips_caches():
+    """From 64 MB of keys and values of all layers of the context on, whichever entry point makes the step."""
+    def past(positions, n_layers, **over):
+        w = dataclasses.replace(workloads.LLAMA70B_DECODE, n_layers=n_layers, mask=(1,) * n_layers, **over)
+        ctx = B.spd_create(B.make_config(w, max_batch=16, max_ctx=1 << 17, max_tokens=16))
+        r = B.lib().spd_decode_past_caches(ctx, (C.c_int32 * len(positions))(*positions), len(positions))
+        B.spd_destroy(ctx)
+        return r
+
+    # (one KV head of 128 per rank: 512 bytes per position and layer)
+    for n_layers in (1, 2, 80):
+        line = -(-(64 << 20) // (512 * n_layers))
+        assert past([line // 2, line - line // 2], n_layers) == 1 and past([line // 2, line - 1 - line // 2], n_layers) == 0, n_layers
+    assert past([4095] * 16, 2) == 0 and past([4095] * 16, 3) == 1 and past([2047], 80) == 1 and past([0], 80) == 0
+    assert [past([-1], 1), past([1 << 17], 1), past([0] * 17, 1)] == [B.SPD_EINVAL] * 3
+    assert B.lib().spd_decode_past_caches(None, None, 1) == B.SPD_EINVAL
+    toy = B.spd_create(B.make_config(workloads.TOY))
+    assert B.lib().spd_decode_past_caches(toy, (C.c_int32 * 1)(16), 1) == 0
+    B.spd_destroy(toy)
