@@ -878,7 +878,7 @@ struct EpiGU {
 
     __device__ __forceinline__ Pre pre(int, int, int) const { return Pre{*wsc}; }
 
-    // narrow groups: feature i of a lane is FFN column cols * pair + 4 g + i, stored by itself
+    // narrow groups: feature i of a lane is FFN column cols * pair + 4 g + i, stored by itself (operator() is for 16 columns; see launch_gemv())
     __device__ __forceinline__ bool by_element() const { return cols != 16; }
     __device__ __forceinline__ void element(int pair, int i, float a, float b, int lane, float rs, const Pre &p) const {
         const int r = lane & 15, row = 4 * (lane >> 4) + i, col = pair * cols + row;
@@ -2736,7 +2736,8 @@ hipError_t launch_gemv(const spd_call &c, const __bf16 *Wp, const __bf16 *Xhi, c
                        const Epi &epi, int rows = 16) {
     const spd_dims &D = *c.D;
     float *kpart = (float *)(c.ws + D.ws_kpart);
-    if (gemv_whole(n_pairs, KT)) {
+    // (narrow groups never in slices: only k_gemv stores them by element, k_gemv_finish takes a group for 16 columns)
+    if (rows != 16 || gemv_whole(n_pairs, KT)) {
         // one workgroup per pair, no slices
         if (KT >= 32) {
             // 16 waves share 512 VGPRs per lane and SIMD.  With as few as
