@@ -2807,6 +2807,7 @@ hipError_t launch_skinny_mt(const spd_call &c, const __bf16 *Wp, const __bf16 *X
                        lds, c.s, Wp, Xhi, Xlo, KT, KS, n_mtiles, rot_step, epi);
     return hipGetLastError();
 }
+inline bool skinny_two_pairs(int n_pairs, int n_mtiles) { return n_pairs % 16 == 0 && n_mtiles >= 8; }      // (single activation planes)
 template <int MODE = 0, class Epi>
 hipError_t launch_skinny(const spd_call &c, bool split, const __bf16 *Wp, const __bf16 *Xhi, size_t plane, int n_pairs, int KT,
                          const Epi &epi, int KS = 1) {
@@ -2825,7 +2826,7 @@ hipError_t launch_skinny(const spd_call &c, bool split, const __bf16 *Wp, const 
     // data that is read once: 70B 128 tokens 104.8 / 103.2 (kept sync point 107.6 / 105.1), 13B 74.4 / 71.1, 4-way 98.4 / 93.9, 7B 58.6 / 58.0.
     // (Seven m-tiles: 70B 97.7 / 98.7, 13B 70.8 / 70.2; fewer draw more than with one pair.)
     if constexpr (MODE == 0)
-        if (!split && n_pairs % 16 == 0 && n_mtiles >= 8)
+        if (!split && skinny_two_pairs(n_pairs, n_mtiles))
             return n_mtiles > 8 ? launch_skinny_mt<4, false, MODE, 2, true>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi)
                                 : launch_skinny_mt<4, false, MODE, 2, false>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi);
     return split ? launch_skinny_mt<8, true, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi)
@@ -2995,16 +2996,18 @@ inline bool merge_in_o(const spd_call &c, int n_pairs, int KT, int n_splits) {
 }
 
 // The output projection's contraction is short (a rank's heads): up to 128 tokens the skinny kernel with the whole epilogue
-// beats slices and their finishing kernel; beyond, 256 x 128 tiles by themselves beat both once the skinny kernel would
-// take two rounds (70B shard, main kernel, us, skinny / tiles: 192 tokens 15.8 / 14.7, 512: 30.9 / 17.2; 13B 384: 10.8 / 11.4, 512:
-// 16.1 / 12.0), and tiles of 128 x 128 beat those as long as they come to one round (such a launch is its reads of X and its writes, which a
-// compute unit makes at 50 GB/s; us per call, 256 x 128 / 128 x 128: 70B 300 tokens 185.6 / 176.2, 512 behind 1536 positions 245.0 / 237.4, 13B 500
-// 159.2 / 152.8, 7B 2 x 200 112.7 / 106.2, 4-way 400 155.1 / 145.7).  With a kept sync point in its epilogue (MID) always the skinny kernel.
+// beats slices and their finishing kernel, and beyond it beats tiles as long as it has two pairs and four m-tiles per workgroup and these come to two and a half
+// rounds of the chip (us per call, skinny / 128 x 128 tiles, by workgroups: 512: 70B 129 tokens 124.2 / 128.6, 256 149.3 / 153.6, 7B 400 97.4 / 101.4, 4-way 512
+// 145.2 / 149.7; 640: 13B 400 124.2 / 125.6, 512 140.2 / 141.6; but 768: 70B 300 171.4 / 170.7, 384 behind 500 positions 193.0 / 191.3; 1024: 512 behind
+// 1536 235.4 / 230.6); with one pair and eight m-tiles, below two rounds (tiles of 256 x 128, main kernel, us, skinny / tiles: 70B 192 tokens 15.8 / 14.7, 512: 30.9 / 17.2).
+// Tiles of 128 x 128 as long as these come to one round, 256 x 128 beyond (such a launch is its reads of X and its writes, and a part of the compute units draws a
+// part of what the chip does; us per call, 256 x 128 / 128 x 128: 70B 256 tokens 161.7 / 153.6, 300 185.6 / 176.2, 512 behind 1536 245.0 / 237.4).
+// With a kept sync point in its epilogue (MID) always the skinny kernel.
 // `merge`: the splits' states of a decode step whose O projection merges them itself (see merge_in_o()).
 template <bool MID>
 hipError_t launch_o(const spd_call &c, bool split, const __bf16 *Wp, const __bf16 *Xhi, size_t plane, int n_pairs, int KT,
                     const EpiOT<MID> &epi, const AttnParts &merge) {
-    const int n_mtiles = (c.M + 15) / 16, zg = (n_mtiles + 7) / 8;
+    const int n_mtiles = (c.M + 15) / 16, wgs = n_pairs * ((n_mtiles + 7) / 8);
     const __bf16 *Xlo = Xhi + plane;
     if (n_mtiles == 1 && merge.o) {
         constexpr int W = GEMV_MERGE_W;
@@ -3026,7 +3029,7 @@ hipError_t launch_o(const spd_call &c, bool split, const __bf16 *Wp, const __bf1
     }
     if (n_mtiles == 1)
         return split ? launch_gemv<true>(c, Wp, Xhi, Xlo, n_pairs, KT, epi) : launch_gemv<false>(c, Wp, Xhi, Xlo, n_pairs, KT, epi);
-    if (n_mtiles <= 8 || (n_mtiles <= SKINNY_MAX_MTILES && (MID || n_pairs * zg < 512)) || !spd_gemm_fits(KT))
+    if (n_mtiles <= 8 || (n_mtiles <= SKINNY_MAX_MTILES && (MID || wgs < (!split && skinny_two_pairs(n_pairs, n_mtiles) ? 641 : 512))) || !spd_gemm_fits(KT))
         return launch_skinny(c, split, Wp, Xhi, plane, n_pairs, KT, epi);
     if constexpr (MID) {
         return hipErrorInvalidValue;         // (see sync_in_o())

@@ -404,6 +404,20 @@ def test_bf16_medium_call_in_square_tiles(gpu, w, q_len, flag, split):
     _one_rank_block(gpu, w, 1, q_len, [0], flag, split, bias_std=0.1 * (q_len % 2))
 
 
+# O projection on either side of 640 workgroups of the skinny kernel (two pairs and four m-tiles each): 160 and 176 pairs at 25 and 32 m-tiles; 512 of
+# 256 pairs at 9 and 16, 768 at 17
+O_160 = Workload(name="160-pairs", hidden=5120, n_q_heads=10, n_kv_heads=2, head_dim=32, ffn=320, n_layers=1, tp=2, dtype=BF16, seed=68, batch=1,
+                 q_len=1, ctx=64, mask=(1,))
+O_176 = dataclasses.replace(O_160, name="176-pairs", hidden=5632, seed=69)
+O_256 = dataclasses.replace(O_160, name="256-pairs", hidden=8192, seed=70)
+
+
+@pytest.mark.parametrize("w,q_len", [(O_160, 385), (O_160, 512), (O_176, 385), (O_176, 512), (O_256, 129), (O_256, 256), (O_256, 257)],
+                         ids=lambda v: getattr(v, "name", v))
+def test_bf16_output_projection_of_medium_call(gpu, w, q_len):
+    _one_rank_block(gpu, w, 1, q_len, [0], 1)
+
+
 # ... and in a model call, where the launch behind it also prepares the next block's first norm: every block against the oracle on the input it had
 @pytest.mark.parametrize("w", [DOWN_129, DOWN_105], ids=lambda w: w.name)
 def test_bf16_medium_model_call_in_square_tiles(gpu, w):
