@@ -633,6 +633,12 @@ extern "C" int spd_decode_past_caches(const spd_ctx *ctx, const int32_t *positio
     return ctx->D.dtype == SPD_BF16 && spd_bf16::decode_past_caches(ctx->D, positions, batch) ? 1 : 0;
 }
 
+extern "C" int spd_prefill_attention_workgroups(int32_t head_dim) {
+    int n = 0;
+    if (head_dim != 32 && head_dim != 64 && head_dim != 96 && head_dim != 128) return SPD_EINVAL;
+    return spd_bf16::prefill_workgroups(head_dim, &n) == hipSuccess ? n : SPD_EHIP;
+}
+
 extern "C" int spd_act_piece_bytes(int32_t mt, int32_t n_mtiles) { return mt < 0 || mt >= n_mtiles ? SPD_EINVAL : spd_act_bytes(mt, n_mtiles); }
 
 extern "C" int spd_gemm_tile_of(int32_t TN, int32_t TM, int32_t rn, int32_t rm, int32_t tile0, int32_t n_tiles, int32_t b,

@@ -2585,27 +2585,32 @@ __global__ void __launch_bounds__(64) k_attn_combine(float *po, int units, int n
     if (alo) *(bf16x4 *)(alo + o) = cvt4h_lo(v.x, v.y, v.z, v.w, hi);
 }
 
+constexpr int PREFILL_ONE_WGS = 2;       // workgroups of one column tile that a compute unit holds
 // Prefill (q_len > 1): grid (groups of CT column tiles x kv heads, 1, sequences), 4 waves.  (The heads side by side: workgroups go to the XCDs in turn, so
 // that an XCD's L2 sees the keys of one or two of four heads; 2048 tokens of 7B, 4 heads, 25.0 -> 19.4 us.)  All four
 // waves work on the same CT tiles of 16 (token, head) columns and deal the causal key range
 // among themselves block by block (the latest tokens attend thousands of keys: one wave walking
 // them alone would be the critical path of the launch); their partial states meet in LDS and
 // every wave finishes a quarter of the (tile, 16-feature slice) outputs.
+// With one tile two workgroups fit a compute unit, and the bound keeps it so: 128 features take exactly the 256 registers of two waves per
+// SIMD, and a compiler that took 258 left one (us, two / one: 70B 2048 tokens behind 2500 85.9 / 108.2, 7B 4-way the same call 91 / 110).  Two tiles of
+// 128 features do not fit twice.  The heads' number divides by its reciprocal: two divisions ahead of the first load cost 1 us of 20 (512 behind 1536).
 template <int DT, int CT>
-__global__ void __launch_bounds__(256) k_attn_prefill(const __bf16 *__restrict__ qbuf, const __bf16 *__restrict__ qlo, const __bf16 *__restrict__ kc,
-                                                      const __bf16 *__restrict__ vc, int q_len, int q, int kv, int max_ctx,
-                                                      __bf16 *__restrict__ ahat, __bf16 *__restrict__ alo, spd_positions P) {
+__global__ void __launch_bounds__(256, CT == 1 ? PREFILL_ONE_WGS : 1) k_attn_prefill(const __bf16 *__restrict__ qbuf, const __bf16 *__restrict__ qlo, const __bf16 *__restrict__ kc,
+                                                      const __bf16 *__restrict__ vc, int q_len, int group, int max_ctx, int n_groups,
+                                                      Divider by_kv, __bf16 *__restrict__ ahat, __bf16 *__restrict__ alo, spd_positions P) {
     constexpr int d = DT * 16;
     extern __shared__ __attribute__((aligned(16))) char ap_lds[];
     f32x4 *so = (f32x4 *)ap_lds;                                   // [4 waves][CT][DT][64 lanes]
     float *sml = (float *)(ap_lds + 4 * CT * DT * 64 * 16);        // [4 waves][CT][2][16]: running max, running sum
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const unsigned group0 = blockIdx.x / (unsigned)kv, n_groups = gridDim.x / (unsigned)kv;
-    const int kvh = (int)(blockIdx.x - group0 * kv), b = blockIdx.z;
-    const int group = q / kv, qd = q * d;
+    const int kv = (int)by_kv.d, b = blockIdx.z;
+    int group0 = by_kv.div(blockIdx.x);
+    group0 -= group0 * kv > (int)blockIdx.x;               // (from 2^32 / kv on it may be one too many)
+    const int kvh = (int)blockIdx.x - group0 * kv, qd = kv * group * d;
     const int n_cols = q_len * group;
     // causal: the later a token, the more keys it attends; the long workgroups are launched first
-    const int ct0 = (int)(n_groups - 1 - group0) * CT;
+    const int ct0 = (n_groups - 1 - group0) * CT;
     const int g = lane >> 4;
     const int pos0 = P.pos[b];
     bf16x8 qf[CT][DT];
@@ -3138,6 +3143,20 @@ int qkv_slices_wanted(int pairs) {
 // MB) 46.2 / 47.0, 13B 8 of 4096, 3 (252 MB) 49.2 / 52.0.  But such a context stands for a slice of a model, whose caches are cold: with three such in
 // turn one layer of 70B 48 of 3000 (74 MB) 90.5 / 88.0, 13B 16 of 4000 (164 MB) 68.9 / 64.8, 7B 64 of 1000 (131 MB) 74.3 / 66.8, four of 70B 16 of 4096
 // (134 MB) 234.4 / 232.6 a call, and below 64 MB level or worse (one of 7B 8 of 4000 42.4 / 43.4, 13B 8 of 2000 44.4 / 44.9): the line lies at 64 MB.
+constexpr int prefill_lds(int DT, int CT) { return 4 * CT * DT * 64 * 16 + 4 * CT * 2 * 16 * 4; }
+
+hipError_t prefill_workgroups(int head_dim, int *n) {
+    const void *f;
+    switch (head_dim) {
+        case 32: f = (const void *)k_attn_prefill<2, 1>; break;
+        case 64: f = (const void *)k_attn_prefill<4, 1>; break;
+        case 96: f = (const void *)k_attn_prefill<6, 1>; break;
+        case 128: f = (const void *)k_attn_prefill<8, 1>; break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, f, 256, prefill_lds(head_dim / 16, 1));
+}
+
 bool decode_past_caches(const spd_dims &D, const int32_t *positions, int sequences) {
     int64_t keys = 0;
     for (int i = 0; i < sequences; ++i) keys += positions[i];
@@ -3294,15 +3313,15 @@ hipError_t attention_half(const spd_call &c, const char *w, char *kvc, const flo
 #define SPD_PREFILL_CT(DTV, CT)                                                                                            \
     {                                                                                                                      \
         const dim3 grid(D.kv * cdiv(n_ct, CT), 1, c.batch);                                                                  \
-        constexpr int lds = 4 * CT * DTV * 64 * 16 + 4 * CT * 2 * 16 * 4;                                                  \
+        constexpr int lds = prefill_lds(DTV, CT);                                                                            \
         static std::once_flag once;                                                                                        \
         static hipError_t attr_err = hipSuccess;                                                                           \
         std::call_once(once, [] {                                                                                          \
             attr_err = hipFuncSetAttribute((const void *)k_attn_prefill<DTV, CT>, hipFuncAttributeMaxDynamicSharedMemorySize, lds); \
         });                                                                                                                \
         SPD_TRY(attr_err);                                                                                                 \
-        hipLaunchKernelGGL((k_attn_prefill<DTV, CT>), grid, dim3(256), lds, c.s, qbuf, qlo, kc, vc, c.q_len, D.q, D.kv,  \
-                           D.max_ctx, ahat, alo, c.pos);                                                                   \
+        hipLaunchKernelGGL((k_attn_prefill<DTV, CT>), grid, dim3(256), lds, c.s, qbuf, qlo, kc, vc, c.q_len, D.group,    \
+                           D.max_ctx, (int)cdiv(n_ct, CT), Divider::by(D.kv), ahat, alo, c.pos);                            \
     }
 #define SPD_PREFILL(DTV)           \
     if (one) SPD_PREFILL_CT(DTV, 1) \

@@ -451,6 +451,13 @@ def test_bf16_skinny_kernel_of_two_pairs(gpu, w, q_len, flag):
     _one_rank_block(gpu, w, 1, q_len, [0], flag, bias_std=0.1 * (q_len % 2))
 
 
+# Two workgroups of the prefill attention with one column tile per compute unit: a few registers more and there is one
+@pytest.mark.parametrize("head_dim", [32, 64, 96, 128])
+def test_bf16_prefill_attention_workgroups(gpu, head_dim):
+    assert B.lib().spd_prefill_attention_workgroups(head_dim) >= 2
+    assert B.lib().spd_prefill_attention_workgroups(head_dim + 16) == B.SPD_EINVAL
+
+
 # Decode attention on caches of 64 MB and more in all layers of the context, which are read past the chip's caches: a model call's first block and a block
 # call of that context have the same bits as a block call of a context of one layer, whose caches are below that, with the QKV projection whole
 # and in slices
