@@ -119,6 +119,11 @@ int spd_decode_qkv_slices(const spd_ctx *ctx, int32_t batch);
  * 1 .. max_batch, a position outside 0 .. max_ctx - 1.  Host only. */
 int spd_decode_past_caches(const spd_ctx *ctx, const int32_t *positions, int32_t batch);
 
+/* ---------------------------------------------------------------- down projection in tiles
+ * Whether a call of that many tokens runs its down projection over the whole of K in tiles of 128 x 128 with the closing sync point in a launch
+ * behind it: 1, or 0 (always on the fp32 path).  SPD_EINVAL: NULL, tokens outside 1 .. max_tokens.  Host only. */
+int spd_down_in_tiles(const spd_ctx *ctx, int32_t tokens);
+
 /* ---------------------------------------------------------------- workgroups of the prefill attention per compute unit
  * How many workgroups of the bf16 path's prefill attention that take one tile of 16 (token, head) columns a compute unit of the current device
  * holds, as the runtime tells from the kernel's registers and LDS.  SPD_EINVAL: head_dim not 32, 64, 96 or 128; SPD_EHIP: the runtime does not tell. */

@@ -103,6 +103,7 @@ _PROTOS = {
     "spd_gemm_panels_fit": (C.c_int, [C.c_int32]),
     "spd_act_piece_bytes": (C.c_int, [C.c_int32, C.c_int32]),
     "spd_decode_past_caches": (C.c_int, [C.c_void_p, C.POINTER(C.c_int32), C.c_int32]),
+    "spd_down_in_tiles": (C.c_int, [C.c_void_p, C.c_int32]),
     "spd_prefill_attention_workgroups": (C.c_int, [C.c_int32]),
     "spd_decode_qkv_slices": (C.c_int, [C.c_void_p, C.c_int32]),
     "spd_gemm_tile_of": (C.c_int, [C.c_int32] * 7 + [C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),

@@ -633,6 +633,11 @@ extern "C" int spd_decode_past_caches(const spd_ctx *ctx, const int32_t *positio
     return ctx->D.dtype == SPD_BF16 && spd_bf16::decode_past_caches(ctx->D, positions, batch) ? 1 : 0;
 }
 
+extern "C" int spd_down_in_tiles(const spd_ctx *ctx, int32_t tokens) {
+    if (!ctx || tokens < 1 || tokens > ctx->D.max_tokens) return SPD_EINVAL;
+    return ctx->D.dtype == SPD_BF16 && spd_bf16::down_in_tiles(ctx->D, tokens, ctx->cfg.act_split == SPD_SPLIT_ALWAYS) ? 1 : 0;
+}
+
 extern "C" int spd_prefill_attention_workgroups(int32_t head_dim) {
     int n = 0;
     if (head_dim != 32 && head_dim != 64 && head_dim != 96 && head_dim != 128) return SPD_EINVAL;

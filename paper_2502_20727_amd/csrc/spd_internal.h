@@ -325,6 +325,7 @@ struct spd_end_sync {
 hipError_t mlp_half(const spd_call &c, const char *w, int spd, float *slot, const spd_end_sync *fuse, bool *fused,
                     bool ss_per_pair);
 int prep_chunks(const spd_call &c);
+bool down_in_tiles(const spd_dims &D, int tokens, bool split);      // is the down projection of such a call whole K in 128 x 128 tiles?
 hipError_t prefill_workgroups(int head_dim, int *n);      // workgroups of the prefill attention with one column tile per compute unit
 bool decode_past_caches(const spd_dims &D, const int32_t *positions, int sequences);      // are a decode step's KV caches read non-temporally?
 int decode_qkv_slices(const spd_dims &D, int sequences);      // K slices of a decode step's QKV projection, 1: none

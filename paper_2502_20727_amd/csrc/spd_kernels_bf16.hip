@@ -2879,6 +2879,19 @@ hipError_t launch_mid(const spd_call &c, const __bf16 *Wp, const __bf16 *X, int 
     return launch_mid_finish(c.s, kpart, KS, n_pairs, n_mtiles, epi);
 }
 
+// K slices of launch_sliced() (1: none) and the tiles they are made of.
+inline int sliced_count(const spd_dims &D, int n_pairs, int KT, int n_mtiles, int *kind) {
+    const int halves = ((2 * n_pairs + 15) / 16) * ((n_mtiles + 7) / 8);
+    *kind = n_mtiles <= 4 ? 0 : (n_mtiles > 8 && (n_pairs >= 64 || halves >= 32) ? 2 : 1);      // 128 x 64, 128 x 128, 256 x 128
+    const int bn = *kind == 2 ? 16 : 8, bm = *kind == 0 ? 4 : 8;
+    const int tiles = ((2 * n_pairs + bn - 1) / bn) * ((n_mtiles + bm - 1) / bm);
+    int KS = 256 / tiles;
+    if (KS > 16) KS = 16;
+    if (KS > KT / 8) KS = KT / 8;
+    while (KS > 1 && (size_t)n_pairs * KS * n_mtiles > D.kpart_tiles) --KS;
+    return KS;
+}
+
 // Projection in K slices: the LDS-tiled GEMM in one launch of (tiles x slices) workgroups, at most one per compute unit,
 // that park their partial sums, and a finishing kernel that adds them in slice order and runs the epilogue.  For
 // calls whose tiles alone leave most compute units idle.  Tile shape: 128 x 64 up to 64 tokens, 256 x 128 beyond 128
@@ -2892,14 +2905,8 @@ hipError_t launch_sliced(const spd_call &c, bool split, const __bf16 *Wp, const 
                          const Epi &epi, bool *done) {
     const spd_dims &D = *c.D;
     const int n_mtiles = (c.M + 15) / 16;
-    const int halves = ((2 * n_pairs + 15) / 16) * ((n_mtiles + 7) / 8);
-    const int kind = n_mtiles <= 4 ? 0 : (n_mtiles > 8 && (n_pairs >= 64 || halves >= 32) ? 2 : 1);      // 128 x 64, 128 x 128, 256 x 128
-    const int bn = kind == 2 ? 16 : 8, bm = kind == 0 ? 4 : 8;
-    const int tiles = ((2 * n_pairs + bn - 1) / bn) * ((n_mtiles + bm - 1) / bm);
-    int KS = 256 / tiles;
-    if (KS > 16) KS = 16;
-    if (KS > KT / 8) KS = KT / 8;
-    while (KS > 1 && (size_t)n_pairs * KS * n_mtiles > D.kpart_tiles) --KS;
+    int kind;
+    const int KS = sliced_count(D, n_pairs, KT, n_mtiles, &kind);
     *done = KS > 1;
     if (!*done) return hipSuccess;
     EpiPark park;
@@ -2935,14 +2942,24 @@ inline bool skinny_first(int n_pairs, int KT, bool split, int n_mtiles) {
 inline int square_tiles(int n_pairs, int n_mtiles) { return (2 * n_pairs + 7) / 8 * ((n_mtiles + 7) / 8); }      // of 128 x 128
 
 // The down projection of 257 to 512 tokens, where it is not the skinny kernel's: 128 x 128 tiles over the whole of K, and the closing sync point a launch
-// of its own, instead of slices and a sync point in the launch that adds them: a slice's rows are written and read once more.  At
-// most one round of the chip and at least a third of one.  us per call, slices / this: 70B 300 tokens 176.2 / 174.3, 400 behind 1000 positions
-// 213.5 / 206.7, 512 behind 1536 237.4 / 235.6; 13B 333 122.3 / 119.1 (sync point kept 133.0 / 131.2), 500 152.8 / 148.6; 7B 4-way 400 145.7 / 142.2; four
-// layers of 13B, 400 tokens 526 / 511.  (200 tokens of 70B 156.4 / 161.4; instead of the skinny kernel, 7B 300 and 500: 87.1 / 89.6, 121.1 / 124.0.)
-inline bool down_whole(int n_pairs, int KT, bool split, int n_mtiles) {
-    const int tiles = square_tiles(n_pairs, n_mtiles);
-    return n_mtiles > 16 && n_mtiles <= SKINNY_MAX_MTILES && tiles >= 96 && tiles <= 256 && spd_gemm_fits(KT) &&
-           !skinny_first(n_pairs, KT, split, n_mtiles);
+// of its own, instead of slices and a sync point in the launch that adds them: a slice's rows are written and read once more.  At most one
+// round of the chip and at least a third of one.  A tile takes 0.3 us per k-tile whatever the number of tiles, slices a part of that and a time that goes with
+// the rows there are: the more slices, the longer K and the fuller the groups of 8 m-tiles, the better for them.  us per call, slices / this: 4 or 5 slices, groups full:
+// 96 pairs x 64 k-tiles 102.7 / 102.0, x 96 128.2 / 131.9, x 128 134.0 / 146.0, x 256 189.8 / 225.6, 128 x 86 140.5 / 143.1, 160 x 108 148.4 / 154.2; 272 tokens (5.7 m-tiles a
+// group) 128 x 86 116.4 / 113.7, 160 x 108 136.4 / 136.5, 128 x 172 180.3 / 186.6; 3 slices, full: 144 x 96 148.0 / 146.8, 160 x 108 179.6 / 180.0, x 216 278.9 / 293.8; 400
+// tokens 161.1 / 159.0, x 216 256.6 / 260.0; 2 slices: 256 x 112 400 tokens 196.8 / 188.7, 512 218.5 / 216.6, x 224 334.1 / 332.2, but 384 tokens 184.0 / 186.3, 304.4 / 309.4.
+// Pairs of planes count twice (128 x 86, 272 to 512 tokens 0.7 .. 4.6 % slower in tiles, 160 x 108 -1.5 .. + 5.4, 256 x 112 -2 .. + 1.7 as above).
+// (200 tokens of 70B 156.4 / 161.4; instead of the skinny kernel, 7B 300 and 500: 87.1 / 89.6, 121.1 / 124.0.)
+inline bool down_whole(const spd_dims &D, int n_pairs, int KT, bool split, int n_mtiles) {
+    const int tiles = square_tiles(n_pairs, n_mtiles), groups = (n_mtiles + 7) / 8;
+    if (n_mtiles <= 16 || n_mtiles > SKINNY_MAX_MTILES || tiles < 96 || tiles > 256 || !spd_gemm_fits(KT) ||
+        skinny_first(n_pairs, KT, split, n_mtiles))
+        return false;
+    int kind;
+    const int KS = sliced_count(D, n_pairs, KT, n_mtiles, &kind);
+    if (KS <= 1) return true;
+    if (KS == 2) return groups != 3 || n_mtiles < 23;
+    return (split ? 2 * KT : KT) <= (KS == 3 ? 104 : 64) + 20 * (8 * groups - n_mtiles) / groups;
 }
 
 // Projection of a call of any size: the weight-streaming kernel up to 16 tokens; up to 512 tokens the skinny kernel for short
@@ -3135,14 +3152,8 @@ int qkv_slices_wanted(int pairs) {
 }
 }  // namespace
 
-// A step goes through the caches of all of the context's layers before it comes to a layer's again, whether its program calls the model or walks the
-// blocks (the weights are read past the chip's caches, 256 MB, anyway).  From 256 MB on nothing is found again; us per layer, block calls walking that
-// many layers, kept / past the caches: 70B 16 of 4096, 12 layers (403 MB) 61.5 / 60.4, 7B 8 of 4000, 8 (524 MB) 43.3 / 41.8, 4 of 2048, 32 (537 MB)
-// 34.8 / 34.1, 13B 1 of 4096, 40 (419 MB) 36.9 / 35.9, 16 of 4000, 6 (983 MB) 69.4 / 66.0; level from 295 to 335 MB.  Of a context of few layers below
-// that, repeated, they are: 70B 16 of 4096, 4 (134 MB) level, 16 of 1000, 16 (131 MB) 58.9 / 59.0, 7B 1 of 2048, 32 (134 MB) 31.9 / 32.0, 32 of 500, 8 (262
-// MB) 46.2 / 47.0, 13B 8 of 4096, 3 (252 MB) 49.2 / 52.0.  But such a context stands for a slice of a model, whose caches are cold: with three such in
-// turn one layer of 70B 48 of 3000 (74 MB) 90.5 / 88.0, 13B 16 of 4000 (164 MB) 68.9 / 64.8, 7B 64 of 1000 (131 MB) 74.3 / 66.8, four of 70B 16 of 4096
-// (134 MB) 234.4 / 232.6 a call, and below 64 MB level or worse (one of 7B 8 of 4000 42.4 / 43.4, 13B 8 of 2000 44.4 / 44.9): the line lies at 64 MB.
+bool down_in_tiles(const spd_dims &D, int tokens, bool split) { return down_whole(D, D.h / 32, D.f_pad / 32, split, (tokens + 15) / 16); }
+
 constexpr int prefill_lds(int DT, int CT) { return 4 * CT * DT * 64 * 16 + 4 * CT * 2 * 16 * 4; }
 
 hipError_t prefill_workgroups(int head_dim, int *n) {
@@ -3157,6 +3168,14 @@ hipError_t prefill_workgroups(int head_dim, int *n) {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, f, 256, prefill_lds(head_dim / 16, 1));
 }
 
+// A step goes through the caches of all of the context's layers before it comes to a layer's again, whether its program calls the model or walks the
+// blocks (the weights are read past the chip's caches, 256 MB, anyway).  From 256 MB on nothing is found again; us per layer, block calls walking that
+// many layers, kept / past the caches: 70B 16 of 4096, 12 layers (403 MB) 61.5 / 60.4, 7B 8 of 4000, 8 (524 MB) 43.3 / 41.8, 4 of 2048, 32 (537 MB)
+// 34.8 / 34.1, 13B 1 of 4096, 40 (419 MB) 36.9 / 35.9, 16 of 4000, 6 (983 MB) 69.4 / 66.0; level from 295 to 335 MB.  Of a context of few layers below
+// that, repeated, they are: 70B 16 of 4096, 4 (134 MB) level, 16 of 1000, 16 (131 MB) 58.9 / 59.0, 7B 1 of 2048, 32 (134 MB) 31.9 / 32.0, 32 of 500, 8 (262
+// MB) 46.2 / 47.0, 13B 8 of 4096, 3 (252 MB) 49.2 / 52.0.  But such a context stands for a slice of a model, whose caches are cold: with three such in
+// turn one layer of 70B 48 of 3000 (74 MB) 90.5 / 88.0, 13B 16 of 4000 (164 MB) 68.9 / 64.8, 7B 64 of 1000 (131 MB) 74.3 / 66.8, four of 70B 16 of 4096
+// (134 MB) 234.4 / 232.6 a call, and below 64 MB level or worse (one of 7B 8 of 4000 42.4 / 43.4, 13B 8 of 2000 44.4 / 44.9): the line lies at 64 MB.
 bool decode_past_caches(const spd_dims &D, const int32_t *positions, int sequences) {
     int64_t keys = 0;
     for (int i = 0; i < sequences; ++i) keys += positions[i];
@@ -3431,7 +3450,7 @@ hipError_t mlp_half(const spd_call &c, const char *w, int spd, float *slot, cons
     // weight-streaming kernels, of the kernel that adds K slices, or of one launch of 256 x 128 tiles.  In a long call's GEMM it gains nothing: measured on the 70B prefill shape, the
     // workgroups of a compute unit reach their epilogues together, so the slot reads do not overlap with
     // anybody's contraction and the fused kernel takes exactly as long as GEMM + rank-sum kernel.
-    const bool whole = down_whole(D.h / 32, D.f_pad / 32, c.sp_m, (M + 15) / 16);
+    const bool whole = down_whole(D, D.h / 32, D.f_pad / 32, c.sp_m, (M + 15) / 16);
     const bool do_fuse = fuse && M <= 16 * SKINNY_MAX_MTILES && !whole;
     if (fused) *fused = do_fuse;
     auto fill = [&](auto &e2) {

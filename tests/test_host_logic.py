@@ -581,6 +581,31 @@ def test_decode_qkv_slices_fill_the_chip():
     B.spd_destroy(toy)
 
 
+def test_down_projection_in_tiles_where_it_is_faster():
+    """257 to 512 tokens: as timed on every shard and on other widths, both ways; lengths within 1 % of each other are left out."""
+    def tiles(tokens, split=0, **over):
+        ctx = B.spd_create(B.make_config(dataclasses.replace(workloads.LLAMA7B_DECODE, **over), max_batch=1, max_ctx=512, max_tokens=512, act_split=split))
+        r = [B.lib().spd_down_in_tiles(ctx, n) for n in tokens]
+        B.spd_destroy(ctx)
+        return r
+
+    b13, b70 = dict(hidden=5120, n_q_heads=40, n_kv_heads=40, ffn=13824), dict(hidden=8192, n_q_heads=64, n_kv_heads=8, ffn=28672)
+    h3 = dict(hidden=3072, n_q_heads=24, n_kv_heads=8)
+    for over, yes, no in [
+            (dict(tp=8), (), (272, 512)), (dict(tp=4), (272,), (384, 512)), (dict(tp=2), (), (272, 320, 384, 400, 448, 512)),
+            (dict(tp=8, **b13), (272, 320, 400, 448, 512), ()), (dict(tp=4, **b13), (400, 448), (320, 384)),
+            (dict(tp=2, **b13), (), (272, 320, 384, 400, 448, 512)),
+            (dict(tp=8, **b70), (272, 320, 400, 448, 512), (200, 384)), (dict(tp=4, **b70), (272, 400, 448), (384,)),
+            (dict(tp=1, ffn=8192, **h3), (), (400, 448, 512)), (dict(tp=2, ffn=8192, **h3), (), (400, 448, 512)),
+            (dict(tp=4, ffn=8192, **h3), (400, 448), (384,)), (dict(tp=2, ffn=6144, **h3), (400,), (512,)),
+            (dict(tp=4, split=B.SPD_SPLIT_ALWAYS), (), (272, 384, 512)), (dict(tp=8, split=B.SPD_SPLIT_ALWAYS, **b70), (272, 448, 512), (384,))]:
+        assert tiles(yes, **over) == [1] * len(yes) and tiles(no, **over) == [0] * len(no), over
+    assert tiles((0, 513)) == [B.SPD_EINVAL] * 2 and B.lib().spd_down_in_tiles(None, 300) == B.SPD_EINVAL
+    toy = B.spd_create(B.make_config(workloads.TOY))
+    assert B.lib().spd_down_in_tiles(toy, 16) == 0
+    B.spd_destroy(toy)
+
+
 def test_decode_caches_read_past_the_chips_caches():
     """From 64 MB of keys and values of all layers of the context on, whichever entry point makes the step."""
     def past(positions, n_layers, **over):
