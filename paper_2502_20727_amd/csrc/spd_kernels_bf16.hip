@@ -1901,9 +1901,11 @@ hipError_t launch_mid_finish(hipStream_t s, const f32x4 *kpart, int KS, int n_pa
 // take) and that the next stage has landed; the copies of the stages after that stay in flight across it.
 // What bounds it: the matrix cores at the clock they hold under load (gate/up of 4096 tokens of the 70B shard runs at 1.3 PFLOP/s, spd_mfma_probe(), the
 // same MFMAs on register-resident random data and nothing else, at 1.63 .. 1.76; matrix cores busy 70 % of the cycles), and
-// in calls of one or two rounds what a compute unit draws through its load path: loads return in order, 52 GB/s of them from the HBM, 90
-// from the last-level cache, 110 from the L2, however many are on their way.  Gate/up of 1000 tokens (256 x 128 tiles), us: the copies alone 112 with the
-// weights from the HBM and 73 from the cache, the MFMAs alone 71, MFMAs and LDS reads 95, all of it 118 and 104.  (The LDS is not it: a kernel of
+// in calls of one or two rounds what a compute unit draws through its load path.  Loads return in order, and a unit with a panel of its own gets 46 to 55 GB/s
+// from the HBM while at most half of the units read, 27 when all do (7 TB/s in all), 92 and 23 from the last-level cache, 104 to 116 from the L2, however many loads are
+// on their way; panels from the HBM that 2, 8, 32 units of an XCD read together 44, 61, 68, but panels shared across XCDs 27: an XCD's L2 takes in 0.9 TB/s.  Gate/up of
+// 1000 tokens (256 x 128 tiles, 224 of them) by itself, us: the copies alone 112 with the weights from the HBM and 73 from the cache, the MFMAs alone 71, MFMAs and
+// LDS reads 95, all of it 118 and 104 (in a call, traced: 131 to 133).  (The LDS is not it: a kernel of
 // nothing but such reads draws 212 bytes per clock and compute unit, and MFMAs with 12 reads per 32 and this barrier run as fast as MFMAs alone.
 // 32 x 32 x 16 MFMAs: 1.63 against 1.78 PFLOP/s on random data.  One of the workgroups that share a panel touching it some stages ahead: copies
 // alone 110 -> 80 us, the kernel 118 -> 115, from the cache 102 -> 106.)
@@ -2825,8 +2827,9 @@ hipError_t launch_skinny(const spd_call &c, bool split, const __bf16 *Wp, const 
         return split ? launch_skinny_mt<4, true, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi)
                      : launch_skinny_mt<4, false, MODE>(c, Wp, Xhi, Xlo, n_pairs, KT, KS, n_mtiles, epi);
     // Two pairs and four m-tiles per workgroup instead of one and eight: as many workgroups, but 64 + 64 rows of operands drawn through a compute
-    // unit's load path instead of 32 + 128, which at 50 GB/s is what bounds these launches; the weights are asked for by two or more
-    // workgroups, on one XCD as long as their number per group of m-tiles is a multiple of 8.  us per call, one pair / two: 13B 333 tokens with the
+    // unit's load path instead of 32 + 128.  Loads return in order, so that a launch takes at least the sum of what a unit reads: down of 128 tokens of
+    // 70B (27 to 30 us) 0.46 MB of weights that two units of an XCD share, at 44 GB/s, 0.46 MB of activations from the L2 at 104 and 0.15 MB of slots at 27, 20 us.
+    // The weights are asked for by two or more workgroups, on one XCD as long as their number per group of m-tiles is a multiple of 8.  us per call, one pair / two: 13B 333 tokens with the
     // kept sync point 125.1 / 121.3, 7B 500 122.2 / 115.8, 270 89.4 / 86.3, 70B 160 141.5 / 139.9.  Eight m-tiles, read by two workgroups at the same time, as
     // data that is read once: 70B 128 tokens 104.8 / 103.2 (kept sync point 107.6 / 105.1), 13B 74.4 / 71.1, 4-way 98.4 / 93.9, 7B 58.6 / 58.0.
     // (Seven m-tiles: 70B 97.7 / 98.7, 13B 70.8 / 70.2; fewer draw more than with one pair.)
