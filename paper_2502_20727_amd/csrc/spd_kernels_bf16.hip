@@ -1067,7 +1067,10 @@ __device__ __forceinline__ float4 merge_splits(const AttnParts &P, int u, int c,
         float mc = M;
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
-            if (s0 + j >= P.n_splits) first.m[j] = -INFINITY;
+            if (s0 + j >= P.n_splits) {
+                first.m[j] = -INFINITY;
+                first.l[j] = 0.f;
+            }
             mc = fmaxf(mc, first.m[j]);
         }
         const float keep = (M == -INFINITY) ? 0.f : __expf(M - mc);
@@ -1075,7 +1078,8 @@ __device__ __forceinline__ float4 merge_splits(const AttnParts &P, int u, int c,
         den *= keep;
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
-            if (first.m[j] == -INFINITY) continue;
+            // (a split without keys; one whose keys all have no score, NaN, has this maximum too, and its sums are NaN)
+            if (first.m[j] == -INFINITY && first.l[j] == 0.f) continue;
             const float sc = __expf(first.m[j] - mc);
             num.x += first.o[j].x * sc; num.y += first.o[j].y * sc; num.z += first.o[j].z * sc; num.w += first.o[j].w * sc;
             den += first.l[j] * sc;

@@ -495,6 +495,34 @@ def test_bf16_decode_of_large_caches(gpu, head_dim, kv, hidden):
     shard.close()
 
 
+# A NaN in the keys of a whole split of the context reaches the output, whichever launch merges the splits: the O projection in one piece or three per
+# thread, or one of its own
+@pytest.mark.parametrize("kv,batch", [(2, 1), (2, 12), (8, 12)], ids=["one-piece", "three-pieces", "own-launch"])
+@pytest.mark.parametrize("first,count", [(0, 512), (256, 256), (700, 1)])
+def test_bf16_decode_keeps_nan_scores(gpu, kv, batch, first, count):
+    import torch
+    w = Workload(name="nan", hidden=3072, n_q_heads=4 * kv, n_kv_heads=2 * kv, head_dim=64, ffn=128, n_layers=1, tp=2, dtype=BF16, seed=71, batch=batch,
+                 q_len=1, ctx=1024, mask=(1,))
+    shard = B.DeviceShard(w, [0], gpu, max_ctx=1024, max_tokens=batch, max_batch=batch)
+    torch.manual_seed(71)
+    shard.load_layer(0, [inputs.layer_shard(w, 0, 0)])
+    cache = shard.kv[0].view(torch.bfloat16).normal_()
+    x, slots, out = torch.randn(batch, w.hidden, device=gpu), torch.zeros(2, batch, w.hidden, device=gpu), torch.empty(batch, w.hidden, device=gpu)
+    call = lambda: B.spd_block_forward(shard.ctx, 0, 1, 0, shard.weights[0], shard.kv[0], [1023] * batch, batch, 1, x, slots.zero_(), out, shard.workspace)
+    call()
+    torch.cuda.synchronize()
+    want = out.clone()
+    keys = cache[:batch * kv * 1024 * 64].view(batch, kv, 1024 // 16, 16 * 64)       # (16 positions a block, features in eights)
+    if count == 1:
+        keys[0, kv - 1, first // 16].view(8, 16, 8)[:, first % 16] = float("nan")
+    else:
+        keys[0, kv - 1, first // 16:(first + count) // 16] = float("nan")
+    call()
+    torch.cuda.synchronize()
+    assert torch.isfinite(want).all() and torch.isnan(out[0]).all() and torch.equal(out[1:], want[1:])
+    shard.close()
+
+
 # the kernel that adds the slices takes 2, 4 or 8 pairs of n-tiles per workgroup, by the number of groups of 8 times m-tiles (lines at 64 and
 # 128): gate/up of 66 pairs (9 groups) on either side of both lines, QKV of 7 pairs
 FIN_66 = Workload(name="66-and-7-pairs", hidden=3232, n_q_heads=10, n_kv_heads=2, head_dim=32, ffn=2112, n_layers=1, tp=2, dtype=BF16,
